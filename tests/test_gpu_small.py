@@ -248,6 +248,16 @@ def test_gqa_varlen_batch_ragged(esp, cuda, Hq, Hkv):
     run_prefill_case(esp, pc)
 
 
+@pytest.mark.parametrize("Hq,Hkv,chunks", [(6, 2, [85, 86, 171, 1]), (5, 1, [51, 52, 103]), (66, 2, [7, 8, 40]), (300, 1, [1, 2, 5]),
+                                           (8, 2, [3, 64, 65, 128] * 17), (4, 4, [2, 255, 256, 257])])
+def test_prefill_packed_rows(esp, cuda, Hq, Hkv, chunks):
+    """Query tiles are 256 (token, query head) rows of a KV head: group sizes that do not divide a tile, groups larger
+    than a tile, chunks that end just before, at and after a tile, and more requests than one scan step looks at."""
+    pc = wl.striped_prefill(f"packed-{Hq}/{Hkv}", chunks, 2, 0, Hq, Hkv, 25, cuda)
+    run_prefill_case(esp, pc)
+    run_retain_case(esp, pc, 26)
+
+
 def test_non_causal_and_tail(esp, cuda):
     pc = wl.contiguous_prefill("noncausal", 130, 0, [(0, 200), (200, 333)], 4, 4, 21, cuda, causal=False)
     run_prefill_case(esp, pc)
