@@ -79,7 +79,10 @@ typedef int32_t esp_status;
  *     only to size the launch).
  *   O [Tq,Hq,D] bf16, LSE [Tq,Hq] float: written for every row.
  *   workspace: at least esp_prefill_workspace_bytes(...) bytes, 256-byte
- *     aligned; contents need not be preserved between calls.  It holds work
+ *     aligned; contents need not be preserved between calls.  It holds, for calls
+ *     with few query rows against many keys, the partial results of the parts the
+ *     keys are cut into (a smaller block, down to 256 bytes, is accepted: such a
+ *     call then runs uncut, and slower), and work
  *     counters that are never cleared: every launch tags them with a number of
  *     its own (a per-process random 32-bit start, then +1 per call), so memory
  *     that has never been written is mistaken for the current launch's counters
@@ -284,7 +287,7 @@ esp_status esp_kv_gather(
  * shard is pool row slot_idx[i] (kv_pos[i] is its global position; cu_kv counts
  * shard rows, i.e. entries of slot_idx).  Same results as esp_kv_gather followed
  * by esp_partial_attn_prefill, which is how it is carried out: the gathered rows
- * are staged in the workspace (2 * Tkv * Hkv * D * 2 bytes on top of the dense
+ * are staged in the workspace (2 * Tkv * Hkv * D * 2 bytes ahead of the dense
  * call's own block).  All other arguments as in esp_partial_attn_prefill.
  */
 esp_status esp_partial_attn_prefill_pool(

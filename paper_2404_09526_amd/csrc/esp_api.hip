@@ -132,7 +132,7 @@ static esp_status prefill_entry(const void* q, const void* k, const void* v, con
     if (!q || !O || !LSE || !q_pos) return fail(ESP_ERR_INVALID_ARG, "prefill: null q/q_pos/O/LSE");
     if (Tkv > 0 && (!k || !v || !kv_pos)) return fail(ESP_ERR_INVALID_ARG, "prefill: null k/v/kv_pos");
     if (!(softmax_scale == softmax_scale) || softmax_scale < 0.f) return fail(ESP_ERR_INVALID_ARG, "prefill: bad softmax_scale");
-    size_t need = prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv);
+    const size_t need = kPrefillCounterBytes;                  // without the room for a split the call runs unsplit
     if (need > 0 && (!workspace || workspace_bytes < need))
         return fail(ESP_ERR_WORKSPACE, "prefill: workspace needs %zu bytes, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if (need > 0 && ((uintptr_t)workspace & 255)) return fail(ESP_ERR_WORKSPACE, "prefill: workspace not 256-byte aligned");
@@ -220,7 +220,7 @@ esp_status esp_partial_attn_prefill_pool(const void* q, const void* k_pool, cons
     if (D != kHeadDim) return fail(ESP_ERR_UNSUPPORTED, "prefill (pool): head_dim %d unsupported (only 128)", D);
     if (Tkv > 0 && !slot_idx) return fail(ESP_ERR_INVALID_ARG, "prefill (pool): null slot_idx");
     const size_t stage = pool_staging_bytes(Tkv, Hkv);
-    const size_t need = esp_prefill_pool_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D);
+    const size_t need = 2 * stage + kPrefillCounterBytes;
     if (!workspace || workspace_bytes < need)
         return fail(ESP_ERR_WORKSPACE, "prefill (pool): workspace needs %zu bytes, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if ((uintptr_t)workspace & 255) return fail(ESP_ERR_WORKSPACE, "prefill (pool): workspace not 256-byte aligned");

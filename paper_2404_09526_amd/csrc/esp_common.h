@@ -64,7 +64,7 @@ esp_status launch_probe_mfma(const void* operands, int64_t operand_bytes, int32_
                              hipStream_t stream);
 esp_status launch_probe_read(const void* src, int64_t bytes, void* sink, hipStream_t stream);
 esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_t parts_f32, void* O, float* LSE_out,
-                        hipStream_t stream);
+                        hipStream_t stream, int32_t o_f32 = 0);
 
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv);
 esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
@@ -82,6 +82,8 @@ esp_status launch_decode_static(const void* q, const void* k_pool, const void* v
                                 const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv,
                                 float softmax_scale, void* O, float* LSE, hipStream_t stream);
 
+constexpr size_t kPrefillCounterBytes = 256;      // what every prefill call needs: its item counter and arrival counts
+// the same, and room for the partial results of the calls that split the key-value rows
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv);
 esp_status launch_prefill(const void* q, const void* k, const void* v, const int32_t* q_pos, const int32_t* kv_pos,
                           const int32_t* cu_q, const int32_t* cu_kv, int32_t batch, int32_t Tq, int32_t Tkv,

@@ -4,12 +4,13 @@
 // distributed decoding, Sec. 4.2).  HBM-streaming: 16 lanes share one (token, head) pair,
 // each owning 8 of the 128 output elements (one 16-byte load per bf16 partial, two per fp32 partial:
 // partials that never leave this GPU, the rounds of a sequence-parallel prefill, may stay in fp32,
-// so that the merged result is rounded to bf16 once and not twice).
+// so that the merged result is rounded to bf16 once and not twice).  The parts of a prefill call that split its
+// key-value rows come here too, and leave as fp32 where the call's own result is a partial (OUT32).
 #include "esp_common.h"
 
 namespace esp {
 
-template <bool F32>
+template <bool F32, bool OUT32>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, int64_t pairs,
                                                     uint4* O, float* LSE_out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -53,24 +54,32 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] *= inv;
     }
+    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = (m == -INFINITY) ? -INFINITY : m + __logf(wsum);
+    if (OUT32) {
+        float4* dst = (float4*)O + (pair * 16 + seg) * 2;
+        dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        dst[1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
+        return;
+    }
     uint4 out;
     out.x = pack_bf16(acc[0], acc[1]);
     out.y = pack_bf16(acc[2], acc[3]);
     out.z = pack_bf16(acc[4], acc[5]);
     out.w = pack_bf16(acc[6], acc[7]);
     O[pair * 16 + seg] = out;
-    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = (m == -INFINITY) ? -INFINITY : m + __logf(wsum);
 }
 
 esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_t parts_f32, void* O, float* LSE_out,
-                        hipStream_t stream) {
+                        hipStream_t stream, int32_t o_f32) {
     int64_t threads = pairs * 16;
     int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "merge: too many rows for one launch");
-    if (parts_f32)
-        hipLaunchKernelGGL(merge_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
+    if (parts_f32 && o_f32)
+        hipLaunchKernelGGL((merge_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
+    else if (parts_f32)
+        hipLaunchKernelGGL((merge_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
     else
-        hipLaunchKernelGGL(merge_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
+        hipLaunchKernelGGL((merge_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
     return check_launch("merge_kernel");
 }
 

@@ -258,6 +258,41 @@ def test_prefill_packed_rows(esp, cuda, Hq, Hkv, chunks):
     run_retain_case(esp, pc, 26)
 
 
+@pytest.mark.parametrize("Hq,Hkv,Tq,shards,causal", [(8, 2, 40, [(0, 3000)], True), (4, 4, 300, [(0, 2050), (2050, 4463)], True),
+                                                     (5, 1, 1, [(0, 1025)], True), (4, 2, 257, [(0, 1600)], False),
+                                                     (2, 2, 1100, [(0, 1100)], True)])
+def test_prefill_few_items_split_the_keys(esp, cuda, Hq, Hkv, Tq, shards, causal):
+    """Calls with few query tiles cut the key-value tiles into parts and merge their results: ragged last tiles, parts no
+    row of a tile can see, bf16 and fp32 outputs, kept rows, rows read from the pool, and a workspace without room for
+    the parts (the call then runs unsplit)."""
+    end = shards[-1][1]
+    pc = wl.contiguous_prefill(f"split-{Hq}/{Hkv}-{Tq}", Tq, end - Tq, shards, Hq, Hkv, 27, cuda, causal=causal)
+    sizes = [hi - lo for lo, hi in shards]
+    counters = esp.esp_prefill_workspace_bytes(Tq, 0, 1, Hq, Hkv, 128)
+    assert all(esp.esp_prefill_workspace_bytes(Tq, n, 1, Hq, Hkv, 128) > counters for n in sizes)      # these calls do split
+    run_prefill_case(esp, pc)
+    run_prefill_case(esp, pc, workspace=torch.empty(counters, dtype=torch.uint8, device=cuda))
+    run_retain_case(esp, pc, 28)
+    run_pool_direct_case(esp, pc, 29)
+
+
+def test_prefill_split_batch_with_an_empty_and_a_short_request(esp, cuda):
+    """A batch of short chunks behind contexts of very different lengths: requests with fewer KV tiles than parts (some
+    parts are empty), one without queries, one without keys."""
+    q_lens, kv_lens, Hq, Hkv = [3, 40, 0, 1, 17, 5], [30, 3000, 64, 0, 1700, 5], 4, 2
+    gen = torch.Generator(device=cuda).manual_seed(30)
+    Tq, Tkv = sum(q_lens), sum(kv_lens)
+    at = lambda parts: torch.tensor(np.concatenate(parts).astype(np.int32), device=cuda)
+    shard = wl.Shard(wl.randn_bf16((Tkv, Hkv, 128), gen, cuda), wl.randn_bf16((Tkv, Hkv, 128), gen, cuda),
+                     at([np.arange(n) for n in kv_lens]), at([[0], np.cumsum(kv_lens)]), max(kv_lens))
+    pc = wl.PrefillCase("split-batch", Hq, Hkv, 128, 128 ** -0.5, True, wl.randn_bf16((Tq, Hq, 128), gen, cuda),
+                        at([max(n - m, 0) + np.arange(m) for m, n in zip(q_lens, kv_lens)]), at([[0], np.cumsum(q_lens)]),
+                        max(q_lens), [shard], 0)
+    assert esp.esp_prefill_workspace_bytes(Tq, Tkv, 6, Hq, Hkv, 128) > esp.esp_prefill_workspace_bytes(Tq, 0, 6, Hq, Hkv, 128)
+    run_prefill_case(esp, pc)
+    run_pool_direct_case(esp, pc, 32)
+
+
 def test_non_causal_and_tail(esp, cuda):
     pc = wl.contiguous_prefill("noncausal", 130, 0, [(0, 200), (200, 333)], 4, 4, 21, cuda, causal=False)
     run_prefill_case(esp, pc)
