@@ -242,89 +242,130 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
 }
 
 
-// One workgroup per (request, head): 4 groups of 64 lanes split the partials, each lane owns
-// two output elements; the groups are then combined through LDS.
+// Combination of the partials of a (request, head) pair: groups of 32 lanes, four output elements a lane, take the
+// partials in turn, four at a time, and then combine among themselves.  The time is latency (offsets -> partials -> result)
+// and, for long requests, the number of trips through the partials; so the loads of a trip are issued together, and a pair
+// gets a workgroup (GROUPS = 8) where its request may have more than 32 partials, a wavefront (GROUPS = 2, four
+// pairs per workgroup, no LDS) otherwise.  Measured (64 lanes a partial, one at a time, always a workgroup -> this):
+// 32 requests of 2K, 32 / 32 heads, 1006 ranges, 3 peers 20.7 -> 9.6 us; 64 of 4K, 32 / 1 heads 12.0 -> 5.7 us; 128 of 16K,
+// 32 / 8 heads 15.9 -> 12.4 us; 89 of 172, 32 / 1 heads, 3 peers 5.3 -> 4.6 us.
 //
 // PEERS: the master of a multi-master decode (Sec. 4.2) also holds the partial results its peers returned for the
-// same queries (bf16 O, natural-log LSE).  They enter the same log-sum-exp combination here, so the local result is
-// never rounded to bf16 on its own and no separate merge launch follows.
-template <bool PEERS>
+// same queries (bf16 O, natural-log LSE).  They enter the same log-sum-exp combination here, shared out among the groups
+// like the partials, so the local result is never rounded to bf16 on its own and no separate merge launch follows.
+constexpr int kCombineShort = 32;
+template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
-                                                             int32_t range, int32_t nt, int32_t Hq,
+                                                             int32_t range, int32_t nt, int32_t Hq, int32_t pairs,
                                                              const float* __restrict__ part_acc,
                                                              const float* __restrict__ part_ml,
                                                              MergeArgs peers, int32_t n_peers,
-                                                             uint32_t* __restrict__ O, float* __restrict__ LSE) {
-    const int b = blockIdx.x / Hq, h = blockIdx.x % Hq;
-    const int dp = threadIdx.x & 63, grp = threadIdx.x >> 6;
+                                                             uint2* __restrict__ O, float* __restrict__ LSE) {
+    constexpr int U = 4;
+    const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
+    const int pair = blockIdx.x * (8 / GROUPS) + grp / GROUPS, g = grp % GROUPS;
+    if (pair >= pairs) return;                                      // (only where a pair is a wavefront: no barrier follows)
+    const int b = pair / Hq, h = pair - b * Hq;
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1];
-    float M = -INFINITY, L = 0.f, a0 = 0.f, a1 = 0.f;
+    float M = -INFINITY, L = 0.f;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    // adds U partials (m: base-2 maximum, l: sum, 0 = nothing; v: l-weighted output)
+    auto add = [&](const float (&m)[U], const float (&l)[U], const float4 (&v)[U]) {
+        float mx = M;
+#pragma unroll
+        for (int u = 0; u < U; ++u) mx = fmaxf(mx, l[u] != 0.f ? m[u] : -INFINITY);
+        if (mx == -INFINITY) return;
+        const float c_old = __builtin_amdgcn_exp2f(M - mx);
+        M = mx;
+        L *= c_old;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] *= c_old;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (l[u] != 0.f) {                                      // keeps the garbage of an empty partial out of the sum
+                const float c = __builtin_amdgcn_exp2f(m[u] - mx);
+                L += l[u] * c;
+                acc[0] += v[u].x * c; acc[1] += v[u].y * c; acc[2] += v[u].z * c; acc[3] += v[u].w * c;
+            }
+        }
+    };
     if (s1 > s0) {
         const int w_lo = s0 / range, w_hi = (s1 - 1) / range;
         const int n = (w_hi - w_lo + 1) * nt;
-        for (int i = grp; i < n; i += 4) {
-            int64_t ph = ((int64_t)(w_lo + b) * nt + i) * Hq + h;   // sub-slots of consecutive ranges are contiguous
-            float2 ml = *(const float2*)(part_ml + ph * 2);
-            if (ml.y == 0.f) continue;                              // a wavefront that saw no token
-            float2 a = *(const float2*)(part_acc + ph * kHeadDim + dp * 2);
-            float mx = fmaxf(M, ml.x);
-            float c_old = __builtin_amdgcn_exp2f(M - mx), c_new = __builtin_amdgcn_exp2f(ml.x - mx);
-            L = L * c_old + ml.y * c_new;
-            a0 = a0 * c_old + a.x * c_new;
-            a1 = a1 * c_old + a.y * c_new;
-            M = mx;
+        const int64_t first = (int64_t)(w_lo + b) * nt;             // sub-slots of consecutive ranges are contiguous
+        for (int i = g; i < n; i += GROUPS * U) {
+            float m[U], l[U];
+            float4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = i + u * GROUPS;
+                const int64_t ph = (first + min(k, n - 1)) * Hq + h;
+                const float2 ml = *(const float2*)(part_ml + ph * 2);
+                v[u] = load_once((const float4*)(part_acc + ph * kHeadDim + lane * 4));
+                m[u] = ml.x;
+                l[u] = k < n ? ml.y : 0.f;
+            }
+            add(m, l, v);
         }
     }
-    __shared__ float sm[4], sl[4], sa[4][128];
-    if (dp == 0) { sm[grp] = M; sl[grp] = L; }
-    sa[grp][dp * 2] = a0;
-    sa[grp][dp * 2 + 1] = a1;
-    __syncthreads();
-    if (grp == 0) {
-        float mx = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-        const int64_t pair = (int64_t)b * Hq + h;
-        float lse_p[ESP_MAX_PARTIALS];                            // the peers' LSE in base-2 units, like mx
-        if (PEERS) {
+    if (PEERS) {
+        for (int p0 = g; p0 < n_peers; p0 += GROUPS * U) {
+            float m[U], l[U];
+            float4 v[U];
 #pragma unroll
-            for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
-                lse_p[p] = (p < n_peers) ? peers.LSE_parts[p][pair] * kLog2e : -INFINITY;
-                mx = fmaxf(mx, lse_p[p]);
+            for (int u = 0; u < U; ++u) {
+                const int p = p0 + u * GROUPS, q = min(p, n_peers - 1);
+                const float lse = peers.LSE_parts[q][pair];
+                const uint2 o = ((const uint2*)peers.O_parts[q])[(int64_t)pair * (kHeadDim / 4) + lane];
+                m[u] = lse * kLog2e;
+                l[u] = p < n_peers && lse != -INFINITY ? 1.f : 0.f;  // a peer's rows are normalised
+                v[u] = make_float4(bf16_lo(o.x), bf16_hi(o.x), bf16_lo(o.y), bf16_hi(o.y));
             }
+            add(m, l, v);
         }
-        float Lt = 0.f, o0 = 0.f, o1 = 0.f;
+    }
+    // ---- the groups' results: exchanged by shuffles within a wavefront, through LDS otherwise
+    float mx, Lt = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+    if (GROUPS == 2) {
+        const float M2 = __shfl_xor(M, 32);
+        mx = fmaxf(M, M2);
+        const float c = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mx);
+        Lt = L * c;
+        Lt += __shfl_xor(Lt, 32);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            o[e] = acc[e] * c;
+            o[e] += __shfl_xor(o[e], 32);
+        }
+    } else {
+        __shared__ float sm[8], sl[8];
+        __shared__ float4 sa[8][32];
+        if (lane == 0) { sm[grp] = M; sl[grp] = L; }
+        sa[grp][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        __syncthreads();
+        if (g != 0) return;
+        mx = sm[0];
+#pragma unroll
+        for (int u = 1; u < 8; ++u) mx = fmaxf(mx, sm[u]);
         if (mx != -INFINITY) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float c = __builtin_amdgcn_exp2f(sm[g] - mx);     // exp2(-inf) = 0 for an idle group
-                Lt += sl[g] * c;
-                o0 += sa[g][dp * 2] * c;
-                o1 += sa[g][dp * 2 + 1] * c;
+            for (int u = 0; u < 8; ++u) {
+                const float c = __builtin_amdgcn_exp2f(sm[u] - mx);  // exp2(-inf) = 0 for an idle group
+                const float4 t = sa[u][lane];
+                Lt += sl[u] * c;
+                o[0] += t.x * c; o[1] += t.y * c; o[2] += t.z * c; o[3] += t.w * c;
             }
-            if (PEERS) {
-#pragma unroll
-                for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
-                    if (p < n_peers) {
-                        const float w = __builtin_amdgcn_exp2f(lse_p[p] - mx);   // a peer's rows are normalised: mass w
-                        const uint32_t o = ((const uint32_t*)peers.O_parts[p])[pair * (kHeadDim / 2) + dp];
-                        if (w != 0.f) {                           // keeps the garbage of an empty partial out of the sum
-                            Lt += w;
-                            o0 += w * bf16_lo(o);
-                            o1 += w * bf16_hi(o);
-                        }
-                    }
-                }
-            }
-            float inv = 1.0f / Lt;
-            o0 *= inv; o1 *= inv;
         }
-        O[pair * (kHeadDim / 2) + dp] = pack_bf16(o0, o1);
-        if (dp == 0) LSE[pair] = (mx == -INFINITY) ? -INFINITY : (mx + __builtin_amdgcn_logf(Lt)) * kLn2;
     }
+    if (g != 0) return;
+    const float inv = mx == -INFINITY ? 0.f : 1.0f / Lt;
+    O[(int64_t)pair * (kHeadDim / 4) + lane] = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
+    if (lane == 0) LSE[pair] = (mx == -INFINITY) ? -INFINITY : (mx + __builtin_amdgcn_logf(Lt)) * kLn2;
 }
 
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
-                                const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv,
-                                float softmax_scale, void* O, float* LSE, hipStream_t stream) {
+                                const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
+                                int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream) {
     const size_t need = decode_workspace_bytes(B, total_tokens, Hq, Hkv);
     if (need > (size_t)ESP_DECODE_STATIC_SCRATCH_BYTES)
         return fail(ESP_ERR_WORKSPACE, "decode (static scratch): this call needs %zu bytes of scratch memory, the built-in block holds %zu; "
@@ -332,13 +373,13 @@ esp_status launch_decode_static(const void* q, const void* k_pool, const void* v
     void* ws = nullptr;
     const esp_status st = static_scratch(&ws);
     if (st != ESP_OK) return st;
-    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, softmax_scale, O, LSE, ws,
+    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, max_len, Hq, Hkv, softmax_scale, O, LSE, ws,
                          (size_t)ESP_DECODE_STATIC_SCRATCH_BYTES, stream);
 }
 
 esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
-                         const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv,
-                         float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
+                         const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
+                         int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
     (void)workspace_bytes;
     DecodeGeom g = decode_geom(total_tokens, Hq, Hkv);
@@ -366,13 +407,18 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
         esp_status st = check_launch("decode_partial_kernel");
         if (st != ESP_OK) return st;
     }
-    const dim3 cgrid((unsigned)((int64_t)B * Hq));
-    if (peers != nullptr && n_peers > 0)
-        hipLaunchKernelGGL(decode_combine_kernel<true>, cgrid, dim3(256), 0, stream, seq_offsets, g.range, g.nt, Hq,
-                           (const float*)part_acc, (const float*)part_ml, *peers, n_peers, (uint32_t*)O, LSE);
-    else
-        hipLaunchKernelGGL(decode_combine_kernel<false>, cgrid, dim3(256), 0, stream, seq_offsets, g.range, g.nt, Hq,
-                           (const float*)part_acc, (const float*)part_ml, MergeArgs{}, 0, (uint32_t*)O, LSE);
+    const int32_t pairs = B * Hq;
+    const bool with_peers = peers != nullptr && n_peers > 0;
+    const bool wave = ((int64_t)max_len / g.range + 2) * g.nt <= kCombineShort;
+#define ESP_COMBINE_LAUNCH(GROUPS, PEERS)                                                                                 \
+    hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), dim3((unsigned)((pairs + 8 / GROUPS - 1) / (8 / GROUPS))), dim3(256), 0, \
+                       stream, seq_offsets, g.range, g.nt, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
+                       with_peers ? *peers : MergeArgs{}, n_peers, (uint2*)O, LSE)
+    if (wave && with_peers) ESP_COMBINE_LAUNCH(2, true);
+    else if (wave) ESP_COMBINE_LAUNCH(2, false);
+    else if (with_peers) ESP_COMBINE_LAUNCH(8, true);
+    else ESP_COMBINE_LAUNCH(8, false);
+#undef ESP_COMBINE_LAUNCH
     return check_launch("decode_combine_kernel");
 }
 

@@ -287,7 +287,7 @@ esp_status esp_partial_attn_decode(const void* q, const void* k_pool, const void
     if ((uintptr_t)workspace & 255) return fail(ESP_ERR_WORKSPACE, "decode: workspace not 256-byte aligned");
     st = decode_validate(slot_idx, seq_offsets, B, total_tokens, max_len, num_slots, stream);
     if (st != ESP_OK) return st;
-    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, softmax_scale, O, LSE,
+    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, max_len, Hq, Hkv, softmax_scale, O, LSE,
                          workspace, workspace_bytes, (hipStream_t)stream);
 }
 
@@ -301,7 +301,7 @@ esp_status esp_partial_attn_decode_static(const void* q, const void* k_pool, con
     if (st != ESP_OK || done) return st;
     st = decode_validate(slot_idx, seq_offsets, B, total_tokens, max_len, num_slots, stream);
     if (st != ESP_OK) return st;
-    return launch_decode_static(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, softmax_scale, O, LSE,
+    return launch_decode_static(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, max_len, Hq, Hkv, softmax_scale, O, LSE,
                                 (hipStream_t)stream);
 }
 
@@ -339,7 +339,7 @@ esp_status esp_partial_attn_decode_merge(const void* q, const void* k_pool, cons
     if ((uintptr_t)workspace & 255) return fail(ESP_ERR_WORKSPACE, "decode: workspace not 256-byte aligned");
     st = decode_validate(slot_idx, seq_offsets, B, total_tokens, max_len, num_slots, stream);
     if (st != ESP_OK) return st;
-    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, softmax_scale, O, LSE,
+    return launch_decode(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, max_len, Hq, Hkv, softmax_scale, O, LSE,
                          workspace, workspace_bytes, (hipStream_t)stream, &peers, n_peers);
 }
 

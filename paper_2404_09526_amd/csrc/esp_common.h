@@ -68,8 +68,8 @@ esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_
 
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv);
 esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
-                         const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv,
-                         float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
+                         const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
+                         int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers = nullptr, int32_t n_peers = 0);
 
 // the partial kernel on the matrix cores (decode_gq.hip): one partial per (range + request, head)
@@ -79,8 +79,8 @@ esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_poo
 
 int32_t set_prefill_sync_ticks(int32_t ticks);   // returns the previous value; negative restores the built-in default
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
-                                const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv,
-                                float softmax_scale, void* O, float* LSE, hipStream_t stream);
+                                const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
+                                int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream);
 
 constexpr size_t kPrefillCounterBytes = 256;      // what every prefill call needs: its item counter and arrival counts
 // the same, and room for the partial results of the calls that split the key-value rows

@@ -436,6 +436,25 @@ def test_decode_merged_with_the_peers_partials_in_one_pass(esp, cuda, Hq, Hkv):
     assert e.value.status == esp.ESP_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(3, 3), (8, 8), (8, 2), (32, 32)])
+@pytest.mark.parametrize("longest,n_peers", [(33, 15), (2000, 4), (9000, 9), (30000, 1)])
+def test_decode_combine_sizes(esp, cuda, Hq, Hkv, longest, n_peers):
+    """The combination of a pair's partials by a wavefront and by a workgroup: one partial, about as many as separate the two
+    forms, many, and up to the largest number of peers (the last one without any token)."""
+    dc = wl.decode_pool(f"combine-{Hq}/{Hkv}-{longest}", [longest, 1, 0, 40], 32768, Hq, Hkv, 38, cuda, n_new=0, n_peers=n_peers)
+    dc.peer_LSE[-1] = float("-inf"); dc.peer_O[-1] = float("nan")
+    _, _, kp, vp = run_decode_case(esp, dc)
+    O, LSE = esp.esp_partial_attn_decode_merge(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, longest,
+                                               list(dc.peer_O), list(dc.peer_LSE), softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    Or, Lr = oracle.partial_attn_decode_all(wl.bits(dc.q), kp, vp, wl.host_i32(dc.slot_idx), wl.host_i32(dc.seq_offsets), dc.scale)
+    Op = np.stack([Or] + [np.nan_to_num(oracle.bf16_bits_to_f64(wl.bits(t)), nan=0.0) for t in dc.peer_O])
+    Lp = np.stack([Lr] + [t.cpu().numpy().astype(np.float64) for t in dc.peer_LSE])
+    Oref, Lref = oracle.merge_partials(Op, Lp)
+    check_o_lse(O.float().cpu().numpy().reshape(-1, dc.D), LSE.cpu().numpy().reshape(-1), Oref.reshape(-1, dc.D), Lref.reshape(-1),
+                f"{dc.name} + {n_peers} peers")
+
+
 def test_decode_many_ranges(esp, cuda):
     """Enough tokens that the token list is cut into many ranges, with requests spanning several of them."""
     lens = wl.lognormal_lengths(24, 3000, 10, 40000, 31)
