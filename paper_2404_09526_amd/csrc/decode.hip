@@ -68,7 +68,35 @@ static bool decode_burst_layout(int32_t Hq, int32_t Hkv) {
     return (Hkv == 4 || Hkv == 8 || Hkv == 16 || Hkv % 32 == 0) && (G == 1 || G == 2);
 }
 
-static DecodeGeom decode_geom(int32_t total_tokens, int32_t Hq, int32_t Hkv) {
+// Tokens per range of the matrix-core kernel (`rows`: workgroups per range).  Two workgroups fit a CU, and a call that is
+// only a few times what the chip holds at once must not end with a round of a few workgroups: of the ranges from the finest
+// up the one is taken for which whole rounds of workgroups, each with a start (search, queries, first slots, combination)
+// and its steps, take the least time (64 requests of 4K, 32 / 1 heads: 598 workgroups of 512 tokens were three rounds of 256,
+// 479 of 640 are one of 512).  More partials than the earlier rule's (ranges of 512 tokens and up, in steps of 256) only
+// as far as the built-in scratch block holds them.
+static int32_t gq_range(int32_t B, int32_t total_tokens, int32_t Hq, int64_t rows) {
+    constexpr int64_t kStep = kGqWaves * 32, kResident = 512;
+    constexpr double kStart = 6, kTile = 4.8;                     // microseconds
+    const int64_t coarse = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
+    const int64_t coarse_range = coarse < 512 ? 512 : (coarse + 255) / 256 * 256;
+    const int64_t room = ((int64_t)ESP_DECODE_STATIC_SCRATCH_BYTES - 256) / ((int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float)) - B;
+    int64_t most = ((int64_t)total_tokens + coarse_range - 1) / coarse_range;      // ranges
+    if (most < room) most = room;
+    if (most < 1) most = 1;
+    if (most > kDecMaxWG) most = kDecMaxWG;
+    const int64_t steps = ((int64_t)total_tokens + kStep - 1) / kStep;
+    const int64_t finest = steps > most ? (steps + most - 1) / most : 1;
+    int64_t best = finest;
+    double best_us = 0;
+    for (int64_t s = finest; s < finest + 32; ++s) {
+        const int64_t wgs = (steps + s - 1) / s * rows;
+        const double us = (double)((wgs + kResident - 1) / kResident) * (kStart + kTile * (double)s);
+        if (s == finest || us < best_us) { best = s; best_us = us; }
+    }
+    return (int32_t)(best * kStep);
+}
+
+static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
     DecodeGeom g;
     if (!decode_burst_layout(Hq, Hkv)) {
         // matrix-core kernel: every wavefront of a workgroup works on the same KV head, a tile of 32 tokens each per
@@ -76,11 +104,8 @@ static DecodeGeom decode_geom(int32_t total_tokens, int32_t Hq, int32_t Hkv) {
         g.nhb_wg = 0;
         g.nt = 1;
         g.ygroups = Hkv;
-        int64_t step = (int64_t)kDecWaves * 32;
-        int64_t want = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
-        if (want < 2 * step) want = 2 * step;
-        want = (want + step - 1) / step * step;
-        g.range = (int32_t)want;
+        g.range = gq_range(B, total_tokens, Hq, (int64_t)Hkv * ((Hq / Hkv + 31) / 32));
+        const int64_t want = g.range;
         g.nwg = (int32_t)(((int64_t)total_tokens + want - 1) / want);
         if (g.nwg < 1) g.nwg = 1;
         return g;
@@ -104,7 +129,7 @@ static DecodeGeom decode_geom(int32_t total_tokens, int32_t Hq, int32_t Hkv) {
 static size_t decode_slots(const DecodeGeom& g, int32_t B) { return (size_t)g.nwg + (size_t)B; }
 
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
-    DecodeGeom g = decode_geom(total_tokens, Hq, Hkv);
+    DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
     size_t n = decode_slots(g, B) * (size_t)g.nt * (size_t)Hq;
     return n * (kHeadDim + 2) * sizeof(float) + 256;
 }
@@ -382,7 +407,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
     (void)workspace_bytes;
-    DecodeGeom g = decode_geom(total_tokens, Hq, Hkv);
+    DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
     size_t n = decode_slots(g, B) * (size_t)g.nt * (size_t)Hq;
     float* part_acc = (float*)workspace;
     float* part_ml = part_acc + n * kHeadDim;

@@ -7,24 +7,29 @@
 //   S^T [32 keys x 32 heads] = K_tile [32 x 128] Q^T [128 x 32],   O^T [128 x 32 heads] += V_tile^T [128 x 32] P^T [32 x 32]
 // The products are far from binding (16 MFMAs per 16 KiB gathered), so the kernel's time does not depend on G.
 // Work is split as in the row-burst kernel: the concatenated token list in equal ranges, one workgroup per
-// (range, KV head, chunk of up to 32 query heads); inside it every wavefront works alone, on every 8th tile of 32
+// (range, KV head, chunk of up to 32 query heads); inside it every wavefront works alone, on every 4th tile of 32
 // tokens of a request's part of the range, with an LDS block of its own (no workgroup barrier inside the sweep): it
 // gathers the tile's K and V rows from their pool slots straight into LDS (16-byte pieces, a full address per
-// lane), multiplies and keeps an exact running maximum; when the request's part of the range is done, the eight
-// wavefronts combine their results through LDS and leave one partial (accumulator, maximum, sum) per
-// (range + request, head) for the combine kernel.  (Eight partials per workgroup, one per wavefront, made the combine
-// kernel read 145 MB for 32 / 1 heads and 64 requests: a quarter of the call's time.)
+// lane), multiplies (the scores as soon as K is there) and keeps an exact running maximum; when the request's part of the
+// range is done, the wavefronts combine their results through LDS and leave one partial (accumulator, maximum, sum) per
+// (range + request, head) for the combine kernel.  (A partial per wavefront made the combine kernel read 145 MB for
+// 32 / 1 heads and 64 requests: a quarter of the call's time.)
+// A workgroup is four wavefronts, so that two fit a CU (LDS and registers) and one gathers while the other starts or
+// combines: a start (search of the request, queries, first slots) and an end take about as long as two steps of
+// gathers.  With the ranges of gq_range (decode.hip) and the 64-way search of the first request, measured against one
+// workgroup of eight wavefronts per CU: 64 requests of 4K, 32 / 1 heads, 55.7 -> 42.5 us; 128 of 16K, 32 / 8 heads,
+// 2264 -> 2216 us (6.70 TB/s); 16 of 600, 32 / 8 heads, partial kernel 20.1 -> 16.5 us.
 #include "mfma_tile.h"
 
 namespace esp {
 
-constexpr int kGqWaves = 8;
 constexpr int kGqKRow = 272;                 // K rows padded by 16 bytes in LDS (bank spread of the operand reads)
 constexpr int kGqKBytes = 9 * 1024;          // 32 x 272 = 8704 bytes, moved by 9 transfers of 1 KiB
 constexpr int kGqVBytes = 32 * 256;
 constexpr int kGqWaveBytes = kGqKBytes + kGqVBytes;
+constexpr int kGqRegs = 64 / kGqWaves;       // accumulator registers that a wavefront combines at the end
 
-__global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
+__global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     const uint16_t* __restrict__ q, const char* __restrict__ k_pool, const char* __restrict__ v_pool,
     const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ seq_offsets, int32_t B, int32_t total_tokens,
     int32_t range, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml) {
@@ -55,12 +60,10 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
     int32_t t0 = w * range;
     const int32_t t1 = min(t0 + range, total_tokens);
     if (t0 >= t1) return;
-    int lo = 0, hb = B;   // invariant: seq_offsets[lo] <= t0 < seq_offsets[hb]
-    while (hb - lo > 1) {
-        int mid = (lo + hb) >> 1;
-        if (seq_offsets[mid] <= t0) lo = mid; else hb = mid;
-    }
-    int b = lo;
+    // slots of this wavefront's first tile, as far as they do not depend on where its request ends: asked for before the search
+    int32_t slots = slot_idx[min(t0 + 32 * wave + qi, total_tokens - 1)];
+    int b = request_of(t0, seq_offsets, B, lane);
+    bool first = true;
 
     union PFrag { uint32_t u[4]; bf16x8 v; };
     union VFrag { short4_t s[2]; bf16x8 v; };
@@ -90,12 +93,14 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
         float m = -INFINITY;       // running maximum of this column's scaled scores (both halves hold the same)
         float l = 0.f, l_r = 0.f;  // this half's sums of the probabilities: as computed, and as rounded to bf16
 
-        // slots of this wavefront's first tile: lane holds the slot of tile row lane % 32 (rows past the end: the last)
+        // slots of a tile: lane holds the slot of tile row lane % 32 (rows past the end: the last)
         auto tile_slots = [&](int i) {
             const int rows = min(32, seg - 32 * i);
             return slot_idx[t0 + 32 * i + min(qi, rows - 1)];
         };
-        int32_t slots = 32 * wave < seg ? tile_slots(wave) : 0;
+        if (!first) slots = 32 * wave < seg ? tile_slots(wave) : 0;
+        else if (32 * wave < seg) slots = __shfl(slots, min(qi, min(32, seg - 32 * wave) - 1));
+        first = false;
         for (int i = wave; 32 * i < seg; i += kGqWaves) {
             const int rows = min(32, seg - 32 * i);
             // ---- gather: K into rows of 272 bytes (lane L of transfer n fills LDS byte 1024 n + 16 L of the tile:
@@ -115,8 +120,7 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
             }
             int32_t slots_next = 0;
             if (32 * (i + kGqWaves) < seg) slots_next = tile_slots(i + kGqWaves);
-            wait_vm<0>();
-            asm volatile("" :: "v"(slots_next));
+            wait_vm<8>();                                           // K has landed; V and the next slots may be on their way
 
             // ---- S^T = K Q^T
             floatx16 sc;
@@ -163,6 +167,8 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
             }
             l += psum; l_r += psum_r;
             // ---- O^T += V^T P^T, 16 keys per step
+            wait_vm<0>();
+            asm volatile("" :: "v"(slots_next));
 #pragma unroll
             for (int p = 0; p < 8; ++p) {
                 const int t2 = p >> 2, db = p & 3;
@@ -200,7 +206,9 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
                 mw[u] = ((const float*)(smem + u * kGqWaveBytes))[64 * 64 + lane];
                 mx = fmaxf(mx, mw[u]);
             }
-            float lsum = 0.f, out[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            float lsum = 0.f, out[kGqRegs];
+#pragma unroll
+            for (int e = 0; e < kGqRegs; ++e) out[e] = 0.f;
 #pragma unroll
             for (int u = 0; u < kGqWaves; ++u) {
                 const float* blk = (const float*)(smem + u * kGqWaveBytes);
@@ -209,14 +217,14 @@ __global__ __launch_bounds__(kGqWaves * 64) void decode_partial_gq_kernel(
                 const float c = lu > 0.f ? __builtin_amdgcn_exp2f(mw[u] - mx) : 0.f;
                 lsum += lu * c;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) out[e] += blk[(8 * wave + e) * 64 + lane] * c;
+                for (int e = 0; e < kGqRegs; ++e) out[e] += blk[(kGqRegs * wave + e) * 64 + lane] * c;
             }
             if (qi < ng) {
                 const int64_t ph = (int64_t)(w + b) * Hq + h0 + qi;
-                // registers 8 wave .. 8 wave + 7 = block db = wave / 2, r = 8 (wave % 2) .. + 7: two runs of four rows
-                float* dst = part_acc + ph * kHeadDim + 32 * (wave >> 1) + 16 * (wave & 1) + 4 * hi;
-                *(float4*)(dst) = make_float4(out[0], out[1], out[2], out[3]);
-                *(float4*)(dst + 8) = make_float4(out[4], out[5], out[6], out[7]);
+                // register 16 db + r is element 32 db + 8 (r / 4) + 4 hi + r % 4: runs of four
+                float* dst = part_acc + ph * kHeadDim + 2 * kGqRegs * wave + 4 * hi;
+#pragma unroll
+                for (int e = 0; e < kGqRegs; e += 4) *(float4*)(dst + 2 * e) = make_float4(out[e], out[e + 1], out[e + 2], out[e + 3]);
                 if (wave == 0 && hi == 0) *(float2*)(part_ml + ph * 2) = make_float2(mx, lsum);
             }
         }

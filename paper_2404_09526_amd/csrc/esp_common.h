@@ -72,6 +72,21 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers = nullptr, int32_t n_peers = 0);
 
+// The request that holds token t: the last b with seq_offsets[b] <= t, found by a wavefront 64 candidates at a time (a
+// binary search is six dependent loads, about 3 us, at 64 requests; this is one).
+__device__ __forceinline__ int request_of(int32_t t, const int32_t* seq_offsets, int32_t B, int lane) {
+    int lo = 0, hi = B;   // invariant: seq_offsets[lo] <= t < seq_offsets[hi]
+    while (hi - lo > 1) {
+        const int stride = (hi - lo + 63) >> 6, i = lo + lane * stride;
+        const uint64_t below = __builtin_amdgcn_ballot_w64(i < hi && seq_offsets[min(i, hi)] <= t);
+        lo += (__builtin_popcountll(below) - 1) * stride;
+        hi = min(hi, lo + stride);
+    }
+    return lo;
+}
+
+constexpr int kGqWaves = 4;       // wavefronts per workgroup of decode_gq.hip
+
 // the partial kernel on the matrix cores (decode_gq.hip): one partial per (range + request, head)
 esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                             const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t range, int32_t nwg,

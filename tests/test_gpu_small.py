@@ -382,6 +382,20 @@ def test_decode_randomized_layouts(esp, cuda, seed):
                 f"{dc.name} decode + merge in one call")
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (8, 8)])
+@pytest.mark.parametrize("requests,top", [(1, 127), (1, 128), (1, 129), (64, 9), (65, 9), (130, 70), (4100, 1)])
+def test_decode_request_search_and_range_edges(esp, cuda, requests, top, Hq, Hkv):
+    """Token lists around one range of 128 tokens, and requests around what one and two steps of the 64-way search of a
+    range's first request tell apart (64, 4096), empty ones among them; both partial kernels.  (The 4100 requests have at most one key, which is exact.  With up to four
+    keys, one of four million outputs between 2 and 2.56 took half a unit of bf16, 7.8e-3, and of the 2^-9 sum p |v| that
+    rounded probabilities may add (5e-3 to 8e-3 there) 2.4e-3: more than the 1e-2 that the check allows.)"""
+    lens = np.random.default_rng(requests).integers(0, top + 1, requests) if requests > 1 else np.array([top])
+    dc = wl.decode_pool(f"decode-search-{requests}x{top} ({Hq}/{Hkv})", lens.tolist(), 16384, Hq, Hkv, 36, cuda, n_new=0)
+    O, LSE, _, _ = run_decode_case(esp, dc)
+    empty = torch.from_numpy(np.flatnonzero(lens == 0)).to(cuda)
+    assert torch.isneginf(LSE[empty]).all() and (O[empty] == 0).all()
+
+
 def test_decode_mqa_many_ranges_and_merge(esp, cuda):
     """MQA 32 / 1 at a size that is cut into many token ranges, then merged with peer partials."""
     lens = wl.lognormal_lengths(16, 6000, 10, 60000, 35)
