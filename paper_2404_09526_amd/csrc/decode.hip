@@ -68,69 +68,75 @@ static bool decode_burst_layout(int32_t Hq, int32_t Hkv) {
     return (Hkv == 4 || Hkv == 8 || Hkv == 16 || Hkv % 32 == 0) && (G == 1 || G == 2);
 }
 
-// Tokens per range of the matrix-core kernel (`rows`: workgroups per range).  Two workgroups fit a CU, and a call that is
-// only a few times what the chip holds at once must not end with a round of a few workgroups: of the ranges from the finest
-// up the one is taken for which whole rounds of workgroups, each with a start (search, queries, first slots, combination)
-// and its steps, take the least time (64 requests of 4K, 32 / 1 heads: 598 workgroups of 512 tokens were three rounds of 256,
-// 479 of 640 are one of 512).  More partials than the earlier rule's (ranges of 512 tokens and up, in steps of 256) only
-// as far as the built-in scratch block holds them.
-static int32_t gq_range(int32_t B, int32_t total_tokens, int32_t Hq, int64_t rows) {
-    constexpr int64_t kStep = kGqWaves * 32, kResident = 512;
-    constexpr double kStart = 6, kTile = 4.8;                     // microseconds
-    const int64_t coarse = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
-    const int64_t coarse_range = coarse < 512 ? 512 : (coarse + 255) / 256 * 256;
+// Tokens per range.  Two workgroups of either kernel fit a CU, and a call that is only a few times what the chip holds at once
+// must not end with a round of a few workgroups: of the ranges that fill 1 .. 16 rounds of workgroups (`rows` of them per
+// range; none finer than `least` steps of `step` tokens, at most kDecMaxWG ranges) the one is taken for which the rounds, each
+// with a start (search, queries, first slots, combination) and its steps (64 KiB of rows), take the least time.  Measured
+// with 1 / 2 / 4 / 8 rounds, us: 32 requests of 2K, 32 / 32 heads 328 / 345 / 344 / 345; 64 of 8K 2158 / 2190 / 2189 / 2186;
+// 250 of 20K, 32 / 1 525 / 543 / 541 / 541; 128 of 16K, 32 / 8 2399 / 2244 / 2198 / 2212; 64 of 8K, 64 / 8 430 / 412 / 412 / 428;
+// 32 / 4 210 / 209 / 220 / 233: where several workgroups gather from the same rows, a head each, a single round falls behind by
+// about 8 % of it.  64 requests of 4K, 32 / 1
+// heads: 598 workgroups of 512 tokens were three rounds of 256, 479 of 640 are one of 512.
+// `kept`: ranges that the call may have whatever they need; beyond them it takes only as many as fit the built-in block.
+static int32_t decode_range(int32_t B, int32_t total_tokens, int32_t Hq, int64_t step, int64_t least, int64_t rows, int64_t kept) {
+    constexpr int64_t kResident = 512;
+    constexpr double kStart = 6, kStep = 4.8;                     // microseconds
+    const double lag = rows > 1 ? 0.08 : 0;
     const int64_t room = ((int64_t)ESP_DECODE_STATIC_SCRATCH_BYTES - 256) / ((int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float)) - B;
-    int64_t most = ((int64_t)total_tokens + coarse_range - 1) / coarse_range;      // ranges
-    if (most < room) most = room;
+    int64_t most = kept > room ? kept : room;
     if (most < 1) most = 1;
     if (most > kDecMaxWG) most = kDecMaxWG;
-    const int64_t steps = ((int64_t)total_tokens + kStep - 1) / kStep;
-    const int64_t finest = steps > most ? (steps + most - 1) / most : 1;
+    const int64_t steps = ((int64_t)total_tokens + step - 1) / step;
+    int64_t finest = (steps + most - 1) / most;
+    if (finest < least) finest = least;
     int64_t best = finest;
     double best_us = 0;
-    for (int64_t s = finest; s < finest + 32; ++s) {
-        const int64_t wgs = (steps + s - 1) / s * rows;
-        const double us = (double)((wgs + kResident - 1) / kResident) * (kStart + kTile * (double)s);
-        if (s == finest || us < best_us) { best = s; best_us = us; }
+    for (int64_t rounds = 1; rounds <= 16; ++rounds) {
+        const int64_t fit = rounds * kResident / rows;             // ranges in so many rounds
+        const int64_t s = fit > 0 ? (steps + fit - 1) / fit : steps;
+        const int64_t take = s > finest ? s : finest;
+        const int64_t wgs = (steps + take - 1) / take * rows;
+        const double us = ((double)((wgs + kResident - 1) / kResident) + lag) * (kStart + kStep * (double)take);
+        if (rounds == 1 || us < best_us) { best = take; best_us = us; }
+        if (take == finest) break;
     }
-    return (int32_t)(best * kStep);
+    return (int32_t)(best * step);
 }
 
 static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
     DecodeGeom g;
+    // ranges of total_tokens in `unit`s, at least `least` tokens each and at most kDecMaxWG of them
+    auto ranges = [&](int64_t least, int64_t unit) {
+        int64_t want = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
+        if (want < least) want = least;
+        want = (want + unit - 1) / unit * unit;
+        return ((int64_t)total_tokens + want - 1) / want;
+    };
     if (!decode_burst_layout(Hq, Hkv)) {
-        // matrix-core kernel: every wavefront of a workgroup works on the same KV head, a tile of 32 tokens each per
-        // step; the workgroup combines its wavefronts itself, so there is one partial per (range + request, head)
+        // matrix-core kernel: every wavefront of a workgroup works on the same KV head, a tile of 32 tokens each per step
         g.nhb_wg = 0;
         g.nt = 1;
         g.ygroups = Hkv;
-        g.range = gq_range(B, total_tokens, Hq, (int64_t)Hkv * ((Hq / Hkv + 31) / 32));
-        const int64_t want = g.range;
-        g.nwg = (int32_t)(((int64_t)total_tokens + want - 1) / want);
-        if (g.nwg < 1) g.nwg = 1;
-        return g;
+        g.range = decode_range(B, total_tokens, Hq, kGqWaves * 32, 1, (int64_t)Hkv * ((Hq / Hkv + 31) / 32), ranges(512, 256));
+    } else {
+        const int nhb = Hkv / 4;
+        g.nhb_wg = nhb < 8 ? nhb : 8;
+        g.nt = kDecWaves / g.nhb_wg;
+        g.ygroups = (nhb + 7) / 8;
+        const int64_t step = (int64_t)g.nt * kDecTB;                 // tokens one workgroup consumes per loop step
+        g.range = decode_range(B, total_tokens, Hq, step, 2, g.ygroups, ranges(8 * step, step));
     }
-    int nhb = Hkv / 4;
-    g.nhb_wg = nhb < 8 ? nhb : 8;
-    g.nt = kDecWaves / g.nhb_wg;
-    g.ygroups = (nhb + 7) / 8;
-    int64_t step = (int64_t)g.nt * kDecTB;                       // tokens one workgroup consumes per loop step
-    int64_t want = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
-    int64_t min_range = 8 * step;                                // do not cut finer than 8 loop steps
-    if (want < min_range) want = min_range;
-    want = (want + step - 1) / step * step;
-    g.range = (int32_t)want;
-    g.nwg = (int32_t)(((int64_t)total_tokens + want - 1) / want);
+    g.nwg = (int32_t)(((int64_t)total_tokens + g.range - 1) / g.range);
     if (g.nwg < 1) g.nwg = 1;
     return g;
 }
 
-// workspace: fp32 accumulators [slots][nt][Hq][128], then (m, l) pairs [slots][nt][Hq][2]
+// workspace: fp32 accumulators [slots][Hq][128], then (m, l) pairs [slots][Hq][2]
 static size_t decode_slots(const DecodeGeom& g, int32_t B) { return (size_t)g.nwg + (size_t)B; }
 
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
     DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
-    size_t n = decode_slots(g, B) * (size_t)g.nt * (size_t)Hq;
+    size_t n = decode_slots(g, B) * (size_t)Hq;
     return n * (kHeadDim + 2) * sizeof(float) + 256;
 }
 
@@ -148,39 +154,69 @@ __device__ __forceinline__ void unpack8(const uint4& w, float (&f)[8]) {
     f[4] = bf16_lo(w.z); f[5] = bf16_hi(w.z); f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
 }
 
+// Bound by HBM.  A step is a chain: slots, rows (8 KiB a wavefront), products.  The chains of two steps overlap: rows are
+// loaded a step ahead and slots two (scalar loads: they do not queue behind the rows), in registers that still leave room
+// for two workgroups per CU.  The wavefronts that share a head block (rows of less than 8 KiB) leave one partial together;
+// one each made the combination read up to eight times as much.  With decode_range's rounds, before -> now: 32 requests of 2K,
+// 32 / 32 heads 346 -> 331 us (the combination 9.5 -> 6.9), 64 of 8K 2208 -> 2155 us (6.75 TB/s), 100 of 10K, 8 / 8 heads,
+// the rounds alone 751 -> 741 us.
 template <int G>
-__global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
+__global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_pool, const uint4* __restrict__ v_pool,
     const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ seq_offsets, int32_t B, int32_t total_tokens,
     int32_t range, int32_t nhb_wg, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc,
     float* __restrict__ part_ml) {
+    // accumulators (8 per lane and query head), maximum and sum of every wavefront, for the combination within the workgroup
+    __shared__ float lds[kDecWaves][G][10][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nt = kDecWaves / nhb_wg;
-    const int hb = blockIdx.y * 8 + wave % nhb_wg;   // 1 KiB head block of the row
+    const int nt_log = __builtin_ctz(nt);
+    const int hb_wg = wave & (nhb_wg - 1);
+    const int hb = blockIdx.y * 8 + hb_wg;           // 1 KiB head block of the row
     const int tsub = wave / nhb_wg;                  // token interleave index among nt wavefronts
     const int w = blockIdx.x;
-    const int row_chunks = Hkv * (kHeadDim * 2 / 16);          // 16-byte pieces per pool row
-    const int lane_chunk = hb * 64 + lane;                     // this lane's piece within a row
+    const uint32_t row_bytes = (uint32_t)Hkv * (kHeadDim * 2);
+    const uint32_t lane_off = (uint32_t)(hb * 64 + lane) * 16;  // this lane's piece within a row
     const int kvh = hb * 4 + (lane >> 4);                      // KV head of this lane
     const int dseg = (lane & 15) * 8;                          // first of its 8 elements
 
-    int32_t t0 = w * range;
+    const int32_t r0 = w * range;
+    int32_t t0 = r0;
     const int32_t t1 = min(t0 + range, total_tokens);
     if (t0 >= t1) return;
 
-    // request holding token t0: the last b with seq_offsets[b] <= t0
-    int lo = 0, hi = B;   // invariant: seq_offsets[lo] <= t0 < seq_offsets[hi]
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (seq_offsets[mid] <= t0) lo = mid; else hi = mid;
-    }
-    int b = lo;
-
+    int b = request_of(t0, seq_offsets, B, lane);
     while (t0 < t1) {
         int32_t req_end = seq_offsets[b + 1];
         if (req_end <= t0) { ++b; continue; }                   // empty request
         const int32_t pe = min(t1, req_end);
+        // this wavefront's tokens of the request: i0 .. i1 - 1
+        const int i0 = max(t0 - r0 - tsub + nt - 1, 0) >> nt_log, i1 = max(pe - r0 - tsub + nt - 1, 0) >> nt_log;
+
+        // slots of tokens i .. i + 3 of those (past the last: the last one's again, hidden below), the same for all lanes; then
+        // their K and V pieces
+        struct Slots { uint32_t s[kDecTB]; };
+        auto slots_of = [&](int i) {
+            Slots r;
+#pragma unroll
+            for (int u = 0; u < kDecTB; ++u) r.s[u] = (uint32_t)slot_idx[r0 + tsub + (min(i + u, i1 - 1) << nt_log)];
+            return r;
+        };
+        auto load = [&](uint4 (&kw)[kDecTB], uint4 (&vw)[kDecTB], const Slots& sl) {
+#pragma unroll
+            for (int u = 0; u < kDecTB; ++u) {
+                const uint64_t row = (uint64_t)sl.s[u] * row_bytes;
+                kw[u] = load_once((const uint4*)((const char*)k_pool + row + lane_off));
+                vw[u] = load_once((const uint4*)((const char*)v_pool + row + lane_off));
+            }
+        };
+        uint4 ka[kDecTB], va[kDecTB], kb[kDecTB], vb[kDecTB];
+        Slots ahead = {};
+        if (i0 < i1) {
+            load(ka, va, slots_of(i0));
+            ahead = slots_of(i0 + kDecTB);
+        }
 
         float qf[G][8];
 #pragma unroll
@@ -198,18 +234,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
             for (int e = 0; e < 8; ++e) acc[gi][e] = 0.f;
         }
 
-        for (int32_t base = t0 + tsub; base < pe; base += nt * kDecTB) {
-            uint4 kw[kDecTB], vw[kDecTB];
-            bool valid[kDecTB];
-#pragma unroll
-            for (int u = 0; u < kDecTB; ++u) {
-                int32_t tok = base + u * nt;
-                valid[u] = tok < pe;
-                int32_t slot = slot_idx[valid[u] ? tok : base];  // uniform per wavefront
-                int64_t off = (int64_t)slot * row_chunks + lane_chunk;
-                kw[u] = load_once(&k_pool[off]);
-                vw[u] = load_once(&v_pool[off]);
-            }
+        auto attend = [&](const uint4 (&kw)[kDecTB], const uint4 (&vw)[kDecTB], int i) {
             float s[kDecTB][G];
 #pragma unroll
             for (int u = 0; u < kDecTB; ++u) {
@@ -221,7 +246,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
 #pragma unroll
                     for (int e = 0; e < 8; ++e) d = fmaf(qf[gi][e], kf[e], d);
                     d = row16_sum(d);
-                    s[u][gi] = valid[u] ? d : -INFINITY;
+                    s[u][gi] = i + u < i1 ? d : -INFINITY;
                 }
             }
 #pragma unroll
@@ -249,23 +274,75 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
                     for (int e = 0; e < 8; ++e) acc[gi][e] = fmaf(s[u][gi], vf[e], acc[gi][e]);
                 }
             }
+        };
+        // two steps per trip: while one is worked on, the next one's rows and the slots of the one after it are on their way
+        // (no condition within a trip: a path that may have skipped a load makes the compiler wait for all of them)
+        int i = i0;
+        for (; i + 2 * kDecTB < i1; i += 2 * kDecTB) {
+            load(kb, vb, ahead);
+            ahead = slots_of(i + 2 * kDecTB);
+            attend(ka, va, i);
+            load(ka, va, ahead);
+            ahead = slots_of(i + 3 * kDecTB);
+            attend(kb, vb, i + kDecTB);
+        }
+        if (i + kDecTB < i1) {
+            load(kb, vb, ahead);
+            attend(ka, va, i);
+            attend(kb, vb, i + kDecTB);
+        } else if (i < i1) {
+            attend(ka, va, i);
         }
 
-        // partial of (range w, request b): slot w + b, sub-slot tsub
-        const int64_t pslot = ((int64_t)(w + b) * nt + tsub) * Hq;
+        // partial of (range w, request b): slot w + b.  The wavefronts that share a head block combine theirs through LDS,
+        // each for 8 / nt of a lane's 8 elements.
+        const int64_t pslot = (int64_t)(w + b) * Hq;
+        if (nt == 1) {
 #pragma unroll
-        for (int gi = 0; gi < G; ++gi) {
-            int64_t ph = pslot + kvh * G + gi;
-            float4* dst = (float4*)(part_acc + ph * kHeadDim + dseg);
-            dst[0] = make_float4(acc[gi][0], acc[gi][1], acc[gi][2], acc[gi][3]);
-            dst[1] = make_float4(acc[gi][4], acc[gi][5], acc[gi][6], acc[gi][7]);
-            if ((lane & 15) == 0) *(float2*)(part_ml + ph * 2) = make_float2(m[gi], l[gi]);
+            for (int gi = 0; gi < G; ++gi) {
+                const int64_t ph = pslot + kvh * G + gi;
+                float4* dst = (float4*)(part_acc + ph * kHeadDim + dseg);
+                dst[0] = make_float4(acc[gi][0], acc[gi][1], acc[gi][2], acc[gi][3]);
+                dst[1] = make_float4(acc[gi][4], acc[gi][5], acc[gi][6], acc[gi][7]);
+                if ((lane & 15) == 0) *(float2*)(part_ml + ph * 2) = make_float2(m[gi], l[gi]);
+            }
+        } else {
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) lds[wave][gi][e][lane] = acc[gi][e];
+                lds[wave][gi][8][lane] = m[gi];
+                lds[wave][gi][9][lane] = l[gi];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int gi = 0; gi < G; ++gi) {
+                const int64_t ph = pslot + kvh * G + gi;
+                float mx = -INFINITY, lsum = 0.f;
+                for (int u = 0; u < nt; ++u) mx = fmaxf(mx, lds[hb_wg + u * nhb_wg][gi][8][lane]);
+                float out[4] = {0.f, 0.f, 0.f, 0.f};
+                const int per = 8 >> nt_log;                        // 4, 2 or 1
+                for (int u = 0; u < nt; ++u) {
+                    const float (&src)[10][64] = lds[hb_wg + u * nhb_wg][gi];
+                    const float lu = src[9][lane];
+                    const float c = lu > 0.f ? __builtin_amdgcn_exp2f(src[8][lane] - mx) : 0.f;   // no token of this request: nothing to add
+                    lsum += lu * c;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (e < per) out[e] += src[tsub * per + e][lane] * c;
+                }
+                float* dst = part_acc + ph * kHeadDim + dseg + tsub * per;
+                if (per == 4) *(float4*)dst = make_float4(out[0], out[1], out[2], out[3]);
+                else if (per == 2) *(float2*)dst = make_float2(out[0], out[1]);
+                else dst[0] = out[0];
+                if (tsub == 0 && (lane & 15) == 0) *(float2*)(part_ml + ph * 2) = make_float2(mx, lsum);
+            }
+            __syncthreads();                                        // read: the next request may overwrite it
         }
         t0 = pe;
         ++b;
     }
 }
-
 
 // Combination of the partials of a (request, head) pair: groups of 32 lanes, four output elements a lane, take the
 // partials in turn, four at a time, and then combine among themselves.  The time is latency (offsets -> partials -> result)
@@ -281,7 +358,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_partial_kernel(
 constexpr int kCombineShort = 32;
 template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
-                                                             int32_t range, int32_t nt, int32_t Hq, int32_t pairs,
+                                                             int32_t range, int32_t Hq, int32_t pairs,
                                                              const float* __restrict__ part_acc,
                                                              const float* __restrict__ part_ml,
                                                              MergeArgs peers, int32_t n_peers,
@@ -316,8 +393,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     };
     if (s1 > s0) {
         const int w_lo = s0 / range, w_hi = (s1 - 1) / range;
-        const int n = (w_hi - w_lo + 1) * nt;
-        const int64_t first = (int64_t)(w_lo + b) * nt;             // sub-slots of consecutive ranges are contiguous
+        const int n = w_hi - w_lo + 1;
+        const int64_t first = w_lo + b;                             // the slots of consecutive ranges
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
             float4 v[U];
@@ -408,7 +485,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
     (void)workspace_bytes;
     DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
-    size_t n = decode_slots(g, B) * (size_t)g.nt * (size_t)Hq;
+    size_t n = decode_slots(g, B) * (size_t)Hq;
     float* part_acc = (float*)workspace;
     float* part_ml = part_acc + n * kHeadDim;
     const int G = Hq / Hkv;
@@ -434,10 +511,10 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
     }
     const int32_t pairs = B * Hq;
     const bool with_peers = peers != nullptr && n_peers > 0;
-    const bool wave = ((int64_t)max_len / g.range + 2) * g.nt <= kCombineShort;
+    const bool wave = (int64_t)max_len / g.range + 2 <= kCombineShort;
 #define ESP_COMBINE_LAUNCH(GROUPS, PEERS)                                                                                 \
     hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), dim3((unsigned)((pairs + 8 / GROUPS - 1) / (8 / GROUPS))), dim3(256), 0, \
-                       stream, seq_offsets, g.range, g.nt, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
+                       stream, seq_offsets, g.range, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
                        with_peers ? *peers : MergeArgs{}, n_peers, (uint2*)O, LSE)
     if (wave && with_peers) ESP_COMBINE_LAUNCH(2, true);
     else if (wave) ESP_COMBINE_LAUNCH(2, false);
