@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     constexpr int kLdsV = 0, kLdsK = kLdsV + kStages * kTileBytes, kLdsPos = kLdsK + kStages * kKTileBytes,
                   kLdsQmm = kLdsPos + kStages * kBN * 4, kLdsSched = kLdsQmm + 2 * kPfWaves * 4,
                   kLdsFlag = kLdsSched + kPfWaves * 64 * 8, kLdsSlot = kLdsFlag + 16,
-                  kLdsTotal = kLdsSlot + (RETAIN ? 8 * kBN * 4 : POOL ? kStages * kBN * 4 : 0);
+                  kLdsK0 = kLdsSlot + (RETAIN ? 8 * kBN * 4 : POOL ? (kStages + 1) * kBN * 4 : 0), kLdsTotal = kLdsK0 + kKTileBytes;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kLdsTotal];
     int32_t (*lds_pos)[kBN] = (int32_t (*)[kBN])(smem + kLdsPos);
     int32_t (*lds_qmm)[kPfWaves] = (int32_t (*)[kPfWaves])(smem + kLdsQmm);
@@ -348,6 +348,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const uint32_t pv0 = POOL ? pool_key(st_r0, (st_p ^ ((st_r0 & 3) << 2)) << 4) : 0;
     const uint32_t pv1 = POOL ? pool_key(st_r1, (st_p ^ ((st_r1 & 3) << 2)) << 4) : 0;
     // the row's address: its slot from ring stage st, one 32 x 32 -> 64-bit multiply-add
+    // (POOL: ring stage kStages holds the slots of tile 0)
     auto pool_slot = [&](int st, uint32_t key) { return *(const int32_t*)(smem + kLdsSlot + st * (kBN * 4) + (key & 0xff)); };
     auto pool_at = [&](const char* base, int32_t slot, uint32_t key) {
         return base + ((uint64_t)(uint32_t)slot * kv_row_bytes + (key >> 8));
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // memory pipeline and stalls the issuing wavefronts).  `tail`: it is the ragged last tile, whose rows past the
     // end re-read the last row (their scores get masked).
     auto fetch_k_part = [&](const char* kt, int st, bool tail, int part) {
-        const uint32_t ko = lds_k0 + st * kKTileBytes;
+        const uint32_t ko = st == kStages ? lds_base + kLdsK0 : lds_k0 + st * kKTileBytes;
         const int n = part == 0 ? wave : part == 1 ? wave + 8 : 16;
         if (part == 2 && wave != 7) return;
         if constexpr (POOL) { load_to_lds_b128_at(ko + 1024 * n, pool_src(kreq, st, part == 0 ? pk0 : part == 1 ? pk1 : pk2)); return; }
@@ -383,14 +384,14 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         else load_to_lds_b128(ko + 1024 * n, kt, part == 0 ? gk0 : part == 1 ? gk1 : gk2);
     };
     // V tile at vt and its positions at pt into V stage st: 2 transfers per wavefront, 3 for wavefront 0
-    auto fetch_v_part = [&](const char* vt, const int32_t* pt, int st, bool tail, int part) {
+    auto fetch_v_part = [&](const char* vt, const int32_t* pt, int st, bool tail, int part, int slot_st = -1) {
         const uint32_t vo = lds_v0 + st * kTileBytes + wave * 2048;
         const int last = tail_rows - 1;
         if (part == 2) {
             if (wave != 0) return;
             load_to_lds_b32(lds_p0 + st * (kBN * 4), pt, (tail ? min(lane, last) : lane) * 4);
         } else if constexpr (POOL) {
-            load_to_lds_b128_at(vo + 1024 * part, pool_src(vreq, st, part == 0 ? pv0 : pv1));
+            load_to_lds_b128_at(vo + 1024 * part, pool_src(vreq, slot_st < 0 ? st : slot_st, part == 0 ? pv0 : pv1));
         } else if (__builtin_expect(tail, 0)) {
             const int r = part == 0 ? st_r0 : st_r1;
             load_to_lds_b128(vo + 1024 * part, vt, v_goff(r, min(r, last)));
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (lane >= tail_rows) ((int32_t*)(smem + kLdsSlot))[(ragged_tile & 7) * kBN + lane] = -1;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
-    // K and V rows of tile t (both in stage st) to the pool, at the top of iteration t.  Every wavefront stores
+    // K and V rows of tile t (both in stage st, K(0) in its own place) to the pool, at the top of iteration t.  Every wavefront stores
     // exactly the LDS bytes its own transfers fill: of V the rows 8w .. 8w+7, of K the 1 KiB pieces w and w + 8 of
     // the padded tile (wavefront 7 also the 17th), lane L the 16 bytes at 1024 n + 16 L, i.e. row B / 272 at
     // B % 272 (nothing if that is padding).  The K stage is refilled during this very iteration, but each
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (!KEEP) return;
         if (t < own_lo || t >= own_hi) return;
         const int32_t* ring = (const int32_t*)(smem + kLdsSlot) + (t & 7) * kBN;
-        const unsigned char* kt = smem + kLdsK + st * kKTileBytes;
+        const unsigned char* kt = smem + (t == 0 ? kLdsK0 : kLdsK + st * kKTileBytes);
         const unsigned char* vt = smem + kLdsV + st * kTileBytes;
         const int r0 = wave * 8 + st_sub, r1 = r0 + 4;
         const int b0 = 1024 * wave + 16 * lane, b1 = b0 + 8192, b2 = 16384 + 16 * lane;
@@ -467,25 +468,38 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int my_qpos = a.causal ? a.q_pos[any_row ? tok0 + token_of(ld_i) : 0] : INT_MAX - 1;   // INT_MAX marks rows past a ragged tail
 
     // the first tiles are requested right away, so that their latency hides behind the Q load and the schedule
-    // scan (tiles the scan later finds hidden are fetched for nothing, which is harmless: they exist)
+    // scan (tiles the scan later finds hidden are fetched for nothing, which is harmless: they exist).  K(0) has a place of its
+    // own, outside the ring: iteration 0 fetches K(4) into stage 0, while a wavefront that is behind may still be at the
+    // scores of tile 0.
+    // POOL: the slots of the first five tiles go first (tile 0's to a fifth ring stage, so that tile 4's need not wait for its
+    // readers), positions and Q are asked for with them, and the transfers start when all of that has landed.  Measured
+    // against slots, transfers, positions and Q one after the other: 64 tokens on 4096 rows, 32 / 32 heads, 35.1 -> 31.6 us; 300
+    // on 20300, 32 / 8, 112.4 -> 109.1 us.  (Dense rows: V(1), K(2) and K(3) held back until positions and Q had landed
+    // gained nothing with many items, and 512 tokens alone took 20.6 instead of 20.2 us.)
+    auto fetch_first = [&]() {
+        if (nkt > 4) {                                               // the usual case, without a conditional in it
+            fetch_k(kreq, kStages, false);
+            fetch_v_part(vreq, preq, 0, false, 0, kStages); fetch_v_part(vreq, preq, 0, false, 1, kStages); fetch_v_part(vreq, preq, 0, false, 2);
+            fetch_k(kreq + tile_bytes, 1, false); fetch_v(vreq + tile_bytes, preq + kBN, 1, false);
+            fetch_k(kreq + 2 * tile_bytes, 2, false);
+            fetch_k(kreq + 3 * tile_bytes, 3, false);
+            fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
+        } else {
+            fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
+            if (nkt > 0) {
+                const bool tail = 0 == ragged_tile;
+                fetch_k(kreq, kStages, tail);
+                fetch_v_part(vreq, preq, 0, tail, 0, kStages); fetch_v_part(vreq, preq, 0, tail, 1, kStages); fetch_v_part(vreq, preq, 0, tail, 2);
+            }
+            if (nkt > 1) { fetch_k(kreq + tile_bytes, 1, 1 == ragged_tile); fetch_v(vreq + tile_bytes, preq + kBN, 1, 1 == ragged_tile); }
+            if (nkt > 2) fetch_k(kreq + 2 * tile_bytes, 2, 2 == ragged_tile);
+            if (nkt > 3) fetch_k(kreq + 3 * tile_bytes, 3, 3 == ragged_tile);
+        }
+    };
     if constexpr (POOL) {
-        // the first four tiles' slots must be in LDS, and visible to every wavefront, before the first transfer
-        fetch_pool_slots(0, 0); fetch_pool_slots(1, 1); fetch_pool_slots(2, 2); fetch_pool_slots(3, 3);
-        wait_vm<0>();
-        wg_barrier();
-    }
-    if (nkt > 4) {                                                   // the usual case, without a conditional in it
-        fetch_k(kreq, 0, false); fetch_v(vreq, preq, 0, false);
-        fetch_k(kreq + tile_bytes, 1, false); fetch_v(vreq + tile_bytes, preq + kBN, 1, false);
-        fetch_k(kreq + 2 * tile_bytes, 2, false);
-        fetch_k(kreq + 3 * tile_bytes, 3, false);
-        fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
+        fetch_pool_slots(0, kStages); fetch_pool_slots(1, 1); fetch_pool_slots(2, 2); fetch_pool_slots(3, 3); fetch_pool_slots(4, 0);
     } else {
-        fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
-        if (nkt > 0) { fetch_k(kreq, 0, 0 == ragged_tile); fetch_v(vreq, preq, 0, 0 == ragged_tile); }
-        if (nkt > 1) { fetch_k(kreq + tile_bytes, 1, 1 == ragged_tile); fetch_v(vreq + tile_bytes, preq + kBN, 1, 1 == ragged_tile); }
-        if (nkt > 2) fetch_k(kreq + 2 * tile_bytes, 2, 2 == ragged_tile);
-        if (nkt > 3) fetch_k(kreq + 3 * tile_bytes, 3, 3 == ragged_tile);
+        fetch_first();
     }
     // V stage 3 stands in for the tile before the first one (the loop multiplies the last chunk of tile j-1 at the
     // start of iteration j): zero it, since stale LDS contents could be NaN patterns; V(3) arrives there later
@@ -556,10 +570,12 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     int n_vis = nkt, first_mask = nkt, n_need = nkt;
     int2* lds_mm = (int2*)(smem + kLdsSched);
     if (a.causal) lds_mm[tid] = mm_first;
+    if constexpr (POOL) {
+        wait_vm<0>();                                               // the slots have landed, and Q: said in a way the compiler understands
+        asm volatile("" :: "v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(qf[4]), "v"(qf[5]), "v"(qf[6]), "v"(qf[7]));
+    }
     wg_barrier();          // LDS only: the Q loads and tile transfers stay in flight
-    // (POOL: every wavefront has issued its first transfers, i.e. read the slots of tile 0: those of tile 4, which
-    // iteration 0 asks for, may replace them; they land before the wait that ends the prologue)
-    fetch_pool_slots(4, 0);
+    if constexpr (POOL) fetch_first();
     if (a.causal) {
         int wg_qmax = lds_qmm[1][0];
 #pragma unroll
@@ -749,7 +765,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // MFMA (32 cycles) in front of every 5-6 other instructions of both wavefronts.
     // On entry: scores of tile j in sbuf[PAR]; frk = K fragments 0, 1 of tile j+1; frv = V^T fragments 12, 13
     // of tile j-1; pf[1][1] = last chunk of tile j-1 (zeros, and a zeroed V stage, when j = 0).
-    // LDS stages: K(t), V(t) and the positions of tile t live in stage t % 4.  Iteration j reads K(j+1), the
+    // LDS stages: K(t), V(t) and the positions of tile t live in stage t % 4 (K(0): in a place of its own).  Iteration j reads K(j+1), the
     // first two fragments of K(j+2), V(j-1) (steps 0, 1) and V(j); it fetches K(j+4) over K(j), last read in
     // iteration j-1, and V(j+2) over V(j-2), last read in the first steps of iteration j-1: both before the
     // barrier that ended iteration j-1.  What a wavefront fetched in iteration j-1 has landed before the barrier
@@ -835,7 +851,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                                     "v"(pf[1][1].v) : "memory");
     };
 
-    // ---- prologue: K(0..3), V(0), V(1) were requested at kernel entry; S^T of tile 0, first fragments
+    // ---- prologue: K(0..3), V(0), V(1) were requested above; S^T of tile 0, first fragments
     wait_vm<0>();
     // the Q fragments have landed with everything else; said in a way the compiler's own bookkeeping of loads
     // in flight understands, or every later reuse of these registers makes it wait for "pending" loads
@@ -844,8 +860,12 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     if (ragged_tile >= 0 && ragged_tile < 2) seal_slots();          // (in every other case before the iteration ahead of its own)
     wg_barrier();
     if (n_need > 0) {
-        read_k(0, 0, 0);
-        read_k(1, 0, 1);
+        const uint32_t k_rd0 = k_rd + (uint32_t)(kLdsK0 - kLdsK);
+        auto read_k0 = [&](int slot, int i) {
+            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd0 + (i & 1) * (32 * kKRow) + (i >> 1) * 32);
+        };
+        read_k0(0, 0);
+        read_k0(1, 1);
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int t = m >> 1, kvb = m & 1;
@@ -854,7 +874,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                 for (int r = 0; r < 16; ++r) sbuf[0][kvb][r] = 0.f;
             }
             sbuf[0][kvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frk[m & 1].v, qf[t], sbuf[0][kvb], 0, 0, 0);
-            read_k(m & 1, m + 2 < 16 ? 0 : 1, (m + 2) & 15);        // ends with fragments 0, 1 of tile 1 (stale if absent)
+            if (m + 2 < 16) read_k0(m & 1, m + 2);
+            else read_k(m & 1, 1, m - 14);                          // ends with fragments 0, 1 of tile 1 (stale if absent)
         }
         read_v(0, 3 * kTileBytes, 12);                              // the zeroed stage: there is no tile -1
         read_v(1, 3 * kTileBytes, 13);

@@ -396,6 +396,27 @@ def test_decode_request_search_and_range_edges(esp, cuda, requests, top, Hq, Hkv
     assert torch.isneginf(LSE[empty]).all() and (O[empty] == 0).all()
 
 
+@pytest.mark.parametrize("Tkv", [1, 64, 65, 128, 191, 256, 257, 320, 321, 384, 449])
+def test_prefill_pool_first_tiles(esp, cuda, Tkv):
+    """One to eight KV tiles, full and ragged, read from the pool: the start of an item (slots of five tiles, then six
+    tiles' transfers) has its cases here.  Bit-equal to the dense call, which is checked against the oracle."""
+    Tq, Hq, Hkv, slots = 70, 8, 2, 1024
+    g = torch.Generator(device=cuda).manual_seed(Tkv)
+    q = wl.randn_bf16((Tq, Hq, 128), g, cuda)
+    kp = wl.randn_bf16((slots, Hkv, 128), g, cuda); vp = wl.randn_bf16((slots, Hkv, 128), g, cuda)
+    idx = torch.randperm(slots, generator=g, device=cuda)[:Tkv].to(torch.int32)
+    q_pos = torch.arange(max(Tkv - Tq, 0), max(Tkv - Tq, 0) + Tq, dtype=torch.int32, device=cuda)
+    kv_pos = torch.arange(Tkv, dtype=torch.int32, device=cuda)
+    k, v = kp[idx.long()].contiguous(), vp[idx.long()].contiguous()
+    O, LSE = esp.esp_partial_attn_prefill(q, k, v, q_pos, kv_pos, softmax_scale=128 ** -0.5)
+    Op, Lp = esp.esp_partial_attn_prefill_pool_direct(q, kp, vp, idx, q_pos, kv_pos, softmax_scale=128 ** -0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(Op, O) and torch.equal(Lp, LSE)
+    Or, Lr = oracle.partial_attn_all(wl.bits(q), wl.bits(k), wl.bits(v), wl.host_i32(q_pos), wl.host_i32(kv_pos), 128 ** -0.5, True)
+    check_o_lse(O.float().cpu().numpy().reshape(-1, 128), LSE.cpu().numpy().reshape(-1), Or.reshape(-1, 128), Lr.reshape(-1),
+                f"first tiles {Tkv}")
+
+
 def test_decode_mqa_many_ranges_and_merge(esp, cuda):
     """MQA 32 / 1 at a size that is cut into many token ranges, then merged with peer partials."""
     lens = wl.lognormal_lengths(16, 6000, 10, 60000, 35)
