@@ -55,6 +55,7 @@ struct DecodeGeom {
     int32_t nhb_wg;     // 1 KiB head blocks handled by one workgroup (1, 2, 4 or 8)
     int32_t nt;         // wavefronts sharing one head block (token interleave) = 8 / nhb_wg
     int32_t ygroups;    // workgroups along y when a row has more than 8 head blocks
+    int32_t kept;       // ranges (with nt partials each) that a workspace always has to hold, see decode_range
 };
 
 // Head counts of the row-burst kernel: whole 1 KiB head blocks (4 KV heads) that split the 8 wavefronts evenly, and
@@ -77,12 +78,12 @@ static bool decode_burst_layout(int32_t Hq, int32_t Hkv) {
 // 32 / 4 210 / 209 / 220 / 233: where several workgroups gather from the same rows, a head each, a single round falls behind by
 // about 8 % of it.  64 requests of 4K, 32 / 1
 // heads: 598 workgroups of 512 tokens were three rounds of 256, 479 of 640 are one of 512.
-// `kept`: ranges that the call may have whatever they need; beyond them it takes only as many as fit the built-in block.
-static int32_t decode_range(int32_t B, int32_t total_tokens, int32_t Hq, int64_t step, int64_t least, int64_t rows, int64_t kept) {
+// `room`: ranges that the workspace holds (as far as the built-in block would, so that both calls agree); `kept`: ranges that
+// every workspace holds which is not refused (those of a simpler rule, by which workspaces are also measured).
+static int32_t decode_range(int32_t total_tokens, int64_t step, int64_t least, int64_t rows, int64_t kept, int64_t room) {
     constexpr int64_t kResident = 512;
     constexpr double kStart = 6, kStep = 4.8;                     // microseconds
     const double lag = rows > 1 ? 0.08 : 0;
-    const int64_t room = ((int64_t)ESP_DECODE_STATIC_SCRATCH_BYTES - 256) / ((int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float)) - B;
     int64_t most = kept > room ? kept : room;
     if (most < 1) most = 1;
     if (most > kDecMaxWG) most = kDecMaxWG;
@@ -103,41 +104,53 @@ static int32_t decode_range(int32_t B, int32_t total_tokens, int32_t Hq, int64_t
     return (int32_t)(best * step);
 }
 
-static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
+static int64_t partial_bytes(int32_t Hq) { return (int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float); }
+
+static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv, size_t bytes) {
     DecodeGeom g;
+    if (bytes > (size_t)ESP_DECODE_STATIC_SCRATCH_BYTES) bytes = ESP_DECODE_STATIC_SCRATCH_BYTES;
+    const int64_t room = ((int64_t)bytes - 256) / partial_bytes(Hq) - B;
     // ranges of total_tokens in `unit`s, at least `least` tokens each and at most kDecMaxWG of them
     auto ranges = [&](int64_t least, int64_t unit) {
         int64_t want = ((int64_t)total_tokens + kDecMaxWG - 1) / kDecMaxWG;
         if (want < least) want = least;
         want = (want + unit - 1) / unit * unit;
-        return ((int64_t)total_tokens + want - 1) / want;
+        return (int32_t)(((int64_t)total_tokens + want - 1) / want);
     };
     if (!decode_burst_layout(Hq, Hkv)) {
         // matrix-core kernel: every wavefront of a workgroup works on the same KV head, a tile of 32 tokens each per step
         g.nhb_wg = 0;
         g.nt = 1;
         g.ygroups = Hkv;
-        g.range = decode_range(B, total_tokens, Hq, kGqWaves * 32, 1, (int64_t)Hkv * ((Hq / Hkv + 31) / 32), ranges(512, 256));
+        g.kept = ranges(512, 256);
+        g.range = decode_range(total_tokens, kGqWaves * 32, 1, (int64_t)Hkv * ((Hq / Hkv + 31) / 32), g.kept, room);
     } else {
         const int nhb = Hkv / 4;
         g.nhb_wg = nhb < 8 ? nhb : 8;
         g.nt = kDecWaves / g.nhb_wg;
         g.ygroups = (nhb + 7) / 8;
         const int64_t step = (int64_t)g.nt * kDecTB;                 // tokens one workgroup consumes per loop step
-        g.range = decode_range(B, total_tokens, Hq, step, 2, g.ygroups, ranges(8 * step, step));
+        g.kept = ranges(8 * step, step);
+        g.range = decode_range(total_tokens, step, 2, g.ygroups, g.kept, room);
     }
     g.nwg = (int32_t)(((int64_t)total_tokens + g.range - 1) / g.range);
     if (g.nwg < 1) g.nwg = 1;
+    if (g.kept < 1) g.kept = 1;
     return g;
 }
 
 // workspace: fp32 accumulators [slots][Hq][128], then (m, l) pairs [slots][Hq][2]
 static size_t decode_slots(const DecodeGeom& g, int32_t B) { return (size_t)g.nwg + (size_t)B; }
 
+// the least a call takes, and what it asks for: room for the ranges it would like to have
+size_t decode_least_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
+    const DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, 0);
+    return ((size_t)g.kept + (size_t)B) * (size_t)g.nt * (size_t)partial_bytes(Hq) + 256;
+}
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv) {
-    DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
-    size_t n = decode_slots(g, B) * (size_t)Hq;
-    return n * (kHeadDim + 2) * sizeof(float) + 256;
+    const DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, ESP_DECODE_STATIC_SCRATCH_BYTES);
+    const size_t want = decode_slots(g, B) * (size_t)partial_bytes(Hq) + 256, least = decode_least_workspace_bytes(B, total_tokens, Hq, Hkv);
+    return want > least ? want : least;
 }
 
 __device__ __forceinline__ float row16_sum(float x) {
@@ -468,7 +481,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                                 const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                                 int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream) {
-    const size_t need = decode_workspace_bytes(B, total_tokens, Hq, Hkv);
+    const size_t need = decode_least_workspace_bytes(B, total_tokens, Hq, Hkv);
     if (need > (size_t)ESP_DECODE_STATIC_SCRATCH_BYTES)
         return fail(ESP_ERR_WORKSPACE, "decode (static scratch): this call needs %zu bytes of scratch memory, the built-in block holds %zu; "
                     "use esp_partial_attn_decode with a workspace", need, (size_t)ESP_DECODE_STATIC_SCRATCH_BYTES);
@@ -483,8 +496,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
-    (void)workspace_bytes;
-    DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv);
+    DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, workspace_bytes);
     size_t n = decode_slots(g, B) * (size_t)Hq;
     float* part_acc = (float*)workspace;
     float* part_ml = part_acc + n * kHeadDim;

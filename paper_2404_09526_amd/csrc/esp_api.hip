@@ -281,7 +281,7 @@ esp_status esp_partial_attn_decode(const void* q, const void* k_pool, const void
     esp_status st = decode_check(q, k_pool, v_pool, num_slots, slot_idx, seq_offsets, B, total_tokens, max_len, Hq, Hkv, D,
                                  softmax_scale, O, LSE, &done);
     if (st != ESP_OK || done) return st;
-    size_t need = decode_workspace_bytes(B, total_tokens, Hq, Hkv);
+    size_t need = decode_least_workspace_bytes(B, total_tokens, Hq, Hkv);
     if (!workspace || workspace_bytes < need)
         return fail(ESP_ERR_WORKSPACE, "decode: workspace needs %zu bytes, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if ((uintptr_t)workspace & 255) return fail(ESP_ERR_WORKSPACE, "decode: workspace not 256-byte aligned");
@@ -333,7 +333,7 @@ esp_status esp_partial_attn_decode_merge(const void* q, const void* k_pool, cons
             peers.LSE_parts[p] = peer_LSE[p];
         }
     }
-    size_t need = decode_workspace_bytes(B, total_tokens, Hq, Hkv);
+    size_t need = decode_least_workspace_bytes(B, total_tokens, Hq, Hkv);
     if (!workspace || workspace_bytes < need)
         return fail(ESP_ERR_WORKSPACE, "decode: workspace needs %zu bytes, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if ((uintptr_t)workspace & 255) return fail(ESP_ERR_WORKSPACE, "decode: workspace not 256-byte aligned");

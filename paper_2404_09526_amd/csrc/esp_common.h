@@ -67,6 +67,7 @@ esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_
                         hipStream_t stream, int32_t o_f32 = 0);
 
 size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv);
+size_t decode_least_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv);
 esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                          const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
