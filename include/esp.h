@@ -38,7 +38,8 @@
  *     decreasing, with no piece above the stated maximum; decode slots must lie
  *     in [0, num_slots); append slots must be below num_slots and, where not
  *     negative, distinct.  A violation returns ESP_ERR_INVALID_ARG.
- *   - A row with no visible key yields O = 0 and LSE = -inf, never NaN.
+ *   - A row with no visible key yields O = 0 and LSE = -inf, never NaN.  A row
+ *     that sees a key with a NaN score yields NaN in both.
  *   - LSE is the natural logarithm of the sum of exp(softmax_scale * q.k)
  *     over the visible keys.
  */
@@ -203,7 +204,8 @@ esp_status esp_partial_attn_decode_merge(
  * results "sent back to the master", Sec. 4.2).  For each (token, head):
  *   m = max_p LSE_p,  w_p = exp(LSE_p - m),
  *   O = sum_p w_p O_p / sum_p w_p,   LSE = m + ln sum_p w_p.
- * Partials with LSE = -inf weigh 0; all -inf gives O = 0, LSE = -inf.
+ * Partials with LSE = -inf weigh 0; all -inf gives O = 0, LSE = -inf.  A NaN
+ * LSE_p makes the pair's O and LSE NaN.
  *
  *   O_parts, LSE_parts: HOST arrays of P device pointers (1 <= P <=
  *     ESP_MAX_PARTIALS) to bf16 [T,Hq,D] and float [T,Hq]; read before return.

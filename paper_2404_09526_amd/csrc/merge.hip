@@ -19,15 +19,18 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
     int seg = (int)(i & 15);
 
     float m = -INFINITY;
+    bool nan = false;                               // a NaN log-sum-exp makes the pair NaN (the maximum passes it over)
     float lse[ESP_MAX_PARTIALS];
 #pragma unroll
     for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
         lse[p] = (p < P) ? parts.LSE_parts[p][pair] : -INFINITY;
         m = fmaxf(m, lse[p]);
+        nan |= lse[p] != lse[p];
     }
+    const bool empty = m == -INFINITY && !nan;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float wsum = 0.f;
-    if (m != -INFINITY) {
+    if (!empty) {
 #pragma unroll
         for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
             if (p < P) {
@@ -54,7 +57,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] *= inv;
     }
-    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = (m == -INFINITY) ? -INFINITY : m + __logf(wsum);
+    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = empty ? -INFINITY : m + __logf(wsum);
     if (OUT32) {
         float4* dst = (float4*)O + (pair * 16 + seg) * 2;
         dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);

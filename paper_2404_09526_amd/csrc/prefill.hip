@@ -1096,8 +1096,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
         }
     }
+    // -inf says that the row saw no key (a sum of 0, exactly), and a merge leaves the row out; a sum that is NaN has to show
     if (row_ok && hi == 0)
-        *(float*)((char*)(a.LSE + row0 + row_of(my_i)) + part * a.lse_part) = ltot > 0.f ? (m_fin + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
+        *(float*)((char*)(a.LSE + row0 + row_of(my_i)) + part * a.lse_part) = ltot != 0.f ? (m_fin + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
     if (claim_from && tid == 0) *lds_next = draw_finish(claim_from, next_item);
     return true;
     };
