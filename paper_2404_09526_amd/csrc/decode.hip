@@ -368,7 +368,11 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
 // PEERS: the master of a multi-master decode (Sec. 4.2) also holds the partial results its peers returned for the
 // same queries (bf16 O, natural-log LSE).  They enter the same log-sum-exp combination here, shared out among the groups
 // like the partials, so the local result is never rounded to bf16 on its own and no separate merge launch follows.
+//
+// A partial whose every score is NaN has the maximum -inf (maxima pass NaN over) and the sum NaN.  It must not be taken for
+// an empty one: only a sum of exactly 0 is, and where no maximum is finite the exponentials are taken against 0.
 constexpr int kCombineShort = 32;
+__device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY ? 0.f : m; }
 template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
                                                              int32_t range, int32_t Hq, int32_t pairs,
@@ -389,8 +393,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         float mx = M;
 #pragma unroll
         for (int u = 0; u < U; ++u) mx = fmaxf(mx, l[u] != 0.f ? m[u] : -INFINITY);
-        if (mx == -INFINITY) return;
-        const float c_old = __builtin_amdgcn_exp2f(M - mx);
+        const float ref = finite_offset(mx);
+        const float c_old = __builtin_amdgcn_exp2f(M - ref);
         M = mx;
         L *= c_old;
 #pragma unroll
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (l[u] != 0.f) {                                      // keeps the garbage of an empty partial out of the sum
-                const float c = __builtin_amdgcn_exp2f(m[u] - mx);
+                const float c = __builtin_amdgcn_exp2f(m[u] - ref);
                 L += l[u] * c;
                 acc[0] += v[u].x * c; acc[1] += v[u].y * c; acc[2] += v[u].z * c; acc[3] += v[u].w * c;
             }
@@ -444,7 +448,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     if (GROUPS == 2) {
         const float M2 = __shfl_xor(M, 32);
         mx = fmaxf(M, M2);
-        const float c = mx == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mx);
+        const float c = __builtin_amdgcn_exp2f(M - finite_offset(mx));
         Lt = L * c;
         Lt += __shfl_xor(Lt, 32);
 #pragma unroll
@@ -462,20 +466,19 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         mx = sm[0];
 #pragma unroll
         for (int u = 1; u < 8; ++u) mx = fmaxf(mx, sm[u]);
-        if (mx != -INFINITY) {
+        const float ref = finite_offset(mx);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float c = __builtin_amdgcn_exp2f(sm[u] - mx);  // exp2(-inf) = 0 for an idle group
-                const float4 t = sa[u][lane];
-                Lt += sl[u] * c;
-                o[0] += t.x * c; o[1] += t.y * c; o[2] += t.z * c; o[3] += t.w * c;
-            }
+        for (int u = 0; u < 8; ++u) {
+            const float c = __builtin_amdgcn_exp2f(sm[u] - ref);      // exp2(-inf) = 0 for an idle group
+            const float4 t = sa[u][lane];
+            Lt += sl[u] * c;
+            o[0] += t.x * c; o[1] += t.y * c; o[2] += t.z * c; o[3] += t.w * c;
         }
     }
     if (g != 0) return;
-    const float inv = mx == -INFINITY ? 0.f : 1.0f / Lt;
+    const float inv = Lt == 0.f ? 0.f : 1.0f / Lt;                  // no token anywhere: exactly 0
     O[(int64_t)pair * (kHeadDim / 4) + lane] = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
-    if (lane == 0) LSE[pair] = (mx == -INFINITY) ? -INFINITY : (mx + __builtin_amdgcn_logf(Lt)) * kLn2;
+    if (lane == 0) LSE[pair] = Lt == 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(Lt)) * kLn2;
 }
 
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,

@@ -91,3 +91,32 @@ def test_merge_keeps_a_nan_partial(esp, cuda, P, dtype):
     torch.cuda.synchronize()
     nan_pattern(O, LSE, hit, f"merge of {P}")
     assert torch.isneginf(LSE[4]).all() and (O[4] == 0).all()
+
+
+# ------------------------------------------------------------------ decode
+@pytest.mark.parametrize("peers", [0, 3])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (8, 8), (16, 16), (32, 32), (8, 4), (8, 2), (32, 8), (6, 3)])
+def test_decode_nan_key_stays_with_its_request_and_head(esp, cuda, Hq, Hkv, peers):
+    """One NaN key in one KV head of a request of one token, of one that fits a range and of one across several: that
+    request's query heads are NaN, everything else is bit for bit what it is without the NaN."""
+    lens = [1, 40, 0, 9000, 1, 700]
+    dc = wl.decode_pool(f"decode-nan ({Hq}/{Hkv})", lens, 16384, Hq, Hkv, 54, cuda, n_new=0)
+    off, slots = wl.host_i32(dc.seq_offsets), wl.host_i32(dc.slot_idx)
+
+    def call():
+        if peers:
+            return esp.esp_partial_attn_decode_merge(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, max(lens),
+                                                     list(dc.peer_O)[:peers], list(dc.peer_LSE)[:peers], softmax_scale=dc.scale)
+        return esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, max(lens), softmax_scale=dc.scale)
+
+    O0, L0 = call()
+    hit = np.zeros((len(lens), Hq), bool)
+    G = Hq // Hkv
+    for r, t, h in ((0, 0, 0), (1, 17, 1), (3, 4321, Hkv - 1)):
+        dc.k_pool[int(slots[off[r] + t]), h] = float("nan")
+        hit[r, h * G:(h + 1) * G] = True
+    O, LSE = call()
+    torch.cuda.synchronize()
+    nan_pattern(O, LSE, hit, dc.name)
+    keep = torch.from_numpy(~hit).to(cuda)
+    assert torch.equal(O[keep].view(torch.int16), O0[keep].view(torch.int16)) and torch.equal(LSE[keep].view(torch.int32), L0[keep].view(torch.int32))
