@@ -371,8 +371,14 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
 //
 // A partial whose every score is NaN has the maximum -inf (maxima pass NaN over) and the sum NaN.  It must not be taken for
 // an empty one: only a sum of exactly 0 is, and where no maximum is finite the exponentials are taken against 0.
+//
+// A peer may mark "no token" with a large negative number instead of -inf and leave its O unwritten, so an output whose weight
+// is 0 is left out rather than multiplied.  In a group that holds peers only (not `own`) that goes for the group's whole sum: it may be
+// such a peer's, taken at weight 1 before anything larger was seen.  (Not for this instance's own partials: those are written
+// whenever their sum is not 0, and a NaN in them has to show.)
 constexpr int kCombineShort = 32;
 __device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY ? 0.f : m; }
+template <int V> struct IC { static constexpr int value = V; };
 template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
                                                              int32_t range, int32_t Hq, int32_t pairs,
@@ -388,8 +394,10 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1];
     float M = -INFINITY, L = 0.f;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    bool own = false;                                               // this group holds partials of this instance
     // adds U partials (m: base-2 maximum, l: sum, 0 = nothing; v: l-weighted output)
-    auto add = [&](const float (&m)[U], const float (&l)[U], const float4 (&v)[U]) {
+    auto add = [&](auto peer_c, const float (&m)[U], const float (&l)[U], const float4 (&v)[U]) {
+        constexpr bool PEER = decltype(peer_c)::value != 0;
         float mx = M;
 #pragma unroll
         for (int u = 0; u < U; ++u) mx = fmaxf(mx, l[u] != 0.f ? m[u] : -INFINITY);
@@ -397,13 +405,15 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         const float c_old = __builtin_amdgcn_exp2f(M - ref);
         M = mx;
         L *= c_old;
+        const bool drop = PEER && !own && c_old == 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] *= c_old;
+        for (int e = 0; e < 4; ++e) acc[e] = drop ? 0.f : acc[e] * c_old;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (l[u] != 0.f) {                                      // keeps the garbage of an empty partial out of the sum
                 const float c = __builtin_amdgcn_exp2f(m[u] - ref);
                 L += l[u] * c;
+                if (PEER && c == 0.f) continue;
                 acc[0] += v[u].x * c; acc[1] += v[u].y * c; acc[2] += v[u].z * c; acc[3] += v[u].w * c;
             }
         }
@@ -424,10 +434,11 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
                 m[u] = ml.x;
                 l[u] = k < n ? ml.y : 0.f;
             }
-            add(m, l, v);
+            add(IC<0>{}, m, l, v);
         }
     }
     if (PEERS) {
+        own = L != 0.f;
         for (int p0 = g; p0 < n_peers; p0 += GROUPS * U) {
             float m[U], l[U];
             float4 v[U];
@@ -440,7 +451,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
                 l[u] = p < n_peers && lse != -INFINITY ? 1.f : 0.f;  // a peer's rows are normalised
                 v[u] = make_float4(bf16_lo(o.x), bf16_hi(o.x), bf16_lo(o.y), bf16_hi(o.y));
             }
-            add(m, l, v);
+            add(IC<1>{}, m, l, v);
         }
     }
     // ---- the groups' results: exchanged by shuffles within a wavefront, through LDS otherwise
@@ -453,13 +464,14 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         Lt += __shfl_xor(Lt, 32);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            o[e] = acc[e] * c;
+            o[e] = PEERS && !own && c == 0.f ? 0.f : acc[e] * c;
             o[e] += __shfl_xor(o[e], 32);
         }
     } else {
         __shared__ float sm[8], sl[8];
+        __shared__ bool so[8];
         __shared__ float4 sa[8][32];
-        if (lane == 0) { sm[grp] = M; sl[grp] = L; }
+        if (lane == 0) { sm[grp] = M; sl[grp] = L; so[grp] = own; }
         sa[grp][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         __syncthreads();
         if (g != 0) return;
@@ -472,6 +484,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
             const float c = __builtin_amdgcn_exp2f(sm[u] - ref);      // exp2(-inf) = 0 for an idle group
             const float4 t = sa[u][lane];
             Lt += sl[u] * c;
+            if (PEERS && !so[u] && c == 0.f) continue;
             o[0] += t.x * c; o[1] += t.y * c; o[2] += t.z * c; o[3] += t.w * c;
         }
     }

@@ -1,5 +1,5 @@
-"""Scores that are not finite: a NaN key must show in O and in LSE of every row that sees it, whichever way a call is cut
-into parts, and nowhere else."""
+"""Scores that are not finite, and partial results that mark "nothing" with a large negative number: a NaN key must show in O
+and in LSE of every row that sees it, whichever way a call is cut into parts, and nowhere else."""
 import numpy as np
 import pytest
 import torch
@@ -120,3 +120,29 @@ def test_decode_nan_key_stays_with_its_request_and_head(esp, cuda, Hq, Hkv, peer
     nan_pattern(O, LSE, hit, dc.name)
     keep = torch.from_numpy(~hit).to(cuda)
     assert torch.equal(O[keep].view(torch.int16), O0[keep].view(torch.int16)) and torch.equal(LSE[keep].view(torch.int32), L0[keep].view(torch.int32))
+
+
+@pytest.mark.parametrize("nothing", [-1e30, float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("longest", [60, 30000])
+@pytest.mark.parametrize("Hq,Hkv,n_peers", [(8, 8, 2), (8, 2, 15), (32, 32, 9)])
+def test_decode_peers_that_mark_nothing_with_a_finite_number(esp, cuda, Hq, Hkv, n_peers, longest, nothing):
+    """Peers whose LSE is the lowest there is, finite, and whose O was never written: weight 0, whichever peers they are,
+    with and without tokens of the request on this instance, whether a pair is combined by a wavefront or a workgroup."""
+    lens = [longest, 0, 1, 700]
+    dc = wl.decode_pool(f"decode-nothing ({Hq}/{Hkv})", lens, 32768, Hq, Hkv, 55, cuda, n_new=0, n_peers=n_peers)
+    kp, vp = wl.bits(dc.k_pool), wl.bits(dc.v_pool)
+    marked = np.random.default_rng(56).random((n_peers, len(lens))) < 0.6
+    marked[0, 1], marked[1, 1] = False, True                              # request 1: one peer that holds something, one that does not
+    marked[:, 3] = True                                                   # request 3: this instance alone
+    for p in range(n_peers):
+        m = torch.from_numpy(marked[p]).to(cuda)
+        dc.peer_LSE[p][m] = nothing
+        dc.peer_O[p][m] = float("nan")
+    O, LSE = esp.esp_partial_attn_decode_merge(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, max(lens),
+                                               list(dc.peer_O), list(dc.peer_LSE), softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    Or, Lr = oracle.partial_attn_decode_all(wl.bits(dc.q), kp, vp, wl.host_i32(dc.slot_idx), wl.host_i32(dc.seq_offsets), dc.scale)
+    Op = np.stack([Or] + [np.nan_to_num(oracle.bf16_bits_to_f64(wl.bits(t)), nan=0.0) for t in dc.peer_O])
+    Lp = np.stack([Lr] + [np.where(marked[p][:, None], -np.inf, dc.peer_LSE[p].cpu().numpy().astype(np.float64)) for p in range(n_peers)])
+    Oref, Lref = oracle.merge_partials(Op, Lp)
+    check_o_lse(O.float().cpu().numpy().reshape(-1, dc.D), LSE.cpu().numpy().reshape(-1), Oref.reshape(-1, dc.D), Lref.reshape(-1), dc.name)
