@@ -186,6 +186,7 @@ esp_status esp_partial_attn_decode_static(
  *   n_peers  : 0 .. ESP_MAX_PARTIALS - 1 (0: plain esp_partial_attn_decode).
  * The pointer arrays are read during the call only.  O / LSE receive the
  * FINAL result and must not overlap a peer's arrays (ESP_ERR_INVALID_ARG).
+ * The peers' arrays need 4-byte alignment (ESP_ERR_INVALID_ARG), O no more.
  * A master that holds no token of a request (seq_offsets[b+1] ==
  * seq_offsets[b]) passes its peers' combination through.  Errors as
  * esp_partial_attn_decode.

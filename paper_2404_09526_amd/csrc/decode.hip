@@ -377,6 +377,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
 // such a peer's, taken at weight 1 before anything larger was seen.  (Not for this instance's own partials: those are written
 // whenever their sum is not 0, and a NaN in them has to show.)
 constexpr int kCombineShort = 32;
+struct U32x2 { uint32_t x, y; };      // O and the peers' O: the calls ask for 4-byte alignment, not for 8
 __device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY ? 0.f : m; }
 template <int V> struct IC { static constexpr int value = V; };
 template <int GROUPS, bool PEERS>
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
                                                              const float* __restrict__ part_acc,
                                                              const float* __restrict__ part_ml,
                                                              MergeArgs peers, int32_t n_peers,
-                                                             uint2* __restrict__ O, float* __restrict__ LSE) {
+                                                             U32x2* __restrict__ O, float* __restrict__ LSE) {
     constexpr int U = 4;
     const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
     const int pair = blockIdx.x * (8 / GROUPS) + grp / GROUPS, g = grp % GROUPS;
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
             for (int u = 0; u < U; ++u) {
                 const int p = p0 + u * GROUPS, q = min(p, n_peers - 1);
                 const float lse = peers.LSE_parts[q][pair];
-                const uint2 o = ((const uint2*)peers.O_parts[q])[(int64_t)pair * (kHeadDim / 4) + lane];
+                const U32x2 o = ((const U32x2*)peers.O_parts[q])[(int64_t)pair * (kHeadDim / 4) + lane];
                 m[u] = lse * kLog2e;
                 l[u] = p < n_peers && lse != -INFINITY ? 1.f : 0.f;  // a peer's rows are normalised
                 v[u] = make_float4(bf16_lo(o.x), bf16_hi(o.x), bf16_lo(o.y), bf16_hi(o.y));
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     }
     if (g != 0) return;
     const float inv = Lt == 0.f ? 0.f : 1.0f / Lt;                  // no token anywhere: exactly 0
-    O[(int64_t)pair * (kHeadDim / 4) + lane] = make_uint2(pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv));
+    O[(int64_t)pair * (kHeadDim / 4) + lane] = U32x2{pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
     if (lane == 0) LSE[pair] = Lt == 0.f ? -INFINITY : (mx + __builtin_amdgcn_logf(Lt)) * kLn2;
 }
 
@@ -543,7 +544,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
 #define ESP_COMBINE_LAUNCH(GROUPS, PEERS)                                                                                 \
     hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), dim3((unsigned)((pairs + 8 / GROUPS - 1) / (8 / GROUPS))), dim3(256), 0, \
                        stream, seq_offsets, g.range, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
-                       with_peers ? *peers : MergeArgs{}, n_peers, (uint2*)O, LSE)
+                       with_peers ? *peers : MergeArgs{}, n_peers, (U32x2*)O, LSE)
     if (wave && with_peers) ESP_COMBINE_LAUNCH(2, true);
     else if (wave) ESP_COMBINE_LAUNCH(2, false);
     else if (with_peers) ESP_COMBINE_LAUNCH(8, true);

@@ -511,6 +511,29 @@ def test_decode_combine_sizes(esp, cuda, Hq, Hkv, longest, n_peers):
                 f"{dc.name} + {n_peers} peers")
 
 
+@pytest.mark.parametrize("longest", [60, 9000])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 2)])
+def test_decode_merge_takes_arrays_aligned_to_four_bytes(esp, cuda, Hq, Hkv, longest):
+    """The peers' O and the output two elements into their allocations: bit for bit the aligned call's result, and nothing
+    written around the output (both forms of the combination)."""
+    dc = wl.decode_pool(f"decode-aligned-4 ({Hq}/{Hkv})", [longest, 0, 33], 16384, Hq, Hkv, 39, cuda, n_new=0)
+
+    def moved(t):
+        flat = torch.zeros(t.numel() + 4, dtype=t.dtype, device=cuda)
+        flat[2:-2].copy_(t.reshape(-1))
+        return flat, flat[2:-2].view(t.shape)
+
+    args = (dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, longest)
+    O, LSE = esp.esp_partial_attn_decode_merge(*args, list(dc.peer_O), list(dc.peer_LSE), softmax_scale=dc.scale)
+    peers = [moved(t)[1] for t in dc.peer_O]
+    around, O4 = moved(torch.zeros_like(O))
+    assert all(t.data_ptr() % 8 == 4 and t.is_contiguous() for t in peers + [O4])
+    _, LSE4 = esp.esp_partial_attn_decode_merge(*args, peers, list(dc.peer_LSE), softmax_scale=dc.scale, O=O4)
+    torch.cuda.synchronize()
+    assert torch.equal(O4.view(torch.int16), O.view(torch.int16)) and torch.equal(LSE4, LSE)
+    assert (around[:2] == 0).all() and (around[-2:] == 0).all()
+
+
 def test_decode_many_ranges(esp, cuda):
     """Enough tokens that the token list is cut into many ranges, with requests spanning several of them."""
     lens = wl.lognormal_lengths(24, 3000, 10, 40000, 31)
