@@ -182,7 +182,16 @@ template <int V> struct IC { static constexpr int value = V; };
 // row, Sec. 4.1 / 4.2: KV that an instance kept stays where it was placed).  The tile transfers take each row from its
 // slot: the slots of tile t travel to a ring of 4 LDS stages (stage t % 4) one iteration before the tile's first
 // transfer is issued, every lane reads the slot of the row its 16 bytes belong to and forms the address itself.
-template <int MODE>
+//
+// ONE (with MODE 0): one request, one query head per KV head, keys uncut: the chunk or the stripe of a multi-head model.  What
+// bounds a short call of that kind is the chain of instructions in front of its first transfer and at its end, and here the
+// rows of a tile are Hq rows apart, known when it is compiled: no float arithmetic for every row that is loaded and stored, no
+// search for request, part and query head.  Measured (any call -> ONE): 256 queries against two shards of 512, 4 / 4 heads, 43.2
+// -> 40.9 us, of which the rows are 0.8, the request's search and the parts 0.7 each (one tile per query head and neither search
+// nor parts took 41.8); 700 against two of 700, 32 / 32 heads, 64.1 -> 61.4 us; 8192 against four of 8192 2004 -> 1987 us.  The
+// same for MODE 1 and 2 gained nothing: 1500 against two of 1500, kept, 8 / 8 heads, 81.9 -> 82.4 us, 2048 against 8192 rows
+// of the pool, 32 / 32 heads, 237.5 -> 237.7 us.
+template <int MODE, bool ONE>
 __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     constexpr bool RETAIN = MODE == 1, POOL = MODE == 2;
     // One LDS block, V stages first: an LDS instruction adds a 16-bit immediate to its address register, so with
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int G = a.G;
+    const int G = ONE ? 1 : a.G;
 
     // ---- one query tile of one KV head (rank: position in the heaviest-first order of query tiles).  Returns false
     //      if there is no such tile.  With `claim_from` set, thread 0 also draws the workgroup's next item from that
@@ -221,7 +230,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         }
     };
     auto process = [&](const int rank, const int vhead, unsigned long long* claim_from) {
-    const int kvh = a.splits > 1 ? vhead / a.splits : vhead, part = a.splits > 1 ? vhead - kvh * a.splits : 0;
+    const bool cut = !ONE && a.splits > 1;
+    const int kvh = cut ? vhead / a.splits : vhead, part = cut ? vhead - kvh * a.splits : 0;
     int row0, n_rows, g0, kv_lo, kv_hi;   // first row of this tile in the [token, head] order, how many it has, query head of
                                           // the group it starts at; rows of its request in the shard
     int tok0;                       // token of the first row
@@ -239,7 +249,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         // The requests are looked at 64 at a time, one per lane, from the last one down: a scan of their tile counts
         // finds the one that holds tile `rank`.
         int tl = 0, r = 0, nt = 0;
-        if (a.batch == 1) {
+        if (ONE || a.batch == 1) {
             nt = __builtin_amdgcn_readfirstlane(tiles_of(0));
             if (rank >= nt) return false;
             tl = nt - 1 - rank;
@@ -286,7 +296,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                 own_hi = tiles;
             }
         }
-        if (a.splits > 1) {                                         // this part's share of the request's tiles, as if it were the shard
+        if (cut) {                                                  // this part's share of the request's tiles, as if it were the shard
             const int tiles = (kv_hi - kv_lo + kBN - 1) / kBN;
             const int t_lo = (int)((int64_t)tiles * part / a.splits), t_hi = (int)((int64_t)tiles * (part + 1) / a.splits);
             kv_hi = min(kv_hi, kv_lo + t_hi * kBN);
@@ -303,9 +313,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     tok0 = __builtin_amdgcn_readfirstlane(tok0); g0 = __builtin_amdgcn_readfirstlane(g0);
     kv_lo = __builtin_amdgcn_readfirstlane(kv_lo); kv_hi = __builtin_amdgcn_readfirstlane(kv_hi);
     own_lo = __builtin_amdgcn_readfirstlane(own_lo); own_hi = __builtin_amdgcn_readfirstlane(own_hi);
-    // token of row i of this tile, counted from tok0 (exact: i + g0 is far below 2^21), and the row's distance from row0
-    auto token_of = [&](int i) { return (int)(((float)(i + g0) + 0.5f) * a.inv_G); };
-    auto row_of = [&](int i) { return i + token_of(i) * (a.Hq - G); };
+    // token of row i of this tile, counted from tok0 (with G > 1 exact: i + g0 is far below 2^21), and the row's distance from row0
+    auto token_of = [&](int i) { return ONE ? i : (int)(((float)(i + g0) + 0.5f) * a.inv_G); };
+    auto row_of = [&](int i) { return ONE ? i * a.Hq : i + token_of(i) * (a.Hq - G); };
     // The rest of the item exists twice in the keeping kernel: as everywhere else, and with an owner's extras.
     // (One body with the extras behind a run-time flag costs the items that own nothing dearly: measured +25 % on
     // a GQA batch, where three items in four own nothing, against +1.6 % with two bodies.)
@@ -1032,7 +1042,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // barrier above ended all tile reads) they come back as 16 lanes x 16 bytes per row, four rows per store.
     // rows of this wavefront that exist (may be <= 0); a part of a split call in which none of them sees a key leaves O
     // unwritten: its LSE, -inf, keeps it out of the merge
-    const int rows_here = a.splits > 1 && n_need == 0 ? 0 : min(32, n_rows - wave * 32);
+    const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - wave * 32);
     char* const O_part = (char*)a.O + part * a.o_part;
     if (!a.o_f32) {
         unsigned char* blk = smem + kLdsK + wave * (32 * kKRow);
@@ -1048,8 +1058,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // same wavefront wrote what it reads next
         int rsub = lane >> 4, c16 = lane & 15;
         asm volatile("" : "+v"(rsub), "+v"(c16));                   // opaque: the row offsets are worked out here, not before the sweep
-        uint16_t* orow = (uint16_t*)O_part + (int64_t)row0 * kHeadDim + 8 * c16;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)row_of(wave * 32 + 4 * i + rsub) * kHeadDim); };
+        uint16_t* orow = (uint16_t*)O_part + (int64_t)(ONE ? row0 + row_of(wave * 32 + rsub) : row0) * kHeadDim + 8 * c16;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(4 * i) : row_of(wave * 32 + 4 * i + rsub)) * kHeadDim); };
         if (rows_here >= 32) {                                      // all rows exist: eight stores in a row, no branches
             uint4 w[8];
 #pragma unroll
@@ -1079,8 +1089,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         int rsub = lane >> 5, c32 = lane & 31;
         asm volatile("" : "+v"(rsub), "+v"(c32));
-        float* orow = (float*)O_part + (int64_t)row0 * kHeadDim + 4 * c32;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)row_of(wave * 32 + 2 * i + rsub) * kHeadDim); };
+        float* orow = (float*)O_part + (int64_t)(ONE ? row0 + row_of(wave * 32 + rsub) : row0) * kHeadDim + 4 * c32;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(2 * i) : row_of(wave * 32 + 2 * i + rsub)) * kHeadDim); };
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             uint4 w[8];
@@ -1247,11 +1257,13 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.sync_ticks = g_sync_ticks.load(std::memory_order_relaxed);
     if (kv_slot && retain_slot) return fail(ESP_ERR_INVALID_ARG, "prefill: rows that are read from the pool are in it already");
     if (kv_slot)
-        hipLaunchKernelGGL(prefill_kernel<2>, dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+        hipLaunchKernelGGL((prefill_kernel<2, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     else if (retain_slot)
-        hipLaunchKernelGGL(prefill_kernel<1>, dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+        hipLaunchKernelGGL((prefill_kernel<1, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+    else if (a.G == 1 && batch == 1 && S == 1)
+        hipLaunchKernelGGL((prefill_kernel<0, true>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     else
-        hipLaunchKernelGGL(prefill_kernel<0>, dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+        hipLaunchKernelGGL((prefill_kernel<0, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     const esp_status st = check_launch("prefill_kernel");
     if (st != ESP_OK || S == 1) return st;
     MergeArgs parts = {};

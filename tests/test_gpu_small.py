@@ -276,6 +276,22 @@ def test_prefill_few_items_split_the_keys(esp, cuda, Hq, Hkv, Tq, shards, causal
     run_pool_direct_case(esp, pc, 29)
 
 
+@pytest.mark.parametrize("H", [1, 5, 32])
+@pytest.mark.parametrize("Tq,Tkv", [(1, 63), (33, 64), (255, 300), (256, 256), (257, 449), (700, 640)])
+def test_prefill_one_request_of_a_multi_head_model(esp, cuda, H, Tq, Tkv):
+    """One request, one query head per KV head, keys uncut has a kernel of its own: against the oracle, and bit for bit
+    against the call with an empty request behind, which takes the general one."""
+    pc = wl.contiguous_prefill(f"one-{H}-{Tq}-{Tkv}", Tq, max(Tkv - Tq, 0), [(0, Tkv)], H, H, 33, cuda)
+    ws = torch.empty(256, dtype=torch.uint8, device=cuda)                  # no room for parts
+    (O, LSE), = run_prefill_case(esp, pc, workspace=ws)
+    s, two = pc.shards[0], lambda n: torch.tensor([0, n, n], dtype=torch.int32, device=cuda)
+    for dtype in (torch.bfloat16, torch.float32):
+        O2, L2 = esp.esp_partial_attn_prefill(pc.q, s.k, s.v, pc.q_pos, s.kv_pos, two(Tq), two(Tkv), Tq, Tkv,
+                                              softmax_scale=pc.scale, workspace=ws, out_dtype=dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(O2.to(torch.bfloat16).view(torch.int16), O.view(torch.int16)) and torch.equal(L2.view(torch.int32), LSE.view(torch.int32))
+
+
 def test_prefill_split_batch_with_an_empty_and_a_short_request(esp, cuda):
     """A batch of short chunks behind contexts of very different lengths: requests with fewer KV tiles than parts (some
     parts are empty), one without queries, one without keys."""
