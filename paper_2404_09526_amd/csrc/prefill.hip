@@ -216,17 +216,16 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     int32_t* lds_next = (int32_t*)(smem + kLdsFlag + 4);
     // The pool counter needs no clearing between launches: its high word names the launch that counted in it.  A
     // draw is one fetch-and-add; if the old value carries this launch's tag, its low word is the ticket.  If not
-    // (the first draws of a launch find the previous launch's count, or whatever a fresh workspace holds), the
-    // drawer starts this launch's count with a compare-and-swap, or draws again if another one has done so.
+    // (a draw before this launch's count was started finds the previous launch's count, or whatever a fresh workspace
+    // holds), the drawer starts it with a compare-and-swap, or draws again if another one has done so.
     auto draw_finish = [&](unsigned long long* ctr, unsigned long long old) {
         if ((uint32_t)(old >> 32) == a.tag) return (int)(uint32_t)old;
-        for (;;) {
-            unsigned long long cur = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t)(cur >> 32) == a.tag)
-                return (int)(uint32_t)__hip_atomic_fetch_add(ctr, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (unsigned long long cur = old + 1;;) {
             if (__hip_atomic_compare_exchange_strong(ctr, &cur, ((unsigned long long)a.tag << 32) | 1ULL, __ATOMIC_RELAXED,
                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
                 return 0;
+            if ((uint32_t)(cur >> 32) == a.tag)
+                return (int)(uint32_t)__hip_atomic_fetch_add(ctr, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     };
     auto process = [&](const int rank, const int vhead, unsigned long long* claim_from) {
@@ -1139,6 +1138,16 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         // are long and alike, a pool could not even them out further, and its items would walk K/V alone
         const int S = M <= L ? 1 : a.group_sync ? (M + L - 1) / L : max(1, (M - L) / L);
         const int pool_items = M > S * L ? (M - S * L) * (split ? 8 : 1) : 0;
+        // One workgroup starts this launch's count of the pool while the others are at their first items (a single round trip: the
+        // last draw of the launch before left a 0).  Without that the first draws start it themselves, and where many items end
+        // at about the same time their failing compare-and-swaps held everyone up: 333, 444, 1111 and 95 tokens against two
+        // shards, 32 / 8 heads (264 items, 256 workgroups), 207 -> 88 us, the rows kept 263 -> 105; four of 512 122 -> 67; six
+        // prompts of 37 .. 2047 against one 69.8 -> 66.4 us.
+        if (pool_items > 0 && p == P - 1 && tid == 0) {
+            for (unsigned long long cur = 0; (uint32_t)(cur >> 32) != a.tag;)
+                if (__hip_atomic_compare_exchange_strong(a.pool, &cur, (unsigned long long)a.tag << 32, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+        }
         int i_pool = 0;
         bool drew = false;
         long long item_started = 0;

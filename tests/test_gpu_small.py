@@ -713,6 +713,24 @@ def test_prefill_more_items_than_workgroups(esp, cuda, Hq, Hkv):
     run_prefill_case(esp, pc)
 
 
+@pytest.mark.parametrize("fill", [0, 255])
+@pytest.mark.parametrize("chunks", [[333, 444, 1111, 95], [512, 512, 512, 512]])
+def test_prefill_with_a_few_more_items_than_workgroups(esp, cuda, chunks, fill):
+    """32 / 8 heads: one or two items per XCD are left for the pool, and every workgroup draws once or twice.  Dense and kept
+    rows, a workspace of zeros and one of ones; the same workspace again, with the counts that the call before left."""
+    pc = wl.striped_prefill(f"few-pool-items {chunks}", chunks, 1, 0, 32, 8, 57, cuda)
+    ws = torch.full((esp.esp_prefill_workspace_bytes(sum(chunks), sum(chunks), 4, 32, 8, 128),), fill, dtype=torch.uint8, device=cuda)
+    (O, LSE), = run_prefill_case(esp, pc, workspace=ws)
+    s = pc.shards[0]
+    for _ in range(3):
+        O2, L2 = esp.esp_partial_attn_prefill(pc.q, s.k, s.v, pc.q_pos, s.kv_pos, pc.cu_q, s.cu_kv, pc.max_q, s.max_kv,
+                                              softmax_scale=pc.scale, O=torch.full_like(O, float("nan")), workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(L2, LSE)
+    if fill == 0:
+        run_retain_case(esp, pc, 58)
+
+
 def test_debug_validation_of_index_arrays(esp, cuda):
     """esp_debug_set_validate(1) (what ESP_DEBUG_VALIDATE=1 in the environment sets at load time): slots outside the pool, slots named twice, offsets that decrease or do not end at the row
     count are refused with ESP_ERR_INVALID_ARG before anything is launched; sound arrays pass and give the usual result."""
