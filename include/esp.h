@@ -25,7 +25,10 @@
  *   - Query head h reads KV head h / (Hq / Hkv).  D must be 128.
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     Work is enqueued asynchronously; the library never synchronises.
- *   - Results are deterministic: the same inputs give the same bits.
+ *   - Results are deterministic: the same inputs give the same bits, in any
+ *     workspace of at least the size that the matching *_bytes() reports (a
+ *     smaller one that is accepted, see the prefill and decode calls, cuts the
+ *     work into fewer parts, and fp32 sums are then added in another order).
  *   - Return value: ESP_OK or a negative esp_status; nothing is enqueued when
  *     an error is returned, except for ESP_ERR_HIP where the launch itself
  *     failed.  esp_last_error() gives a thread-local message.
@@ -57,7 +60,7 @@ typedef int32_t esp_status;
 #define ESP_OK                0
 #define ESP_ERR_INVALID_ARG  (-1) /* null pointer, negative size, Hq % Hkv != 0, P out of range */
 #define ESP_ERR_UNSUPPORTED  (-2) /* D != 128                                                   */
-#define ESP_ERR_WORKSPACE    (-3) /* workspace missing or smaller than the matching *_bytes()  */
+#define ESP_ERR_WORKSPACE    (-3) /* workspace missing or too small for the call               */
 #define ESP_ERR_HIP          (-4) /* a HIP launch failed; see esp_last_error()                 */
 
 #define ESP_MAX_PARTIALS 16
@@ -83,8 +86,9 @@ typedef int32_t esp_status;
  *     aligned; contents need not be preserved between calls.  It holds, for calls
  *     with few query rows against many keys, the partial results of the parts the
  *     keys are cut into (a smaller block, down to 256 bytes, is accepted: such a
- *     call then runs uncut, and slower), and work
- *     counters that are never cleared: every launch tags them with a number of
+ *     call then runs uncut, and slower; the size does not grow with Tq and Tkv
+ *     throughout, so a block for several calls takes the largest of theirs), and
+ *     work counters that are never cleared: every launch tags them with a number of
  *     its own (a per-process random 32-bit start, then +1 per call), so memory
  *     that has never been written is mistaken for the current launch's counters
  *     with probability 2^-32 per fresh workspace (query tiles would then be
@@ -137,6 +141,10 @@ esp_status esp_partial_attn_prefill_f32(
  *   seq_offsets[B] = total_tokens; max_len >= every request's length.
  *   O [B,Hq,D] bf16, LSE [B,Hq] float.
  *   workspace: at least esp_decode_workspace_bytes(...) bytes, 256-byte aligned.
+ *     A smaller one is accepted down to room for ranges of 512 tokens or a
+ *     1024th of total_tokens, whichever is more (eight steps of the kernel on
+ *     the layouts read in whole rows, see below); the call then runs on fewer
+ *     ranges than it would like, and may be slower.
  * Every Hq that is a multiple of Hkv is accepted (MHA, GQA, MQA).  With 4, 8, 16 or
  * a multiple of 32 KV heads and 1 or 2 query heads per KV head a pool row is read
  * in whole-row bursts and multiplied on the vector ALU; every other layout is read

@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
                 for (int u = 0; u < nt; ++u) {
                     const float (&src)[10][64] = lds[hb_wg + u * nhb_wg][gi];
                     const float lu = src[9][lane];
-                    const float c = lu > 0.f ? __builtin_amdgcn_exp2f(src[8][lane] - mx) : 0.f;   // no token of this request: nothing to add
+                    const float c = lu > 0.f ? __builtin_amdgcn_exp2f(src[8][lane] - mx) : 0.f;   // no token of this request: nothing to add (a NaN sum shows in lu * c)
                     lsum += lu * c;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)

@@ -16,7 +16,7 @@
 // 32 / 1 heads and 64 requests: a quarter of the call's time.)
 // A workgroup is four wavefronts, so that two fit a CU (LDS and registers) and one gathers while the other starts or
 // combines: a start (search of the request, queries, first slots) and an end take about as long as two steps of
-// gathers.  With the ranges of gq_range (decode.hip) and the 64-way search of the first request, measured against one
+// gathers.  With the ranges of decode_range (decode.hip) and the 64-way search of the first request, measured against one
 // workgroup of eight wavefronts per CU: 64 requests of 4K, 32 / 1 heads, 55.7 -> 42.5 us; 128 of 16K, 32 / 8 heads,
 // 2264 -> 2216 us (6.70 TB/s); 16 of 600, 32 / 8 heads, partial kernel 20.1 -> 16.5 us.
 #include "mfma_tile.h"
@@ -185,10 +185,10 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
 
         // ---- the partial of (range + request): O^T accumulated the ROUNDED probabilities, so each wavefront first
         //      brings it to the scale of its unrounded sum (the combine kernel divides by the sum that travels with
-        //      the partial, and takes the log-sum-exp from it); then the 8 wavefronts' results are combined through
+        //      the partial, and takes the log-sum-exp from it); then the wavefronts' results are combined through
         //      LDS (their tile blocks are free now): register rho of every lane to row rho of the wavefront's block,
-        //      64 lanes x 4 bytes a row, then maximum and sum; wavefront j combines registers 8j .. 8j+7 of all
-        //      eight and writes them out.  One partial per (range + request, head) leaves the workgroup.
+        //      64 lanes x 4 bytes a row, then maximum and sum; wavefront j combines kGqRegs registers, from kGqRegs j
+        //      on, of all of them and writes them out.  One partial per (range + request, head) leaves the workgroup.
         const float l_tot = half_swap_sum(l), lr_tot = half_swap_sum(l_r);
         const float fix = lr_tot > 0.f ? l_tot / lr_tot : 0.f;
         float* mine = (float*)(smem + wave * kGqWaveBytes);
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
             for (int u = 0; u < kGqWaves; ++u) {
                 const float* blk = (const float*)(smem + u * kGqWaveBytes);
                 const float lu = blk[65 * 64 + lane];
-                // a wavefront without a tile of this request (sum 0) has nothing to add
+                // a wavefront without a tile of this request (sum 0) has nothing to add; a NaN sum shows in lu * c
                 const float c = lu > 0.f ? __builtin_amdgcn_exp2f(mw[u] - mx) : 0.f;
                 lsum += lu * c;
 #pragma unroll

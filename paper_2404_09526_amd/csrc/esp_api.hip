@@ -31,7 +31,7 @@ esp_status check_launch(const char* what) {
 
 static bool heads_ok(int32_t Hq, int32_t Hkv) { return Hq > 0 && Hkv > 0 && Hq % Hkv == 0; }
 // head counts the decode kernels cover: all (a row-burst kernel for 4, 8, 16 or a multiple of 32 KV heads with query
-// groups of 1, 2, 4 or 8; a per-head kernel for every other combination)
+// groups of 1 or 2; the matrix-core kernel for every other combination)
 static bool decode_heads_supported(int32_t Hq, int32_t Hkv) { return heads_ok(Hq, Hkv); }
 
 // ESP_DEBUG_VALIDATE=1 in the environment: the content of the device index arrays, trusted otherwise, is checked on

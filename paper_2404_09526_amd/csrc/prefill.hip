@@ -170,7 +170,7 @@ template <int V> struct IC { static constexpr int value = V; };
 //     that remain).  Under a causal mask these are the tiles on its diagonal, the last ones of its sweep, which
 //     run the masked iteration anyway: the work is spread evenly over the items and costs each of them little;
 //   * any other request (a chunk against a long prefix): one item owns every tile, the last query tile's, or the
-//     first one's where the workgroups of a KV head walk the shard together (its turn comes in the last round).
+//     first one's where the workgroups of an XCD walk a KV head's rows together (its turn comes last of that head's).
 // An owner sweeps at least up to its last owned tile (tiles it cannot see pass through LDS without arithmetic), runs
 // the masked iteration from its first owned tile on, finds the slots in a ring of 8 LDS stages (the first four owned
 // tiles' slots are fetched at the start, the others with their K tiles), and stores the sweep's last four tiles, which
