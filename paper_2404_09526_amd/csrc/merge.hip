@@ -19,45 +19,44 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
     int seg = (int)(i & 15);
 
     float m = -INFINITY;
-    bool nan = false;                               // a NaN log-sum-exp makes the pair NaN (the maximum passes it over)
     float lse[ESP_MAX_PARTIALS];
 #pragma unroll
     for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
         lse[p] = (p < P) ? parts.LSE_parts[p][pair] : -INFINITY;
         m = fmaxf(m, lse[p]);
-        nan |= lse[p] != lse[p];
     }
-    const bool empty = m == -INFINITY && !nan;
+    // The maximum passes a NaN log-sum-exp over; its weight is NaN and makes the pair NaN, also where there is nothing but -inf
+    // beside it: the weights are then taken against 0.  (A test of all sixteen for NaN took 0.25 us of the 28.7 of a split call
+    // of 64 tokens on 4096 rows, 32 / 8 heads.)
+    const float ref = m == -INFINITY ? 0.f : m;
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float wsum = 0.f;
-    if (!empty) {
 #pragma unroll
-        for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
-            if (p < P) {
-                // an empty partial (LSE = -inf) gets weight exp(-inf) = 0
-                float w = __expf(lse[p] - m);
-                wsum += w;
-                float f[8];
-                if (F32) {
-                    const float4* src = (const float4*)parts.O_parts[p] + (pair * 16 + seg) * 2;
-                    const float4 a = load_once(&src[0]), b = load_once(&src[1]);
-                    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-                } else {
-                    const uint4 o = load_once(&((const uint4*)parts.O_parts[p])[pair * 16 + seg]);
-                    f[0] = bf16_lo(o.x); f[1] = bf16_hi(o.x); f[2] = bf16_lo(o.y); f[3] = bf16_hi(o.y);
-                    f[4] = bf16_lo(o.z); f[5] = bf16_hi(o.z); f[6] = bf16_lo(o.w); f[7] = bf16_hi(o.w);
-                }
-                if (w != 0.f) {  // keeps non-finite garbage of an empty partial out of the sum
+    for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
+        if (p < P) {
+            // an empty partial (LSE = -inf) gets weight exp(-inf) = 0
+            float w = __expf(lse[p] - ref);
+            wsum += w;
+            float f[8];
+            if (F32) {
+                const float4* src = (const float4*)parts.O_parts[p] + (pair * 16 + seg) * 2;
+                const float4 a = load_once(&src[0]), b = load_once(&src[1]);
+                f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+            } else {
+                const uint4 o = load_once(&((const uint4*)parts.O_parts[p])[pair * 16 + seg]);
+                f[0] = bf16_lo(o.x); f[1] = bf16_hi(o.x); f[2] = bf16_lo(o.y); f[3] = bf16_hi(o.y);
+                f[4] = bf16_lo(o.z); f[5] = bf16_hi(o.z); f[6] = bf16_lo(o.w); f[7] = bf16_hi(o.w);
+            }
+            if (w != 0.f) {  // keeps non-finite garbage of an empty partial out of the sum
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[e] += w * f[e];
-                }
+                for (int e = 0; e < 8; ++e) acc[e] += w * f[e];
             }
         }
-        float inv = 1.0f / wsum;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] *= inv;
     }
-    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = empty ? -INFINITY : m + __logf(wsum);
+    const float inv = wsum == 0.f ? 0.f : 1.0f / wsum;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] *= inv;
+    if (LSE_out != nullptr && seg == 0) LSE_out[pair] = wsum == 0.f ? -INFINITY : m + __logf(wsum);
     if (OUT32) {
         float4* dst = (float4*)O + (pair * 16 + seg) * 2;
         dst[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
