@@ -75,9 +75,12 @@ static bool decode_burst_layout(int32_t Hq, int32_t Hkv) {
 // with a start (search, queries, first slots, combination) and its steps (64 KiB of rows), take the least time.  Measured
 // with 1 / 2 / 4 / 8 rounds, us: 32 requests of 2K, 32 / 32 heads 328 / 345 / 344 / 345; 64 of 8K 2158 / 2190 / 2189 / 2186;
 // 250 of 20K, 32 / 1 525 / 543 / 541 / 541; 128 of 16K, 32 / 8 2399 / 2244 / 2198 / 2212; 64 of 8K, 64 / 8 430 / 412 / 412 / 428;
-// 32 / 4 210 / 209 / 220 / 233: where several workgroups gather from the same rows, a head each, a single round falls behind by
-// about 8 % of it.  64 requests of 4K, 32 / 1
-// heads: 598 workgroups of 512 tokens were three rounds of 256, 479 of 640 are one of 512.
+// 32 / 4 210 / 213 / 221 / 233.  Where eight or more workgroups gather from the same rows, a head each, a long single round falls
+// behind (2 rounds against 1: 128 of 4K, 32 / 8 433 / 456, 30 of 20K, 40 / 8 357 / 373, 100 of 6K, 12 / 12 697 / 706; short ones
+// not: 32 of 2K, 32 / 8 50.0 / 50.3), with two to four it does not (24 / 3, 6 / 3, 16 / 2, 32 / 4: one is best by 0 .. 6 %).
+// The 8 % stand for the former and do not decide the latter.  Over 18 shapes with 1, 2, 3, 4, 6, 8 and 16 rounds the rule's choice was
+// within 3 % of the best in fifteen and 5 % in all.  64 requests of 4K, 32 / 1 heads: 598 workgroups of 512 tokens were three
+// rounds of 256, 479 of 640 are one of 512.
 // `room`: ranges that the workspace holds (as far as the built-in block would, so that both calls agree); `kept`: ranges that
 // every workspace holds which is not refused (those of a simpler rule, by which workspaces are also measured).
 static int32_t decode_range(int32_t total_tokens, int64_t step, int64_t least, int64_t rows, int64_t kept, int64_t room) {

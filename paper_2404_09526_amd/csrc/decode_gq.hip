@@ -18,7 +18,7 @@
 // combines: a start (search of the request, queries, first slots) and an end take about as long as two steps of
 // gathers.  With the ranges of decode_range (decode.hip) and the 64-way search of the first request, measured against one
 // workgroup of eight wavefronts per CU: 64 requests of 4K, 32 / 1 heads, 55.7 -> 42.5 us; 128 of 16K, 32 / 8 heads,
-// 2264 -> 2216 us (6.70 TB/s); 16 of 600, 32 / 8 heads, partial kernel 20.1 -> 16.5 us.
+// 2337 -> 2291 us (6.45 TB/s; processes differ by as much); 16 of 600, 32 / 8 heads, partial kernel 20.1 -> 16.5 us.
 #include "mfma_tile.h"
 
 namespace esp {

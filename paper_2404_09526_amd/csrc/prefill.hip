@@ -1255,9 +1255,9 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     // Order of the items: head by head where the query tiles of a head do not differ much (the shard reaches at least a
     // quarter of the chunk's length before the chunk), so that all workgroups of an XCD walk one head's K/V at a time and a
     // head comes through the L2 once per (workgroups / query tiles); by query tile, heaviest first, where the sweeps
-    // are a triangle: there the light items have to come last.  Measured, by query tile -> by head, 32 / 32 heads: 1488
-    // rows on 210407 4.97 -> 4.38 ms, 32768 on 262144 111.8 -> 108.1 ms, 8 / 8 heads, 5999 on 8578 182 -> 176 us; against it
-    // 8192 on 8192: 1.934 -> 1.965 ms for four shards.  Without the XCD split consecutive items sit on different XCDs and
+    // are a triangle: there the light items have to come last.  Measured in turn, by query tile -> by head, 32 / 32 heads: 1488
+    // rows on 210407 4.84 -> 4.24 ms, 32768 on 262144 105.4 -> 103.9 ms, 8 / 8 heads, 5999 on 8578 159 -> 151 us, 32 / 8, 4096 on
+    // 65536 the same; against it 8192 on 8192: 1.934 -> 1.965 ms for four shards.  Without the XCD split consecutive items sit on different XCDs and
     // "by head" would spread a head over all of them (300 on 20300 rows, 32 / 8 heads: 114 -> 117 us).
     a.by_head = a.heads_per_xcd > 0 && batch == 1 && 4 * (int64_t)Tkv >= 5 * (int64_t)Tq;
     // start-of-round waits: one request with at least 512 KV tiles and a query chunk of at most an eighth of them
