@@ -8,10 +8,10 @@ Tolerances (bf16 output, fp32 accumulation):
        nothing for the error the value carries BEFORE it is rounded: the probabilities are rounded to bf16 for the
        second product, half a unit each, 2^-9 relative.  That term is added from 4.0 up; below, where the format
        mostly leaves room (half a unit is 0.0078 in [2, 4)), it is not: between 2 and 2.56 the bound is a check that
-       inputs with very many rows of two to four keys may exceed, by up to 0.0078 + 2^-9 sum p |v| against 0.01.  (Without it, an element whose exact value sits
-       just above 4.0156, the midpoint of two bf16 values, and that was 4e-4 off before the rounding, fails at
-       1.024 x the bound: seen once.)  How many compared elements fell into the scaled
-       region is returned (`o_scaled`) and printed.  AND per (row, head)
+       inputs with very many rows of two to four keys may exceed, by up to 0.0078 + 2^-9 sum p |v| against 0.01.
+       (Without the term, an element whose exact value sits just above 4.0156, the midpoint of two bf16 values, and
+       that was 4e-4 off before the rounding, fails at 1.024 x the bound: seen once.)  How many compared elements
+       fell into the scaled region is returned (`o_scaled`) and printed.  AND per (row, head)
        max|dO| <= 2^-7 * max|O_ref| + 1e-5 and cosine >= 0.999 (these keep the test meaningful for long KV,
        where |O| ~ 1/sqrt(n) is tiny and an all-zero output would pass the absolute bound): 2^-8 for the one
        rounding of the output to bf16, another 2^-8 for the bf16 probabilities of the second product.  Every
