@@ -53,6 +53,24 @@ __device__ __forceinline__ void load_to_lds_b32(uint32_t lds_addr, const void* g
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                  :: "s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
 }
+// The same to lds_addr + off: with `off` known when it is compiled (the stage of a ring in an unrolled loop) all stages share one
+// scalar register.  One each, the addresses of the prefill kernel's ring were 24 of them: the rest did not fit, and its loop
+// read them back from vector lanes.
+#define ESP_TO_LDS(INSTR, OFF_OPERAND, ...) \
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\t" INSTR :: "s"(lds_addr), OFF_OPERAND(off), __VA_ARGS__ : "memory", "m0", "scc")
+__device__ __forceinline__ void load_to_lds_b128(uint32_t lds_addr, int off, const void* gbase, uint32_t voff) {
+    if (__builtin_constant_p(off)) ESP_TO_LDS("global_load_lds_dwordx4 %2, %3", "i", "v"(voff), "s"(gbase));
+    else ESP_TO_LDS("global_load_lds_dwordx4 %2, %3", "s", "v"(voff), "s"(gbase));
+}
+__device__ __forceinline__ void load_to_lds_b128_at(uint32_t lds_addr, int off, const void* src) {
+    if (__builtin_constant_p(off)) ESP_TO_LDS("global_load_lds_dwordx4 %2, off", "i", "v"(src));
+    else ESP_TO_LDS("global_load_lds_dwordx4 %2, off", "s", "v"(src));
+}
+__device__ __forceinline__ void load_to_lds_b32(uint32_t lds_addr, int off, const void* gbase, uint32_t voff) {
+    if (__builtin_constant_p(off)) ESP_TO_LDS("global_load_lds_dword %2, %3", "i", "v"(voff), "s"(gbase));
+    else ESP_TO_LDS("global_load_lds_dword %2, %3", "s", "v"(voff), "s"(gbase));
+}
+#undef ESP_TO_LDS
 template <int N>
 __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }

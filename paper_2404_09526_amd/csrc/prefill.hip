@@ -369,43 +369,45 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     auto fetch_pool_slots = [&](int t, int st) {
         if (!POOL || wave != 6 || t >= nkt) return;
         const int rows = min(kBN, kv_len - t * kBN);
-        load_to_lds_b32(lds_base0 + kLdsSlot + st * (kBN * 4), slot_req + t * kBN, min(lane, rows - 1) * 4);
+        load_to_lds_b32(lds_base0, kLdsSlot + st * (kBN * 4), slot_req + t * kBN, min(lane, rows - 1) * 4);
     };
     // the same inside the sweep's plain iterations, where the tile is a full one that exists: nothing to work out
     const uint32_t lane4 = lane * 4;
     auto fetch_pool_slots_full = [&](int t, int st) {
-        load_to_lds_b32(lds_base0 + kLdsSlot + st * (kBN * 4), slot_req + t * kBN, lane4);
+        load_to_lds_b32(lds_base0, kLdsSlot + st * (kBN * 4), slot_req + t * kBN, lane4);
     };
     const int32_t* preq = a.kv_pos + kv_lo;
     const uint32_t lds_base = lds_base0;
-    const uint32_t lds_k0 = lds_base + kLdsK, lds_v0 = lds_base + kLdsV, lds_p0 = lds_base + kLdsPos;
+    const uint32_t lds_k0 = lds_base + kLdsK, lds_v0 = lds_base + kLdsV;
+    const uint32_t lds_kw = lds_base + wave * 1024, lds_vw = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
 
     // K tile at kt into K stage st: 2 transfers per wavefront, 3 for wavefront 7; `part` picks one of them, so that
     // the sweep can spread them over an iteration (a burst of transfers from all wavefronts at once backs up the
     // memory pipeline and stalls the issuing wavefronts).  `tail`: it is the ragged last tile, whose rows past the
     // end re-read the last row (their scores get masked).
     auto fetch_k_part = [&](const char* kt, int st, bool tail, int part) {
-        const uint32_t ko = st == kStages ? lds_base + kLdsK0 : lds_k0 + st * kKTileBytes;
+        const uint32_t base = part == 2 ? lds_base : lds_kw;
+        const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + 8192 * part;
         const int n = part == 0 ? wave : part == 1 ? wave + 8 : 16;
         if (part == 2 && wave != 7) return;
-        if constexpr (POOL) { load_to_lds_b128_at(ko + 1024 * n, pool_src(kreq, st, part == 0 ? pk0 : part == 1 ? pk1 : pk2)); return; }
-        if (__builtin_expect(tail, 0)) load_to_lds_b128(ko + 1024 * n, kt, k_goff(n, tail_rows - 1));
-        else load_to_lds_b128(ko + 1024 * n, kt, part == 0 ? gk0 : part == 1 ? gk1 : gk2);
+        if constexpr (POOL) { load_to_lds_b128_at(base, off, pool_src(kreq, st, part == 0 ? pk0 : part == 1 ? pk1 : pk2)); return; }
+        if (__builtin_expect(tail, 0)) load_to_lds_b128(base, off, kt, k_goff(n, tail_rows - 1));
+        else load_to_lds_b128(base, off, kt, part == 0 ? gk0 : part == 1 ? gk1 : gk2);
     };
     // V tile at vt and its positions at pt into V stage st: 2 transfers per wavefront, 3 for wavefront 0
     auto fetch_v_part = [&](const char* vt, const int32_t* pt, int st, bool tail, int part, int slot_st = -1) {
-        const uint32_t vo = lds_v0 + st * kTileBytes + wave * 2048;
+        const int off = kLdsV + st * kTileBytes + 1024 * part;
         const int last = tail_rows - 1;
         if (part == 2) {
             if (wave != 0) return;
-            load_to_lds_b32(lds_p0 + st * (kBN * 4), pt, (tail ? min(lane, last) : lane) * 4);
+            load_to_lds_b32(lds_base, kLdsPos + st * (kBN * 4), pt, (tail ? min(lane, last) : lane) * 4);
         } else if constexpr (POOL) {
-            load_to_lds_b128_at(vo + 1024 * part, pool_src(vreq, slot_st < 0 ? st : slot_st, part == 0 ? pv0 : pv1));
+            load_to_lds_b128_at(lds_vw, off, pool_src(vreq, slot_st < 0 ? st : slot_st, part == 0 ? pv0 : pv1));
         } else if (__builtin_expect(tail, 0)) {
             const int r = part == 0 ? st_r0 : st_r1;
-            load_to_lds_b128(vo + 1024 * part, vt, v_goff(r, min(r, last)));
+            load_to_lds_b128(lds_vw, off, vt, v_goff(r, min(r, last)));
         } else {
-            load_to_lds_b128(vo + 1024 * part, vt, part == 0 ? gv0 : gv1);
+            load_to_lds_b128(lds_vw, off, vt, part == 0 ? gv0 : gv1);
         }
     };
     auto fetch_k = [&](const char* kt, int st, bool tail) {
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     auto fetch_slots = [&](int t) {
         if (!KEEP || wave != 6 || t < own_lo || t >= own_hi) return;
         const int rows = min(kBN, kv_len - t * kBN);
-        load_to_lds_b32(lds_base + kLdsSlot + (t & 7) * (kBN * 4), sreq + t * kBN, min(lane, rows - 1) * 4);
+        load_to_lds_b32(lds_base, kLdsSlot + (t & 7) * (kBN * 4), sreq + t * kBN, min(lane, rows - 1) * 4);
     };
     // Slots past the end of a ragged last tile become -1 (wavefront 6, once the tile's slots have landed and a
     // barrier before anyone reads them), so that the stores test the slot alone.
@@ -469,46 +471,74 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
 
     // ---- this lane's query row (column of S^T); its position is needed first (schedule scan), so it is loaded first
     const int qi = lane & 31, hi = lane >> 5;
-    const int my_i = wave * 32 + qi;
-    const bool row_ok = my_i < n_rows;
-    const int ld_i = row_ok ? my_i : n_rows - 1;
+    int bl = lane, bw = wave;                                       // opaque, as at the scan of the requests: what is worked out from
+    asm volatile("" : "+v"(bl), "+s"(bw));                          // these once per item does not live through the sweep
+    const int ld_i = min(bw * 32 + (bl & 31), n_rows - 1);
     const bool any_row = n_rows > 0;                                  // (an empty tile of the keeping variant: any row will do)
     // effective query position: non-causal rows see every real key
     const int my_qpos = a.causal ? a.q_pos[any_row ? tok0 + token_of(ld_i) : 0] : INT_MAX - 1;   // INT_MAX marks rows past a ragged tail
 
-    // the first tiles are requested right away, so that their latency hides behind the Q load and the schedule
-    // scan (tiles the scan later finds hidden are fetched for nothing, which is harmless: they exist).  K(0) has a place of its
-    // own, outside the ring: iteration 0 fetches K(4) into stage 0, while a wavefront that is behind may still be at the
-    // scores of tile 0.
-    // POOL: the slots of the first five tiles go first (tile 0's to a fifth ring stage, so that tile 4's need not wait for its
-    // readers), positions and Q are asked for with them, and the transfers start when all of that has landed.  Measured
-    // against slots, transfers, positions and Q one after the other: 64 tokens on 4096 rows, 32 / 32 heads, 35.1 -> 31.6 us; 300
-    // on 20300, 32 / 8, 112.4 -> 109.1 us.  (Dense rows: V(1), K(2) and K(3) held back until positions and Q had landed
-    // gained nothing with many items, and 512 tokens alone took 20.6 instead of 20.2 us.)
-    auto fetch_first = [&]() {
-        if (nkt > 4) {                                               // the usual case, without a conditional in it
-            fetch_k(kreq, kStages, false);
-            fetch_v_part(vreq, preq, 0, false, 0, kStages); fetch_v_part(vreq, preq, 0, false, 1, kStages); fetch_v_part(vreq, preq, 0, false, 2);
-            fetch_k(kreq + tile_bytes, 1, false); fetch_v(vreq + tile_bytes, preq + kBN, 1, false);
-            fetch_k(kreq + 2 * tile_bytes, 2, false);
-            fetch_k(kreq + 3 * tile_bytes, 3, false);
-            fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
-        } else {
-            fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
-            if (nkt > 0) {
-                const bool tail = 0 == ragged_tile;
-                fetch_k(kreq, kStages, tail);
-                fetch_v_part(vreq, preq, 0, tail, 0, kStages); fetch_v_part(vreq, preq, 0, tail, 1, kStages); fetch_v_part(vreq, preq, 0, tail, 2);
-            }
-            if (nkt > 1) { fetch_k(kreq + tile_bytes, 1, 1 == ragged_tile); fetch_v(vreq + tile_bytes, preq + kBN, 1, 1 == ragged_tile); }
-            if (nkt > 2) fetch_k(kreq + 2 * tile_bytes, 2, 2 == ragged_tile);
-            if (nkt > 3) fetch_k(kreq + 3 * tile_bytes, 3, 3 == ragged_tile);
+    // ---- smallest / largest key position of the KV tiles of this request, to LDS, 512 tiles at a time: 16 lanes a tile, four
+    //      positions a lane, so that a load is 1 KiB in a row, at any 4-byte alignment; past the request's end the last four
+    //      again.  (So a last tile of one to three rows takes rows of the tile before in: it may be seen or masked where it need
+    //      not be, never the other way round.)  A thread per tile touched 64 cache lines with each of sixteen loads, and took the
+    //      positions one by one where a request's rows do not start on 16 bytes: 6 us of the 11 before an item's first tile.
+    int2* lds_mm = (int2*)(smem + kLdsSched);
+    constexpr int kBoundTiles = kPfWaves * 64;
+    struct __attribute__((packed, aligned(4))) Pos4 { int32_t x, y, z, w; };
+    auto load_bounds = [&](auto& v, int base, int g0) {              // groups of four tiles: g0 + wave, + 8, ...
+#pragma unroll
+        for (int u = 0; u < (int)(sizeof v / sizeof v[0]); ++u) {
+            const int row = (base + 4 * (g0 + 8 * u + bw)) * kBN + 4 * bl;
+            v[u] = *(const Pos4*)(preq + min(row, kv_len - 4));
         }
     };
+    auto least = [](int x, int y) { return min(x, y); };
+    auto most = [](int x, int y) { return max(x, y); };
+    auto row16 = [](int x, auto op) {                               // over the 16 lanes of a tile, by rotations
+        x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, false));
+        x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x124, 0xf, 0xf, false));
+        x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x122, 0xf, 0xf, false));
+        return op(x, __builtin_amdgcn_update_dpp(0, x, 0x121, 0xf, 0xf, false));
+    };
+    auto store_bounds = [&](const auto& v, int g0) {                 // (of tiles past the last: not read)
+#pragma unroll
+        for (int u = 0; u < (int)(sizeof v / sizeof v[0]); ++u) {
+            const int mn = row16(min(min(v[u].x, v[u].y), min(v[u].z, v[u].w)), least);
+            const int mx = row16(max(max(v[u].x, v[u].y), max(v[u].z, v[u].w)), most);
+            const int at = 4 * (g0 + 8 * u + bw) + (bl >> 4);
+            if ((bl & 15) == 0 && at < kBoundTiles) lds_mm[at] = make_int2(mn, mx);
+        }
+    };
+    const bool few_keys = kv_len < 4;                               // no four rows to load: see below
+    Pos4 pos_first[4] = {};
+    if (a.causal && !few_keys) load_bounds(pos_first, 0, 0);
+
+    // ---- the item's first requests, in two groups, so that what the schedule and the scores of tile 0 wait for does not queue
+    //      behind the rest.  First: query positions, bounds, K(0) with its positions, and Q.  K(0) has a place of its own, outside
+    //      the ring: iteration 0 fetches K(4) into stage 0, while a wavefront that is behind may still be at the scores of tile 0.
+    //      Q goes through LDS, laid out in whole rows (chunk c of row r at c ^ (r % 16)): fetched as fragments, 16-byte pieces of 32
+    //      rows with every load, it took as long as all the tiles' transfers.  It lies where V(1), V(2), K(4) and K(3) go later.
+    //      POOL: the slots of the first five tiles go first (tile 0's to a fifth ring stage, so that tile 4's need not wait for its
+    //      readers), and K(0) is in the second group.
+    //      An item's set-up, measured (all transfers, then positions, then bounds, then Q, each waiting for the one before -> this):
+    //      11.0 -> 7.4 us with six prompts of 37 .. 2047 tokens, 32 / 8 heads, 9.8 -> 8.1 us with 8192 rows on 8192, 32 / 32 heads.
+    //      Calls: the six prompts 65.0 -> 59.3 us, 300 tokens on 20300 rows of the pool, 32 / 8 heads, 110.6 -> 108.0, 1000 .. 8192
+    //      against two shards, kept, 1504 -> 1464, 8192 against four shards and their merge 2038 -> 2024 (that one is bound by power).
+    const uint32_t q_off = bw < 4 ? kLdsV + kTileBytes + bw * 8192 : kLdsK + (bw < 6 ? 0 : 3 * kKTileBytes) + (bw & 1) * 8192;
     if constexpr (POOL) {
         fetch_pool_slots(0, kStages); fetch_pool_slots(1, 1); fetch_pool_slots(2, 2); fetch_pool_slots(3, 3); fetch_pool_slots(4, 0);
-    } else {
-        fetch_first();
+    } else if (nkt > 0) {
+        fetch_k(kreq, kStages, 0 == ragged_tile);
+    }
+    if (nkt > 0) fetch_v_part(vreq, preq, 0, 0 == ragged_tile, 2);
+    {
+        const char* qp = (const char*)a.q + (any_row ? (int64_t)row0 * (kHeadDim * 2) : 0);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) {
+            const int r = 4 * n + (bl >> 4), i = max(min(32 * bw + r, n_rows - 1), 0);
+            load_to_lds_b128_at(lds_base + q_off, 1024 * n, qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4));
+        }
     }
     // V stage 3 stands in for the tile before the first one (the loop multiplies the last chunk of tile j-1 at the
     // start of iteration j): zero it, since stale LDS contents could be NaN patterns; V(3) arrives there later
@@ -520,52 +550,11 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (tid == 0) *(int32_t*)(smem + kLdsFlag) = 0;      // "redo with the plain sweep" flag, see below
     }
 
-    // ---- smallest / largest key position of KV tile t of this request, found by one thread: 16 loads of four
-    //      positions when the request's positions are 16-byte aligned and the tile is full, one position at a
-    //      time (index clamped to the last row) otherwise.  The loads of this thread's first tile are issued here,
-    //      ahead of the barrier below, so that their latency overlaps the Q loads.
-    const bool pos_vec_ok = (((uintptr_t)preq) & 15) == 0;
-    auto tile_bounds = [&](int t) {
-        int mn = INT_MAX, mx = INT_MIN;                             // beyond the end: hidden, needs no mask
-        if (t < nkt) {
-            if (pos_vec_ok && (t + 1) * kBN <= kv_len) {
-                const int4* pp = (const int4*)(preq + t * kBN);
-                int4 v[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = pp[e];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    mn = min(min(mn, v[e].x), min(v[e].y, min(v[e].z, v[e].w)));
-                    mx = max(max(mx, v[e].x), max(v[e].y, max(v[e].z, v[e].w)));
-                }
-            } else {
-                for (int e = 0; e < kBN; ++e) {
-                    const int pv = preq[min(t * kBN + e, kv_len - 1)];
-                    mn = min(mn, pv);
-                    mx = max(mx, pv);
-                }
-            }
-        }
-        return make_int2(mn, mx);
-    };
-    int2 mm_first = make_int2(INT_MAX, INT_MIN);
-    if (a.causal) mm_first = tile_bounds(tid);
-
-    // ---- the Q fragment of this lane's row
-    bf16x8 qf[8];
-    {
-        const uint16_t* qp = a.q + (int64_t)(any_row ? row0 + row_of(ld_i) : 0) * kHeadDim + 8 * hi;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) qf[t] = *(const bf16x8*)(qp + 16 * t);
-    }
-    int wave_qmin = my_qpos, wave_qmax = my_qpos;
-#pragma unroll
-    for (int s = 16; s >= 1; s >>= 1) {
-        wave_qmin = min(wave_qmin, __shfl_xor(wave_qmin, s));
-        wave_qmax = max(wave_qmax, __shfl_xor(wave_qmax, s));
-    }
-    wave_qmin = __builtin_amdgcn_readfirstlane(wave_qmin);
-    wave_qmax = __builtin_amdgcn_readfirstlane(wave_qmax);
+    wait_vm<0>();
+    if (ragged_tile == 0) seal_tail(0);
+    // the wavefront's smallest and largest query position (lanes l and l | 32 hold the same row)
+    auto of_two = [](int x, auto op) { return op(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)); };
+    const int wave_qmin = of_two(row16(my_qpos, least), least), wave_qmax = of_two(row16(my_qpos, most), most);
     if (lane == 0) { lds_qmm[0][wave] = wave_qmin; lds_qmm[1][wave] = wave_qmax; }
 
     // ---- tile schedule of this workgroup: n_vis = 1 + last tile some row can see (tiles before it that are
@@ -573,32 +562,61 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     //      this wavefront has to mask (every later tile is masked too, which is exact for ascending positions
     //      and merely redundant otherwise); n_need = 1 + last tile a row of this wavefront can see: beyond it
     //      the wavefront only keeps up its share of the transfers and the barriers.
-    //      The bounds of 512 tiles at a time (one per thread) go through LDS; every wavefront then reads them all,
+    //      The bounds of 512 tiles at a time go through LDS; every wavefront then reads them all,
     //      64 per step, and wavefront-wide ballots turn its three tests into bit masks whose highest / lowest set
     //      bit is the answer: no exchange of candidates, and one barrier for requests of up to 512 tiles.
     int n_vis = nkt, first_mask = nkt, n_need = nkt;
-    int2* lds_mm = (int2*)(smem + kLdsSched);
-    if (a.causal) lds_mm[tid] = mm_first;
-    if constexpr (POOL) {
-        wait_vm<0>();                                               // the slots have landed, and Q: said in a way the compiler understands
-        asm volatile("" :: "v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(qf[4]), "v"(qf[5]), "v"(qf[6]), "v"(qf[7]));
+    auto rest_of_bounds = [&](int base) {
+        for (int g = base == 0 ? 4 * kPfWaves : 0; 4 * g < min(kBoundTiles, nkt - base); g += 8 * kPfWaves) {
+            Pos4 v[8];
+            load_bounds(v, base, g);
+            store_bounds(v, g);
+        }
+    };
+    if (a.causal && !few_keys) {
+        store_bounds(pos_first, 0);
+        rest_of_bounds(0);
+    } else if (a.causal && tid == 0 && kv_len > 0) {
+        int mn = INT_MAX, mx = INT_MIN;
+        for (int e = 0; e < kv_len; ++e) { mn = min(mn, preq[e]); mx = max(mx, preq[e]); }
+        lds_mm[0] = make_int2(mn, mx);
     }
-    wg_barrier();          // LDS only: the Q loads and tile transfers stay in flight
-    if constexpr (POOL) fetch_first();
+    wg_barrier();
+    // second group: what iteration 0 needs, in flight under the schedule scan and the scores of tile 0 (tiles the scan finds hidden are
+    // fetched for nothing, which is harmless: they exist)
+    fetch_slots(own_lo); fetch_slots(own_lo + 1); fetch_slots(own_lo + 2); fetch_slots(own_lo + 3);
+    if (nkt > 4) {                                                   // the usual case, without a conditional in it
+        if constexpr (POOL) fetch_k(kreq, kStages, false);
+        fetch_k(kreq + tile_bytes, 1, false);
+        fetch_v_part(vreq, preq, 0, false, 0, kStages); fetch_v_part(vreq, preq, 0, false, 1, kStages);
+        fetch_k(kreq + 2 * tile_bytes, 2, false);
+        fetch_v_part(vreq, preq + kBN, 1, false, 2);
+    } else if (nkt > 0) {
+        const bool tail = 0 == ragged_tile;
+        if constexpr (POOL) fetch_k(kreq, kStages, tail);
+        if (nkt > 1) fetch_k(kreq + tile_bytes, 1, 1 == ragged_tile);
+        fetch_v_part(vreq, preq, 0, tail, 0, kStages); fetch_v_part(vreq, preq, 0, tail, 1, kStages);
+        if (nkt > 2) fetch_k(kreq + 2 * tile_bytes, 2, 2 == ragged_tile);
+        if (nkt > 1) fetch_v_part(vreq, preq + kBN, 1, 1 == ragged_tile, 2);
+    }
+    bf16x8 qf[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+        qf[t] = *(const ESP_LDS bf16x8*)(uintptr_t)((lds_base + q_off + (bl & 31) * 256 + (((bl >> 5) ^ (bl & 15)) << 4)) ^ (t << 5));
     if (a.causal) {
         int wg_qmax = lds_qmm[1][0];
 #pragma unroll
         for (int w = 1; w < kPfWaves; ++w) wg_qmax = max(wg_qmax, lds_qmm[1][w]);
         int last_vis = -1, fm = nkt, lw = -1;
-        for (int base = 0; base < nkt; base += kPfWaves * 64) {
+        for (int base = 0; base < nkt; base += kBoundTiles) {
             if (base > 0) {
                 wg_barrier();                                       // everyone has read the previous 512
-                lds_mm[tid] = tile_bounds(base + tid);
+                rest_of_bounds(base);
                 wg_barrier();
             }
-            const int cnt = min(kPfWaves * 64, nkt - base);
+            const int cnt = min(kBoundTiles, nkt - base);
             for (int t0 = 0; t0 < cnt; t0 += 64) {
-                const int2 mm = lds_mm[t0 + lane];                  // past the last tile: (INT_MAX, INT_MIN)
+                const int2 mm = t0 + lane < cnt ? lds_mm[t0 + lane] : make_int2(INT_MAX, INT_MIN);   // past the last tile: hidden, needs no mask
                 const uint64_t vis = __builtin_amdgcn_ballot_w64(mm.x <= wg_qmax);
                 if (vis) last_vis = base + t0 + 63 - __builtin_clzll(vis);
                 const uint64_t mk = __builtin_amdgcn_ballot_w64(mm.y > wave_qmin);
@@ -832,7 +850,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                 }
                 if (KEEP && !PLAIN && do_k && j >= own_lo) fetch_slots(j + 4);
                 if constexpr (POOL) {
-                    if (do_k && wave == 7) load_to_lds_b128_at(lds_k0 + ST * kKTileBytes + 1024 * 16, pool_at(kreq, pslot, pk2));
+                    if (do_k && wave == 7) load_to_lds_b128_at(lds_base, kLdsK + ST * kKTileBytes + 1024 * 16, pool_at(kreq, pslot, pk2));
                 } else if (do_k) {
                     fetch_k_part(k_next, ST, tail_k, 2);
                 }
@@ -840,9 +858,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
             if constexpr (POOL) {
                 if (do_k && (m == 3 || m == 6))
-                    load_to_lds_b128_at(lds_k0 + ST * kKTileBytes + 1024 * (m == 3 ? wave : wave + 8), pool_at(kreq, pslot, m == 3 ? pk0 : pk1));
+                    load_to_lds_b128_at(lds_kw, kLdsK + ST * kKTileBytes + 8192 * (m / 6), pool_at(kreq, pslot, m == 3 ? pk0 : pk1));
                 if (do_v && (m == 9 || m == 12))
-                    load_to_lds_b128_at(lds_v0 + ST2 * kTileBytes + wave * 2048 + 1024 * (m / 12), pool_at(vreq, pslot, m == 9 ? pv0 : pv1));
+                    load_to_lds_b128_at(lds_vw, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(vreq, pslot, m == 9 ? pv0 : pv1));
             } else {
                 if (do_k && (m == 3 || m == 6)) fetch_k_part(k_next, ST, tail_k, m / 6);
                 if (do_v && (m == 9 || m == 12)) fetch_v_part(v_next, p_next, ST2, tail_v, m / 12);
@@ -860,15 +878,10 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                                     "v"(pf[1][1].v) : "memory");
     };
 
-    // ---- prologue: K(0..3), V(0), V(1) were requested above; S^T of tile 0, first fragments
-    wait_vm<0>();
-    // the Q fragments have landed with everything else; said in a way the compiler's own bookkeeping of loads
-    // in flight understands, or every later reuse of these registers makes it wait for "pending" loads
-    asm volatile("" :: "v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]), "v"(qf[4]), "v"(qf[5]), "v"(qf[6]), "v"(qf[7]));
-    if (ragged_tile >= 0 && ragged_tile < 2) seal_tail(ragged_tile);
-    if (ragged_tile >= 0 && ragged_tile < 2) seal_slots();          // (in every other case before the iteration ahead of its own)
-    wg_barrier();
-    if (n_need > 0) {
+    // ---- prologue: S^T of tile 0 (POOL: once K(0) has landed with the rest of the second group); then, behind the barrier at which
+    //      all wavefronts have read their Q rows, V(1) and K(3); first fragments
+    auto first_scores = [&]() {
+        if (n_need <= 0) return;
         const uint32_t k_rd0 = k_rd + (uint32_t)(kLdsK0 - kLdsK);
         auto read_k0 = [&](int slot, int i) {
             frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd0 + (i & 1) * (32 * kKRow) + (i >> 1) * 32);
@@ -884,16 +897,39 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
             sbuf[0][kvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frk[m & 1].v, qf[t], sbuf[0][kvb], 0, 0, 0);
             if (m + 2 < 16) read_k0(m & 1, m + 2);
-            else read_k(m & 1, 1, m - 14);                          // ends with fragments 0, 1 of tile 1 (stale if absent)
         }
-        read_v(0, 3 * kTileBytes, 12);                              // the zeroed stage: there is no tile -1
-        read_v(1, 3 * kTileBytes, 13);
         // the offset starts at the exact row maximum of tile 0 wherever the row sees a key there (with ascending
         // positions: whenever it sees any key at all), so that the largest probability of a short row is exactly 1
         // and takes no bf16 rounding; rows still without a key keep the stand-in 0
         if (0 >= mask_from) apply_mask(sbuf[0], 0);
         const float tm0 = row_max(sbuf[0]);
         if (tm0 != -INFINITY) { m_use = tm0; lim = kSumLimit; }
+    };
+    if constexpr (!POOL) first_scores();
+    // (POOL: the slots of tile 1 are read ahead of the barrier, since iteration 0 fetches those of tile 5 over them)
+    int32_t v1_slot0 = 0, v1_slot1 = 0;
+    if constexpr (POOL) { v1_slot0 = pool_slot(1, pv0); v1_slot1 = pool_slot(1, pv1); }
+    wait_vm<0>();
+    if (ragged_tile == 1) seal_tail(1);
+    if (ragged_tile >= 0 && ragged_tile < 2) seal_slots();          // (in every other case before the iteration ahead of its own)
+    wg_barrier();
+    // what iterations 1 and 2 need (a sweep that is shorter does not wait for it)
+    if (n_vis > 1) {
+        if constexpr (POOL) {
+            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes, pool_at(vreq, v1_slot0, pv0));
+            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes + 1024, pool_at(vreq, v1_slot1, pv1));
+        } else {
+            fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 0);
+            fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 1);
+        }
+    }
+    if (n_vis > 3) fetch_k(kreq + 3 * tile_bytes, 3, 3 == ragged_tile);
+    if constexpr (POOL) first_scores();
+    if (n_need > 0) {
+        read_k(0, 1, 0);                                            // (stale if there is no tile 1)
+        read_k(1, 1, 1);
+        read_v(0, 3 * kTileBytes, 12);                              // the zeroed stage: there is no tile -1
+        read_v(1, 3 * kTileBytes, 13);
     }
     // the sweep: a loop with a single exit over groups of four tiles (the stage of a tile is a compile-time
     // constant), then the zero to three tiles left over
@@ -1036,15 +1072,22 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const float ltot = half_swap_sum(lsum);
     const float ltot_r = half_swap_sum(lsum + lcorr);
     const float inv = ltot_r > 0.f ? 1.0f / ltot_r : 0.f;
+    // -inf says that the row saw no key (a sum of 0, exactly), and a merge leaves the row out; a sum that is NaN has to show
+    // (first, while no store is in flight that a wait for anything else would have to sit out)
+    int el = lane, ew = wave;                                       // opaque: the addresses are worked out here, not before the sweep
+    asm volatile("" : "+v"(el), "+s"(ew));
+    const int my_i = ew * 32 + el, e_qi = el & 31, e_hi = el >> 5;
+    if (el < 32 && my_i < n_rows)
+        *(float*)((char*)(a.LSE + row0 + row_of(my_i)) + part * a.lse_part) = ltot != 0.f ? (m_fin + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
     // O goes through LDS so that it leaves in whole rows: a lane holds 8-byte pieces of one row, 16 of them spread
     // over the 256 bytes; written to a wavefront-private 32 x 272-byte block (the K stages are free by now: the
     // barrier above ended all tile reads) they come back as 16 lanes x 16 bytes per row, four rows per store.
     // rows of this wavefront that exist (may be <= 0); a part of a split call in which none of them sees a key leaves O
     // unwritten: its LSE, -inf, keeps it out of the merge
-    const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - wave * 32);
+    const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - ew * 32);
     char* const O_part = (char*)a.O + part * a.o_part;
     if (!a.o_f32) {
-        unsigned char* blk = smem + kLdsK + wave * (32 * kKRow);
+        unsigned char* blk = smem + kLdsK + ew * (32 * kKRow);
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1052,13 +1095,12 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                 uint2 w;
                 w.x = pack_bf16(oacc[db][4 * bb + 0] * inv, oacc[db][4 * bb + 1] * inv);
                 w.y = pack_bf16(oacc[db][4 * bb + 2] * inv, oacc[db][4 * bb + 3] * inv);
-                *(uint2*)(blk + qi * kKRow + (32 * db + 8 * bb + 4 * hi) * 2) = w;
+                *(uint2*)(blk + e_qi * kKRow + (32 * db + 8 * bb + 4 * e_hi) * 2) = w;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // same wavefront wrote what it reads next
-        int rsub = lane >> 4, c16 = lane & 15;
-        asm volatile("" : "+v"(rsub), "+v"(c16));                   // opaque: the row offsets are worked out here, not before the sweep
-        uint16_t* orow = (uint16_t*)O_part + (int64_t)(ONE ? row0 + row_of(wave * 32 + rsub) : row0) * kHeadDim + 8 * c16;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(4 * i) : row_of(wave * 32 + 4 * i + rsub)) * kHeadDim); };
+        const int rsub = el >> 4, c16 = el & 15;
+        uint16_t* orow = (uint16_t*)O_part + (int64_t)(ONE ? row0 + row_of(ew * 32 + rsub) : row0) * kHeadDim + 8 * c16;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(4 * i) : row_of(ew * 32 + 4 * i + rsub)) * kHeadDim); };
         if (rows_here >= 32) {                                      // all rows exist: eight stores in a row, no branches
             uint4 w[8];
 #pragma unroll
@@ -1078,18 +1120,17 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         // the eight blocks of 32 rows fill the V and K stages exactly.  Two rows per store, 16 stores.
         constexpr int kFRow = 4 * kHeadDim + 16;
         static_assert(kPfWaves * 32 * kFRow <= kStages * (kTileBytes + kKTileBytes), "fp32 output staging must fit the tile stages");
-        unsigned char* blk = smem + kLdsV + wave * (32 * kFRow);
+        unsigned char* blk = smem + kLdsV + ew * (32 * kFRow);
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int bb = 0; bb < 4; ++bb)
-                *(float4*)(blk + qi * kFRow + (32 * db + 8 * bb + 4 * hi) * 4) =
+                *(float4*)(blk + e_qi * kFRow + (32 * db + 8 * bb + 4 * e_hi) * 4) =
                     make_float4(oacc[db][4 * bb + 0] * inv, oacc[db][4 * bb + 1] * inv, oacc[db][4 * bb + 2] * inv, oacc[db][4 * bb + 3] * inv);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        int rsub = lane >> 5, c32 = lane & 31;
-        asm volatile("" : "+v"(rsub), "+v"(c32));
-        float* orow = (float*)O_part + (int64_t)(ONE ? row0 + row_of(wave * 32 + rsub) : row0) * kHeadDim + 4 * c32;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(2 * i) : row_of(wave * 32 + 2 * i + rsub)) * kHeadDim); };
+        const int rsub = el >> 5, c32 = el & 31;
+        float* orow = (float*)O_part + (int64_t)(ONE ? row0 + row_of(ew * 32 + rsub) : row0) * kHeadDim + 4 * c32;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(2 * i) : row_of(ew * 32 + 2 * i + rsub)) * kHeadDim); };
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             uint4 w[8];
@@ -1105,9 +1146,6 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
         }
     }
-    // -inf says that the row saw no key (a sum of 0, exactly), and a merge leaves the row out; a sum that is NaN has to show
-    if (row_ok && hi == 0)
-        *(float*)((char*)(a.LSE + row0 + row_of(my_i)) + part * a.lse_part) = ltot != 0.f ? (m_fin + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
     if (claim_from && tid == 0) *lds_next = draw_finish(claim_from, next_item);
     return true;
     };

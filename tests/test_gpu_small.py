@@ -258,6 +258,26 @@ def test_prefill_packed_rows(esp, cuda, Hq, Hkv, chunks):
     run_retain_case(esp, pc, 26)
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(4, 2), (4, 4)])
+@pytest.mark.parametrize("chunks", [[1, 2, 3, 4, 5, 66, 67, 129, 130, 191] * 12, [8195, 63, 2], [257] * 16])
+def test_prefill_bounds_of_ragged_requests(esp, cuda, Hq, Hkv, chunks):
+    """The positions of a request's KV tiles are read four at a time from wherever its rows start: requests of fewer than
+    four rows, last tiles of one to three, every alignment, more tiles than the first loads cover; positions in order and
+    not, and query rows past the end of a tile.  Values are a quarter of N(0,1), |O| < 2: there half a unit in the last place of
+    O (2^-8) and the rounding of the probabilities (2^-9 of |O|) stay below the bar of 1e-2 together, whatever few keys do."""
+    g = torch.Generator(device="cpu").manual_seed(31)
+    for shuffled in (False, True):
+        pc = wl.striped_prefill(f"bounds-{Hq}/{Hkv}", chunks, 1, 0, Hq, Hkv, 30, cuda)
+        pc.shards[0].v.mul_(0.25)
+        if shuffled and sum(chunks) < 8000:
+            perm = torch.randperm(pc.q_pos.numel(), generator=g)
+            pc.shards[0].kv_pos = pc.shards[0].kv_pos[perm.to(cuda)].contiguous()   # rows keep their data, positions go anywhere in the batch
+        elif shuffled:
+            continue
+        run_prefill_case(esp, pc)
+        run_pool_direct_case(esp, pc, 32)
+
+
 @pytest.mark.parametrize("Hq,Hkv,Tq,shards,causal", [(8, 2, 40, [(0, 3000)], True), (4, 4, 300, [(0, 2050), (2050, 4463)], True),
                                                      (5, 1, 1, [(0, 1025)], True), (4, 2, 257, [(0, 1600)], False),
                                                      (2, 2, 1100, [(0, 1100)], True)])
