@@ -41,8 +41,8 @@
 #include <chrono>
 #include <random>
 
-#include "esp_common.h"
 #include "mfma_tile.h"
+#include "prefill.h"
 
 namespace esp {
 
@@ -90,32 +90,58 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
     return g_sync_ticks.exchange(ticks < 0 ? (int32_t)kSyncTicks : ticks > 1000000 ? 1000000 : ticks, std::memory_order_relaxed);
 }
 
-// Split of the key-value rows.  A query tile is one item, and few of them (a follow-up turn of a few hundred tokens, a
-// shard with few heads) leave most of the 256 CUs idle, or busy for one round and a fraction.  Then every request's KV tiles
-// are cut into S equal parts, each an item of its own with its partial result in fp32 in the workspace, and the merge
-// kernel combines them.  S is what this estimate of the call's time asks for; every item costs a set-up and an
-// epilogue (about 10 us) beside its tiles (1.5 us each), the merge a launch and its traffic.
-// Items of a chunk at the end of a long context are alike, so rounds count whole; where the chunk is most of the shard the
-// sweeps are a triangle, which the item pool evens out.  Measured (unsplit -> split):
-// 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 114 us; 1488 on 210407, 32 / 32 heads, 4.83 -> 4.38 ms.
-static int32_t prefill_splits(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    constexpr double kCus = 256, kTile = 1.5, kItem = 10, kMerge = 6, kBytesPerUs = 4e6;
-    if (Tq <= 0 || Tkv <= 0) return 1;
+// Which kernel a call runs on, and in how many parts its key-value rows are cut.  A query tile of the main kernel is one item, and
+// few of them (a follow-up turn of a few hundred tokens, a shard with few heads) leave most of the 256 CUs idle, or busy for one
+// round and a fraction.  Then every request's KV tiles are cut into S equal parts, each an item of its own with its partial result
+// in fp32 in the workspace, and the merge kernel combines them.  Few rows, or few keys, are better off on the kernel of
+// prefill_short.hip, cut or not.  The choice is the least of these estimates of the call's time, in us, fitted to 57 shapes of
+// 1 .. 3000 tokens on 27 .. 262000 rows, 4 / 4 .. 64 / 8 heads, each with up to sixteen choices; the one taken was within 6 % of
+// the best of them in all but a few (10 %, 32 / 8 heads, 130 tokens on 3130 rows).
+// Main kernel: an item costs a set-up and an epilogue (8.5) beside its tiles (1.45 each; 0.8 where only one wavefront has rows,
+// as the others then only move tiles), the merge a launch (4) and its traffic.  Items of a chunk at the end of a long context are
+// alike, so rounds count whole; where the chunk is most of the shard the sweeps are a triangle, which the item pool evens out.
+// Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each while K and V come from the caches, 2.5 once they are more than
+// the 256 MB that the last of those holds), but no faster than its row blocks can be fed from the L2 (12.5 TB/s).  Several row
+// blocks of a head share its K and V only on one XCD, i.e. where heads times parts is a multiple of 8 (51 tokens on 29013 rows,
+// 12 / 12 heads: 43 us in 8 parts, 40 in 10, 62 in 9).
+// Measured (main kernel, best cut -> this): 27 tokens on 27, 32 / 8 heads, 10.5 -> 5.9 us, 256 on 512, 4 / 4, 17.9 -> 10.0,
+// 1024 on 1024, 8 / 8, 26.1 -> 14.8, 16 on 2016, 32 / 8, 19.6 -> 13.5, 100 on 3100, 8 / 8, 23.0 -> 15.8, 31 on 70195, 4 / 4, 62.3
+// -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
+// 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
+// Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
+struct PrefillPlan { int32_t splits, use_short, main_splits; };   // main_splits: what the main kernel would be given
+static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t most_splits) {
+    constexpr double kCus = 256, kTileLeast = 0.7, kTileRows = 0.75, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
+    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6;
+    if (Tq <= 0 || Tkv <= 0) return {1, 0, 1};
     const double rows = (double)Tq * (Hq / Hkv);
     const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
     const double tiles = ceil((double)Tkv / batch / kBN);
     const double seen = Tq < Tkv ? 1.0 - 0.5 * Tq / Tkv : 0.5;        // of the tiles, on average, with the chunk at the shard's end
+    const double kTile = kTileLeast + kTileRows * fmin(rows / batch / kBM, 1);
     int32_t best = 1;
     double best_us = 0;
-    for (int32_t S = 1; S <= ESP_MAX_PARTIALS && tiles >= 4 * S; ++S) {
+    auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
+    for (int32_t S = 1; S <= most_splits && (S == 1 || tiles >= 4 * S); ++S) {
         const double n = items * S / kCus;
         double us;
         if (seen > 0.8) us = ceil(n) * (seen * tiles / S * kTile + kItem);
         else us = fmax(tiles / S * kTile + kItem, (n + 0.3) * (seen * tiles / S * kTile + kItem));
-        if (S > 1) us += kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs;
-        if (S == 1 || us < 0.95 * best_us) { best = S; best_us = us; }
+        us += merge_us(S);
+        if (S == 1 || us < 0.97 * best_us) { best = S; best_us = us; }
     }
-    return best;
+    PrefillPlan plan = {best, 0, best};
+    const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
+    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), swept = blocks / Hkv / batch * seen * kv_bytes;
+    for (int32_t S = 1; S <= most_splits && (S == 1 || 2 * tiles >= kShortWaves * S); ++S) {
+        if (S > 1 && blocks > Hkv * batch && Hkv * S % 8 != 0) continue;
+        if ((rows / kShortRows + batch) * Hkv * S > 4e6) break;      // one workgroup each: what a launch holds
+        const double n = blocks * S / kCus, steps = ceil(2 * tiles / S / kShortWaves);
+        double us = (seen > 0.8 ? ceil(n) : n <= 1 ? 1 : n + 0.3) * (kShortItem + (kv_bytes > 2e8 ? kShortFar : kShortStep) * steps);
+        us = fmax(us, swept / kShortBytesPerUs) + merge_us(S);
+        if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1, best}; best_us = us; }
+    }
+    return plan;
 }
 // bytes of the parts' results: O [S][Tq, Hq, 128] fp32, then LSE [S][Tq, Hq], each part on a 256-byte boundary
 static size_t split_o_bytes(int32_t Tq, int32_t Hq) { return (size_t)Tq * Hq * kHeadDim * 4; }
@@ -123,38 +149,9 @@ static size_t split_lse_bytes(int32_t Tq, int32_t Hq) { return ((size_t)Tq * Hq 
 static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S * (split_o_bytes(Tq, Hq) + split_lse_bytes(Tq, Hq)) : 0; }
 
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    return kPrefillCounterBytes + split_bytes(prefill_splits(Tq, Tkv, batch, Hq, Hkv), Tq, Hq);
+    const PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);   // (either way: the size is that of the main kernel at least)
+    return kPrefillCounterBytes + split_bytes(plan.splits > plan.main_splits ? plan.splits : plan.main_splits, Tq, Hq);
 }
-
-struct PrefillArgs {
-    const uint16_t* q; const uint16_t* k; const uint16_t* v;
-    const int32_t* q_pos; const int32_t* kv_pos; const int32_t* cu_q; const int32_t* cu_kv;
-    const int32_t* retain_slot;       // [Tkv] pool slot of every shard row (negative: not kept), or null: nothing is kept
-    const int32_t* kv_slot;           // [Tkv] pool slot of every shard row when k and v ARE the token pools; null: dense shard
-    uint16_t* k_pool; uint16_t* v_pool;
-    void* O; float* LSE;              // O: bf16 [Tq, Hq, 128], or fp32 of the same shape when o_f32 is set
-    int32_t batch, Tq, Tkv, Hq, Hkv, causal, o_f32;
-    // Packed rows: the rows of a KV head are the (token, query head of the group) pairs in memory order, row rho of a
-    // request being token rho / G, query head kvh * G + rho % G, and a query tile is 256 of them.  A group's heads
-    // see the same keys, so nothing else changes; but a tile spans 256 / G tokens instead of 256: less of it is masked at
-    // the diagonal, a short chunk fills a tile G times better, and its Q and O rows are contiguous runs of G.
-    // Measured (one tile per query head -> packed, 32 / 8 heads): six prompts of 37 .. 2047 tokens 79.7 -> 69.1 us, a
-    // batch of 1000 .. 8192 tokens against two shards, rows kept, 1.470 -> 1.415 ms, 300 tokens against 20300
-    // 379.6 -> 368.3 us.
-    int32_t G;                        // query heads per KV head
-    float inv_G;
-    // Split KV: every request's KV tiles in `splits` parts, an item each ("KV head" h * splits + part in the deal of the
-    // items); part p's O and LSE lie p * o_part and p * lse_part bytes behind the first part's
-    int32_t splits;
-    int64_t o_part, lse_part;
-    int32_t q_tiles, heads_per_xcd;   // upper bound of the number of query tiles of a KV head; (KV head, part) pairs per XCD (0: no split)
-    unsigned long long* pool;         // counter of the item pool: launch tag (high word), draws so far (low word)
-    uint32_t tag;                     // this launch's tag
-    int32_t by_head;                  // items of an XCD in order of KV head (and part), not of query tile
-    int32_t group_sync;               // the workgroups of an XCD start their dealt rounds together
-    int32_t sync_ticks;               // longest such wait, in ticks of the 100 MHz wall clock
-    float scale_log2;
-};
 
 constexpr int kStages = 4;            // LDS stages per operand; tile j lives in stage j % 4
 constexpr float kSumLimit = 1048576.f;  // 2^20: a tile's probability sum above this refreshes the offset
@@ -1249,6 +1246,15 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     }
 }
 
+static esp_status merge_parts(const PrefillArgs& a, void* O, float* LSE, int32_t o_f32, hipStream_t stream) {
+    MergeArgs parts = {};
+    for (int32_t p = 0; p < a.splits; ++p) {
+        parts.O_parts[p] = (const char*)a.O + p * a.o_part;
+        parts.LSE_parts[p] = (const float*)((const char*)a.LSE + p * a.lse_part);
+    }
+    return launch_merge(parts, a.splits, (int64_t)a.Tq * a.Hq, 1, O, LSE, stream, o_f32);
+}
+
 esp_status launch_prefill(const void* q, const void* k, const void* v, const int32_t* q_pos, const int32_t* kv_pos,
                           const int32_t* cu_q, const int32_t* cu_kv, int32_t batch, int32_t Tq, int32_t Tkv,
                           int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv, float softmax_scale,
@@ -1260,8 +1266,10 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
     a.q_pos = q_pos; a.kv_pos = kv_pos; a.cu_q = cu_q; a.cu_kv = cu_kv;
     const size_t counters = kPrefillCounterBytes;
-    int32_t S = prefill_splits(Tq, Tkv, batch, Hq, Hkv);
-    if (workspace_bytes < counters + split_bytes(S, Tq, Hq)) S = 1;   // a block without room for the parts
+    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);
+    if (workspace_bytes < counters + split_bytes(plan.splits, Tq, Hq))   // a block without room for the parts
+        plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, 1);
+    const int32_t S = plan.splits;
     a.splits = S;
     if (S > 1) {
         a.O = (char*)workspace + counters;
@@ -1279,6 +1287,11 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.scale_log2 = softmax_scale * kLog2e;
     a.G = Hq / Hkv;
     a.inv_G = 1.0f / (float)a.G;
+    if (kv_slot && retain_slot) return fail(ESP_ERR_INVALID_ARG, "prefill: rows that are read from the pool are in it already");
+    if (plan.use_short) {
+        const esp_status st = launch_prefill_short(a, stream);
+        return st != ESP_OK || S == 1 ? st : merge_parts(a, O, LSE, o_f32, stream);
+    }
     a.q_tiles = prefill_q_tiles_bound(Tq, a.G, batch);
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -1302,7 +1315,6 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     // (a chunk against a long prefix: every query tile then sees nearly all of the shard, the items are alike)
     a.group_sync = a.by_head && S == 1 && Tkv >= 512 * kBN && (int64_t)Tkv >= 8 * (int64_t)Tq;
     a.sync_ticks = g_sync_ticks.load(std::memory_order_relaxed);
-    if (kv_slot && retain_slot) return fail(ESP_ERR_INVALID_ARG, "prefill: rows that are read from the pool are in it already");
     if (kv_slot)
         hipLaunchKernelGGL((prefill_kernel<2, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     else if (retain_slot)
@@ -1313,12 +1325,7 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
         hipLaunchKernelGGL((prefill_kernel<0, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     const esp_status st = check_launch("prefill_kernel");
     if (st != ESP_OK || S == 1) return st;
-    MergeArgs parts = {};
-    for (int32_t p = 0; p < S; ++p) {
-        parts.O_parts[p] = (const char*)a.O + p * a.o_part;
-        parts.LSE_parts[p] = (const float*)((const char*)a.LSE + p * a.lse_part);
-    }
-    return launch_merge(parts, S, (int64_t)Tq * Hq, 1, O, LSE, stream, o_f32);
+    return merge_parts(a, O, LSE, o_f32, stream);
 }
 
 }  // namespace esp

@@ -312,6 +312,32 @@ def test_prefill_one_request_of_a_multi_head_model(esp, cuda, H, Tq, Tkv):
         assert torch.equal(O2.to(torch.bfloat16).view(torch.int16), O.view(torch.int16)) and torch.equal(L2.view(torch.int32), LSE.view(torch.int32))
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 4), (6, 2), (40, 8)])
+@pytest.mark.parametrize("Tq,Tkv", [(1, 1), (31, 31), (32, 32), (33, 65), (64, 255), (11, 257), (96, 289), (7, 2100)])
+def test_prefill_of_few_rows(esp, cuda, Tq, Tkv, Hq, Hkv, causal):
+    """Row blocks of 32 with and without a remainder, key tiles of 32 with and without one, fewer and more of them than
+    wavefronts, uncut and cut; dense rows and pool rows, sorted and shuffled, one request and, with others around it, a batch."""
+    pc = wl.contiguous_prefill(f"few-{Hq}/{Hkv}-{Tq}-{Tkv}", Tq, Tkv - Tq, [(0, Tkv)], Hq, Hkv, 61, cuda, causal=causal)
+    run_prefill_case(esp, pc)
+    run_pool_direct_case(esp, pc, 62)
+    run_retain_case(esp, pc, 64)
+    s, gen = pc.shards[0], torch.Generator(device=cuda).manual_seed(63)
+    mix = torch.randperm(Tkv, generator=gen, device=cuda)
+    s.k, s.v, s.kv_pos = s.k[mix].contiguous(), s.v[mix].contiguous(), s.kv_pos[mix].contiguous()
+    (O, LSE), = run_prefill_case(esp, pc, workspace=torch.empty(256, dtype=torch.uint8, device=cuda))
+    # the same request third of five, between one without rows, one without keys and two more: bit for bit
+    q_at, kv_at = [0, 0, 2, 2 + Tq, 5 + Tq, 5 + Tq], [0, 9, 9, 9 + Tkv, 9 + Tkv, 12 + Tkv]
+    around = lambda t, lo, hi: torch.cat([t[:1].expand(lo, *t.shape[1:]), t, t[:1].expand(hi, *t.shape[1:])]).contiguous()
+    at = lambda x: torch.tensor(x, dtype=torch.int32, device=cuda)
+    O5, L5 = esp.esp_partial_attn_prefill(around(pc.q, 2, 3), around(s.k, 9, 3), around(s.v, 9, 3), around(pc.q_pos, 2, 3),
+                                          around(s.kv_pos, 9, 3), at(q_at), at(kv_at), max(Tq, 3), max(Tkv, 9), softmax_scale=pc.scale,
+                                          causal=causal, workspace=torch.empty(256, dtype=torch.uint8, device=cuda))
+    torch.cuda.synchronize()
+    assert torch.isneginf(L5[:2]).all() and torch.isneginf(L5[2 + Tq:]).all() and not O5[:2].any() and not O5[2 + Tq:].any()
+    assert torch.equal(O5[2:2 + Tq].view(torch.int16), O.view(torch.int16)) and torch.equal(L5[2:2 + Tq].view(torch.int32), LSE.view(torch.int32))
+
+
 def test_prefill_split_batch_with_an_empty_and_a_short_request(esp, cuda):
     """A batch of short chunks behind contexts of very different lengths: requests with fewer KV tiles than parts (some
     parts are empty), one without queries, one without keys."""
