@@ -107,6 +107,23 @@ static int32_t decode_range(int32_t total_tokens, int64_t step, int64_t least, i
     return (int32_t)(best * step);
 }
 
+// Ranges by request.  Where calls are short, a range that crosses into the next request costs more than its share of the work: its
+// requests are worked on one after the other, each with a start and an end (3 us), and such a workgroup ends last.  Then the
+// ranges are counted from each request's first token on: `parts` of them for each, enough for the longest, and the workgroups of
+// those that a request does not have return at once.  Returns that number, or 0: ranges along the whole list.
+// Taken where all of them, the empty ones too, are on the chip at once, and either ranges that are crossed into are many or they
+// are single steps.  (A second round costs more than is won: 16 of 550, 32 / 8 heads, 1024 workgroups for 280, 16.6 -> 20.2 us.)  Partials lie at (first token's range + part + request): as far apart as
+// along the list, in the same number of slots.  Measured (along the list -> by request): 4 requests of 320, 4 / 4 heads, 11.2 -> 8.6
+// us; 12 of 90, 8 / 4, 17.1 -> 12.2; 4 of 180, 32 / 1, 15.9 -> 8.8; 4 of 200, 32 / 4, 11.5 -> 8.5; 2 of 97, 12 / 12,
+// 10.8 -> 8.2; left alone: 100 of 234, 8 / 8, 25.1 (30.4), 3 of 5600, 32 / 8, 22.0 (22.9).
+static int32_t decode_parts(const DecodeGeom& g, int32_t B, int32_t max_len, int32_t Hq, int32_t Hkv) {
+    const bool gq = g.nhb_wg == 0;
+    const int64_t rows = gq ? (int64_t)Hkv * ((Hq / Hkv + 31) / 32) : g.ygroups;
+    const int64_t parts = ((int64_t)max_len + g.range - 1) / g.range;
+    const bool crossed = (int64_t)B * 20 >= (int64_t)g.nwg * 3, single = gq && g.range == kGqWaves * 32;
+    return B > 1 && (crossed || single) && B * parts * rows <= 512 ? (int32_t)parts : 0;
+}
+
 static int64_t partial_bytes(int32_t Hq) { return (int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float); }
 
 static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv, size_t bytes) {
@@ -180,7 +197,7 @@ template <int G>
 __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
     const uint16_t* __restrict__ q, const uint4* __restrict__ k_pool, const uint4* __restrict__ v_pool,
     const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ seq_offsets, int32_t B, int32_t total_tokens,
-    int32_t range, int32_t nhb_wg, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc,
+    int32_t range, int32_t parts, int32_t nhb_wg, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc,
     float* __restrict__ part_ml) {
     // accumulators (8 per lane and query head), maximum and sum of every wavefront, for the combination within the workgroup
     __shared__ float lds[kDecWaves][G][10][64];
@@ -191,18 +208,25 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
     const int hb_wg = wave & (nhb_wg - 1);
     const int hb = blockIdx.y * 8 + hb_wg;           // 1 KiB head block of the row
     const int tsub = wave / nhb_wg;                  // token interleave index among nt wavefronts
-    const int w = blockIdx.x;
+    int w = blockIdx.x;
     const uint32_t row_bytes = (uint32_t)Hkv * (kHeadDim * 2);
     const uint32_t lane_off = (uint32_t)(hb * 64 + lane) * 16;  // this lane's piece within a row
     const int kvh = hb * 4 + (lane >> 4);                      // KV head of this lane
     const int dseg = (lane & 15) * 8;                          // first of its 8 elements
 
-    const int32_t r0 = w * range;
+    int b;
+    int32_t r0, t1;
+    if (parts > 0) {
+        const RequestRange at = request_range(w, parts, range, B, seq_offsets);
+        b = at.b; r0 = at.t0; t1 = at.t1; w = at.w;
+        if (r0 >= t1) return;
+    } else {
+        r0 = w * range;
+        t1 = min(r0 + range, total_tokens);
+        if (r0 >= t1) return;
+        b = request_of(r0, seq_offsets, B, lane);
+    }
     int32_t t0 = r0;
-    const int32_t t1 = min(t0 + range, total_tokens);
-    if (t0 >= t1) return;
-
-    int b = request_of(t0, seq_offsets, B, lane);
     while (t0 < t1) {
         int32_t req_end = seq_offsets[b + 1];
         if (req_end <= t0) { ++b; continue; }                   // empty request
@@ -385,7 +409,7 @@ __device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY 
 template <int V> struct IC { static constexpr int value = V; };
 template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
-                                                             int32_t range, int32_t Hq, int32_t pairs,
+                                                             int32_t range, int32_t parts, int32_t Hq, int32_t pairs,
                                                              const float* __restrict__ part_acc,
                                                              const float* __restrict__ part_ml,
                                                              MergeArgs peers, int32_t n_peers,
@@ -423,9 +447,8 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         }
     };
     if (s1 > s0) {
-        const int w_lo = s0 / range, w_hi = (s1 - 1) / range;
-        const int n = w_hi - w_lo + 1;
-        const int64_t first = w_lo + b;                             // the slots of consecutive ranges
+        const int n = parts > 0 ? min(parts, (s1 - s0 + range - 1) / range) : (s1 - 1) / range - s0 / range + 1;
+        const int64_t first = s0 / range + b;                             // the slots of consecutive ranges
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
             float4 v[U];
@@ -517,21 +540,22 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
     DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, workspace_bytes);
+    const int32_t parts = decode_parts(g, B, max_len, Hq, Hkv);
     size_t n = decode_slots(g, B) * (size_t)Hq;
     float* part_acc = (float*)workspace;
     float* part_ml = part_acc + n * kHeadDim;
     const int G = Hq / Hkv;
     if (total_tokens > 0 && g.nhb_wg == 0) {
-        esp_status st = launch_decode_gq(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, g.range, g.nwg, Hq, Hkv,
+        esp_status st = launch_decode_gq(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, g.range, parts, g.nwg, Hq, Hkv,
                                          softmax_scale * kLog2e, part_acc, part_ml, stream);
         if (st != ESP_OK) return st;
     } else if (total_tokens > 0) {
-        dim3 grid(g.nwg, g.ygroups), block(kDecWaves * 64);
+        dim3 grid(parts > 0 ? B * parts : g.nwg, g.ygroups), block(kDecWaves * 64);
         float sl2 = softmax_scale * kLog2e;
 #define ESP_DECODE_LAUNCH(GG)                                                                                   \
     hipLaunchKernelGGL(decode_partial_kernel<GG>, grid, block, 0, stream, (const uint16_t*)q,                   \
                        (const uint4*)k_pool, (const uint4*)v_pool, slot_idx, seq_offsets, B, total_tokens,      \
-                       g.range, g.nhb_wg, Hq, Hkv, sl2, part_acc, part_ml)
+                       g.range, parts, g.nhb_wg, Hq, Hkv, sl2, part_acc, part_ml)
         switch (G) {
             case 1: ESP_DECODE_LAUNCH(1); break;
             case 2: ESP_DECODE_LAUNCH(2); break;
@@ -546,7 +570,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
     const bool wave = (int64_t)max_len / g.range + 2 <= kCombineShort;
 #define ESP_COMBINE_LAUNCH(GROUPS, PEERS)                                                                                 \
     hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), dim3((unsigned)((pairs + 8 / GROUPS - 1) / (8 / GROUPS))), dim3(256), 0, \
-                       stream, seq_offsets, g.range, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
+                       stream, seq_offsets, g.range, parts, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
                        with_peers ? *peers : MergeArgs{}, n_peers, (U32x2*)O, LSE)
     if (wave && with_peers) ESP_COMBINE_LAUNCH(2, true);
     else if (wave) ESP_COMBINE_LAUNCH(2, false);

@@ -26,7 +26,7 @@ namespace esp {
 __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     const uint16_t* __restrict__ q, const char* __restrict__ k_pool, const char* __restrict__ v_pool,
     const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ seq_offsets, int32_t B, int32_t total_tokens,
-    int32_t range, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml) {
+    int32_t range, int32_t parts, int32_t Hq, int32_t Hkv, float scale_log2, float* __restrict__ part_acc, float* __restrict__ part_ml) {
     __shared__ __attribute__((aligned(1024))) unsigned char smem[kGqWaves * kColWaveBytes];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     const int g0 = blockIdx.z * 32;
     const int ng = min(32, G - g0);                             // query heads of this chunk: columns 0 .. ng-1
     const int h0 = kvh * G + g0;
-    const int w = blockIdx.x;
+    int w = blockIdx.x;
     const uint32_t row_bytes = (uint32_t)Hkv * (kHeadDim * 2);
     const char* kbase = k_pool + (uint32_t)kvh * (kHeadDim * 2);
     const char* vbase = v_pool + (uint32_t)kvh * (kHeadDim * 2);
@@ -46,12 +46,21 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     Columns cols;
     cols.place(lds_k, lane);
 
-    int32_t t0 = w * range;
-    const int32_t t1 = min(t0 + range, total_tokens);
-    if (t0 >= t1) return;
-    // slots of this wavefront's first tile, as far as they do not depend on where its request ends: asked for before the search
-    int32_t slots = slot_idx[min(t0 + 32 * wave + qi, total_tokens - 1)];
-    int b = request_of(t0, seq_offsets, B, lane);
+    int b;
+    int32_t t0, t1, slots;
+    if (parts > 0) {
+        const RequestRange at = request_range(w, parts, range, B, seq_offsets);
+        b = at.b; t0 = at.t0; t1 = at.t1; w = at.w;
+        if (t0 >= t1) return;
+        slots = slot_idx[min(t0 + 32 * wave + qi, t1 - 1)];
+    } else {
+        t0 = w * range;
+        t1 = min(t0 + range, total_tokens);
+        if (t0 >= t1) return;
+        // slots of this wavefront's first tile, as far as they do not depend on where its request ends: asked for before the search
+        slots = slot_idx[min(t0 + 32 * wave + qi, total_tokens - 1)];
+        b = request_of(t0, seq_offsets, B, lane);
+    }
     bool first = true;
 
     while (t0 < t1) {
@@ -131,13 +140,13 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
 }
 
 esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
-                            const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t range, int32_t nwg,
+                            const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t range, int32_t parts, int32_t nwg,
                             int32_t Hq, int32_t Hkv, float scale_log2, float* part_acc, float* part_ml, hipStream_t stream) {
     const int G = Hq / Hkv;
     const int chunks = (G + 31) / 32;
     if (Hkv > 65535 || chunks > 65535) return fail(ESP_ERR_UNSUPPORTED, "decode: too many heads for one launch");
-    hipLaunchKernelGGL(decode_partial_gq_kernel, dim3(nwg, Hkv, chunks), dim3(kGqWaves * 64), 0, stream, (const uint16_t*)q,
-                       (const char*)k_pool, (const char*)v_pool, slot_idx, seq_offsets, B, total_tokens, range, Hq, Hkv,
+    hipLaunchKernelGGL(decode_partial_gq_kernel, dim3(parts > 0 ? B * parts : nwg, Hkv, chunks), dim3(kGqWaves * 64), 0, stream, (const uint16_t*)q,
+                       (const char*)k_pool, (const char*)v_pool, slot_idx, seq_offsets, B, total_tokens, range, parts, Hq, Hkv,
                        scale_log2, part_acc, part_ml);
     return check_launch("decode_partial_gq_kernel");
 }

@@ -458,6 +458,21 @@ def test_decode_request_search_and_range_edges(esp, cuda, requests, top, Hq, Hkv
     assert torch.isneginf(LSE[empty]).all() and (O[empty] == 0).all()
 
 
+@pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8), (8, 4, 64)])
+@pytest.mark.parametrize("requests", [2, 7, 8])
+def test_decode_ranges_by_request(esp, cuda, requests, Hq, Hkv, unit):
+    """Few short requests, each cut into ranges of its own: requests one token around one and two ranges, longer and empty ones,
+    an even and an odd number; and a length bound that says too little, of which the last range takes what is left."""
+    lens = [2 * unit + 1, 0, unit - 1, unit, unit + 1, 1, 2 * unit, 3 * unit + 5][:requests]
+    dc = wl.decode_pool(f"decode-by-request-{requests} ({Hq}/{Hkv})", lens, 4096, Hq, Hkv, 39, cuda, n_new=0)
+    O, LSE, _, _ = run_decode_case(esp, dc)
+    assert torch.isneginf(LSE[1]).all() and (O[1] == 0).all()
+    O1, L1 = esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, unit, softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    # other sums in another order, rounded once: a unit of bf16 in O, 2^-8, and fp32 sums in the LSE
+    assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("Hq,Hkv,ranges,waves", [(32, 8, 6, 1), (8, 8, 24, 4), (32, 32, 94, 1), (16, 16, 47, 2)])
 def test_decode_on_the_least_workspace(esp, cuda, Hq, Hkv, ranges, waves):
     """3000 tokens: the smallest workspace a call takes (ranges of 512 tokens on the matrix cores, of eight steps with a
