@@ -100,6 +100,18 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+def _load_marshal():
+    path = os.path.join(_PKG, "_marshal.so")
+    if not os.path.exists(path):
+        raise ImportError(f"{path} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`.")
+    from . import _marshal
+    at = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    _marshal.bind(_stream, *(at(f) for f in (lib.esp_kv_append, lib.esp_partial_attn_decode, lib.esp_partial_attn_decode_merge,
+                                              lib.esp_partial_attn_prefill, lib.esp_partial_attn_prefill_f32, lib.esp_merge_partials,
+                                              lib.esp_merge_partials_f32)))
+    return _marshal
+
+
 def last_error() -> str:
     return lib.esp_last_error().decode()
 
@@ -137,6 +149,11 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
+# The checks of the calls below once more in native code (csrc/marshal.cpp): a function of it makes the call and returns its status where
+# everything is given, plain and right, and returns None otherwise.
+_marshal = _load_marshal()
+
+
 def _workspace(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
@@ -165,6 +182,10 @@ def esp_partial_attn_prefill(q, k, v, q_pos, kv_pos, cu_q=None, cu_kv=None, max_
     Returns (O [Tq,Hq,D], LSE fp32 [Tq,Hq]) of attention against this one KV shard.  O is bf16
     (esp_partial_attn_prefill) or, if `O` is a float32 tensor or out_dtype is torch.float32, fp32
     (esp_partial_attn_prefill_f32)."""
+    status = _marshal.prefill(q, k, v, q_pos, kv_pos, cu_q, cu_kv, max_q, max_kv, softmax_scale, causal, O, LSE, workspace)
+    if status is not None:
+        _check(status)
+        return O, LSE
     _dev(q, torch.bfloat16, "q"); _dev(k, torch.bfloat16, "k"); _dev(v, torch.bfloat16, "v")
     _dev(q_pos, torch.int32, "q_pos"); _dev(kv_pos, torch.int32, "kv_pos")
     Tq, Hq, D = q.shape
@@ -250,6 +271,10 @@ def esp_partial_attn_decode(q, k_pool, v_pool, slot_idx, seq_offsets, max_len, s
                             O=None, LSE=None, workspace=None):
     """q [B,Hq,D] bf16, pools [S,Hkv,D] bf16, slot_idx int32 [total], seq_offsets int32 [B+1].
     Returns (O bf16 [B,Hq,D], LSE fp32 [B,Hq]) of attention against the resident pool rows."""
+    status = _marshal.decode(q, k_pool, v_pool, slot_idx, seq_offsets, max_len, softmax_scale, O, LSE, workspace)
+    if status is not None:
+        _check(status)
+        return O, LSE
     _dev(q, torch.bfloat16, "q"); _dev(k_pool, torch.bfloat16, "k_pool"); _dev(v_pool, torch.bfloat16, "v_pool")
     _dev(slot_idx, torch.int32, "slot_idx"); _dev(seq_offsets, torch.int32, "seq_offsets")
     B, Hq, D = q.shape
@@ -298,6 +323,10 @@ def esp_partial_attn_decode_merge(q, k_pool, v_pool, slot_idx, seq_offsets, max_
                                   peer_LSE: Sequence[torch.Tensor], softmax_scale=None, O=None, LSE=None, workspace=None):
     """esp_partial_attn_decode combined, in the same pass, with the partial results peers returned for the same
     queries (peer_O[p] bf16 [B,Hq,D], peer_LSE[p] fp32 [B,Hq]).  Returns the final (O bf16, LSE fp32)."""
+    status = _marshal.decode(q, k_pool, v_pool, slot_idx, seq_offsets, max_len, softmax_scale, O, LSE, workspace, peer_O, peer_LSE)
+    if status is not None:
+        _check(status)
+        return O, LSE
     _dev(q, torch.bfloat16, "q"); _dev(k_pool, torch.bfloat16, "k_pool"); _dev(v_pool, torch.bfloat16, "v_pool")
     _dev(slot_idx, torch.int32, "slot_idx"); _dev(seq_offsets, torch.int32, "seq_offsets")
     B, Hq, D = q.shape
@@ -333,6 +362,10 @@ def esp_merge_partials(O_parts: Sequence[torch.Tensor], LSE_parts: Sequence[torc
                        want_lse: bool = True):
     """Combine P partial results (O_p bf16 or, all of them, fp32 [T,Hq,D]; LSE_p fp32 [T,Hq]) into
     (O bf16, LSE fp32 or None): esp_merge_partials or esp_merge_partials_f32 by the partials' type."""
+    status = _marshal.merge(O_parts, LSE_parts, O, LSE)
+    if status is not None:
+        _check(status)
+        return O, LSE
     P = len(O_parts)
     if P != len(LSE_parts):
         raise ValueError("merge: O_parts and LSE_parts differ in length")
@@ -363,6 +396,9 @@ def esp_merge_partials(O_parts: Sequence[torch.Tensor], LSE_parts: Sequence[torc
 
 def esp_kv_append(k, v, slot_idx, k_pool, v_pool) -> None:
     """k_pool[slot_idx[t]] = k[t], v_pool[slot_idx[t]] = v[t] for slot_idx[t] >= 0 (in place)."""
+    status = _marshal.kv_append(k, v, slot_idx, k_pool, v_pool)
+    if status is not None:
+        return _check(status)
     _dev(k, torch.bfloat16, "k"); _dev(v, torch.bfloat16, "v"); _dev(slot_idx, torch.int32, "slot_idx")
     _dev(k_pool, torch.bfloat16, "k_pool"); _dev(v_pool, torch.bfloat16, "v_pool")
     T, Hkv, D = k.shape

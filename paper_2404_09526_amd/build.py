@@ -1,4 +1,4 @@
-"""Builds libesp.so (HIP, gfx950 only) in-tree with hipcc.  No GPU is needed to build."""
+"""Builds libesp.so (HIP, gfx950 only, hipcc) and the binding's argument checks (_marshal.so, g++) in-tree.  No GPU is needed to build."""
 from __future__ import annotations
 
 import glob
@@ -10,6 +10,9 @@ ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libesp.so")
 SOURCES = sorted(glob.glob(os.path.join(PKG, "csrc", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(PKG, "csrc", "*.h"))) + [os.path.join(ROOT, "include", "esp.h")]
+
+MARSHAL = os.path.join(PKG, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(PKG, "csrc", "marshal.cpp")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -43,5 +46,23 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
     return LIB
 
 
+def build_marshal() -> str:
+    """Compile the native argument checks against the installed torch.  Returns the module's path."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(base, "include"),
+           "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           MARSHAL_SOURCE, "-o", MARSHAL, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath," + os.path.join(base, "lib")]
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + proc.stdout)
+    return MARSHAL
+
+
 if __name__ == "__main__":
     print(build_lib(force=True, verbose=True))
+    print(build_marshal())
