@@ -10,7 +10,12 @@
 
 namespace esp {
 
-template <bool F32, bool OUT32>
+// The partials are loaded N at a time, in up to GROUPS groups: all of them up to four; beyond, four at a time where the call is bound
+// by the chain of loads (up to 4096 pairs), one at a time where it is bound by the memory and registers for more only cost
+// wavefronts.  Measured, us (one at a time, each behind a test for P -> this): two fp32 partials of 256 x 4 pairs 3.5 -> 3.0, sixteen of
+// 31 x 4 9.7 -> 7.2, eight of 32 x 32 5.6 -> 4.7, twelve of 64 x 32 8.8 -> 7.0, four of 1488 x 32 23.7 -> 21.7, four bf16 ones of 8192 x 32 59.5
+// -> 56.1; six fp32 ones of 300 x 32 7.6, with four at a time 8.2; four of 8192 x 32 113 -> 112 (5.4 TB/s).
+template <bool F32, bool OUT32, int N, int GROUPS>
 __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, int64_t pairs,
                                                     uint4* O, float* LSE_out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -19,11 +24,13 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
     int seg = (int)(i & 15);
 
     float m = -INFINITY;
-    float lse[ESP_MAX_PARTIALS];
+    float lse[GROUPS][N];
 #pragma unroll
-    for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
-        lse[p] = (p < P) ? parts.LSE_parts[p][pair] : -INFINITY;
-        m = fmaxf(m, lse[p]);
+    for (int g = 0; g < GROUPS; ++g) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) lse[g][u] = g == 0 || N * g + u < P ? parts.LSE_parts[N * g + u][pair] : -INFINITY;
+#pragma unroll
+        for (int u = 0; u < N; ++u) m = fmaxf(m, lse[g][u]);
     }
     // The maximum passes a NaN log-sum-exp over; its weight is NaN and makes the pair NaN, also where there is nothing but -inf
     // beside it: the weights are then taken against 0.  (A test of all sixteen for NaN took 0.25 us of the 28.7 of a split call
@@ -32,21 +39,31 @@ __global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, 
     float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     float wsum = 0.f;
 #pragma unroll
-    for (int p = 0; p < ESP_MAX_PARTIALS; ++p) {
-        if (p < P) {
-            // an empty partial (LSE = -inf) gets weight exp(-inf) = 0
-            float w = __expf(lse[p] - ref);
-            wsum += w;
+    for (int g = 0; g < GROUPS; ++g) {
+        if (g > 0 && N * g >= P) continue;
+        constexpr int kPieces = F32 ? 2 : 1;
+        uint4 piece[N][kPieces] = {};
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            if (g > 0 && N * g + u >= P) continue;
+            const uint4* src = (const uint4*)parts.O_parts[N * g + u] + (pair * 16 + seg) * kPieces;
+#pragma unroll
+            for (int e = 0; e < kPieces; ++e) piece[u][e] = load_once(&src[e]);
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
             float f[8];
             if (F32) {
-                const float4* src = (const float4*)parts.O_parts[p] + (pair * 16 + seg) * 2;
-                const float4 a = load_once(&src[0]), b = load_once(&src[1]);
-                f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+                const float4 x = __builtin_bit_cast(float4, piece[u][0]), y = __builtin_bit_cast(float4, piece[u][kPieces - 1]);
+                f[0] = x.x; f[1] = x.y; f[2] = x.z; f[3] = x.w; f[4] = y.x; f[5] = y.y; f[6] = y.z; f[7] = y.w;
             } else {
-                const uint4 o = load_once(&((const uint4*)parts.O_parts[p])[pair * 16 + seg]);
+                const uint4 o = piece[u][0];
                 f[0] = bf16_lo(o.x); f[1] = bf16_hi(o.x); f[2] = bf16_lo(o.y); f[3] = bf16_hi(o.y);
                 f[4] = bf16_lo(o.z); f[5] = bf16_hi(o.z); f[6] = bf16_lo(o.w); f[7] = bf16_hi(o.w);
             }
+            // an empty partial (LSE = -inf) gets weight exp(-inf) = 0
+            const float w = __expf(lse[g][u] - ref);
+            wsum += w;
             if (w != 0.f) {  // keeps non-finite garbage of an empty partial out of the sum
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[e] += w * f[e];
@@ -76,12 +93,20 @@ esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_
     int64_t threads = pairs * 16;
     int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "merge: too many rows for one launch");
-    if (parts_f32 && o_f32)
-        hipLaunchKernelGGL((merge_kernel<true, true>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
-    else if (parts_f32)
-        hipLaunchKernelGGL((merge_kernel<true, false>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
-    else
-        hipLaunchKernelGGL((merge_kernel<false, false>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out);
+#define ESP_MERGE_KERNEL(F32, OUT32, N, GROUPS) \
+    hipLaunchKernelGGL((merge_kernel<F32, OUT32, N, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, (uint4*)O, LSE_out)
+#define ESP_MERGE_LAUNCH(F32, OUT32)                                  \
+    if (P == 1) ESP_MERGE_KERNEL(F32, OUT32, 1, 1);                   \
+    else if (P == 2) ESP_MERGE_KERNEL(F32, OUT32, 2, 1);              \
+    else if (P == 3) ESP_MERGE_KERNEL(F32, OUT32, 3, 1);              \
+    else if (P == 4) ESP_MERGE_KERNEL(F32, OUT32, 4, 1);              \
+    else if (pairs <= 4096) ESP_MERGE_KERNEL(F32, OUT32, 4, ESP_MAX_PARTIALS / 4); \
+    else ESP_MERGE_KERNEL(F32, OUT32, 1, ESP_MAX_PARTIALS);
+    if (parts_f32 && o_f32) { ESP_MERGE_LAUNCH(true, true) }
+    else if (parts_f32) { ESP_MERGE_LAUNCH(true, false) }
+    else { ESP_MERGE_LAUNCH(false, false) }
+#undef ESP_MERGE_LAUNCH
+#undef ESP_MERGE_KERNEL
     return check_launch("merge_kernel");
 }
 

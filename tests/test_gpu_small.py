@@ -660,6 +660,22 @@ def test_merge_kernel(esp, cuda, P):
     assert torch.equal(O0.view(torch.int16), Om.view(torch.int16))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("P,T", [(3, 37), (5, 37), (8, 512), (9, 37), (5, 513), (16, 513)])
+def test_merge_groups_of_partials(esp, cuda, P, T, dtype):
+    """Partials loaded in one group, in groups with and without a remainder (up to 4096 pairs, 512 x 8), and one at a time beyond."""
+    g = torch.Generator(device=cuda).manual_seed(80 + P)
+    Os = [torch.randn((T, 8, 128), generator=g, device=cuda).to(dtype) for _ in range(P)]
+    Ls = [torch.randn((T, 8), generator=g, device=cuda) * 4 for _ in range(P)]
+    Ls[P - 1][::2] = float("-inf")
+    Os[P - 1][::2] = float("nan")
+    O, LSE = esp.esp_merge_partials(Os, Ls)
+    torch.cuda.synchronize()
+    Oref, Lref = oracle.merge_partials(np.nan_to_num(np.stack([o.double().cpu().numpy() for o in Os]), nan=0.0),
+                                       np.stack([l.double().cpu().numpy() for l in Ls]))
+    check_o_lse(O.float().cpu().numpy().reshape(-1, 128), LSE.cpu().numpy().reshape(-1), Oref.reshape(-1, 128), Lref.reshape(-1), f"merge {P} x {T}")
+
+
 def test_device_side_errors_are_reported_not_thrown(esp, cuda):
     q = torch.zeros((4, 4, 64), dtype=torch.bfloat16, device=cuda)
     with pytest.raises(esp.EspError) as e:
