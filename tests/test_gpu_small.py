@@ -786,6 +786,26 @@ def test_prefill_scores_beyond_the_optimistic_range_take_the_exact_sweep(esp, cu
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("what", ["sink", "half-row", "overflow", "underflow"])
+def test_prefill_of_many_heads_whatever_the_scores(esp, cuda, what):
+    """The four kinds of scores above on 64 / 32 heads: too many rows for the kernel of short calls, so these go through the main
+    one's pipelined pass, its moves of the offset, and its exact sweep; dense rows and pool rows."""
+    Tq, Tkv = 300, 1100
+    pc = wl.contiguous_prefill(f"many-heads-{what}", Tq, 2000, [(0, Tkv)], 64, 32, 45, cuda, causal=False)
+    s, u = pc.shards[0], torch.ones(128, dtype=torch.bfloat16, device=cuda)
+    if what == "sink":
+        s.k[300:303] *= 40.0
+        s.k[0:64] *= 0.01
+    else:
+        pc.q[:] = (pc.q.float() * 0.05 + 1.5).to(torch.bfloat16)
+        s.k[:] = (s.k.float() * 0.05 - (12.0 if what == "underflow" else 0.0)).to(torch.bfloat16)
+        for idx, c in {"half-row": ((300, 1.5), (523, 2.5), (1004, 3.5)), "overflow": ((777, 16.0), (1090, 15.5)), "underflow": ((100, 12.0), (101, 12.0))}[what]:
+            s.k[idx] = c * u
+    run_prefill_case(esp, pc)
+    run_pool_direct_case(esp, pc, 46)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv", [(4, 2), (8, 8)])
 def test_prefill_more_items_than_workgroups(esp, cuda, Hq, Hkv):
     """More (query tile, head) items than the launch has workgroups, so every persistent workgroup works through
