@@ -447,8 +447,11 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
         }
     };
     if (s1 > s0) {
-        const int n = parts > 0 ? min(parts, (s1 - s0 + range - 1) / range) : (s1 - 1) / range - s0 / range + 1;
-        const int64_t first = s0 / range + b;                             // the slots of consecutive ranges
+        const int w_lo = s0 / range;
+        const int64_t first = w_lo + b;                             // the slots of consecutive ranges
+        int n;
+        if (parts > 0) n = min(parts, (s1 - s0 + range - 1) / range);
+        else n = (s1 - 1) / range - w_lo + 1;
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
             float4 v[U];

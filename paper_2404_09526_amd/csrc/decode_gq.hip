@@ -23,6 +23,7 @@
 
 namespace esp {
 
+template <bool BY_REQUEST>
 __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     const uint16_t* __restrict__ q, const char* __restrict__ k_pool, const char* __restrict__ v_pool,
     const int32_t* __restrict__ slot_idx, const int32_t* __restrict__ seq_offsets, int32_t B, int32_t total_tokens,
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
 
     int b;
     int32_t t0, t1, slots;
-    if (parts > 0) {
+    if (BY_REQUEST) {
         const RequestRange at = request_range(w, parts, range, B, seq_offsets);
         b = at.b; t0 = at.t0; t1 = at.t1; w = at.w;
         if (t0 >= t1) return;
@@ -145,9 +146,13 @@ esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_poo
     const int G = Hq / Hkv;
     const int chunks = (G + 31) / 32;
     if (Hkv > 65535 || chunks > 65535) return fail(ESP_ERR_UNSUPPORTED, "decode: too many heads for one launch");
-    hipLaunchKernelGGL(decode_partial_gq_kernel, dim3(parts > 0 ? B * parts : nwg, Hkv, chunks), dim3(kGqWaves * 64), 0, stream, (const uint16_t*)q,
-                       (const char*)k_pool, (const char*)v_pool, slot_idx, seq_offsets, B, total_tokens, range, parts, Hq, Hkv,
-                       scale_log2, part_acc, part_ml);
+#define ESP_GQ_LAUNCH(BY_REQUEST, RANGES)                                                                                                 \
+    hipLaunchKernelGGL(decode_partial_gq_kernel<BY_REQUEST>, dim3(RANGES, Hkv, chunks), dim3(kGqWaves * 64), 0, stream, (const uint16_t*)q, \
+                       (const char*)k_pool, (const char*)v_pool, slot_idx, seq_offsets, B, total_tokens, range, parts, Hq, Hkv,            \
+                       scale_log2, part_acc, part_ml)
+    if (parts > 0) ESP_GQ_LAUNCH(true, B * parts);
+    else ESP_GQ_LAUNCH(false, nwg);
+#undef ESP_GQ_LAUNCH
     return check_launch("decode_partial_gq_kernel");
 }
 
