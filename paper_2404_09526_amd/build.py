@@ -24,14 +24,14 @@ FLAGS = [
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS)
+    for built, sources in ((LIB, SOURCES + HEADERS), (MARSHAL, [MARSHAL_SOURCE, os.path.join(ROOT, "include", "esp.h")])):
+        if not os.path.exists(built) or any(os.path.getmtime(f) > os.path.getmtime(built) for f in sources):
+            return True
+    return False
 
 
 def build_lib(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP source into libesp.so.  Returns the library path."""
+    """Compile every HIP source into libesp.so, and the binding's argument checks.  Returns the library path."""
     if not force and not is_stale():
         return LIB
     cmd = [HIPCC] + FLAGS + SOURCES + ["-o", LIB]
@@ -43,6 +43,7 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
+    build_marshal()
     return LIB
 
 
@@ -65,4 +66,3 @@ def build_marshal() -> str:
 
 if __name__ == "__main__":
     print(build_lib(force=True, verbose=True))
-    print(build_marshal())
