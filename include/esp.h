@@ -17,7 +17,7 @@
  *   - Every data pointer is DEVICE memory owned by the caller unless a
  *     parameter says "host".  The library never allocates, frees or keeps
  *     device memory.  Its only state between calls is process-wide and small:
- *     a launch counter that tags the prefill workspace (see there) and the two
+ *     a launch counter that tags the prefill workspace (see there) and the
  *     debugging switches at the end of this file.
  *   - bf16 tensors are passed as `const void*` (16-bit patterns); layouts are
  *     token-major and dense: Q/O [T, Hq, D], K/V [T, Hkv, D], pools
@@ -397,7 +397,7 @@ esp_status esp_fit_prefill_model(
     double* coef);
 
 /*
- * Debugging switches (process-wide; each returns the previous setting).
+ * Debugging switches (the first two process-wide; each returns the previous setting).
  *   esp_debug_set_validate: the host-side check of device index arrays described at
  *     the top (default: ESP_DEBUG_VALIDATE in the environment, read once at load time).
  *   esp_debug_set_prefill_sync_ticks: the longest time, in ticks of the 100 MHz wall
@@ -405,9 +405,22 @@ esp_status esp_fit_prefill_model(
  *     the start of a round (default 15000, or ESP_PREFILL_SYNC_TICKS read once at load
  *     time; 0 makes every such wait give up at once; negative restores the default).
  *     It changes timing only, never results.
+ *   esp_debug_set_prefill_plan: there are two prefill kernels, one for calls with few
+ *     query rows, and a call's keys may be cut into parts.  By default (0) both follow
+ *     from an estimate of the call's time; n > 0 makes every prefill call of the CALLING
+ *     THREAD run on the main kernel in n parts, n < 0 on the other one in -n, at most
+ *     ESP_MAX_PARTIALS (in one where the workspace does not hold them; anything beyond
+ *     restores the default).  The workspace sizes asked for on this thread follow.
+ *     For tests that are about one of the kernels.
+ * and, changing nothing,
+ *   esp_debug_prefill_plan: what a call of these sizes with such a workspace would run
+ *     on now, in the same form (0: the sizes are not valid).  Host code.
  */
 int32_t esp_debug_set_validate(int32_t on);
 int32_t esp_debug_set_prefill_sync_ticks(int32_t ticks);
+int32_t esp_debug_set_prefill_plan(int32_t plan);
+int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv,
+                               int32_t Hq, int32_t Hkv, size_t workspace_bytes);
 
 /* Message of the last error on the calling thread (static storage, never NULL). */
 const char* esp_last_error(void);

@@ -85,6 +85,14 @@ const char* esp_last_error(void) { return g_err; }
 
 int32_t esp_debug_set_validate(int32_t on) { return g_validate.exchange(on ? 1 : 0, std::memory_order_relaxed); }
 int32_t esp_debug_set_prefill_sync_ticks(int32_t ticks) { return set_prefill_sync_ticks(ticks); }
+int32_t esp_debug_set_prefill_plan(int32_t plan) {
+    return set_prefill_plan(plan < -ESP_MAX_PARTIALS || plan > ESP_MAX_PARTIALS ? 0 : plan);
+}
+int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv,
+                               size_t workspace_bytes) {
+    if (Tq < 0 || Tkv < 0 || batch < 1 || !heads_ok(Hq, Hkv)) return 0;
+    return query_prefill_plan(workspace_bytes, Tq, Tkv, batch, max_q, max_kv, Hq, Hkv);
+}
 const char* esp_version(void) { return "esp 0.1 gfx950"; }
 
 size_t esp_prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t D) {

@@ -105,6 +105,11 @@ esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_poo
                             int32_t Hq, int32_t Hkv, float scale_log2, float* part_acc, float* part_ml, hipStream_t stream);
 
 int32_t set_prefill_sync_ticks(int32_t ticks);   // returns the previous value; negative restores the built-in default
+// which kernel prefill calls of this thread run on, in how many parts: n: the main one in n, -n: the one for few rows in n, 0: by
+// estimate.  Returns the previous value.
+int32_t set_prefill_plan(int32_t plan);
+// what a call of these sizes would run on (the same form; never 0)
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv);
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                                 const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                                 int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream);

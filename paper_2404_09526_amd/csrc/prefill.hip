@@ -110,10 +110,15 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
 struct PrefillPlan { int32_t splits, use_short, main_splits; };   // main_splits: what the main kernel would be given
+static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
 static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t most_splits) {
     constexpr double kCus = 256, kTileLeast = 0.7, kTileRows = 0.75, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
     constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6;
     if (Tq <= 0 || Tkv <= 0) return {1, 0, 1};
+    if (t_forced_plan != 0) {
+        const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
+        return {S, t_forced_plan < 0 ? 1 : 0, S};
+    }
     const double rows = (double)Tq * (Hq / Hkv);
     const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
     const double tiles = ceil((double)Tkv / batch / kBN);
@@ -151,6 +156,23 @@ static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S 
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
     const PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);   // (either way: the size is that of the main kernel at least)
     return kPrefillCounterBytes + split_bytes(plan.splits > plan.main_splits ? plan.splits : plan.main_splits, Tq, Hq);
+}
+
+int32_t set_prefill_plan(int32_t plan) {
+    const int32_t before = t_forced_plan;
+    t_forced_plan = plan;
+    return before;
+}
+// with a workspace of so many bytes, in the form of set_prefill_plan's argument
+static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
+    const PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);
+    if (workspace_bytes >= kPrefillCounterBytes + split_bytes(plan.splits, Tq, Hq)) return plan;
+    return prefill_plan(Tq, Tkv, batch, Hq, Hkv, 1);               // a block without room for the parts
+}
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv) {
+    (void)max_q; (void)max_kv;
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, Hq, Hkv);
+    return plan.use_short ? -plan.splits : plan.splits;
 }
 
 constexpr int kStages = 4;            // LDS stages per operand; tile j lives in stage j % 4
@@ -1266,9 +1288,7 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
     a.q_pos = q_pos; a.kv_pos = kv_pos; a.cu_q = cu_q; a.cu_kv = cu_kv;
     const size_t counters = kPrefillCounterBytes;
-    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);
-    if (workspace_bytes < counters + split_bytes(plan.splits, Tq, Hq))   // a block without room for the parts
-        plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, 1);
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, Hq, Hkv);
     const int32_t S = plan.splits;
     a.splits = S;
     if (S > 1) {

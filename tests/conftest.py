@@ -18,3 +18,28 @@ def cuda():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     return torch.device("cuda:0")
+
+
+# Which of the two prefill kernels a call runs on, and whether its keys are cut, follows from its sizes: tests of small calls that are
+# about a kernel, or about both, say so.  (1, 3: the main kernel, uncut and in three parts; -1, -3: the one for few rows.)
+def on_plan(plan):
+    from paper_2404_09526_amd import binding
+    before = binding.esp_debug_set_prefill_plan(plan)
+    assert binding.esp_debug_prefill_plan(40, 3000, 1, 40, 3000, 8, 2) == plan
+    yield plan
+    assert binding.esp_debug_set_prefill_plan(before) == plan
+
+
+@pytest.fixture(params=[1, 3, -1, -3], ids=["main", "main-cut", "short", "short-cut"])
+def each_prefill_plan(request, cuda):
+    yield from on_plan(request.param)
+
+
+@pytest.fixture(params=[3, -3], ids=["main-cut", "short-cut"])
+def each_prefill_cut(request, cuda):
+    yield from on_plan(request.param)
+
+
+@pytest.fixture
+def main_prefill_kernel(cuda):
+    yield from on_plan(1)

@@ -28,6 +28,7 @@ def nan_pattern(O, LSE, hit, what):
 @pytest.mark.parametrize("out", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("at", [100, 2980])
 @pytest.mark.parametrize("room", ["split", "whole"])
+@pytest.mark.usefixtures("each_prefill_cut")
 def test_prefill_nan_key_shows_however_the_keys_are_cut(esp, cuda, room, at, out):
     """40 tokens at the end of 3000: one NaN key that all rows see, in the first part, and one on the diagonal.  The dense
     call, the call that keeps rows and the one on pool rows; a workspace for the parts and one without room for them."""
@@ -60,6 +61,7 @@ def test_prefill_nan_key_shows_however_the_keys_are_cut(esp, cuda, room, at, out
         check_o_lse(O.float().cpu().numpy()[rows, heads], LSE.cpu().numpy()[rows, heads], Or, Lr, f"{what}, rows without the key")
 
 
+@pytest.mark.usefixtures("each_prefill_cut")
 def test_prefill_nan_query_row_in_a_split_call(esp, cuda):
     """Every part's result of such a row is NaN, and so is their combination."""
     pc = wl.contiguous_prefill("nan-query", 40, 2960, [(0, 3000)], 8, 2, 52, cuda)

@@ -1,0 +1,32 @@
+"""Which prefill kernel a call runs on, and in how many parts (host code; no GPU)."""
+import threading
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def esp():
+    from paper_2404_09526_amd import binding
+    return binding
+
+
+def test_a_forced_plan_holds_for_its_thread_and_for_the_workspaces_it_asks_for(esp):
+    sizes = (40, 3000, 1, 40, 3000, 8, 2)
+    by_estimate, room = esp.esp_debug_prefill_plan(*sizes), esp.esp_prefill_workspace_bytes(40, 3000, 1, 8, 2, 128)
+    assert by_estimate != 0
+    part = 40 * 8 * (128 + 1) * 4
+    for plan in (1, 5, -1, -7):
+        assert esp.esp_debug_set_prefill_plan(plan) == 0
+        try:
+            need = 256 + (abs(plan) * part if abs(plan) > 1 else 0)
+            assert esp.esp_debug_prefill_plan(*sizes) == plan and esp.esp_prefill_workspace_bytes(40, 3000, 1, 8, 2, 128) == need
+            assert esp.esp_debug_prefill_plan(*sizes, workspace_bytes=256) == (1 if plan > 0 else -1)
+            there = []
+            t = threading.Thread(target=lambda: there.append((esp.esp_debug_prefill_plan(*sizes), esp.esp_prefill_workspace_bytes(40, 3000, 1, 8, 2, 128))))
+            t.start(); t.join()
+            assert there == [(by_estimate, room)]
+        finally:
+            assert esp.esp_debug_set_prefill_plan(0) == plan
+    assert esp.esp_debug_prefill_plan(*sizes) == by_estimate
+    assert esp.esp_debug_set_prefill_plan(17) == 0 and esp.esp_debug_set_prefill_plan(0) == 0            # beyond ESP_MAX_PARTIALS: none
+    assert esp.esp_debug_prefill_plan(40, 3000, 1, 40, 3000, 8, 3) == 0                                  # Hq % Hkv
