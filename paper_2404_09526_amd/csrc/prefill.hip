@@ -109,15 +109,15 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
 // 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
-struct PrefillPlan { int32_t splits, use_short, main_splits; };   // main_splits: what the main kernel would be given
+struct PrefillPlan { int32_t splits, use_short; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
 static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t most_splits) {
     constexpr double kCus = 256, kTileLeast = 0.7, kTileRows = 0.75, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
     constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6;
-    if (Tq <= 0 || Tkv <= 0) return {1, 0, 1};
+    if (Tq <= 0 || Tkv <= 0) return {1, 0};
     if (t_forced_plan != 0) {
         const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
-        return {S, t_forced_plan < 0 ? 1 : 0, S};
+        return {S, t_forced_plan < 0 ? 1 : 0};
     }
     const double rows = (double)Tq * (Hq / Hkv);
     const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
@@ -135,7 +135,7 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
         us += merge_us(S);
         if (S == 1 || us < 0.97 * best_us) { best = S; best_us = us; }
     }
-    PrefillPlan plan = {best, 0, best};
+    PrefillPlan plan = {best, 0};
     const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
     const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), swept = blocks / Hkv / batch * seen * kv_bytes;
     for (int32_t S = 1; S <= most_splits && (S == 1 || 2 * tiles >= kShortWaves * S); ++S) {
@@ -144,7 +144,7 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
         const double n = blocks * S / kCus, steps = ceil(2 * tiles / S / kShortWaves);
         double us = (seen > 0.8 ? ceil(n) : n <= 1 ? 1 : n + 0.3) * (kShortItem + (kv_bytes > 2e8 ? kShortFar : kShortStep) * steps);
         us = fmax(us, swept / kShortBytesPerUs) + merge_us(S);
-        if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1, best}; best_us = us; }
+        if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1}; best_us = us; }
     }
     return plan;
 }
@@ -154,8 +154,7 @@ static size_t split_lse_bytes(int32_t Tq, int32_t Hq) { return ((size_t)Tq * Hq 
 static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S * (split_o_bytes(Tq, Hq) + split_lse_bytes(Tq, Hq)) : 0; }
 
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    const PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);   // (either way: the size is that of the main kernel at least)
-    return kPrefillCounterBytes + split_bytes(plan.splits > plan.main_splits ? plan.splits : plan.main_splits, Tq, Hq);
+    return kPrefillCounterBytes + split_bytes(prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS).splits, Tq, Hq);
 }
 
 int32_t set_prefill_plan(int32_t plan) {

@@ -30,3 +30,14 @@ def test_a_forced_plan_holds_for_its_thread_and_for_the_workspaces_it_asks_for(e
     assert esp.esp_debug_prefill_plan(*sizes) == by_estimate
     assert esp.esp_debug_set_prefill_plan(17) == 0 and esp.esp_debug_set_prefill_plan(0) == 0            # beyond ESP_MAX_PARTIALS: none
     assert esp.esp_debug_prefill_plan(40, 3000, 1, 40, 3000, 8, 3) == 0                                  # Hq % Hkv
+
+
+def room_for(parts, Tq, Hq):
+    return 256 + (parts * (Tq * Hq * 512 + (Tq * Hq * 4 + 255) // 256 * 256) if parts > 1 else 0)
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 4), (32, 8), (64, 8), (12, 12)])
+def test_one_request_asks_for_the_room_that_its_parts_take(esp, Hq, Hkv):
+    for Tq, Tkv in ((1, 1), (1100, 1100), (1024, 1024), (256, 512), (40, 3000), (300, 20300), (31, 70195), (2000, 9000), (1488, 210407)):
+        parts = abs(esp.esp_debug_prefill_plan(Tq, Tkv, 1, Tq, Tkv, Hq, Hkv))
+        assert esp.esp_prefill_workspace_bytes(Tq, Tkv, 1, Hq, Hkv, 128) == room_for(parts, Tq, Hq), (Tq, Tkv, parts)
