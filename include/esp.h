@@ -79,15 +79,18 @@ typedef int32_t esp_status;
  *   cu_q, cu_kv: int32 [batch+1] prefix offsets of the requests packed in q and
  *     in the shard (request r owns rows cu[r]..cu[r+1]); both NULL with
  *     batch = 1 means one request spanning everything.
- *   max_q, max_kv: upper bounds on a request's row counts (host-known; used
- *     only to size the launch).
+ *   max_q, max_kv: upper bounds on a request's row counts (host-known).  Results
+ *     do not depend on them but for the order of fp32 sums; whether and how the
+ *     keys of a batch are cut into parts follows the longest request, max_kv, so
+ *     a bound that is far from it costs time.
  *   O [Tq,Hq,D] bf16, LSE [Tq,Hq] float: written for every row.
  *   workspace: at least esp_prefill_workspace_bytes(...) bytes, 256-byte
  *     aligned; contents need not be preserved between calls.  It holds, for calls
  *     with few query rows against many keys, the partial results of the parts the
  *     keys are cut into (a smaller block, down to 256 bytes, is accepted: such a
  *     call then runs uncut, and slower; the size does not grow with Tq and Tkv
- *     throughout, so a block for several calls takes the largest of theirs), and
+ *     throughout, so a block for several calls takes the largest of theirs; for a
+ *     batch it covers requests of unequal length too, up to 64 MB of parts), and
  *     work counters that are never cleared: every launch tags them with a number of
  *     its own (a per-process random 32-bit start, then +1 per call), so memory
  *     that has never been written is mistaken for the current launch's counters

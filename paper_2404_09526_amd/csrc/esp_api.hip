@@ -90,8 +90,8 @@ int32_t esp_debug_set_prefill_plan(int32_t plan) {
 }
 int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv,
                                size_t workspace_bytes) {
-    if (Tq < 0 || Tkv < 0 || batch < 1 || !heads_ok(Hq, Hkv)) return 0;
-    return query_prefill_plan(workspace_bytes, Tq, Tkv, batch, max_q, max_kv, Hq, Hkv);
+    if (Tq < 0 || Tkv < 0 || batch < 1 || max_q < 0 || max_q > Tq || max_kv < 0 || max_kv > Tkv || !heads_ok(Hq, Hkv)) return 0;
+    return query_prefill_plan(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
 }
 const char* esp_version(void) { return "esp 0.1 gfx950"; }
 
@@ -149,7 +149,7 @@ static esp_status prefill_entry(const void* q, const void* k, const void* v, con
         if (st == ESP_OK) st = check_offsets("prefill: cu_kv", cu_kv, batch, Tkv, max_kv, (hipStream_t)stream);
         if (st != ESP_OK) return st;
     }
-    return launch_prefill(q, k, v, q_pos, kv_pos, cu_q, cu_kv, batch, Tq, Tkv, max_q, max_kv, Hq, Hkv,
+    return launch_prefill(q, k, v, q_pos, kv_pos, cu_q, cu_kv, batch, Tq, Tkv, max_kv, Hq, Hkv,
                           softmax_scale, causal, o_f32, O, LSE, workspace, workspace_bytes,
                           Tkv > 0 ? retain_slot : nullptr, k_pool, v_pool, Tkv > 0 ? kv_slot : nullptr, (hipStream_t)stream);
 }

@@ -109,7 +109,7 @@ int32_t set_prefill_sync_ticks(int32_t ticks);   // returns the previous value; 
 // estimate.  Returns the previous value.
 int32_t set_prefill_plan(int32_t plan);
 // what a call of these sizes would run on (the same form; never 0)
-int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv);
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv);
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                                 const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                                 int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream);
@@ -119,7 +119,7 @@ constexpr size_t kPrefillCounterBytes = 256;      // what every prefill call nee
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv);
 esp_status launch_prefill(const void* q, const void* k, const void* v, const int32_t* q_pos, const int32_t* kv_pos,
                           const int32_t* cu_q, const int32_t* cu_kv, int32_t batch, int32_t Tq, int32_t Tkv,
-                          int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv, float softmax_scale,
+                          int32_t max_kv, int32_t Hq, int32_t Hkv, float softmax_scale,
                           int32_t causal, int32_t o_f32, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                           const int32_t* retain_slot, void* k_pool, void* v_pool, const int32_t* kv_slot,
                           hipStream_t stream);

@@ -109,52 +109,88 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
 // 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
+// Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
+// last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
+// which rows the longest request has is not known.  Over 309 random batches that it may cut differently (time against the even
+// cut's): any gain promised 0.76 on average, 15 of them 3 .. 21 % slower; a fifth 0.77 and 8; three tenths 0.82 and 1.
+// Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 64.6 -> 32.1 us, 8 on 200000
+// beside 63 of 8 on 512 2222 -> 479, 300 on 20300 beside three of 300 on 600 330 -> 169; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
+// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
 struct PrefillPlan { int32_t splits, use_short; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
-static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t most_splits) {
+static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, int32_t most_splits) {
     constexpr double kCus = 256, kTileLeast = 0.7, kTileRows = 0.75, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
-    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6;
+    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
     if (Tq <= 0 || Tkv <= 0) return {1, 0};
     if (t_forced_plan != 0) {
         const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
         return {S, t_forced_plan < 0 ? 1 : 0};
     }
-    const double rows = (double)Tq * (Hq / Hkv);
-    const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
-    const double tiles = ceil((double)Tkv / batch / kBN);
+    const double rows = (double)Tq * (Hq / Hkv), tiles = ceil((double)Tkv / batch / kBN);
     const double seen = Tq < Tkv ? 1.0 - 0.5 * Tq / Tkv : 0.5;        // of the tiles, on average, with the chunk at the shard's end
+    const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
     const double kTile = kTileLeast + kTileRows * fmin(rows / batch / kBM, 1);
-    int32_t best = 1;
-    double best_us = 0;
-    auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
-    for (int32_t S = 1; S <= most_splits && (S == 1 || tiles >= 4 * S); ++S) {
-        const double n = items * S / kCus;
-        double us;
-        if (seen > 0.8) us = ceil(n) * (seen * tiles / S * kTile + kItem);
-        else us = fmax(tiles / S * kTile + kItem, (n + 0.3) * (seen * tiles / S * kTile + kItem));
-        us += merge_us(S);
-        if (S == 1 || us < 0.97 * best_us) { best = S; best_us = us; }
-    }
-    PrefillPlan plan = {best, 0};
     const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
-    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), swept = blocks / Hkv / batch * seen * kv_bytes;
-    for (int32_t S = 1; S <= most_splits && (S == 1 || 2 * tiles >= kShortWaves * S); ++S) {
-        if (S > 1 && blocks > Hkv * batch && Hkv * S % 8 != 0) continue;
-        if ((rows / kShortRows + batch) * Hkv * S > 4e6) break;      // one workgroup each: what a launch holds
-        const double n = blocks * S / kCus, steps = ceil(2 * tiles / S / kShortWaves);
-        double us = (seen > 0.8 ? ceil(n) : n <= 1 ? 1 : n + 0.3) * (kShortItem + (kv_bytes > 2e8 ? kShortFar : kShortStep) * steps);
-        us = fmax(us, swept / kShortBytesPerUs) + merge_us(S);
-        if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1}; best_us = us; }
-    }
-    return plan;
+    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), step = kv_bytes > 2e8 ? kShortFar : kShortStep;
+    // `longest`: tiles of the longest request, or of all alike (`tiles`)
+    auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
+    auto main_us = [&](int32_t S, double longest) {
+        const double n = items * S / kCus, item = seen * tiles / S * kTile + kItem;
+        double us = seen > 0.8 ? ceil(n) * item : fmax(tiles / S * kTile + kItem, (n + 0.3) * item);
+        if (longest > tiles) us = fmax(us, fmax(n - 1, 0) * item + longest / S * kTile + kItem);
+        return us + merge_us(S);
+    };
+    auto short_us = [&](int32_t S, double longest) {
+        const double n = blocks * S / kCus, item = kShortItem + step * ceil(2 * tiles / S / kShortWaves);
+        double us = (seen > 0.8 ? ceil(n) : n <= 1 ? 1 : n + 0.3) * item, swept = blocks / Hkv / batch * seen * kv_bytes;
+        if (longest > tiles) {
+            us = fmax(us, fmax(n - 1, 0) * item + kShortItem + step * ceil(2 * longest / S / kShortWaves));
+            swept = fmax(swept, blocks / batch * longest * kBN * (4 * kHeadDim));
+        }
+        return fmax(us, swept / kShortBytesPerUs) + merge_us(S);
+    };
+    auto least = [&](double longest) {
+        PrefillPlan plan = {1, 0};
+        double best_us = main_us(1, longest);
+        for (int32_t S = 2; S <= most_splits && longest >= 4 * S; ++S) {
+            const double us = main_us(S, longest);
+            if (us < 0.97 * best_us) { plan = {S, 0}; best_us = us; }
+        }
+        for (int32_t S = 1; S <= most_splits && (S == 1 || 2 * longest >= kShortWaves * S); ++S) {
+            if (S > 1 && blocks > Hkv * batch && Hkv * S % 8 != 0) continue;
+            if ((rows / kShortRows + batch) * Hkv * S > 4e6) break;  // one workgroup each: what a launch holds
+            const double us = short_us(S, longest);
+            if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1}; best_us = us; }
+        }
+        return plan;
+    };
+    const PrefillPlan even = least(tiles);
+    const double longest = ceil((double)max_kv / kBN);
+    if (longest <= tiles) return even;
+    const PrefillPlan uneven = least(longest);
+    auto us_of = [&](const PrefillPlan& p) { return p.use_short ? short_us(p.splits, longest) : main_us(p.splits, longest); };
+    return us_of(uneven) < kUnevenGain * us_of(even) ? uneven : even;
 }
 // bytes of the parts' results: O [S][Tq, Hq, 128] fp32, then LSE [S][Tq, Hq], each part on a 256-byte boundary
 static size_t split_o_bytes(int32_t Tq, int32_t Hq) { return (size_t)Tq * Hq * kHeadDim * 4; }
 static size_t split_lse_bytes(int32_t Tq, int32_t Hq) { return ((size_t)Tq * Hq * 4 + 255) / 256 * 256; }
 static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S * (split_o_bytes(Tq, Hq) + split_lse_bytes(Tq, Hq)) : 0; }
 
+// Parts that a call may run in.  For a batch the workspace is asked for before the longest request is known: it has room for what
+// equal requests are cut in, and for what the batch would be cut in if one request held all keys, the latter as far as kUnevenBytes go
+// (which few rows fit, and cutting helps only those: the merge of 64 MB of parts takes 30 us).
+constexpr size_t kUnevenBytes = 64 << 20;
+static int32_t prefill_most_splits(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
+    int32_t most = prefill_plan(Tq, Tkv, batch, 0, Hq, Hkv, ESP_MAX_PARTIALS).splits;
+    if (batch > 1) {
+        int32_t uneven = prefill_plan(Tq, Tkv, batch, Tkv, Hq, Hkv, ESP_MAX_PARTIALS).splits;
+        while (uneven > most && split_bytes(uneven, Tq, Hq) > kUnevenBytes) --uneven;
+        if (uneven > most) most = uneven;
+    }
+    return most;
+}
 size_t prefill_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    return kPrefillCounterBytes + split_bytes(prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS).splits, Tq, Hq);
+    return kPrefillCounterBytes + split_bytes(prefill_most_splits(Tq, Tkv, batch, Hq, Hkv), Tq, Hq);
 }
 
 int32_t set_prefill_plan(int32_t plan) {
@@ -162,15 +198,18 @@ int32_t set_prefill_plan(int32_t plan) {
     t_forced_plan = plan;
     return before;
 }
-// with a workspace of so many bytes, in the form of set_prefill_plan's argument
-static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    const PrefillPlan plan = prefill_plan(Tq, Tkv, batch, Hq, Hkv, ESP_MAX_PARTIALS);
+// what a call with a workspace of so many bytes runs on
+static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
+    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, ESP_MAX_PARTIALS);
+    if (batch > 1 && plan.splits > 1) {                            // (a larger workspace than was asked for changes nothing)
+        const int32_t most = prefill_most_splits(Tq, Tkv, batch, Hq, Hkv);
+        if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, most);
+    }
     if (workspace_bytes >= kPrefillCounterBytes + split_bytes(plan.splits, Tq, Hq)) return plan;
-    return prefill_plan(Tq, Tkv, batch, Hq, Hkv, 1);               // a block without room for the parts
+    return prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, 1);       // a block without room for the parts
 }
-int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv) {
-    (void)max_q; (void)max_kv;
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, Hq, Hkv);
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
     return plan.use_short ? -plan.splits : plan.splits;
 }
 
@@ -1278,16 +1317,15 @@ static esp_status merge_parts(const PrefillArgs& a, void* O, float* LSE, int32_t
 
 esp_status launch_prefill(const void* q, const void* k, const void* v, const int32_t* q_pos, const int32_t* kv_pos,
                           const int32_t* cu_q, const int32_t* cu_kv, int32_t batch, int32_t Tq, int32_t Tkv,
-                          int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv, float softmax_scale,
+                          int32_t max_kv, int32_t Hq, int32_t Hkv, float softmax_scale,
                           int32_t causal, int32_t o_f32, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                           const int32_t* retain_slot, void* k_pool, void* v_pool, const int32_t* kv_slot,
                           hipStream_t stream) {
-    (void)max_q; (void)max_kv;
     PrefillArgs a;
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
     a.q_pos = q_pos; a.kv_pos = kv_pos; a.cu_q = cu_q; a.cu_kv = cu_kv;
     const size_t counters = kPrefillCounterBytes;
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, Hq, Hkv);
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
     const int32_t S = plan.splits;
     a.splits = S;
     if (S > 1) {

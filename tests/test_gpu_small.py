@@ -345,22 +345,40 @@ def test_prefill_of_few_rows(esp, cuda, Tq, Tkv, Hq, Hkv, causal):
     assert torch.equal(O5[2:2 + Tq].view(torch.int16), O.view(torch.int16)) and torch.equal(L5[2:2 + Tq].view(torch.int32), LSE.view(torch.int32))
 
 
+def ragged_batch(name, q_lens, kv_lens, Hq, Hkv, seed, device):
+    """One shard: q_lens[r] tokens at the end of kv_lens[r] rows."""
+    gen = torch.Generator(device=device).manual_seed(seed)
+    Tq, Tkv = sum(q_lens), sum(kv_lens)
+    at = lambda parts: torch.tensor(np.concatenate(parts).astype(np.int32), device=device)
+    shard = wl.Shard(wl.randn_bf16((Tkv, Hkv, 128), gen, device), wl.randn_bf16((Tkv, Hkv, 128), gen, device),
+                     at([np.arange(n) for n in kv_lens]), at([[0], np.cumsum(kv_lens)]), max(kv_lens))
+    return wl.PrefillCase(name, Hq, Hkv, 128, 128 ** -0.5, True, wl.randn_bf16((Tq, Hq, 128), gen, device),
+                          at([max(n - m, 0) + np.arange(m) for m, n in zip(q_lens, kv_lens)]), at([[0], np.cumsum(q_lens)]),
+                          max(q_lens), [shard], 0)
+
+
 @pytest.mark.usefixtures("each_prefill_cut")
 def test_prefill_split_batch_with_an_empty_and_a_short_request(esp, cuda):
     """A batch of short chunks behind contexts of very different lengths: requests with fewer KV tiles than parts (some
     parts are empty), one without queries, one without keys."""
     q_lens, kv_lens, Hq, Hkv = [3, 40, 0, 1, 17, 5], [30, 3000, 64, 0, 1700, 5], 4, 2
-    gen = torch.Generator(device=cuda).manual_seed(30)
-    Tq, Tkv = sum(q_lens), sum(kv_lens)
-    at = lambda parts: torch.tensor(np.concatenate(parts).astype(np.int32), device=cuda)
-    shard = wl.Shard(wl.randn_bf16((Tkv, Hkv, 128), gen, cuda), wl.randn_bf16((Tkv, Hkv, 128), gen, cuda),
-                     at([np.arange(n) for n in kv_lens]), at([[0], np.cumsum(kv_lens)]), max(kv_lens))
-    pc = wl.PrefillCase("split-batch", Hq, Hkv, 128, 128 ** -0.5, True, wl.randn_bf16((Tq, Hq, 128), gen, cuda),
-                        at([max(n - m, 0) + np.arange(m) for m, n in zip(q_lens, kv_lens)]), at([[0], np.cumsum(q_lens)]),
-                        max(q_lens), [shard], 0)
+    pc, Tq, Tkv = ragged_batch("split-batch", q_lens, kv_lens, Hq, Hkv, 30, cuda), sum(q_lens), sum(kv_lens)
     assert esp.esp_prefill_workspace_bytes(Tq, Tkv, 6, Hq, Hkv, 128) > esp.esp_prefill_workspace_bytes(Tq, 0, 6, Hq, Hkv, 128)
     run_prefill_case(esp, pc)
     run_pool_direct_case(esp, pc, 32)
+
+
+@pytest.mark.parametrize("q_lens,kv_lens,Hq,Hkv,main", [([16] * 8, [90, 512, 6000, 512, 64, 512, 300, 17], 32, 8, False),
+                                                        ([400] * 4, [500, 500, 5000, 500], 16, 4, True)])
+def test_prefill_batch_of_unequal_contexts(esp, cuda, q_lens, kv_lens, Hq, Hkv, main):
+    """One long conversation beside short ones, cut for the long one's sake: on either kernel, by the estimate, in the workspace asked for."""
+    pc = ragged_batch("unequal", q_lens, kv_lens, Hq, Hkv, 34, cuda)
+    plan = esp.esp_debug_prefill_plan(sum(q_lens), sum(kv_lens), len(q_lens), max(q_lens), max(kv_lens), Hq, Hkv)
+    even = esp.esp_debug_prefill_plan(sum(q_lens), sum(kv_lens), len(q_lens), max(q_lens), 0, Hq, Hkv)
+    assert abs(plan) > abs(even) and (plan > 0) == main
+    run_prefill_case(esp, pc)
+    run_retain_case(esp, pc, 35)
+    run_pool_direct_case(esp, pc, 36)
 
 
 @pytest.mark.usefixtures("each_prefill_plan")

@@ -1,4 +1,6 @@
 """Which prefill kernel a call runs on, and in how many parts (host code; no GPU)."""
+import math
+import random
 import threading
 
 import pytest
@@ -41,3 +43,41 @@ def test_one_request_asks_for_the_room_that_its_parts_take(esp, Hq, Hkv):
     for Tq, Tkv in ((1, 1), (1100, 1100), (1024, 1024), (256, 512), (40, 3000), (300, 20300), (31, 70195), (2000, 9000), (1488, 210407)):
         parts = abs(esp.esp_debug_prefill_plan(Tq, Tkv, 1, Tq, Tkv, Hq, Hkv))
         assert esp.esp_prefill_workspace_bytes(Tq, Tkv, 1, Hq, Hkv, 128) == room_for(parts, Tq, Hq), (Tq, Tkv, parts)
+
+
+# (new tokens, tokens in the shard) of the requests, query heads, KV heads, least parts that the longest request has to be cut in: uncut,
+# or cut as the average request would be, its walk by one workgroup set the time of the call (us, cut by the average -> by the longest)
+UNEVEN = [([(16, 8192)] + [(16, 512)] * 7, 32, 8, 3),           # 64 -> 32
+          ([(32, 16384)] + [(32, 512)] * 7, 8, 8, 4),            # 70 -> 35
+          ([(32, 60000)] + [(32, 64)] * 31, 4, 4, 8),            # 408 -> 68
+          ([(8, 200000)] + [(8, 512)] * 63, 32, 8, 6),           # 2210 -> 480
+          ([(300, 20300)] + [(300, 600)] * 3, 32, 8, 3)]         # 324 -> 161
+
+
+@pytest.mark.parametrize("requests,Hq,Hkv,parts", UNEVEN)
+def test_the_longest_request_of_a_batch_is_cut(esp, requests, Hq, Hkv, parts):
+    new, rows = zip(*requests)
+    sizes, heads = (sum(new), sum(rows), len(requests)), (Hq, Hkv)
+    room = esp.esp_prefill_workspace_bytes(*sizes, *heads, 128)
+    plan = esp.esp_debug_prefill_plan(*sizes, max(new), max(rows), *heads, workspace_bytes=room)
+    assert abs(plan) >= parts and room_for(abs(plan), sum(new), Hq) <= room
+    assert esp.esp_debug_prefill_plan(*sizes, max(new), max(rows), *heads) == plan          # no other in a larger workspace
+    # requests of one length are cut as their average says, whether or not the bound on it is a row or two too high
+    even = -(-sum(rows) // len(requests))
+    assert esp.esp_debug_prefill_plan(*sizes, max(new), even, *heads) == esp.esp_debug_prefill_plan(*sizes, max(new), 0, *heads)
+
+
+def test_a_batch_never_runs_in_more_parts_than_its_workspace_holds(esp):
+    rng = random.Random(7)
+    size = lambda top: int(math.exp(rng.uniform(0, math.log(top))))
+    for _ in range(2000):
+        Hkv = rng.choice((1, 2, 4, 8, 12, 32))
+        Hq, batch = Hkv * rng.choice((1, 2, 4, 8)), rng.randint(1, 64)
+        new, rows = [size(3000) for _ in range(batch)], [size(100000) for _ in range(batch)]
+        sizes = (sum(new), sum(rows), batch)
+        room = esp.esp_prefill_workspace_bytes(*sizes, Hq, Hkv, 128)
+        for longest in (max(rows), sum(rows)) if batch > 1 else (sum(rows),):
+            q = max(new) if batch > 1 else sum(new)
+            plan = esp.esp_debug_prefill_plan(*sizes, q, longest, Hq, Hkv)
+            assert room_for(abs(plan), sum(new), Hq) <= room and 1 <= abs(plan) <= 16
+            assert esp.esp_debug_prefill_plan(*sizes, q, longest, Hq, Hkv, workspace_bytes=room) == plan
