@@ -88,7 +88,7 @@ typedef int32_t esp_status;
  *     aligned; contents need not be preserved between calls.  It holds, for calls
  *     with few query rows against many keys, the partial results of the parts the
  *     keys are cut into (a smaller block, down to 256 bytes, is accepted: such a
- *     call then runs uncut, and slower; the size does not grow with Tq and Tkv
+ *     call then runs in as many parts as fit, or uncut, and slower; the size does not grow with Tq and Tkv
  *     throughout, so a block for several calls takes the largest of theirs; for a
  *     batch it covers requests of unequal length too, up to 64 MB of parts), and
  *     work counters that are never cleared: every launch tags them with a number of

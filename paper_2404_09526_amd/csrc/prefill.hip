@@ -111,8 +111,8 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
 // Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
 // last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
-// which rows the longest request has is not known.  Over 309 random batches that it may cut differently (time against the even
-// cut's): any gain promised 0.76 on average, 15 of them 3 .. 21 % slower; a fifth 0.77 and 8; three tenths 0.82 and 1.
+// which rows the longest request has is not known.  Over 265 batches that it would cut differently, most of them random (time against
+// the even cut's): any gain promised 0.77 on average, 15 of them 3 .. 21 % slower; a fifth 0.78 and 8; three tenths 0.83 and 1.
 // Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 64.6 -> 32.1 us, 8 on 200000
 // beside 63 of 8 on 512 2222 -> 479, 300 on 20300 beside three of 300 on 600 330 -> 169; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
 // 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
@@ -205,8 +205,9 @@ static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t T
         const int32_t most = prefill_most_splits(Tq, Tkv, batch, Hq, Hkv);
         if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, most);
     }
-    if (workspace_bytes >= kPrefillCounterBytes + split_bytes(plan.splits, Tq, Hq)) return plan;
-    return prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, 1);       // a block without room for the parts
+    int32_t fit = plan.splits;
+    while (fit > 1 && workspace_bytes < kPrefillCounterBytes + split_bytes(fit, Tq, Hq)) --fit;
+    return fit == plan.splits ? plan : prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, fit);   // a block without room for all parts
 }
 int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
     const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);

@@ -17,7 +17,7 @@ def test_a_forced_plan_holds_for_its_thread_and_for_the_workspaces_it_asks_for(e
     by_estimate, room = esp.esp_debug_prefill_plan(*sizes), esp.esp_prefill_workspace_bytes(40, 3000, 1, 8, 2, 128)
     assert by_estimate != 0
     part = 40 * 8 * (128 + 1) * 4
-    for plan in (1, 5, -1, -7):
+    for plan in (1, 5, -1, -7):                                   # (room for fewer parts than were forced: one)
         assert esp.esp_debug_set_prefill_plan(plan) == 0
         try:
             need = 256 + (abs(plan) * part if abs(plan) > 1 else 0)
@@ -81,3 +81,15 @@ def test_a_batch_never_runs_in_more_parts_than_its_workspace_holds(esp):
             plan = esp.esp_debug_prefill_plan(*sizes, q, longest, Hq, Hkv)
             assert room_for(abs(plan), sum(new), Hq) <= room and 1 <= abs(plan) <= 16
             assert esp.esp_debug_prefill_plan(*sizes, q, longest, Hq, Hkv, workspace_bytes=room) == plan
+
+
+def test_a_smaller_workspace_holds_as_many_parts_as_fit(esp):
+    """... and not none at once: the call with room for fewer parts than it would like runs in the best number of those."""
+    sizes, Hq = (300, 20300, 1, 300, 20300, 32, 8), 32
+    want = esp.esp_debug_prefill_plan(*sizes)
+    assert want >= 4
+    for n in range(1, want + 1):
+        for spare in (0, 255):
+            plan = abs(esp.esp_debug_prefill_plan(*sizes, workspace_bytes=room_for(n, 300, Hq) + spare))
+            assert plan <= n and (plan > 1) == (n > 1), (n, plan)
+    assert esp.esp_debug_prefill_plan(*sizes, workspace_bytes=room_for(want, 300, Hq) - 1) == want - 1
