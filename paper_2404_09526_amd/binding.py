@@ -148,6 +148,19 @@ def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
     return t
 
 
+def _out(t: torch.Tensor, dtype, numel: int, name: str) -> None:
+    """An output that the call writes `numel` elements of (a larger one is the caller's business)."""
+    _dev(t, dtype, name)
+    if t.numel() < numel:
+        raise ValueError(f"{name}: {numel} elements are written, it has {t.numel()}")
+
+
+def _scratch(t: torch.Tensor) -> torch.Tensor:
+    if not (t.is_cuda and t.is_contiguous()):
+        raise ValueError("workspace: must be contiguous and live in device memory")
+    return t
+
+
 def _stream():
     """The current stream of the current device (asked for after a tensor on a device was seen: the runtime is up)."""
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
@@ -233,7 +246,7 @@ def esp_partial_attn_prefill(q, k, v, q_pos, kv_pos, cu_q=None, cu_kv=None, max_
     call = lib.esp_partial_attn_prefill_f32 if O.dtype == torch.float32 else lib.esp_partial_attn_prefill
     _check(call(_ptr(q), _ptr(k), _ptr(v), _ptr(q_pos), _ptr(kv_pos), _ptr(cu_q), _ptr(cu_kv),
                                         batch, Tq, Tkv, int(max_q), int(max_kv), Hq, Hkv, D, float(softmax_scale),
-                                        int(bool(causal)), _ptr(O), _ptr(LSE), _ptr(workspace), workspace.numel(),
+                                        int(bool(causal)), _ptr(O), _ptr(LSE), _ptr(_scratch(workspace)), workspace.numel(),
                                         _stream()))
     return O, LSE
 
@@ -277,7 +290,7 @@ def esp_partial_attn_prefill_retain(q, k, v, q_pos, kv_pos, retain_slot, k_pool,
     _check(lib.esp_partial_attn_prefill_retain(_ptr(q), _ptr(k), _ptr(v), _ptr(q_pos), _ptr(kv_pos), _ptr(cu_q), _ptr(cu_kv), batch,
                                                Tq, Tkv, int(max_q), int(max_kv), Hq, Hkv, D, float(softmax_scale),
                                                int(bool(causal)), _ptr(retain_slot), _ptr(k_pool), _ptr(v_pool), k_pool.shape[0],
-                                               1 if O.dtype == torch.float32 else 0, _ptr(O), _ptr(LSE), _ptr(workspace),
+                                               1 if O.dtype == torch.float32 else 0, _ptr(O), _ptr(LSE), _ptr(_scratch(workspace)),
                                                workspace.numel(), _stream()))
     return O, LSE
 
@@ -303,12 +316,12 @@ def esp_partial_attn_decode(q, k_pool, v_pool, slot_idx, seq_offsets, max_len, s
         O = torch.empty_like(q)
     if LSE is None:
         LSE = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    _dev(O, torch.bfloat16, "O"); _dev(LSE, torch.float32, "LSE")
+    _out(O, torch.bfloat16, B * Hq * D, "O"); _out(LSE, torch.float32, B * Hq, "LSE")
     if workspace is None:
         workspace = _workspace(esp_decode_workspace_bytes(B, total, int(max_len), Hq, Hkv, D), q.device)
     _check(lib.esp_partial_attn_decode(_ptr(q), _ptr(k_pool), _ptr(v_pool), S, _ptr(slot_idx), _ptr(seq_offsets), B,
                                        total, int(max_len), Hq, Hkv, D, float(softmax_scale), _ptr(O), _ptr(LSE),
-                                       _ptr(workspace), workspace.numel(), _stream()))
+                                       _ptr(_scratch(workspace)), workspace.numel(), _stream()))
     return O, LSE
 
 
@@ -327,7 +340,7 @@ def esp_partial_attn_decode_static(q, k_pool, v_pool, slot_idx, seq_offsets, max
         O = torch.empty_like(q)
     if LSE is None:
         LSE = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    _dev(O, torch.bfloat16, "O"); _dev(LSE, torch.float32, "LSE")
+    _out(O, torch.bfloat16, B * Hq * D, "O"); _out(LSE, torch.float32, B * Hq, "LSE")
     _check(lib.esp_partial_attn_decode_static(_ptr(q), _ptr(k_pool), _ptr(v_pool), S, _ptr(slot_idx), _ptr(seq_offsets), B,
                                               slot_idx.numel(), int(max_len), Hq, Hkv, D, float(softmax_scale), _ptr(O), _ptr(LSE),
                                               _stream()))
@@ -362,14 +375,14 @@ def esp_partial_attn_decode_merge(q, k_pool, v_pool, slot_idx, seq_offsets, max_
         O = torch.empty_like(q)
     if LSE is None:
         LSE = torch.empty((B, Hq), dtype=torch.float32, device=q.device)
-    _dev(O, torch.bfloat16, "O"); _dev(LSE, torch.float32, "LSE")
+    _out(O, torch.bfloat16, B * Hq * D, "O"); _out(LSE, torch.float32, B * Hq, "LSE")
     if workspace is None:
         workspace = _workspace(esp_decode_workspace_bytes(B, total, int(max_len), Hq, Hkv, D), q.device)
     op = (ctypes.c_void_p * max(P, 1))(*[t.data_ptr() for t in peer_O])
     lp = (ctypes.c_void_p * max(P, 1))(*[t.data_ptr() for t in peer_LSE])
     _check(lib.esp_partial_attn_decode_merge(_ptr(q), _ptr(k_pool), _ptr(v_pool), S, _ptr(slot_idx), _ptr(seq_offsets), B,
                                              total, int(max_len), Hq, Hkv, D, float(softmax_scale), op, lp, P,
-                                             _ptr(O), _ptr(LSE), _ptr(workspace), workspace.numel(), _stream()))
+                                             _ptr(O), _ptr(LSE), _ptr(_scratch(workspace)), workspace.numel(), _stream()))
     return O, LSE
 
 
@@ -399,9 +412,11 @@ def esp_merge_partials(O_parts: Sequence[torch.Tensor], LSE_parts: Sequence[torc
         T *= s
     if O is None:
         O = torch.empty(O_parts[0].shape, dtype=torch.bfloat16, device=O_parts[0].device)
-    _dev(O, torch.bfloat16, "O")
+    _out(O, torch.bfloat16, T * Hq * D, "O")
     if LSE is None and want_lse:
         LSE = torch.empty(O_parts[0].shape[:-1], dtype=torch.float32, device=O.device)
+    if LSE is not None:
+        _out(LSE, torch.float32, T * Hq, "LSE")
     op = (ctypes.c_void_p * P)(*[t.data_ptr() for t in O_parts])
     lp = (ctypes.c_void_p * P)(*[t.data_ptr() for t in LSE_parts])
     call = lib.esp_merge_partials_f32 if pdt == torch.float32 else lib.esp_merge_partials
@@ -495,14 +510,14 @@ def esp_partial_attn_prefill_pool(q, k_pool, v_pool, slot_idx, q_pos, kv_pos, cu
         _check(lib.esp_partial_attn_prefill_pool_direct(_ptr(q), _ptr(k_pool), _ptr(v_pool), S, _ptr(slot_idx), _ptr(q_pos),
                                                         _ptr(kv_pos), _ptr(cu_q), _ptr(cu_kv), batch, Tq, Tkv, int(max_q), int(max_kv),
                                                         Hq, Hkv, D, float(softmax_scale), 1 if causal else 0,
-                                                        1 if odt == torch.float32 else 0, _ptr(O), _ptr(LSE), _ptr(workspace),
+                                                        1 if odt == torch.float32 else 0, _ptr(O), _ptr(LSE), _ptr(_scratch(workspace)),
                                                         workspace.numel(), _stream()))
         return O, LSE
     if workspace is None:
         workspace = _workspace(esp_prefill_pool_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D), q.device)
     _check(lib.esp_partial_attn_prefill_pool(_ptr(q), _ptr(k_pool), _ptr(v_pool), S, _ptr(slot_idx), _ptr(q_pos), _ptr(kv_pos),
                                              _ptr(cu_q), _ptr(cu_kv), batch, Tq, Tkv, int(max_q), int(max_kv), Hq, Hkv, D,
-                                             float(softmax_scale), 1 if causal else 0, _ptr(O), _ptr(LSE), _ptr(workspace),
+                                             float(softmax_scale), 1 if causal else 0, _ptr(O), _ptr(LSE), _ptr(_scratch(workspace)),
                                              workspace.numel(), _stream()))
     return O, LSE
 

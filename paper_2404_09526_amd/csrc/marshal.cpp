@@ -36,6 +36,15 @@ const at::Tensor* dev(PyObject* o, at::ScalarType type) {
     const at::Tensor* t = plain(o);
     return t && t->scalar_type() == type && t->is_contiguous() ? t : nullptr;
 }
+// an output that this many elements of are written
+const at::Tensor* out(PyObject* o, at::ScalarType type, int64_t numel) {
+    const at::Tensor* t = dev(o, type);
+    return t && t->numel() >= numel ? t : nullptr;
+}
+const at::Tensor* scratch(PyObject* o) {
+    const at::Tensor* t = plain(o);
+    return t && t->is_contiguous() ? t : nullptr;
+}
 bool small(PyObject* o, int32_t& v) {
     if (!PyLong_CheckExact(o)) return false;
     int over = 0;
@@ -118,9 +127,10 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         if (n != 10 && n != 12) return nullptr;
         const at::Tensor *q = dev(a[0], BF16), *kp = dev(a[1], BF16), *vp = dev(a[2], BF16), *slots = dev(a[3], I32), *off = dev(a[4], I32);
-        const at::Tensor *O = dev(a[7], BF16), *L = dev(a[8], F32), *ws = plain(a[9]);
-        if (!q || !kp || !vp || !slots || !off || !O || !L || !ws || q->dim() != 3 || kp->dim() != 3) return nullptr;
+        if (!q || !kp || !vp || !slots || !off || q->dim() != 3 || kp->dim() != 3) return nullptr;
         const int64_t B = q->size(0), Hq = q->size(1), D = q->size(2), S = kp->size(0), H = kp->size(1), total = slots->numel();
+        const at::Tensor *O = out(a[7], BF16, q->numel()), *L = out(a[8], F32, B * Hq), *ws = scratch(a[9]);
+        if (!O || !L || !ws) return nullptr;
         int32_t max_len;
         float scale;
         if (vp->sizes() != kp->sizes() || kp->size(2) != D || off->numel() != B + 1 || !small(a[5], max_len) || !scale_of(a[6], D, scale))
@@ -148,7 +158,7 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         if (n != 14) return nullptr;
         const at::Tensor *q = dev(a[0], BF16), *k = dev(a[1], BF16), *v = dev(a[2], BF16), *qp = dev(a[3], I32), *kp = dev(a[4], I32);
-        const at::Tensor *O = plain(a[11]), *L = dev(a[12], F32), *ws = plain(a[13]);
+        const at::Tensor *O = plain(a[11]), *L = dev(a[12], F32), *ws = scratch(a[13]);
         if (!q || !k || !v || !qp || !kp || !O || !L || !ws || q->dim() != 3 || k->dim() != 3 || qp->dim() != 1 || kp->dim() != 1) return nullptr;
         const bool f32 = O->scalar_type() == F32;
         const int64_t Tq = q->size(0), Hq = q->size(1), D = q->size(2), Tk = k->size(0), H = k->size(1);
@@ -190,8 +200,8 @@ PyObject* prefill(PyObject*, PyObject* const* a, Py_ssize_t n) {
 PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
     return guarded([&]() -> PyObject* {
         if (n != 4 || (!PyList_CheckExact(a[0]) && !PyTuple_CheckExact(a[0])) || PySequence_Fast_GET_SIZE(a[0]) == 0) return nullptr;
-        const at::Tensor *first = plain(PySequence_Fast_GET_ITEM(a[0], 0)), *O = dev(a[2], BF16), *L = plain(a[3]);
-        if (!first || !O || !L || first->dim() < 2) return nullptr;
+        const at::Tensor* first = plain(PySequence_Fast_GET_ITEM(a[0], 0));
+        if (!first || first->dim() < 2) return nullptr;
         const bool f32 = first->scalar_type() == F32;
         Parts po, pl;
         const auto sizes = first->sizes();
@@ -200,6 +210,8 @@ PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
         const int64_t Hq = sizes[sizes.size() - 2], D = sizes[sizes.size() - 1];
         int64_t T = 1;
         for (size_t i = 0; i + 2 < sizes.size(); ++i) T *= sizes[i];
+        const at::Tensor *O = out(a[2], BF16, first->numel()), *L = out(a[3], F32, T * Hq);
+        if (!O || !L) return nullptr;
         void* s;
         if (!fits({T, Hq, D}) || !stream_of(s)) return nullptr;
         void* pO = O->data_ptr();

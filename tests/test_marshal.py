@@ -72,7 +72,7 @@ def test_what_was_refused_stays_refused(cuda, name):
     from paper_2404_09526_amd import binding as esp
     call, kw, _ = calls(esp, cuda)[name]
     for key, t in kw.items():
-        if not isinstance(t, torch.Tensor) or key == "workspace" or (name, key) == ("merge-f32", "LSE"):
+        if not isinstance(t, torch.Tensor) or key == "workspace":
             continue
         wide = torch.stack([t, t], dim=-1)[..., 0]
         for bad in (t.cpu(), t.to(torch.float64), wide):
@@ -86,3 +86,35 @@ def test_what_was_refused_stays_refused(cuda, name):
     if name in shorter:
         with pytest.raises(ValueError):
             call(**(kw | {shorter[name]: kw[shorter[name]][:-1].contiguous()}))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES[:-1])
+def test_an_output_too_small_for_what_is_written_is_refused(cuda, name):
+    """One row short, of another type, on the host or spread out; a larger output is the caller's business and is written as far as
+    the call goes.  A workspace on the host, or one whose bytes are not its own."""
+    from paper_2404_09526_amd import binding as esp
+    call, kw, outs = calls(esp, cuda)[name]
+    names = [name] + (["decode-static"] if name == "decode" else [])
+    for which in names:
+        if which == "decode-static":
+            call, kw = esp.esp_partial_attn_decode_static, {k: v for k, v in kw.items() if k != "workspace"}
+        for key in outs:
+            t = kw[key]
+            for bad in (t[:-1].contiguous(), t.to(torch.float16), t.cpu(), torch.stack([t, t], dim=-1)[..., 0]):
+                with pytest.raises(ValueError):
+                    call(**(kw | {key: bad}))
+        if not name.startswith("prefill"):                          # (prefill asks for the very shape)
+            for o in outs:
+                kw[o].zero_()
+            call(**kw)
+            room = {o: torch.full((kw[o].shape[0] + 2,) + kw[o].shape[1:], 7, dtype=kw[o].dtype, device=cuda) for o in outs}
+            call(**(kw | room))
+            torch.cuda.synchronize()
+            for o in outs:
+                n = kw[o].shape[0]
+                assert torch.equal(room[o][:n], kw[o]) and (room[o][n:] == 7).all()
+        if "workspace" in kw:
+            for bad in (kw["workspace"].cpu(), kw["workspace"][:1].expand(1 << 20), kw["workspace"][::2]):
+                with pytest.raises(ValueError):
+                    call(**(kw | {"workspace": bad}))
