@@ -7,10 +7,13 @@ no CPU or PyTorch fallback.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional, Sequence
 
 import torch
+
+from . import build
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libesp.so")
@@ -104,16 +107,23 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+class _PythonAlone:
+    """In place of the native argument checks where they are not built for this torch and Python: every call goes through the Python ones."""
+    kv_append = decode = prefill = merge = staticmethod(lambda *args: None)
+
+
 def _load_marshal():
-    path = os.path.join(_PKG, "_marshal.so")
+    path = build.marshal_path()
     if not os.path.exists(path):
-        raise ImportError(f"{path} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`.")
-    from . import _marshal
+        return _PythonAlone
+    spec = importlib.util.spec_from_file_location(f"{__package__}._marshal", path)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)
     at = lambda f: ctypes.cast(f, ctypes.c_void_p).value
-    _marshal.bind(_stream, *(at(f) for f in (lib.esp_kv_append, lib.esp_partial_attn_decode, lib.esp_partial_attn_decode_merge,
-                                              lib.esp_partial_attn_prefill, lib.esp_partial_attn_prefill_f32, lib.esp_merge_partials,
-                                              lib.esp_merge_partials_f32)))
-    return _marshal
+    m.bind(_stream, *(at(f) for f in (lib.esp_kv_append, lib.esp_partial_attn_decode, lib.esp_partial_attn_decode_merge,
+                                      lib.esp_partial_attn_prefill, lib.esp_partial_attn_prefill_f32, lib.esp_merge_partials,
+                                      lib.esp_merge_partials_f32)))
+    return m
 
 
 def last_error() -> str:
@@ -167,7 +177,9 @@ def _stream():
 
 
 # The checks of the calls below once more in native code (csrc/marshal.cpp): a function of it makes the call and returns its status where
-# everything is given, plain and right, and returns None otherwise.
+# everything is given, plain and right, and returns None otherwise.  The calls that have them are those whose time the host sets: a
+# decode step's and the short prefill's; kept rows, pool rows and gathers pass more work to the GPU than the Python in front takes, and
+# the decode on the built-in block is for code that is captured once.
 _marshal = _load_marshal()
 
 

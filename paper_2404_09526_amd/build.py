@@ -1,9 +1,11 @@
-"""Builds libesp.so (HIP, gfx950 only, hipcc) and the binding's argument checks (_marshal.so, g++) in-tree.  No GPU is needed to build."""
+"""Builds libesp.so (HIP, gfx950 only, hipcc) and the binding's argument checks (g++) in-tree.  No GPU is needed to build."""
 from __future__ import annotations
 
 import glob
 import os
+import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -11,7 +13,6 @@ LIB = os.path.join(PKG, "libesp.so")
 SOURCES = sorted(glob.glob(os.path.join(PKG, "csrc", "*.hip")))
 HEADERS = sorted(glob.glob(os.path.join(PKG, "csrc", "*.h"))) + [os.path.join(ROOT, "include", "esp.h")]
 
-MARSHAL = os.path.join(PKG, "_marshal.so")
 MARSHAL_SOURCE = os.path.join(PKG, "csrc", "marshal.cpp")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -23,11 +24,21 @@ FLAGS = [
 ]
 
 
+def marshal_path() -> str:
+    """The native argument checks unpack torch's and Python's own objects: the file is named after those that it is built for, so that
+    after a change of either it is not found (and built again) rather than loaded."""
+    import torch
+    return os.path.join(PKG, f"_marshal.torch-{torch.__version__}-abi{int(torch._C._GLIBCXX_USE_CXX11_ABI)}{sysconfig.get_config_var('EXT_SUFFIX')}")
+
+
+def _older(built: str, sources) -> bool:
+    return not os.path.exists(built) or any(os.path.getmtime(f) > os.path.getmtime(built) for f in sources)
+
+
 def is_stale() -> bool:
-    for built, sources in ((LIB, SOURCES + HEADERS), (MARSHAL, [MARSHAL_SOURCE, os.path.join(ROOT, "include", "esp.h")])):
-        if not os.path.exists(built) or any(os.path.getmtime(f) > os.path.getmtime(built) for f in sources):
-            return True
-    return False
+    if _older(LIB, SOURCES + HEADERS):
+        return True
+    return shutil.which("g++") is not None and _older(marshal_path(), [MARSHAL_SOURCE, os.path.join(ROOT, "include", "esp.h")])
 
 
 def build_lib(force: bool = True, verbose: bool = False) -> str:
@@ -43,25 +54,27 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
-    build_marshal()
+    if shutil.which("g++") is not None:
+        build_marshal()
+    else:
+        print("g++ is missing: the binding's native argument checks are not built, its Python checks are used alone")
     return LIB
 
 
 def build_marshal() -> str:
     """Compile the native argument checks against the installed torch.  Returns the module's path."""
-    import sysconfig
     import torch
-    base = os.path.dirname(torch.__file__)
+    base, path = os.path.dirname(torch.__file__), marshal_path()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-w",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(base, "include"),
            "-I" + os.path.join(base, "include", "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
-           MARSHAL_SOURCE, "-o", MARSHAL, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
+           MARSHAL_SOURCE, "-o", path, "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10",
            "-Wl,-rpath," + os.path.join(base, "lib")]
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode != 0:
         raise RuntimeError("g++ failed:\n" + proc.stdout)
-    return MARSHAL
+    return path
 
 
 if __name__ == "__main__":

@@ -1,9 +1,16 @@
 """The native argument checks in front of the calls that are made step after step: the same results, bit for bit, and the same
 refusals as the Python beside them, which every call that is not plain still goes through."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 from paper_2404_09526_amd import workloads as wl
+
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class Plainless(torch.Tensor):
@@ -118,3 +125,17 @@ def test_an_output_too_small_for_what_is_written_is_refused(cuda, name):
             for bad in (kw["workspace"].cpu(), kw["workspace"][:1].expand(1 << 20), kw["workspace"][::2]):
                 with pytest.raises(ValueError):
                     call(**(kw | {"workspace": bad}))
+
+
+def test_the_native_checks_are_loaded_for_this_torch_only_and_can_be_missing(monkeypatch):
+    """Built for another torch, or not built, they are not looked at: the package comes up on its Python checks, and a build is due."""
+    code = ("from paper_2404_09526_amd import build; build.marshal_path = lambda: '/nonexistent/_marshal.so'\n"
+            "from paper_2404_09526_amd import binding as b\n"
+            "assert b._marshal.decode(1, 2) is None and b._marshal.merge() is None and 'gfx950' in b.version()")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+    from paper_2404_09526_amd import binding, build
+    build.build_lib(force=False)
+    assert not build.is_stale() and binding._load_marshal() is not binding._PythonAlone
+    here = build.marshal_path()
+    monkeypatch.setattr(torch, "__version__", "0.0.1+other")
+    assert build.marshal_path() != here and build.is_stale() and binding._load_marshal() is binding._PythonAlone
