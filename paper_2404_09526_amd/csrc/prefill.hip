@@ -592,10 +592,18 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     if (nkt > 0) fetch_v_part(vreq, preq, 0, 0 == ragged_tile, 2);
     {
         const char* qp = (const char*)a.q + (any_row ? (int64_t)row0 * (kHeadDim * 2) : 0);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) {
+        auto q_src = [&](int n) {
             const int r = 4 * n + (bl >> 4), i = max(min(32 * bw + r, n_rows - 1), 0);
-            load_to_lds_b128_at(lds_base + q_off, 1024 * n, qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4));
+            return qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4);
+        };
+        if (__builtin_expect(((uintptr_t)a.q & 15) != 0, 0)) {      // not on 16 bytes: through registers, whose loads take any alignment
+            struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
+#pragma unroll 1
+            for (int n = 0; n < 8; ++n)
+                *(ESP_LDS u32x4*)(uintptr_t)(lds_base + q_off + 1024 * n + 16 * bl) = __builtin_bit_cast(u32x4, *(const Any16*)q_src(n));
+        } else {
+#pragma unroll
+            for (int n = 0; n < 8; ++n) load_to_lds_b128_at(lds_base + q_off, 1024 * n, q_src(n));
         }
     }
     // V stage 3 stands in for the tile before the first one (the loop multiplies the last chunk of tile j-1 at the

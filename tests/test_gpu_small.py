@@ -401,6 +401,33 @@ def test_unsorted_positions(esp, cuda):
 
 
 @pytest.mark.usefixtures("each_prefill_plan")
+@pytest.mark.parametrize("Hq,Hkv,Tq", [(4, 4, 300), (8, 2, 70)])
+def test_prefill_queries_at_any_alignment(esp, cuda, Hq, Hkv, Tq):
+    """Q one, two and four elements into its allocation: bit for bit the aligned call, on dense, kept and pool rows."""
+    Tkv = 500
+    pc = wl.contiguous_prefill(f"q-alignment-{Hq}/{Hkv}", Tq, Tkv - Tq, [(0, Tkv)], Hq, Hkv, 47, cuda)
+    s = pc.shards[0]
+    slots = torch.randperm(Tkv, generator=torch.Generator(device=cuda).manual_seed(48), device=cuda).to(torch.int32)
+    kp, vp = torch.zeros_like(s.k), torch.zeros_like(s.v)
+    esp.esp_kv_append(s.k, s.v, slots, kp, vp)
+    common = dict(softmax_scale=pc.scale)
+    calls = (lambda q: esp.esp_partial_attn_prefill(q, s.k, s.v, pc.q_pos, s.kv_pos, **common),
+             lambda q: esp.esp_partial_attn_prefill_retain(q, s.k, s.v, pc.q_pos, s.kv_pos, slots, torch.empty_like(kp), torch.empty_like(vp), **common),
+             lambda q: esp.esp_partial_attn_prefill_pool_direct(q, kp, vp, slots, pc.q_pos, s.kv_pos, **common))
+    for what, call in enumerate(calls):
+        O, LSE = call(pc.q)
+        for off in (1, 2, 4):
+            say(f"call {what}, Q {2 * off} bytes off")
+            room = torch.empty(pc.q.numel() + 8, dtype=torch.bfloat16, device=cuda)
+            q = room[off:off + pc.q.numel()].view(pc.q.shape)
+            q.copy_(pc.q)
+            assert q.data_ptr() % 16 == 2 * off
+            O2, L2 = call(q)
+            torch.cuda.synchronize()
+            assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(L2.view(torch.int32), LSE.view(torch.int32)), (what, off)
+
+
+@pytest.mark.usefixtures("each_prefill_plan")
 def test_query_chunk_before_every_key(esp, cuda):
     """A whole workgroup of queries sees nothing: O = 0, LSE = -inf everywhere, and the merge ignores it."""
     pc = wl.contiguous_prefill("allhidden", 64, 0, [(1000, 1200), (0, 64)], 4, 4, 23, cuda)
