@@ -596,7 +596,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             const int r = 4 * n + (bl >> 4), i = max(min(32 * bw + r, n_rows - 1), 0);
             return qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4);
         };
-        if (__builtin_expect(((uintptr_t)a.q & 15) != 0, 0)) {      // not on 16 bytes: through registers, whose loads take any alignment
+        if (__builtin_expect(a.q_odd, 0)) {      // not on 16 bytes: through registers, whose loads take any alignment
             struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
 #pragma unroll 1
             for (int n = 0; n < 8; ++n)
@@ -1353,6 +1353,7 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.scale_log2 = softmax_scale * kLog2e;
     a.G = Hq / Hkv;
     a.inv_G = 1.0f / (float)a.G;
+    a.q_odd = ((uintptr_t)q & 15) != 0;
     if (kv_slot && retain_slot) return fail(ESP_ERR_INVALID_ARG, "prefill: rows that are read from the pool are in it already");
     if (plan.use_short) {
         const esp_status st = launch_prefill_short(a, stream);
