@@ -111,11 +111,16 @@ static int32_t decode_range(int32_t total_tokens, int64_t step, int64_t least, i
 // requests are worked on one after the other, each with a start and an end (3 us), and such a workgroup ends last.  Then the
 // ranges are counted from each request's first token on: `parts` of them for each, enough for the longest, and the workgroups of
 // those that a request does not have return at once.  Returns that number, or 0: ranges along the whole list.
-// Taken where all of them, the empty ones too, are on the chip at once, and either ranges that are crossed into are many or they
-// are single steps.  (A second round costs more than is won: 16 of 550, 32 / 8 heads, 1024 workgroups for 280, 16.6 -> 20.2 us.)  Partials lie at (first token's range + part + request): as far apart as
-// along the list, in the same number of slots.  Measured (along the list -> by request): 4 requests of 320, 4 / 4 heads, 11.2 -> 8.6
-// us; 12 of 90, 8 / 4, 17.1 -> 12.2; 4 of 180, 32 / 1, 15.9 -> 8.8; 4 of 200, 32 / 4, 11.5 -> 8.5; 2 of 97, 12 / 12,
-// 10.8 -> 8.2; left alone: 100 of 234, 8 / 8, 25.1 (30.4), 3 of 5600, 32 / 8, 22.0 (22.9).
+// Taken where all of them, the empty ones too, are on the chip at once, and either ranges that are crossed into are many (at least 3
+// requests to 20 ranges) or they are single steps.  (A second round costs more than is won: 16 of 550, 32 / 8 heads, 1024 workgroups
+// for 280, 16.6 -> 20.2 us.)  Partials lie at (first token's range + part + request): as far apart as along the list, in the same number
+// of slots.  Measured (along the list -> by request): 4 requests of 320, 4 / 4 heads, 11.2 -> 8.6 us; 12 of 90, 8 / 4,
+// 17.1 -> 12.2; 4 of 180, 32 / 1, 15.9 -> 8.8; 4 of 200, 32 / 4, 11.5 -> 8.5; 2 of 97, 12 / 12, 10.8 -> 8.2.
+// At the line of 3 to 20, 6.7 ranges a request: 8 / 8 heads, 2 of 200 (6.5) 12.1 -> 9.7, 4 of 210 (6.8) 11.8, by request it would be
+// 9.6.  It lies on the safe side: on the row-burst kernel by request stays ahead while the workgroups are few (16 / 16, 4 of 350,
+// 22 ranges each, 12.2, would be 10.2) and falls behind once they are about as many as the chip holds (16 / 16, 8 of 570 13.4 / 13.9,
+// 4 of 940 13.6 / 14.1; 8 / 8, 2 of 3900 15.1 / 16.0); on the matrix cores it does so earlier (12 / 12, 2 of 3000, 12 each, 14.4 / 15.9).
+// Left alone besides: 100 of 234, 8 / 8, 25.1 (30.4), 3 of 5600, 32 / 8, 22.0 (22.9).
 static int32_t decode_parts(const DecodeGeom& g, int32_t B, int32_t max_len, int32_t Hq, int32_t Hkv) {
     const bool gq = g.nhb_wg == 0;
     const int64_t rows = gq ? (int64_t)Hkv * ((Hq / Hkv + 31) / 32) : g.ygroups;

@@ -140,7 +140,7 @@ static esp_status prefill_entry(const void* q, const void* k, const void* v, con
     if (!q || !O || !LSE || !q_pos) return fail(ESP_ERR_INVALID_ARG, "prefill: null q/q_pos/O/LSE");
     if (Tkv > 0 && (!k || !v || !kv_pos)) return fail(ESP_ERR_INVALID_ARG, "prefill: null k/v/kv_pos");
     if (!(softmax_scale == softmax_scale) || softmax_scale < 0.f) return fail(ESP_ERR_INVALID_ARG, "prefill: bad softmax_scale");
-    const size_t need = kPrefillCounterBytes;                  // without the room for a split the call runs unsplit
+    const size_t need = kPrefillCounterBytes;                  // without room for parts the call runs uncut
     if (need > 0 && (!workspace || workspace_bytes < need))
         return fail(ESP_ERR_WORKSPACE, "prefill: workspace needs %zu bytes, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if (need > 0 && ((uintptr_t)workspace & 255)) return fail(ESP_ERR_WORKSPACE, "prefill: workspace not 256-byte aligned");

@@ -244,9 +244,8 @@ template <int V> struct IC { static constexpr int value = V; };
 // ONE (with MODE 0): one request, one query head per KV head, keys uncut: the chunk or the stripe of a multi-head model.  What
 // bounds a short call of that kind is the chain of instructions in front of its first transfer and at its end, and here the
 // rows of a tile are Hq rows apart, known when it is compiled: no float arithmetic for every row that is loaded and stored, no
-// search for request, part and query head.  Measured (any call -> ONE): 256 queries against two shards of 512, 4 / 4 heads, 43.2
-// -> 40.9 us, of which the rows are 0.8, the request's search and the parts 0.7 each (one tile per query head and neither search
-// nor parts took 41.8); 700 against two of 700, 32 / 32 heads, 64.1 -> 61.4 us; 8192 against four of 8192 2004 -> 1987 us.  The
+// search for request, part and query head.  Measured, 32 / 32 heads (any call -> ONE): 700 on 700 23.4 -> 22.3 us, against two of 700
+// 49.8 -> 46.9 us; 1500 on 1500 39.4 -> 38.1; 4000 on 20000 962 -> 960; 8192 against four of 8192 1824 -> 1808 us.  The
 // same for MODE 1 and 2 gained nothing: 1500 against two of 1500, kept, 8 / 8 heads, 81.9 -> 82.4 us, 2048 against 8192 rows
 // of the pool, 32 / 32 heads, 237.5 -> 237.7 us.
 template <int MODE, bool ONE>
