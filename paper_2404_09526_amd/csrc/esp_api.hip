@@ -214,8 +214,8 @@ static size_t pool_staging_bytes(int32_t Tkv, int32_t Hkv) {
 }
 
 size_t esp_prefill_pool_workspace_bytes(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv, int32_t D) {
-    (void)D;
-    return 2 * pool_staging_bytes(Tkv, Hkv) + prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv);
+    const size_t dense = esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D);
+    return dense == 0 ? 0 : 2 * pool_staging_bytes(Tkv, Hkv) + dense;     // 0: the call would be refused
 }
 
 esp_status esp_partial_attn_prefill_pool(const void* q, const void* k_pool, const void* v_pool, int64_t num_slots,

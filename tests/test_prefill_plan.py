@@ -93,3 +93,10 @@ def test_a_smaller_workspace_holds_as_many_parts_as_fit(esp):
             plan = abs(esp.esp_debug_prefill_plan(*sizes, workspace_bytes=room_for(n, 300, Hq) + spare))
             assert plan <= n and (plan > 1) == (n > 1), (n, plan)
     assert esp.esp_debug_prefill_plan(*sizes, workspace_bytes=room_for(want, 300, Hq) - 1) == want - 1
+
+
+def test_the_size_of_a_call_that_would_be_refused_is_zero_for_pool_rows_too(esp):
+    """No KV heads divided by zero."""
+    for Tq, Tkv, batch, Hq, Hkv, D in ((4, 4, 1, 4, 0, 128), (4, 4, 0, 4, 2, 128), (4, 4, 1, 5, 2, 128), (-1, 4, 1, 4, 2, 128), (4, 4, 1, 4, 2, 64)):
+        assert esp.esp_prefill_pool_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) == esp.esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) == 0
+    assert esp.esp_prefill_pool_workspace_bytes(4, 5, 1, 4, 2, 128) == 256 + 2 * 5 * 2 * 256
