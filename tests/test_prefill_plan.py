@@ -1,4 +1,5 @@
 """Which prefill kernel a call runs on, and in how many parts (host code; no GPU)."""
+import ctypes
 import math
 import random
 import threading
@@ -100,3 +101,15 @@ def test_the_size_of_a_call_that_would_be_refused_is_zero_for_pool_rows_too(esp)
     for Tq, Tkv, batch, Hq, Hkv, D in ((4, 4, 1, 4, 0, 128), (4, 4, 0, 4, 2, 128), (4, 4, 1, 5, 2, 128), (-1, 4, 1, 4, 2, 128), (4, 4, 1, 4, 2, 64)):
         assert esp.esp_prefill_pool_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) == esp.esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) == 0
     assert esp.esp_prefill_pool_workspace_bytes(4, 5, 1, 4, 2, 128) == 256 + 2 * 5 * 2 * 256
+
+
+def test_a_forced_plan_whose_launch_would_not_fit_is_refused(esp):
+    one, nul = ctypes.c_void_p(256), ctypes.c_void_p(0)             # never dereferenced: refused before anything is launched
+    Tq = 1 << 30
+    assert esp.esp_debug_set_prefill_plan(-16) == 0
+    try:
+        st = esp.lib.esp_partial_attn_prefill(one, one, one, one, one, nul, nul, 1, Tq, 64, Tq, 64, 8, 1, 128, ctypes.c_float(0.1), 1, one, one,
+                                              one, 1 << 62, nul)
+        assert st == esp.ESP_ERR_UNSUPPORTED and "forced" in esp.last_error()
+    finally:
+        esp.esp_debug_set_prefill_plan(0)
