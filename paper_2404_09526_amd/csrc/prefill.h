@@ -12,7 +12,6 @@ struct PrefillArgs {
     uint16_t* k_pool; uint16_t* v_pool;
     void* O; float* LSE;              // O: bf16 [Tq, Hq, 128], or fp32 of the same shape when o_f32 is set
     int32_t batch, Tq, Tkv, Hq, Hkv, causal, o_f32;
-    int32_t q_odd;                    // q does not lie on 16 bytes
     // Packed rows: the rows of a KV head are the (token, query head of the group) pairs in memory order, row rho of a
     // request being token rho / G, query head kvh * G + rho % G, and a query tile is 256 of them.  A group's heads
     // see the same keys, so nothing else changes; but a tile spans 256 / G tokens instead of 256: less of it is masked at
@@ -33,6 +32,7 @@ struct PrefillArgs {
     int32_t group_sync;               // the workgroups of an XCD start their dealt rounds together
     int32_t sync_ticks;               // longest such wait, in ticks of the 100 MHz wall clock
     float scale_log2;
+    int32_t q_odd;                    // q does not lie on 16 bytes
 };
 
 // The kernel for calls with few query rows (prefill_short.hip): a.splits parts; the other fields as for the main kernel.

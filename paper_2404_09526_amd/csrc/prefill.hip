@@ -236,6 +236,9 @@ template <int V> struct IC { static constexpr int value = V; };
 // ahead of the iteration's transfers, so that the hand-counted waits still see those as the newest operations in
 // flight (they have to sit out the stores, though, which is why the tiles at the end are left for later).
 //
+// MODE 3: MODE 1 for a Q that does not lie on 16 bytes.  (The other modes ask a.q_odd.  This one has no scalar register left for the
+// question: 1000 .. 8192 tokens, kept, 32 / 8 heads, 654 us without it, 661 with; Q through registers in every call 0.4 .. 1 % more.)
+//
 // POOL (MODE 2): the shard's rows live in the token pool (a.k / a.v are the pools, a.kv_slot the slot of every shard
 // row, Sec. 4.1 / 4.2: KV that an instance kept stays where it was placed).  The tile transfers take each row from its
 // slot: the slots of tile t travel to a ring of 4 LDS stages (stage t % 4) one iteration before the tile's first
@@ -250,7 +253,7 @@ template <int V> struct IC { static constexpr int value = V; };
 // of the pool, 32 / 32 heads, 237.5 -> 237.7 us.
 template <int MODE, bool ONE>
 __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
-    constexpr bool RETAIN = MODE == 1, POOL = MODE == 2;
+    constexpr bool RETAIN = MODE == 1 || MODE == 3, POOL = MODE == 2;
     // One LDS block, V stages first: an LDS instruction adds a 16-bit immediate to its address register, so with
     // each array's base folded into the per-lane register every operand read of the loop needs no address math.
     constexpr int kLdsV = 0, kLdsK = kLdsV + kStages * kTileBytes, kLdsPos = kLdsK + kStages * kKTileBytes,
@@ -595,8 +598,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             const int r = 4 * n + (bl >> 4), i = max(min(32 * bw + r, n_rows - 1), 0);
             return qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4);
         };
-        if (__builtin_expect(a.q_odd, 0)) {      // not on 16 bytes: through registers, whose loads take any alignment
-            struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
+        struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
+        if (MODE == 3 || (!RETAIN && __builtin_expect(a.q_odd, 0))) {   // not on 16 bytes: through registers, whose loads take any alignment
 #pragma unroll 1
             for (int n = 0; n < 8; ++n)
                 *(ESP_LDS u32x4*)(uintptr_t)(lds_base + q_off + 1024 * n + 16 * bl) = __builtin_bit_cast(u32x4, *(const Any16*)q_src(n));
@@ -1383,6 +1386,8 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.sync_ticks = g_sync_ticks.load(std::memory_order_relaxed);
     if (kv_slot)
         hipLaunchKernelGGL((prefill_kernel<2, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+    else if (retain_slot && a.q_odd)
+        hipLaunchKernelGGL((prefill_kernel<3, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     else if (retain_slot)
         hipLaunchKernelGGL((prefill_kernel<1, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
     else if (a.G == 1 && batch == 1 && S == 1)

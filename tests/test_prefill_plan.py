@@ -110,6 +110,6 @@ def test_a_forced_plan_whose_launch_would_not_fit_is_refused(esp):
     try:
         st = esp.lib.esp_partial_attn_prefill(one, one, one, one, one, nul, nul, 1, Tq, 64, Tq, 64, 8, 1, 128, ctypes.c_float(0.1), 1, one, one,
                                               one, 1 << 62, nul)
-        assert st == esp.ESP_ERR_UNSUPPORTED and "forced" in esp.last_error()
+        assert st == esp.ESP_ERR_UNSUPPORTED and "too many rows" in esp.last_error()
     finally:
         esp.esp_debug_set_prefill_plan(0)
