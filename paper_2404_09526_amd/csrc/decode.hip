@@ -109,24 +109,29 @@ static int32_t decode_range(int32_t total_tokens, int64_t step, int64_t least, i
 
 // Ranges by request.  Where calls are short, a range that crosses into the next request costs more than its share of the work: its
 // requests are worked on one after the other, each with a start and an end (3 us), and such a workgroup ends last.  Then the
-// ranges are counted from each request's first token on: `parts` of them for each, enough for the longest, and the workgroups of
-// those that a request does not have return at once.  Returns that number, or 0: ranges along the whole list.
-// Taken where all of them, the empty ones too, are on the chip at once, and either ranges that are crossed into are many (at least 3
-// requests to 20 ranges) or they are single steps.  (A second round costs more than is won: 16 of 550, 32 / 8 heads, 1024 workgroups
-// for 280, 16.6 -> 20.2 us.)  Partials lie at (first token's range + part + request): as far apart as along the list, in the same number
-// of slots.  Measured (along the list -> by request): 4 requests of 320, 4 / 4 heads, 11.2 -> 8.6 us; 12 of 90, 8 / 4,
-// 17.1 -> 12.2; 4 of 180, 32 / 1, 15.9 -> 8.8; 4 of 200, 32 / 4, 11.5 -> 8.5; 2 of 97, 12 / 12, 10.8 -> 8.2.
-// At the line of 3 to 20, 6.7 ranges a request: 8 / 8 heads, 2 of 200 (6.5) 12.1 -> 9.7, 4 of 210 (6.8) 11.8, by request it would be
-// 9.6.  It lies on the safe side: on the row-burst kernel by request stays ahead while the workgroups are few (16 / 16, 4 of 350,
-// 22 ranges each, 12.2, would be 10.2) and falls behind once they are about as many as the chip holds (16 / 16, 8 of 570 13.4 / 13.9,
-// 4 of 940 13.6 / 14.1; 8 / 8, 2 of 3900 15.1 / 16.0); on the matrix cores it does so earlier (12 / 12, 2 of 3000, 12 each, 14.4 / 15.9).
-// Left alone besides: 100 of 234, 8 / 8, 25.1 (30.4), 3 of 5600, 32 / 8, 22.0 (22.9).
+// ranges are counted from each request's first token on.  Partials lie at (first token's range + part + request): as far apart as along
+// the list, in the same number of slots.  Returns 0: ranges along the whole list; n > 0: n of them for each request, enough for the longest
+// by the caller's bound (request_part: no search, but the workgroups of parts that a request does not have start for nothing); -1: as many
+// as each request has (request_range).
+// Measured in turn, along the list -> by request (* with n for each): 16 of 900, 32 / 8 heads, 23.6 -> 21.7 us; 25 of 196, 32 / 8, 23.8 -> 16.1;
+// 99 of 182, 4 / 4, 28.0 -> 20.3; 24 of 950, 32 / 4, 24.9 -> 22.1; 64 of 4800, 32 / 1, 42.8 -> 40.8; 7 of 430, 8 / 8, 17.4 -> 15.1; 6 of 250,
+// 8 / 8, 14.3 -> 11.3*; 10 of 183, 32 / 8, 14.4 -> 11.5*.  Found by search where n for each would do: 0.1 .. 0.5 us more (11.5 -> 12.0 us, 10 of
+// 183), 25 of 121, 40 / 8, 12.1 -> 14.2.
+// The lines, over 240 shapes of 2 .. 226 requests: by request only where its ranges are on the chip at once, expected half a range more
+// than along the list for each request.  Beyond, the shorter ranges at the end wait for a whole one: 78 of 3400, 8 / 8 heads, 547
+// workgroups for 508, 182 -> 212 us, 43 of 5300, 12 / 12, 238 -> 274 (a few calls of one to five steps would gain: 45 of 176, 40 / 8, 672 for
+// 496, 24.9 -> 21.4).  Up to there every call gained or was within 3 %; beyond twelve steps a range nothing is left to gain (10 of 4300, 32 / 32,
+// 22 steps, 128.9 / 130.0; 14 of 29600, 4 / 4, 26 steps, 143.5 / 147.4).  n for each: up to 256 workgroups, and up to 512 where
+// requests are at least 3 to 20 ranges or ranges are single steps.
 static int32_t decode_parts(const DecodeGeom& g, int32_t B, int32_t max_len, int32_t Hq, int32_t Hkv) {
+    if (B <= 1) return 0;
     const bool gq = g.nhb_wg == 0;
     const int64_t rows = gq ? (int64_t)Hkv * ((Hq / Hkv + 31) / 32) : g.ygroups;
     const int64_t parts = ((int64_t)max_len + g.range - 1) / g.range;
-    const bool crossed = (int64_t)B * 20 >= (int64_t)g.nwg * 3, single = gq && g.range == kGqWaves * 32;
-    return B > 1 && (crossed || single) && B * parts * rows <= 512 ? (int32_t)parts : 0;
+    const int32_t steps = g.range / (gq ? kGqWaves * 32 : g.nt * kDecTB);
+    const bool crossed = (int64_t)B * 20 >= (int64_t)g.nwg * 3, single = gq && steps == 1;
+    if (B * parts * rows <= (crossed || single ? 512 : 256)) return (int32_t)parts;
+    return (g.nwg + (int64_t)B / 2) * rows <= 512 && steps <= 12 ? -1 : 0;
 }
 
 static int64_t partial_bytes(int32_t Hq) { return (int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float); }
@@ -220,21 +225,24 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
     const int dseg = (lane & 15) * 8;                          // first of its 8 elements
 
     int b;
-    int32_t r0, t1;
-    if (parts > 0) {
-        const RequestRange at = request_range(w, parts, range, B, seq_offsets);
-        b = at.b; r0 = at.t0; t1 = at.t1; w = at.w;
+    int32_t r0, t1, req_end;
+    if (parts != 0) {
+        const RequestRange at = parts > 0 ? request_part(w, parts, range, B, seq_offsets) : request_range(w, range, B, seq_offsets, lane);
+        b = at.b; r0 = at.t0; t1 = req_end = at.t1; w = at.w;
         if (r0 >= t1) return;
     } else {
         r0 = w * range;
         t1 = min(r0 + range, total_tokens);
         if (r0 >= t1) return;
-        b = request_of(r0, seq_offsets, B, lane);
+        const RequestAt at = request_of(r0, seq_offsets, B, lane);
+        b = at.b; req_end = at.end;
     }
     int32_t t0 = r0;
     while (t0 < t1) {
-        int32_t req_end = seq_offsets[b + 1];
-        if (req_end <= t0) { ++b; continue; }                   // empty request
+        if (t0 > r0) {
+            req_end = seq_offsets[b + 1];
+            if (req_end <= t0) { ++b; continue; }               // empty request
+        }
         const int32_t pe = min(t1, req_end);
         // this wavefront's tokens of the request: i0 .. i1 - 1
         const int i0 = max(t0 - r0 - tsub + nt - 1, 0) >> nt_log, i1 = max(pe - r0 - tsub + nt - 1, 0) >> nt_log;
@@ -454,9 +462,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     if (s1 > s0) {
         const int w_lo = s0 / range;
         const int64_t first = w_lo + b;                             // the slots of consecutive ranges
-        int n;
-        if (parts > 0) n = min(parts, (s1 - s0 + range - 1) / range);
-        else n = (s1 - 1) / range - w_lo + 1;
+        const int whole = (s1 - s0 + range - 1) / range, n = parts == 0 ? (s1 - 1) / range - w_lo + 1 : parts > 0 ? min(parts, whole) : whole;
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
             float4 v[U];
@@ -558,7 +564,7 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                                          softmax_scale * kLog2e, part_acc, part_ml, stream);
         if (st != ESP_OK) return st;
     } else if (total_tokens > 0) {
-        dim3 grid(parts > 0 ? B * parts : g.nwg, g.ygroups), block(kDecWaves * 64);
+        dim3 grid(parts > 0 ? B * parts : parts < 0 ? g.nwg + B : g.nwg, g.ygroups), block(kDecWaves * 64);
         float sl2 = softmax_scale * kLog2e;
 #define ESP_DECODE_LAUNCH(GG)                                                                                   \
     hipLaunchKernelGGL(decode_partial_kernel<GG>, grid, block, 0, stream, (const uint16_t*)q,                   \

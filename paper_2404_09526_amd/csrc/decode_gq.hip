@@ -48,10 +48,10 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     cols.place(lds_k, lane);
 
     int b;
-    int32_t t0, t1, slots;
+    int32_t t0, t1, req_end, slots;
     if (BY_REQUEST) {
-        const RequestRange at = request_range(w, parts, range, B, seq_offsets);
-        b = at.b; t0 = at.t0; t1 = at.t1; w = at.w;
+        const RequestRange at = parts > 0 ? request_part(w, parts, range, B, seq_offsets) : request_range(w, range, B, seq_offsets, lane);
+        b = at.b; t0 = at.t0; t1 = req_end = at.t1; w = at.w;
         if (t0 >= t1) return;
         slots = slot_idx[min(t0 + 32 * wave + qi, t1 - 1)];
     } else {
@@ -60,13 +60,16 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
         if (t0 >= t1) return;
         // slots of this wavefront's first tile, as far as they do not depend on where its request ends: asked for before the search
         slots = slot_idx[min(t0 + 32 * wave + qi, total_tokens - 1)];
-        b = request_of(t0, seq_offsets, B, lane);
+        const RequestAt at = request_of(t0, seq_offsets, B, lane);
+        b = at.b; req_end = at.end;
     }
     bool first = true;
 
     while (t0 < t1) {
-        const int32_t req_end = seq_offsets[b + 1];
-        if (req_end <= t0) { ++b; continue; }                   // empty request
+        if (!first) {
+            req_end = seq_offsets[b + 1];
+            if (req_end <= t0) { ++b; continue; }               // empty request
+        }
         const int32_t pe = min(t1, req_end);
         const int32_t seg = pe - t0;                            // tokens of request b inside this range
 
@@ -151,6 +154,7 @@ esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_poo
                        (const char*)k_pool, (const char*)v_pool, slot_idx, seq_offsets, B, total_tokens, range, parts, Hq, Hkv,            \
                        scale_log2, part_acc, part_ml)
     if (parts > 0) ESP_GQ_LAUNCH(true, B * parts);
+    else if (parts < 0) ESP_GQ_LAUNCH(true, nwg + B);
     else ESP_GQ_LAUNCH(false, nwg);
 #undef ESP_GQ_LAUNCH
     return check_launch("decode_partial_gq_kernel");

@@ -73,28 +73,62 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers = nullptr, int32_t n_peers = 0);
 
-// The request that holds token t: the last b with seq_offsets[b] <= t, found by a wavefront 64 candidates at a time (a
-// binary search is six dependent loads, about 3 us, at 64 requests; this is one).
-__device__ __forceinline__ int request_of(int32_t t, const int32_t* seq_offsets, int32_t B, int lane) {
-    int lo = 0, hi = B;   // invariant: seq_offsets[lo] <= t < seq_offsets[hi]
-    while (hi - lo > 1) {
-        const int stride = (hi - lo + 63) >> 6, i = lo + lane * stride;
-        const uint64_t below = __builtin_amdgcn_ballot_w64(i < hi && seq_offsets[min(i, hi)] <= t);
-        lo += (__builtin_popcountll(below) - 1) * stride;
+// The request that holds token t, the last b with seq_offsets[b] <= t, and where it ends; found by a wavefront 64 candidates at a
+// time (a binary search is six dependent loads, about 3 us, at 64 requests; this is one).
+struct RequestAt { int32_t b, end; };
+__device__ __forceinline__ RequestAt request_of(int32_t t, const int32_t* seq_offsets, int32_t B, int lane) {
+    int lo = 0, hi = B, end = 0;   // invariant: seq_offsets[lo] <= t < seq_offsets[hi]
+    do {
+        const int stride = (hi - lo + 63) >> 6, i = min(lo + lane * stride, hi), next = min(i + 1, B);
+        const int32_t at = seq_offsets[i], after = seq_offsets[next];
+        const uint64_t below = __builtin_amdgcn_ballot_w64(i < hi && at <= t);
+        const int l = max(__builtin_popcountll(below) - 1, 0);
+        lo += l * stride;
         hi = min(hi, lo + stride);
-    }
-    return lo;
+        end = __builtin_amdgcn_readlane(after, l);
+    } while (hi - lo > 1);
+    return {lo, end};
 }
 
-// Workgroup i of a launch whose ranges are counted from each request's first token on, `parts` to a request (the last one takes what
-// is left of a request longer than the caller said): tokens t0 .. t1 - 1 of request b; its partial is that of range w.
+// Ranges counted from each request's first token on: workgroup i of a launch works on tokens t0 .. t1 - 1 of request b, its partial is that of
+// range w along the list.
+struct RequestRange { int32_t b, t0, t1, w; };
+// `parts` of them for each request (the last one takes what is left of a request longer than the caller said).
 // The parts of a request and the requests of a part lie on all XCDs in turn: consecutive workgroups do, so that takes an odd
 // number of them from one part to the next (all parts of a request on one XCD: 31 us for 16 requests of 900, 32 / 8 heads, against 21).
-struct RequestRange { int32_t b, t0, t1, w; };
-__device__ __forceinline__ RequestRange request_range(int32_t i, int32_t parts, int32_t range, int32_t B, const int32_t* seq_offsets) {
+__device__ __forceinline__ RequestRange request_part(int32_t i, int32_t parts, int32_t range, int32_t B, const int32_t* seq_offsets) {
     const int32_t part = i / B, at = i - part * B, b = (B & 1) != 0 ? at : (at + B - part % B) % B;
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1], t0 = s0 + part * range;
     return {b, t0, part == parts - 1 ? s1 : min(t0 + range, s1), s0 / range + part};
+}
+// As many as each request has: the whole ranges of all requests first, then what is left of each, so that workgroups which find no
+// room at first have little to do.  Requests are looked at 64 at a time, one per lane; a scan finds the one that holds range i.
+__device__ __forceinline__ RequestRange request_range(int32_t i, int32_t range, int32_t B, const int32_t* seq_offsets, int lane) {
+#pragma unroll 1
+    for (int rest = 0; rest < 2; ++rest) {
+#pragma unroll 1
+        for (int base = 0; base < B; base += 64) {
+            const int b = min(base + lane, B - 1);
+            const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1], whole = (s1 - s0) / range;
+            const int32_t n = base + lane >= B ? 0 : rest ? (s1 - s0 > whole * range ? 1 : 0) : whole;
+            int32_t upto = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int32_t below = __shfl_up(upto, d);
+                if (lane >= d) upto += below;
+            }
+            const uint64_t hit = __builtin_amdgcn_ballot_w64(upto > i);
+            if (hit) {
+                const int l = __builtin_ctzll(hit);
+                const int32_t start = __builtin_amdgcn_readlane(s0, l), end = __builtin_amdgcn_readlane(s1, l);
+                const int32_t part = rest ? __builtin_amdgcn_readlane(whole, l) : i - (__builtin_amdgcn_readlane(upto, l) - __builtin_amdgcn_readlane(n, l));
+                const int32_t t0 = start + part * range;
+                return {base + l, t0, min(t0 + range, end), start / range + part};
+            }
+            i -= __builtin_amdgcn_readlane(upto, 63);
+        }
+    }
+    return {0, 0, 0, 0};                                            // the launch is an upper bound
 }
 
 constexpr int kGqWaves = 4;       // wavefronts per workgroup of decode_gq.hip

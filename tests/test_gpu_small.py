@@ -530,6 +530,25 @@ def test_decode_ranges_by_request(esp, cuda, requests, Hq, Hkv, unit):
     assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8)])
+@pytest.mark.parametrize("requests", [9, 64, 65, 130])
+def test_decode_ranges_found_by_search(esp, cuda, requests, Hq, Hkv, unit):
+    """As many ranges as each request has, the whole ones of all requests first: one request far longer than the others, so that room for
+    as many in each would not fit; requests around one range, empty ones at the start, inside and at the end; counts of requests around one
+    and two steps of the search.  The bound on the lengths does not matter here."""
+    rng = np.random.default_rng(requests)
+    lens = rng.choice([0, 1, unit // 4, unit - 1, unit, unit + 1], requests, p=[0.2, 0.2, 0.45, 0.05, 0.05, 0.05])
+    lens[requests // 2] = 45 * unit + 3 if unit < 128 else 31 * unit + 3
+    lens[0] = lens[-1] = 0
+    dc = wl.decode_pool(f"decode-search-{requests} ({Hq}/{Hkv})", lens.tolist(), 16384, Hq, Hkv, 43, cuda, n_new=0)
+    O, LSE, _, _ = run_decode_case(esp, dc)
+    assert torch.isneginf(LSE[0]).all() and (O[-1] == 0).all()
+    O1, L1 = esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, int(lens.sum()), softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    # the partials combined in another order, rounded once: a unit of bf16 in O, 2^-8, and fp32 sums in the LSE
+    assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("Hq,Hkv,ranges,waves", [(32, 8, 6, 1), (8, 8, 24, 4), (32, 32, 94, 1), (16, 16, 47, 2)])
 def test_decode_on_the_least_workspace(esp, cuda, Hq, Hkv, ranges, waves):
     """3000 tokens: the smallest workspace a call takes (ranges of 512 tokens on the matrix cores, of eight steps with a
