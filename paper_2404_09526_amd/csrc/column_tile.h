@@ -8,22 +8,15 @@
 
 namespace esp {
 
-constexpr int kColKRow = 272;                 // K rows padded by 16 bytes in LDS (bank spread of the operand reads)
-constexpr int kColKBytes = 9 * 1024;          // 32 x 272 = 8704 bytes, moved by 9 transfers of 1 KiB
-constexpr int kColVBytes = 32 * 256;          // rows of 256 bytes, their 16-byte chunks XOR-swizzled by the row
-constexpr int kColWaveBytes = kColKBytes + kColVBytes;
+constexpr int kColKBytes = 32 * 256;          // K and V rows of 256 bytes, their 16-byte chunks XOR-swizzled by the row
+constexpr int kColVBytes = 32 * 256;
+constexpr int kColWaveBytes = 66 * 256;       // the tile, and two rows more for the combination
 
-// lane L of K transfer n fills LDS byte 1024 n + 16 L of the tile: byte `within` of row `row` (padding fetches the row's first bytes)
-struct ColPiece { int row, within; };
-__device__ __forceinline__ ColPiece col_k_piece(int n, int lane) {
-    const int at = 1024 * n + 16 * lane, within = at % kColKRow;
-    return {min(at / kColKRow, 31), within < 256 ? within : 0};
-}
-// of V transfer n: chunk c of row r holds global chunk c ^ 4 (r % 4)
-__device__ __forceinline__ ColPiece col_v_piece(int n, int lane) {
-    const int row = 4 * n + (lane >> 4);
-    return {row, ((lane & 15) ^ ((row & 3) << 2)) << 4};
-}
+// Both tiles are moved by eight transfers of 1 KiB: lane L of transfer n fills chunk L % 16 of row col_row, with these bytes of the row
+// in memory: chunk c of row r holds chunk c ^ (r % 16) of K, c ^ 4 (r % 4) of V.
+__device__ __forceinline__ int col_row(int n, int lane) { return 4 * n + (lane >> 4); }
+__device__ __forceinline__ int col_k_within(int n, int lane) { return ((lane & 15) ^ (lane >> 4) ^ (4 * (n & 3))) << 4; }
+__device__ __forceinline__ int col_v_within(int lane) { return ((lane & 15) ^ (lane >> 4 << 2)) << 4; }
 
 struct Columns {
     floatx16 oacc[4];
@@ -33,7 +26,7 @@ struct Columns {
 
     __device__ __forceinline__ void place(uint32_t lds_k, int lane) {
         const int qi = lane & 31, hi = lane >> 5, j16 = lane & 15, jq = j16 >> 2, dblk = (lane >> 4) & 1;
-        k_rd = lds_k + qi * kColKRow + hi * 16;
+        k_rd = lds_k + qi * 256 + ((hi ^ (qi & 15)) << 4);
 #pragma unroll
         for (int db = 0; db < 4; ++db)
             v_rd[db] = lds_k + kColKBytes + (4 * hi + jq) * 256 + ((((db ^ jq) << 2) + 2 * dblk + ((j16 & 3) >> 1)) << 4) + (j16 & 1) * 8;
@@ -53,7 +46,7 @@ struct Columns {
         for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
-            const bf16x8 kf = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd + t * 32);
+            const bf16x8 kf = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd ^ (t << 5));
             sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[t], sc, 0, 0, 0);
         }
         return sc;

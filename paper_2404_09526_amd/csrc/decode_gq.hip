@@ -97,16 +97,14 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
         for (int i = wave; 32 * i < seg; i += kGqWaves) {
             const int rows = min(32, seg - 32 * i);
             // ---- gather
-#pragma unroll
-            for (int n = 0; n < 9; ++n) {
-                const ColPiece at = col_k_piece(n, lane);
-                load_to_lds_b128_at_nt(lds_k + 1024 * n, kbase + ((uint64_t)(uint32_t)__shfl(slots, at.row) * row_bytes + at.within));
-            }
+uint64_t row_at[8];
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
-                const ColPiece at = col_v_piece(n, lane);
-                load_to_lds_b128_at_nt(lds_v + 1024 * n, vbase + ((uint64_t)(uint32_t)__shfl(slots, at.row) * row_bytes + at.within));
+                row_at[n] = (uint64_t)(uint32_t)__shfl(slots, col_row(n, lane)) * row_bytes;
+                load_to_lds_b128_at_nt(lds_k + 1024 * n, kbase + (row_at[n] + col_k_within(n, lane)));
             }
+#pragma unroll
+            for (int n = 0; n < 8; ++n) load_to_lds_b128_at_nt(lds_v + 1024 * n, vbase + (row_at[n] + col_v_within(lane)));
             int32_t slots_next = 0;
             if (32 * (i + kGqWaves) < seg) slots_next = tile_slots(i + kGqWaves);
             wait_vm<8>();                                           // K has landed; V and the next slots may be on their way

@@ -53,6 +53,10 @@ __device__ __forceinline__ void load_to_lds_b32(uint32_t lds_addr, const void* g
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                  :: "s"(lds_addr), "v"(voff), "s"(gbase) : "memory", "m0");
 }
+__device__ __forceinline__ void load_to_lds_b32_at(uint32_t lds_addr, const void* src) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :: "s"(lds_addr), "v"(src) : "memory", "m0");
+}
 // The same to lds_addr + off: with `off` known when it is compiled (the stage of a ring in an unrolled loop) all stages share one
 // scalar register.  One each, the addresses of the prefill kernel's ring were 24 of them: the rest did not fit, and its loop
 // read them back from vector lanes.

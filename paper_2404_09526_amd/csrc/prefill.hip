@@ -357,7 +357,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         }
         if (cut) {                                                  // this part's share of the request's tiles, as if it were the shard
             const int tiles = (kv_hi - kv_lo + kBN - 1) / kBN;
-            const int t_lo = (int)((int64_t)tiles * part / a.splits), t_hi = (int)((int64_t)tiles * (part + 1) / a.splits);
+            const int t_lo = (uint32_t)(tiles * part) / (uint32_t)a.splits, t_hi = (uint32_t)(tiles * (part + 1)) / (uint32_t)a.splits;   // (below 2^29)
             kv_hi = min(kv_hi, kv_lo + t_hi * kBN);
             kv_lo = min(kv_lo + t_lo * kBN, kv_hi);
             if (RETAIN) {

@@ -5,6 +5,12 @@
 // eight wavefronts take the tiles of 32 keys in turn, each alone, with an LDS block of its own and no barrier until the end,
 // and combine their results through LDS (column_tile.h).  A row block re-reads all of its K and V from the L2, eight times as often
 // as there, and a row costs several times as much: the launcher picks by an estimate of both times (prefill.hip).
+// A wavefront's own chain is two round trips before its first product (the request's bounds; everything else) and one for each tile
+// that follows, which starts as soon as the block that it lands in has been read.  Measured (positions, then queries and rows, each
+// tile's rows asked for when the one before is done -> this; kernel alone): 256 on 512, 4 / 4 heads, 9.9 -> 8.3 us, 16 on 2016 rows of the
+// pool, 32 / 8, 9.5 -> 8.3, 64 on 576 11.7 -> 9.9, 64 kept 8.4 -> 7.7, a single tile (27 on 27) 5.7 -> 5.8; calls: 130 on 3130, 32 / 8, 26.8
+// -> 23.5, 200 on 5200, 16 / 16, 28.4 -> 25.7, 17 on 517, 40 / 8, 9.7 -> 8.4, 31 on 70195, 4 / 4, 63.2 -> 59.8.  The next tile's rows in
+// registers while this one is in LDS (64 of them, 228 in all) was slower everywhere, 27 on 27 5.6 -> 6.8, 300 on 20300 280 -> 298 us.
 #include <limits.h>
 #include <math.h>
 
@@ -19,14 +25,15 @@ namespace esp {
 template <int MODE>
 __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(PrefillArgs a) {
     constexpr bool KEEP = MODE == 1, POOL = MODE == 2;
-    constexpr int kPosAt = kShortWaves * kColWaveBytes;             // key positions of a tile that has to be masked, per wavefront
-    __shared__ __attribute__((aligned(1024))) unsigned char smem[kPosAt + kShortWaves * 32 * 4];
+    constexpr int kListStages = 4;
+    constexpr int kQAt = kShortWaves * kColWaveBytes, kListAt = kQAt + kShortRows * kHeadDim * 2, kQPosAt = kListAt + kShortWaves * kListStages * 256;
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[kQPosAt + kShortWaves * 256];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int qi = lane & 31, hi = lane >> 5;
     // the row blocks of a (KV head, part) lie heads x parts workgroups apart: on one XCD where that is a multiple of 8
-    const int vheads = a.Hkv * a.splits, vhead = blockIdx.x % vheads;
-    const int kvh = vhead / a.splits, part = vhead - kvh * a.splits;
+    const uint32_t vheads = a.Hkv * a.splits, block = blockIdx.x / vheads, vhead = blockIdx.x - block * vheads;
+    const int kvh = a.splits == 1 ? vhead : vhead / (uint32_t)a.splits, part = vhead - kvh * a.splits;
     const int G = a.G;
 
     // ---- the request and the row block in it: requests are looked at 64 at a time, one per lane
@@ -34,7 +41,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(Pref
         const int n = ((a.cu_q ? a.cu_q[r + 1] - a.cu_q[r] : a.Tq) * G + kShortRows - 1) / kShortRows;
         return KEEP && n == 0 && a.cu_kv && a.cu_kv[r + 1] > a.cu_kv[r] ? 1 : n;
     };
-    int r = 0, blk = blockIdx.x / vheads;
+    int r = 0, blk = block;
     if (a.batch > 1) {
         bool found = false;
         for (int base = 0; base < a.batch; base += 64) {
@@ -65,38 +72,81 @@ __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(Pref
     int kv_lo = a.cu_kv ? a.cu_kv[r] : 0;
     const int kv_end = a.cu_kv ? a.cu_kv[r + 1] : a.Tkv;
     const int all_tiles = (kv_end - kv_lo + 31) / 32;
-    const int t_lo = (int)((int64_t)all_tiles * part / a.splits), t_hi = (int)((int64_t)all_tiles * (part + 1) / a.splits);
+    int t_lo = 0, t_hi = all_tiles;
+    if (a.splits > 1) {                                             // (32 bits: at most 2^26 tiles and 16 parts)
+        t_lo = (uint32_t)(all_tiles * part) / (uint32_t)a.splits;
+        t_hi = (uint32_t)(all_tiles * (part + 1)) / (uint32_t)a.splits;
+    }
     const int kv_len = min(kv_end - kv_lo, t_hi * 32) - t_lo * 32;  // this part's rows (may be none)
     kv_lo += t_lo * 32;
     const int tiles = (kv_len + 31) / 32;
 
-    // ---- this lane's row (column of S^T; rows past the end repeat the last): token and query head of the group
-    const int my = any_row ? rho + min(qi, n_rows - 1) : 0, tok = any_row ? qs + my / G : 0, row = tok * a.Hq + kvh * G + my % G;
-    const int my_qpos = a.causal ? a.q_pos[tok] : INT_MAX - 1;      // non-causal rows see every key that exists
-
+    // ---- row i of the block: token and query head of the group (rows past the end repeat the last)
+    const int tok0 = qs + (int)((uint32_t)rho / (uint32_t)G), g0 = (uint32_t)rho % (uint32_t)G, row0 = tok0 * a.Hq + kvh * G + g0;
+    auto row_of = [&](int i, int& tok) {
+        const int j = min(i, n_rows - 1), t = (int)(((float)(j + g0) + 0.5f) * a.inv_G);   // (exact: j + g0 is far below 2^21)
+        tok = tok0 + t;
+        return row0 + j + t * (a.Hq - G);
+    };
     const uint32_t row_bytes = (uint32_t)a.Hkv * (kHeadDim * 2);
     const char* kbase = (const char*)a.k + (uint32_t)kvh * (kHeadDim * 2);
     const char* vbase = (const char*)a.v + (uint32_t)kvh * (kHeadDim * 2);
-    // position and pool slot of tile row lane % 32; rows past the end: a position nobody sees, the last row's slot (KEEP: none)
-    auto tile_pos = [&](int i) {
-        const int at = 32 * i + qi;
-        const int p = a.causal ? a.kv_pos[kv_lo + min(at, kv_len - 1)] : 0;
-        return at < kv_len ? p : INT_MAX;
-    };
-    auto tile_slots = [&](int i) {
-        const int at = 32 * i + qi;
-        if (KEEP) return at < kv_len ? a.retain_slot[kv_lo + at] : -1;
-        return POOL ? a.kv_slot[kv_lo + min(at, kv_len - 1)] : 0;
-    };
-    int pos = 0, slots = 0;
-    if (wave < tiles) { pos = tile_pos(wave); slots = tile_slots(wave); }
-    bf16x8 qf[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) qf[t] = __builtin_bit_cast(bf16x8, *(const uint4*)(a.q + (int64_t)row * kHeadDim + 8 * hi + 16 * t));
+    const uint32_t lds = (uint32_t)(uintptr_t)(ESP_LDS unsigned char*)smem;
+    const uint32_t lds_k = lds + wave * kColWaveBytes, lds_v = lds_k + kColKBytes;
 
-    const uint32_t lds_k = (uint32_t)(uintptr_t)(ESP_LDS unsigned char*)smem + wave * kColWaveBytes;
-    const uint32_t lds_v = lds_k + kColKBytes;
-    int32_t* const lds_pos = (int32_t*)(smem + kPosAt) + wave * 32;
+    // ---- everything that the first tile needs is asked for at once, by transfers whose waits are counted by hand: queries, positions,
+    //      lists and, of dense rows, the rows, seen or not (they exist).  Taken one after the other, positions, then queries and rows,
+    //      these were two round trips; and queries fetched by every wavefront as fragments, 16-byte pieces of 32 rows, took as
+    //      long as a tile.
+    // Lists of a tile: lane L holds the position of tile row L % 32, or in the upper half (KEEP, POOL) its pool slot; rows past the end
+    // repeat the last.  They lie in a ring of four stages.
+    const int32_t* my_list = a.causal ? a.kv_pos + kv_lo : POOL ? a.kv_slot + kv_lo : (const int32_t*)a.k;
+    if (KEEP && hi) my_list = a.retain_slot + kv_lo;
+    if (POOL && hi) my_list = a.kv_slot + kv_lo;
+    const uint32_t lds_list = lds + kListAt + wave * (kListStages * 256);
+    auto fetch_list = [&](int i, int st) { load_to_lds_b32_at(lds_list + st * 256, my_list + min(32 * i + qi, kv_len - 1)); };
+    auto list = [&](int st) { return (int32_t*)(smem + kListAt + (wave * kListStages + st) * 256); };
+    const uint32_t row_at = (lane >> 4) * row_bytes;
+    auto fetch = [&](uint32_t to, const char* base, int i, int st, bool is_k) {
+        const uint32_t last = min(32, kv_len - 32 * i) - 1;
+        const char* tile = base + (int64_t)(kv_lo + 32 * i) * row_bytes;
+        if constexpr (POOL) {
+            int32_t slot[8];
+#pragma unroll
+            for (int n = 0; n < 8; ++n) slot[n] = list(st)[32 + col_row(n, lane)];
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+                load_to_lds_b128_at(to + 1024 * n, base + ((uint64_t)(uint32_t)slot[n] * row_bytes + (is_k ? col_k_within(n, lane) : col_v_within(lane))));
+        } else {
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+                load_to_lds_b128(to + 1024 * n, tile, min(row_at + 4 * n * row_bytes, last * row_bytes) + (is_k ? col_k_within(n, lane) : col_v_within(lane)));
+        }
+    };
+    if (wave < tiles) {
+        fetch_list(wave, 0);
+        fetch_list(wave + kShortWaves, 1);
+        if constexpr (!POOL) fetch(lds_k, kbase, wave, 0, true);
+    }
+    int tok = 0, row = 0;                                           // this lane's (column of S^T)
+    if (any_row) row = row_of(qi, tok);
+    if (a.causal) load_to_lds_b32_at(lds + kQPosAt + wave * 256, a.q_pos + tok);
+    {
+        int t;
+        const int r4 = 4 * wave + (lane >> 4), at = any_row ? row_of(r4, t) : 0;
+        const char* src = (const char*)a.q + (int64_t)at * (kHeadDim * 2) + (((lane ^ r4) & 15) << 4);
+        struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
+        if (__builtin_expect(a.q_odd, 0)) *(ESP_LDS u32x4*)(uintptr_t)(lds + kQAt + 1024 * wave + 16 * lane) = __builtin_bit_cast(u32x4, *(const Any16*)src);
+        else load_to_lds_b128_at(lds + kQAt + 1024 * wave, src);
+    }
+    if (!POOL && wave < tiles) {
+        fetch(lds_v, vbase, wave, 0, false);
+        wait_vm<8>();
+    } else {
+        wait_vm<0>();
+    }
+    const int my_qpos = a.causal ? ((const int32_t*)(smem + kQPosAt))[wave * 64 + lane] : INT_MAX - 1;   // non-causal rows see every key that exists
+
     Columns cols;
     cols.place(lds_k, lane);
     cols.clear();
@@ -112,34 +162,46 @@ __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(Pref
     };
     const int q_min = of_rows(my_qpos, least), q_max = of_rows(my_qpos, most);
     const int n_blk = KEEP ? blocks_of(r) : 1;
+    // position of tile row lane % 32; of rows past the end one that nobody sees
+    auto tile_pos = [&](int i, int st) { return 32 * i + qi >= kv_len ? INT_MAX : a.causal ? list(st)[qi] : 0; };
+    // (a key may sit at the lowest position there is: a block without rows sees nothing all the same)
+    auto is_seen = [&](int pos) { return any_row && of_rows(pos, least) <= q_max; };
+    auto is_owned = [&](int i) { return KEEP && (t_lo + i) % n_blk == blk; };
 
-    for (int i = wave; i < tiles; i += kShortWaves) {
-        // (a key may sit at the lowest position there is: a block without rows sees nothing all the same)
-        const bool seen = any_row && of_rows(pos, least) <= q_max, mask = of_rows(pos, most) > q_min;
-        const bool owned = KEEP && (t_lo + i) % n_blk == blk;
-        const int last = min(32, kv_len - 32 * i) - 1, next = i + kShortWaves;
-        int pos_next = 0, slots_next = 0;
-        if (!seen && !owned) {                                      // a tile that no row can see
-            if (next < tiles) { pos_next = tile_pos(next); slots_next = tile_slots(next); }
-            pos = pos_next; slots = slots_next;
-            continue;
+    int pos = INT_MAX;
+    bool seen = false, owned = false;
+    if (wave < tiles) { pos = tile_pos(wave, 0); seen = is_seen(pos); owned = is_owned(wave); }
+    if constexpr (POOL) {
+        if (seen) { fetch(lds_k, kbase, wave, 0, true); fetch(lds_v, vbase, wave, 0, false); }
+    }
+    wg_barrier();                                                   // all queries are there
+    bf16x8 qf[8];
+    const uint32_t q_rd = lds + kQAt + qi * 256 + ((hi ^ (qi & 15)) << 4);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) qf[t] = *(const ESP_LDS bf16x8*)(uintptr_t)(q_rd ^ (t << 5));
+
+    int st = 0;
+    for (int i = wave; i < tiles; i += kShortWaves, st = (st + 1) % kListStages) {
+        // Here the rows of tile i are on their way where it is seen or owned, V last; the lists of the next tile before them.
+        const int next = i + kShortWaves, st1 = (st + 1) % kListStages, st2 = (st + 2) % kListStages;
+        const bool has_next = next < tiles;
+        if (seen || owned) wait_vm<8>(); else wait_vm<0>();
+        const int pos_next = has_next ? tile_pos(next, st1) : INT_MAX;
+        const bool seen_next = has_next && is_seen(pos_next), owned_next = has_next && is_owned(next), wanted_next = seen_next || owned_next;
+        // The next tile's K follows as soon as the scores are taken, its V as soon as this tile's has been read; not past an owned tile,
+        // whose rows leave after its products, and whose stores the waits would count.
+        const bool ahead = !KEEP || !owned;
+        floatx16 sc;
+        if (seen) sc = cols.scores(qf);
+        if (ahead && has_next) {
+            if (seen) asm volatile("" :: "v"(sc));                  // K has been read
+            fetch_list(next + kShortWaves, st2);
+            if (wanted_next) fetch(lds_k, kbase, next, st1, true);
         }
-        const int64_t tile_at = (int64_t)(kv_lo + 32 * i) * row_bytes;
-        auto fetch = [&](uint32_t lds, const char* base, ColPiece at) {
-            if constexpr (POOL) load_to_lds_b128_at(lds, base + ((uint64_t)(uint32_t)__shfl(slots, at.row) * row_bytes + at.within));
-            else load_to_lds_b128(lds, base + tile_at, (uint32_t)min(at.row, last) * row_bytes + at.within);
-        };
-#pragma unroll
-        for (int n = 0; n < 9; ++n) fetch(lds_k + 1024 * n, kbase, col_k_piece(n, lane));
-        if (next < tiles) { pos_next = tile_pos(next); slots_next = tile_slots(next); }
-#pragma unroll
-        for (int n = 0; n < 8; ++n) fetch(lds_v + 1024 * n, vbase, col_v_piece(n, lane));
-        wait_vm<8>();                                               // K (and what the next tile needs first) has landed
-
         if (seen) {
-            floatx16 sc = cols.scores(qf);
-            if (mask) {
-                if (lane < 32) lds_pos[lane] = pos;
+            if (of_rows(pos, most) > q_min) {
+                int32_t* const lds_pos = list(st);
+                if (32 * i + 32 > kv_len && lane < 32) lds_pos[lane] = pos;   // the ragged last tile: positions past the end
 #pragma unroll
                 for (int bb = 0; bb < 4; ++bb) {
                     const int4 kp = *(const int4*)(lds_pos + 8 * bb + 4 * hi);
@@ -151,27 +213,32 @@ __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(Pref
             }
             Columns::PFrag pf[2];
             cols.weigh(sc, a.scale_log2, pf);
-            wait_vm<0>();
-            asm volatile("" :: "v"(pos_next), "v"(slots_next));
+            if (ahead && wanted_next) wait_vm<9>(); else wait_vm<0>();
             cols.accumulate(pf);
         }
         if (owned) {
             if (!seen) wait_vm<0>();
             // what this wavefront fetched, to the rows' slots (lane L of transfer n: the 16 bytes it brought)
-            auto keep = [&](char* pool, int lds_at, ColPiece at, bool is_row) {
-                const int32_t slot = __shfl(slots, at.row);
+            auto keep = [&](char* pool, int lds_at, int n, int within) {
+                const int32_t slot = 32 * i + col_row(n, lane) < kv_len ? list(st)[32 + col_row(n, lane)] : -1;
                 const uint4 w = *(const uint4*)(smem + wave * kColWaveBytes + lds_at + 16 * lane);
-                if (is_row && slot >= 0) *(uint4*)(pool + (uint32_t)kvh * (kHeadDim * 2) + ((uint64_t)(uint32_t)slot * row_bytes + at.within)) = w;
+                if (slot >= 0) *(uint4*)(pool + (uint32_t)kvh * (kHeadDim * 2) + ((uint64_t)(uint32_t)slot * row_bytes + within)) = w;
             };
 #pragma unroll
-            for (int n = 0; n < 9; ++n)
-                keep((char*)a.k_pool, 1024 * n, col_k_piece(n, lane), (1024 * n + 16 * lane) % kColKRow < 256 && 1024 * n + 16 * lane < 32 * kColKRow);
+            for (int n = 0; n < 8; ++n) keep((char*)a.k_pool, 1024 * n, n, col_k_within(n, lane));
 #pragma unroll
-            for (int n = 0; n < 8; ++n) keep((char*)a.v_pool, kColKBytes + 1024 * n, col_v_piece(n, lane), true);
+            for (int n = 0; n < 8; ++n) keep((char*)a.v_pool, kColKBytes + 1024 * n, n, col_v_within(lane));
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // read before the next tile's transfers overwrite it
         }
-        pos = pos_next; slots = slots_next;
+        if (!ahead && has_next) {
+            wait_vm<0>();
+            fetch_list(next + kShortWaves, st2);
+            if (wanted_next) fetch(lds_k, kbase, next, st1, true);
+        }
+        if (wanted_next) fetch(lds_v, vbase, next, st1, false);
+        pos = pos_next; seen = seen_next; owned = owned_next;
     }
+    wait_vm<0>();
 
     constexpr int N = 64 / kShortWaves;
     float out[N], mx, lsum;

@@ -345,6 +345,21 @@ def test_prefill_of_few_rows(esp, cuda, Tq, Tkv, Hq, Hkv, causal):
     assert torch.equal(O5[2:2 + Tq].view(torch.int16), O.view(torch.int16)) and torch.equal(L5[2:2 + Tq].view(torch.int32), LSE.view(torch.int32))
 
 
+@pytest.mark.parametrize("Tkv", [257, 512, 800, 1031])
+@pytest.mark.parametrize("seen", ["later", "first", "odd"])
+@pytest.mark.usefixtures("each_prefill_plan")
+def test_prefill_tiles_seen_and_hidden_in_turn(esp, cuda, Tkv, seen):
+    """Positions that change between visible and hidden every 256 rows, a wavefront's tiles of the kernel for few rows: its first one
+    hidden, its later ones hidden, every other one; dense, kept (hidden tiles are kept too) and pool rows."""
+    pc = wl.contiguous_prefill(f"turns-{seen}-{Tkv}", 70, Tkv - 70, [(0, Tkv)], 8, 2, 63, cuda)
+    group = torch.arange(Tkv, device=cuda) // 256
+    hidden = {"later": group == 0, "first": group > 0, "odd": group % 2 == 0}[seen]
+    pc.shards[0].kv_pos = (pc.shards[0].kv_pos + hidden.to(torch.int32) * (1 << 20)).contiguous()
+    run_prefill_case(esp, pc)
+    run_retain_case(esp, pc, 64)
+    run_pool_direct_case(esp, pc, 65)
+
+
 def ragged_batch(name, q_lens, kv_lens, Hq, Hkv, seed, device):
     """One shard: q_lens[r] tokens at the end of kv_lens[r] rows."""
     gen = torch.Generator(device=device).manual_seed(seed)
