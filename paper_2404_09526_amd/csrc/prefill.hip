@@ -100,14 +100,20 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // Main kernel: an item costs a set-up and an epilogue (8.5) beside its tiles (1.45 each; 0.8 where only one wavefront has rows,
 // as the others then only move tiles), the merge a launch (4) and its traffic.  Items of a chunk at the end of a long context are
 // alike, so rounds count whole; where the chunk is most of the shard the sweeps are a triangle, which the item pool evens out.
-// Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each while K and V come from the caches, 2.5 once they are more than
-// the 256 MB that the last of those holds), but no faster than its row blocks can be fed from the L2 (12.5 TB/s).  Several row
+// In a triangle a tile costs less, but for an owner of kept rows (1.05: a wavefront past its last one leaves the matrix pipe to the other), and where the items are one
+// round and uncut, halves of query tiles are paired (PAIRED at the kernel): 12 beside 0.5 .. 0.9 a tile of the longest sweep,
+// the more the more CUs are at it.
+// Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each, 1.3 in a triangle, while K and V come from the caches, 2.5 once they are more
+// than the 256 MB that the last of those holds; on average 0.75 of the last row block's in a triangle), but no faster than its row blocks can be fed from the L2 (12.5 TB/s).  Several row
 // blocks of a head share its K and V only on one XCD, i.e. where heads times parts is a multiple of 8 (51 tokens on 29013 rows,
 // 12 / 12 heads: 43 us in 8 parts, 40 in 10, 62 in 9).
 // Measured (main kernel, best cut -> this): 27 tokens on 27, 32 / 8 heads, 10.5 -> 5.9 us, 256 on 512, 4 / 4, 17.9 -> 10.0,
 // 1024 on 1024, 8 / 8, 26.1 -> 14.8, 16 on 2016, 32 / 8, 19.6 -> 13.5, 100 on 3100, 8 / 8, 23.0 -> 15.8, 31 on 70195, 4 / 4, 62.3
 // -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
 // 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
+// With the terms of the triangle, over 32 shapes of 512 .. 14000 tokens, 4 / 4 .. 40 / 8 heads, the choice is 0.7 % from the best of up to seven on
+// average, 11 % at most (without them 6 %, 37 %): 512 on 512, 32 / 8, 14.1 (main kernel 17.7), 5000 on 5000, 4 / 4, 47.0 in four parts (uncut 64.5),
+// 6000 on 6000, 8 / 8, 83.5 uncut (two parts 88.6); kept: 700 on 700, 32 / 8, 25.0 (main kernel 28.6), two of 2000, 16 / 16, 113 in two parts (uncut 117).
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
 // Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
 // last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
@@ -118,9 +124,18 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
 struct PrefillPlan { int32_t splits, use_short; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
-static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, int32_t most_splits) {
-    constexpr double kCus = 256, kTileLeast = 0.7, kTileRows = 0.75, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
-    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
+constexpr double kCus = 256;
+// rounds of the main kernel's items, uncut (the lengths of a batch's requests are not known: half a ragged tile each)
+static double prefill_rounds(int32_t Tq, int32_t batch, int32_t Hq, int32_t Hkv) {
+    const double rows = (double)Tq * (Hq / Hkv);
+    return Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch) / kCus;
+}
+static bool prefill_paired(double rounds, int32_t S) { return S == 1 && rounds <= 1; }
+// `kept`: rows are kept on the way; such items stay side by side (each owns the tiles on its diagonal).
+static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool kept, int32_t most_splits) {
+    constexpr double kTileLeast = 0.7, kTileRows = 0.75, kTileTriangle = 1.05, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
+    constexpr double kPairTile = 0.5, kPairTileFull = 0.4, kPairItem = 12;
+    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortTriangle = 1.3, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
     if (Tq <= 0 || Tkv <= 0) return {1, 0};
     if (t_forced_plan != 0) {
         const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
@@ -128,21 +143,27 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
     }
     const double rows = (double)Tq * (Hq / Hkv), tiles = ceil((double)Tkv / batch / kBN);
     const double seen = Tq < Tkv ? 1.0 - 0.5 * Tq / Tkv : 0.5;        // of the tiles, on average, with the chunk at the shard's end
-    const double items = Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch);
-    const double kTile = kTileLeast + kTileRows * fmin(rows / batch / kBM, 1);
+    const double rounds = prefill_rounds(Tq, batch, Hq, Hkv);
+    const bool triangle = seen <= 0.8;
+    const double kTile = fmin(kTileLeast + kTileRows * fmin(rows / batch / kBM, 1), triangle && !kept ? kTileTriangle : HUGE_VAL);
     const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
-    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), step = kv_bytes > 2e8 ? kShortFar : kShortStep;
+    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), step = kv_bytes > 2e8 ? kShortFar : triangle ? kShortTriangle + (kShortStep - kShortTriangle) * (seen - 0.5) / 0.3 : kShortStep;
     // `longest`: tiles of the longest request, or of all alike (`tiles`)
     auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
     auto main_us = [&](int32_t S, double longest) {
-        const double n = items * S / kCus, item = seen * tiles / S * kTile + kItem;
-        double us = seen > 0.8 ? ceil(n) * item : fmax(tiles / S * kTile + kItem, (n + 0.3) * item);
-        if (longest > tiles) us = fmax(us, fmax(n - 1, 0) * item + longest / S * kTile + kItem);
+        const double n = rounds * S, item = seen * tiles / S * kTile + kItem;
+        double us = triangle ? fmax(tiles / S * kTile + kItem, (n + 0.3) * item) : ceil(n) * item;
+        if (triangle && !kept && prefill_paired(rounds, S)) {
+            const double alike = Tq < Tkv ? 1 - (double)Tq / Tkv : 0;   // of the tiles, seen by all rows
+            us = fmin(us, fmax(longest, tiles) * (alike * kTileTriangle + (1 - alike) * (kPairTile + kPairTileFull * n)) + kPairItem);
+        } else if (longest > tiles) {
+            us = fmax(us, fmax(n - 1, 0) * item + longest / S * kTile + kItem);
+        }
         return us + merge_us(S);
     };
     auto short_us = [&](int32_t S, double longest) {
         const double n = blocks * S / kCus, item = kShortItem + step * ceil(2 * tiles / S / kShortWaves);
-        double us = (seen > 0.8 ? ceil(n) : n <= 1 ? 1 : n + 0.3) * item, swept = blocks / Hkv / batch * seen * kv_bytes;
+        double us = !triangle ? ceil(n) * item : n <= 1 ? item : fmax(item, (n + 0.3) * (kShortItem + (0.5 + 0.5 * seen) * (item - kShortItem))), swept = blocks / Hkv / batch * seen * kv_bytes;
         if (longest > tiles) {
             us = fmax(us, fmax(n - 1, 0) * item + kShortItem + step * ceil(2 * longest / S / kShortWaves));
             swept = fmax(swept, blocks / batch * longest * kBN * (4 * kHeadDim));
@@ -181,9 +202,14 @@ static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S 
 // (which few rows fit, and cutting helps only those: the merge of 64 MB of parts takes 30 us).
 constexpr size_t kUnevenBytes = 64 << 20;
 static int32_t prefill_most_splits(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    int32_t most = prefill_plan(Tq, Tkv, batch, 0, Hq, Hkv, ESP_MAX_PARTIALS).splits;
+    auto splits = [&](int32_t max_kv) {                              // (kept rows or not: not known either)
+        const int32_t plain = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, false, ESP_MAX_PARTIALS).splits;
+        const int32_t kept = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, true, ESP_MAX_PARTIALS).splits;
+        return plain > kept ? plain : kept;
+    };
+    int32_t most = splits(0);
     if (batch > 1) {
-        int32_t uneven = prefill_plan(Tq, Tkv, batch, Tkv, Hq, Hkv, ESP_MAX_PARTIALS).splits;
+        int32_t uneven = splits(Tkv);
         while (uneven > most && split_bytes(uneven, Tq, Hq) > kUnevenBytes) --uneven;
         if (uneven > most) most = uneven;
     }
@@ -199,18 +225,18 @@ int32_t set_prefill_plan(int32_t plan) {
     return before;
 }
 // what a call with a workspace of so many bytes runs on
-static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
-    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, ESP_MAX_PARTIALS);
+static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool kept) {
+    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, ESP_MAX_PARTIALS);
     if (batch > 1 && plan.splits > 1) {                            // (a larger workspace than was asked for changes nothing)
         const int32_t most = prefill_most_splits(Tq, Tkv, batch, Hq, Hkv);
-        if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, most);
+        if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, most);
     }
     int32_t fit = plan.splits;
     while (fit > 1 && workspace_bytes < kPrefillCounterBytes + split_bytes(fit, Tq, Hq)) --fit;
-    return fit == plan.splits ? plan : prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, fit);   // a block without room for all parts
+    return fit == plan.splits ? plan : prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, fit);   // a block without room for all parts
 }
 int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, false);
     return plan.use_short ? -plan.splits : plan.splits;
 }
 
@@ -251,9 +277,19 @@ template <int V> struct IC { static constexpr int value = V; };
 // 49.8 -> 46.9 us; 1500 on 1500 39.4 -> 38.1; 4000 on 20000 962 -> 960; 8192 against four of 8192 1824 -> 1808 us.  The
 // same for MODE 1 and 2 gained nothing: 1500 against two of 1500, kept, 8 / 8 heads, 81.9 -> 82.4 us, 2048 against 8192 rows
 // of the pool, 32 / 32 heads, 237.5 -> 237.7 us.
-template <int MODE, bool ONE>
+//
+// PAIRED (with MODE 0 and 2, uncut): where a causal call's items are one round of workgroups, its time is the longest sweep's, the last query
+// tile's, while a workgroup of the first ones has nothing left to do.  So a tile is 128 rows from the end of the request and the 128 as
+// far from its start: every workgroup has a long and a short half, and where only the long one is left, one wavefront per SIMD,
+// a tile takes 0.75 us in place of 1.05.  The wavefronts' rows are counted from each one's own first row then.  Over more than one round the deal
+// evens the items out, and one wavefront per SIMD leaves the matrix pipe idle: 1200 and 1100 tokens, 32 / 8 heads (296 items), 36.7 us
+// side by side, 46.4 paired, 3000, 32 / 8, 78.4 and 88.5, 8192, 32 / 32, 446 and 486.  Measured (side by side -> paired, or the best cut ->
+// paired): 2048 on 2048, 32 / 8, 49.4 -> 43.6 us; 1000, 32 / 32, 28.1 -> 24.7; 4000, 16 / 16, 81.7 -> 70.8; 3000, 12 / 12, 50.2 -> 45.4;
+// 6000, 8 / 8, 88.6 -> 83.2; 4000, 300, 1500, 600 and 900, 8 / 8, 76.2 -> 60.8; 2000 on 2000 rows of the pool, 32 / 8, 57.0 -> 50.1.
+template <int MODE, bool ONE, bool PAIRED>
 __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     constexpr bool RETAIN = MODE == 1 || MODE == 3, POOL = MODE == 2;
+    constexpr int kTileRow = PAIRED ? 0 : 32, kHalf = kBM / 2;      // rows of the tile ahead of each wavefront's own (PAIRED: counted from its own)
     // One LDS block, V stages first: an LDS instruction adds a 16-bit immediate to its address register, so with
     // each array's base folded into the per-lane register every operand read of the loop needs no address math.
     constexpr int kLdsV = 0, kLdsK = kLdsV + kStages * kTileBytes, kLdsPos = kLdsK + kStages * kKTileBytes,
@@ -289,9 +325,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         }
     };
     auto process = [&](const int rank, const int vhead, unsigned long long* claim_from) {
-    const bool cut = !ONE && a.splits > 1;
+    const bool cut = !ONE && !PAIRED && a.splits > 1;
     const int kvh = cut ? vhead / a.splits : vhead, part = cut ? vhead - kvh * a.splits : 0;
-    int row0, n_rows, g0, kv_lo, kv_hi;   // first row of this tile in the [token, head] order, how many it has, query head of
+    int row0, n_rows, g0, kv_lo, kv_hi;   // first row of this tile (PAIRED: of this wavefront) in the [token, head] order, how many it has, query head of
                                           // the group it starts at; rows of its request in the shard
     int tok0;                       // token of the first row
     int own_lo = 0, own_hi = 0;     // KV tiles of the request whose rows this item keeps in the pool (none: equal)
@@ -339,8 +375,14 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             if (!found) return false;
         }
         const int qs = a.cu_q ? a.cu_q[r] : 0, qe = a.cu_q ? a.cu_q[r + 1] : a.Tq;
-        const int rho = tl * kBM;
+        int rho = tl * kBM;
         n_rows = min(kBM, (qe - qs) * G - rho);
+        if constexpr (PAIRED) {                                     // (of this wavefront; without rows, any of the tile's will do for what is loaded)
+            const int total = (qe - qs) * G, lower = nt - 1 - tl, upper = (total + kHalf - 1) / kHalf - 1 - lower;
+            rho = (wave < kPfWaves / 2 ? lower : upper) * kHalf + (wave & (kPfWaves / 2 - 1)) * 32;
+            n_rows = wave >= kPfWaves / 2 && upper == lower ? 0 : max(min(32, total - rho), 0);
+            if (n_rows == 0) rho = lower * kHalf;
+        }
         tok0 = qs + rho / G;
         g0 = rho % G;
         row0 = tok0 * a.Hq + kvh * G + g0;
@@ -357,7 +399,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         }
         if (cut) {                                                  // this part's share of the request's tiles, as if it were the shard
             const int tiles = (kv_hi - kv_lo + kBN - 1) / kBN;
-            const int t_lo = (uint32_t)(tiles * part) / (uint32_t)a.splits, t_hi = (uint32_t)(tiles * (part + 1)) / (uint32_t)a.splits;   // (below 2^29)
+            const int t_lo = (int)((int64_t)tiles * part / a.splits), t_hi = (int)((int64_t)tiles * (part + 1) / a.splits);
             kv_hi = min(kv_hi, kv_lo + t_hi * kBN);
             kv_lo = min(kv_lo + t_lo * kBN, kv_hi);
             if (RETAIN) {
@@ -533,8 +575,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int qi = lane & 31, hi = lane >> 5;
     int bl = lane, bw = wave;                                       // opaque, as at the scan of the requests: what is worked out from
     asm volatile("" : "+v"(bl), "+s"(bw));                          // these once per item does not live through the sweep
-    const int ld_i = min(bw * 32 + (bl & 31), n_rows - 1);
-    const bool any_row = n_rows > 0;                                  // (an empty tile of the keeping variant: any row will do)
+    const int ld_i = PAIRED ? max(min(bl & 31, n_rows - 1), 0) : min(bw * 32 + (bl & 31), n_rows - 1);
+    const bool any_row = PAIRED || n_rows > 0;                        // (an empty tile of the keeping variant: any row will do)
     // effective query position: non-causal rows see every real key
     const int my_qpos = a.causal ? a.q_pos[any_row ? tok0 + token_of(ld_i) : 0] : INT_MAX - 1;   // INT_MAX marks rows past a ragged tail
 
@@ -595,7 +637,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     {
         const char* qp = (const char*)a.q + (any_row ? (int64_t)row0 * (kHeadDim * 2) : 0);
         auto q_src = [&](int n) {
-            const int r = 4 * n + (bl >> 4), i = max(min(32 * bw + r, n_rows - 1), 0);
+            const int r = 4 * n + (bl >> 4), i = max(min(kTileRow * bw + r, n_rows - 1), 0);
             return qp + (int64_t)row_of(i) * (kHeadDim * 2) + (((bl ^ r) & 15) << 4);
         };
         struct __attribute__((packed, aligned(2))) Any16 { uint32_t x, y, z, w; };
@@ -698,7 +740,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         n_need = lw + 1;
         if (KEEP) n_vis = max(n_vis, own_hi);                       // every owned tile passes through LDS, seen or not
     }
-    if (wave * 32 >= n_rows) n_need = 0;                            // a wavefront without rows: transfers and barriers only
+    if (kTileRow * wave >= n_rows) n_need = 0;                           // a wavefront without rows: transfers and barriers only
 
     // ---- operand read offsets
     // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> one base per lane, the rest are immediates
@@ -1144,7 +1186,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // (first, while no store is in flight that a wait for anything else would have to sit out)
     int el = lane, ew = wave;                                       // opaque: the addresses are worked out here, not before the sweep
     asm volatile("" : "+v"(el), "+s"(ew));
-    const int my_i = ew * 32 + el, e_qi = el & 31, e_hi = el >> 5;
+    const int my_i = kTileRow * ew + el, e_qi = el & 31, e_hi = el >> 5;
     if (el < 32 && my_i < n_rows)
         *(float*)((char*)(a.LSE + row0 + row_of(my_i)) + part * a.lse_part) = ltot != 0.f ? (m_fin + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
     // O goes through LDS so that it leaves in whole rows: a lane holds 8-byte pieces of one row, 16 of them spread
@@ -1152,7 +1194,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // barrier above ended all tile reads) they come back as 16 lanes x 16 bytes per row, four rows per store.
     // rows of this wavefront that exist (may be <= 0); a part of a split call in which none of them sees a key leaves O
     // unwritten: its LSE, -inf, keeps it out of the merge
-    const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - ew * 32);
+    const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - kTileRow * ew);
     char* const O_part = (char*)a.O + part * a.o_part;
     if (!a.o_f32) {
         unsigned char* blk = smem + kLdsK + ew * (32 * kKRow);
@@ -1167,8 +1209,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // same wavefront wrote what it reads next
         const int rsub = el >> 4, c16 = el & 15;
-        uint16_t* orow = (uint16_t*)O_part + (int64_t)(ONE ? row0 + row_of(ew * 32 + rsub) : row0) * kHeadDim + 8 * c16;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(4 * i) : row_of(ew * 32 + 4 * i + rsub)) * kHeadDim); };
+        uint16_t* orow = (uint16_t*)O_part + (int64_t)(ONE ? row0 + row_of(kTileRow * ew + rsub) : row0) * kHeadDim + 8 * c16;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(4 * i) : row_of(kTileRow * ew + 4 * i + rsub)) * kHeadDim); };
         if (rows_here >= 32) {                                      // all rows exist: eight stores in a row, no branches
             uint4 w[8];
 #pragma unroll
@@ -1197,8 +1239,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                     make_float4(oacc[db][4 * bb + 0] * inv, oacc[db][4 * bb + 1] * inv, oacc[db][4 * bb + 2] * inv, oacc[db][4 * bb + 3] * inv);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         const int rsub = el >> 5, c32 = el & 31;
-        float* orow = (float*)O_part + (int64_t)(ONE ? row0 + row_of(ew * 32 + rsub) : row0) * kHeadDim + 4 * c32;
-        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(2 * i) : row_of(ew * 32 + 2 * i + rsub)) * kHeadDim); };
+        float* orow = (float*)O_part + (int64_t)(ONE ? row0 + row_of(kTileRow * ew + rsub) : row0) * kHeadDim + 4 * c32;
+        auto out = [&](int i) { return (uint4*)(orow + (int64_t)(ONE ? row_of(2 * i) : row_of(kTileRow * ew + 2 * i + rsub)) * kHeadDim); };
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             uint4 w[8];
@@ -1336,7 +1378,7 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
     a.q_pos = q_pos; a.kv_pos = kv_pos; a.cu_q = cu_q; a.cu_kv = cu_kv;
     const size_t counters = kPrefillCounterBytes;
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, retain_slot != nullptr);
     const int32_t S = plan.splits;
     a.splits = S;
     if (S > 1) {
@@ -1383,17 +1425,19 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     // start-of-round waits: one request with at least 512 KV tiles and a query chunk of at most an eighth of them
     // (a chunk against a long prefix: every query tile then sees nearly all of the shard, the items are alike)
     a.group_sync = a.by_head && S == 1 && Tkv >= 512 * kBN && (int64_t)Tkv >= 8 * (int64_t)Tq;
+    const bool paired = a.causal && !retain_slot && prefill_paired(prefill_rounds(Tq, batch, Hq, Hkv), S);
     a.sync_ticks = g_sync_ticks.load(std::memory_order_relaxed);
-    if (kv_slot)
-        hipLaunchKernelGGL((prefill_kernel<2, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
-    else if (retain_slot && a.q_odd)
-        hipLaunchKernelGGL((prefill_kernel<3, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
-    else if (retain_slot)
-        hipLaunchKernelGGL((prefill_kernel<1, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
-    else if (a.G == 1 && batch == 1 && S == 1)
-        hipLaunchKernelGGL((prefill_kernel<0, true>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
-    else
-        hipLaunchKernelGGL((prefill_kernel<0, false>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a);
+#define ESP_PREFILL_LAUNCH(...) hipLaunchKernelGGL((prefill_kernel<__VA_ARGS__>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a)
+    const bool one = a.G == 1 && batch == 1 && S == 1;
+    if (kv_slot && paired) ESP_PREFILL_LAUNCH(2, false, true);
+    else if (kv_slot) ESP_PREFILL_LAUNCH(2, false, false);
+    else if (retain_slot && a.q_odd) ESP_PREFILL_LAUNCH(3, false, false);
+    else if (retain_slot) ESP_PREFILL_LAUNCH(1, false, false);
+    else if (one && paired) ESP_PREFILL_LAUNCH(0, true, true);
+    else if (one) ESP_PREFILL_LAUNCH(0, true, false);
+    else if (paired) ESP_PREFILL_LAUNCH(0, false, true);
+    else ESP_PREFILL_LAUNCH(0, false, false);
+#undef ESP_PREFILL_LAUNCH
     const esp_status st = check_launch("prefill_kernel");
     if (st != ESP_OK || S == 1) return st;
     return merge_parts(a, O, LSE, o_f32, stream);

@@ -318,6 +318,22 @@ def test_prefill_one_request_of_a_multi_head_model(esp, cuda, H, Tq, Tkv):
         assert torch.equal(O2.to(torch.bfloat16).view(torch.int16), O.view(torch.int16)) and torch.equal(L2.view(torch.int32), LSE.view(torch.int32))
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(3, 3), (8, 2), (5, 1)])
+@pytest.mark.parametrize("chunks,first", [([1], 0), ([127, 0, 3], 0), ([128], 7), ([129, 40, 513], 0), ([255], 0), ([256, 257], 0), ([385], 300),
+                                          ([384, 63, 640, 1], 0), ([700], 0), ([1100], 65)])
+@pytest.mark.usefixtures("main_prefill_kernel")
+def test_prefill_halves_of_tiles_in_pairs(esp, cuda, Hq, Hkv, chunks, first):
+    """Calls of one round pair the 128 rows at one end of a request with those at the other: odd and even numbers of halves, halves
+    that are not full, a middle one alone, requests of one half or none, wavefronts without rows, keys ahead of the chunk (`first`); dense
+    and pool rows, bf16 and fp32 (one request with as many KV heads as query heads has an instance of its own)."""
+    if first:
+        pc = wl.contiguous_prefill(f"pairs-{Hq}/{Hkv}", chunks[0], first, [(0, first + chunks[0])], Hq, Hkv, 34, cuda)
+    else:
+        pc = wl.striped_prefill(f"pairs-{Hq}/{Hkv}", chunks, 1, 0, Hq, Hkv, 34, cuda)
+    run_prefill_case(esp, pc)
+    run_pool_direct_case(esp, pc, 35)
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (6, 2), (40, 8)])
 @pytest.mark.parametrize("Tq,Tkv", [(1, 1), (31, 31), (32, 32), (33, 65), (64, 255), (11, 257), (96, 289), (7, 2100)])
