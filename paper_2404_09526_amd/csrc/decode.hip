@@ -238,11 +238,9 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
         b = at.b; req_end = at.end;
     }
     int32_t t0 = r0;
-    while (t0 < t1) {
-        if (t0 > r0) {
-            req_end = seq_offsets[b + 1];
-            if (req_end <= t0) { ++b; continue; }               // empty request
-        }
+    while (t0 < t1 && b < B) {                                  // (tokens past the offsets' end belong to no request)
+        if (t0 > r0) req_end = seq_offsets[b + 1];
+        if (req_end <= t0) { ++b; continue; }                   // empty request, or the last one where the range starts past its end
         const int32_t pe = min(t1, req_end);
         // this wavefront's tokens of the request: i0 .. i1 - 1
         const int i0 = max(t0 - r0 - tsub + nt - 1, 0) >> nt_log, i1 = max(pe - r0 - tsub + nt - 1, 0) >> nt_log;

@@ -65,11 +65,9 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     }
     bool first = true;
 
-    while (t0 < t1) {
-        if (!first) {
-            req_end = seq_offsets[b + 1];
-            if (req_end <= t0) { ++b; continue; }               // empty request
-        }
+    while (t0 < t1 && b < B) {                                  // (tokens past the offsets' end belong to no request)
+        if (!first) req_end = seq_offsets[b + 1];
+        if (req_end <= t0) { ++b; continue; }                   // empty request, or the last one where the range starts past its end
         const int32_t pe = min(t1, req_end);
         const int32_t seg = pe - t0;                            // tokens of request b inside this range
 

@@ -561,6 +561,20 @@ def test_decode_ranges_by_request(esp, cuda, requests, Hq, Hkv, unit):
     assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (4, 4), (8, 8), (32, 32), (8, 4)])
+@pytest.mark.parametrize("lens", [[200], [3], [700, 0], [40, 0, 300]])
+def test_decode_slots_past_the_offsets_belong_to_no_request(esp, cuda, Hq, Hkv, lens):
+    """A slot list that is longer than its offsets, by many ranges: ranges that start past the last request, one that it ends in;
+    one request, for which ranges lie along the list, and a few.  The slots past the end are rows of the pool, never attended."""
+    dc = wl.decode_pool(f"decode-long-list ({Hq}/{Hkv})", lens, 16384, Hq, Hkv, 45, cuda, n_new=0)
+    O, LSE, _, _ = run_decode_case(esp, dc)
+    longer = torch.cat([dc.slot_idx, torch.arange(9000, dtype=torch.int32, device=cuda)])
+    O1, L1 = esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, longer, dc.seq_offsets, max(lens), softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    # the partials combined in another order, rounded once: a unit of bf16 in O, 2^-8, and fp32 sums in the LSE
+    assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8)])
 @pytest.mark.parametrize("requests", [9, 64, 65, 130])
 def test_decode_ranges_found_by_search(esp, cuda, requests, Hq, Hkv, unit):
