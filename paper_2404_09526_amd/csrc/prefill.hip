@@ -117,11 +117,12 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
 // Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
 // last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
-// which rows the longest request has is not known.  Over 265 batches that it would cut differently, most of them random (time against
+// which rows the longest request has is not known (in a triangle it is, as good as: there the choice follows the longest).  Over 265 batches that it would cut differently, most of them random (time against
 // the even cut's): any gain promised 0.77 on average, 15 of them 3 .. 21 % slower; a fifth 0.78 and 8; three tenths 0.83 and 1.
 // Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 64.6 -> 32.1 us, 8 on 200000
 // beside 63 of 8 on 512 2222 -> 479, 300 on 20300 beside three of 300 on 600 330 -> 169; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
-// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
+// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).  In a triangle, by the average -> by the longest: 2000 tokens
+// beside fifteen of 32, 8 / 8, 34.3 -> 30.3; 4000 beside seven of 32, 4 / 4, 55.3 -> 47.7; 6000 beside fifteen of 32, 4 / 4, 75.4 -> 67.9.
 struct PrefillPlan { int32_t splits, use_short; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
 constexpr double kCus = 256;
@@ -148,25 +149,36 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
     const double kTile = fmin(kTileLeast + kTileRows * fmin(rows / batch / kBM, 1), triangle && !kept ? kTileTriangle : HUGE_VAL);
     const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
     const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), step = kv_bytes > 2e8 ? kShortFar : triangle ? kShortTriangle + (kShortStep - kShortTriangle) * (seen - 0.5) / 0.3 : kShortStep;
-    // `longest`: tiles of the longest request, or of all alike (`tiles`)
+    // `longest`: tiles of the longest request, or of all alike (`tiles`).  In a triangle the requests of a batch are taken to have rows as they
+    // have keys, and a batch takes no less than its longest alone.
+    auto rows_of = [&](double longest) { return rows * fmin(longest * kBN / Tkv, 1); };
     auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
     auto main_us = [&](int32_t S, double longest) {
-        const double n = rounds * S, item = seen * tiles / S * kTile + kItem;
-        double us = triangle ? fmax(tiles / S * kTile + kItem, (n + 0.3) * item) : ceil(n) * item;
         if (triangle && !kept && prefill_paired(rounds, S)) {
             const double alike = Tq < Tkv ? 1 - (double)Tq / Tkv : 0;   // of the tiles, seen by all rows
-            us = fmin(us, fmax(longest, tiles) * (alike * kTileTriangle + (1 - alike) * (kPairTile + kPairTileFull * n)) + kPairItem);
-        } else if (longest > tiles) {
-            us = fmax(us, fmax(n - 1, 0) * item + longest / S * kTile + kItem);
+            return longest * (alike * kTileTriangle + (1 - alike) * (kPairTile + kPairTileFull * rounds)) + kPairItem;
+        }
+        auto item_of = [&](double t) { return seen * t / S * kTile + kItem; };
+        auto rounds_us = [&](double n, double t) { return triangle ? fmax(t / S * kTile + kItem, (n + 0.3) * item_of(t)) : ceil(n) * item_of(t); };
+        double us = rounds_us(rounds * S, tiles);
+        if (longest > tiles) {
+            us = fmax(us, fmax(rounds * S - 1, 0) * item_of(tiles) + longest / S * kTile + kItem);
+            if (triangle) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kBM) / kCus * S, longest));
         }
         return us + merge_us(S);
     };
     auto short_us = [&](int32_t S, double longest) {
-        const double n = blocks * S / kCus, item = kShortItem + step * ceil(2 * tiles / S / kShortWaves);
-        double us = !triangle ? ceil(n) * item : n <= 1 ? item : fmax(item, (n + 0.3) * (kShortItem + (0.5 + 0.5 * seen) * (item - kShortItem))), swept = blocks / Hkv / batch * seen * kv_bytes;
+        auto item_of = [&](double t) { return kShortItem + step * ceil(2 * t / S / kShortWaves); };
+        auto rounds_us = [&](double n, double t) {
+            const double item = item_of(t);
+            return !triangle ? ceil(n) * item : n <= 1 ? item : fmax(item, (n + 0.3) * (kShortItem + (0.5 + 0.5 * seen) * (item - kShortItem)));
+        };
+        double us = rounds_us(blocks * S / kCus, tiles), swept = blocks / Hkv / batch * seen * kv_bytes;
         if (longest > tiles) {
-            us = fmax(us, fmax(n - 1, 0) * item + kShortItem + step * ceil(2 * longest / S / kShortWaves));
-            swept = fmax(swept, blocks / batch * longest * kBN * (4 * kHeadDim));
+            us = fmax(us, fmax(blocks * S / kCus - 1, 0) * item_of(tiles) + item_of(longest));
+            const double their_rows = triangle ? rows_of(longest) / kShortRows * seen * Hkv : blocks / batch;
+            swept = fmax(swept, their_rows * longest * kBN * (4 * kHeadDim));
+            if (triangle) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kShortRows) / kCus * S, longest));
         }
         return fmax(us, swept / kShortBytesPerUs) + merge_us(S);
     };
@@ -185,10 +197,11 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
         }
         return plan;
     };
-    const PrefillPlan even = least(tiles);
     const double longest = ceil((double)max_kv / kBN);
-    if (longest <= tiles) return even;
+    if (longest <= tiles) return least(tiles);
     const PrefillPlan uneven = least(longest);
+    if (triangle) return uneven;
+    const PrefillPlan even = least(tiles);
     auto us_of = [&](const PrefillPlan& p) { return p.use_short ? short_us(p.splits, longest) : main_us(p.splits, longest); };
     return us_of(uneven) < kUnevenGain * us_of(even) ? uneven : even;
 }

@@ -68,6 +68,23 @@ def test_the_longest_request_of_a_batch_is_cut(esp, requests, Hq, Hkv, parts):
     assert esp.esp_debug_prefill_plan(*sizes, max(new), even, *heads) == esp.esp_debug_prefill_plan(*sizes, max(new), 0, *heads)
 
 
+# lengths of prompts, heads, the plans that were within 10 % of the best measured (us, best of these; the others)
+UNEVEN_PROMPTS = [([2000] + [32] * 15, 8, 8, {-1}),                                               # 30.3; uncut on the main kernel 34.3
+                  ([4000] + [32] * 7, 4, 4, {-1, 3}),                                             # 44.7; uncut 55.3
+                  ([6000] + [32] * 15, 4, 4, {2, 3, 4}),                                          # 67.9; uncut 75.4, the kernel for few rows 88.0
+                  ([8000] + [64] * 7, 4, 4, {1, 2, 3, 5}),                                        # 89.2; the kernel for few rows 144.1
+                  ([102, 105, 115, 231, 235, 250, 266, 276, 378, 616, 815, 1228], 4, 4, {-1})]    # 23.6; uncut 27.1
+
+
+@pytest.mark.parametrize("prompts,Hq,Hkv,good", UNEVEN_PROMPTS)
+def test_one_long_prompt_beside_short_ones(esp, prompts, Hq, Hkv, good):
+    """A batch takes no less than its longest request does: neither where that is the paired sweep of a call of one round nor where
+    the kernel for few rows has most of its blocks there."""
+    sizes = (sum(prompts), sum(prompts), len(prompts))
+    plan = esp.esp_debug_prefill_plan(*sizes, max(prompts), max(prompts), Hq, Hkv, workspace_bytes=esp.esp_prefill_workspace_bytes(*sizes, Hq, Hkv, 128))
+    assert plan in good
+
+
 def test_a_batch_never_runs_in_more_parts_than_its_workspace_holds(esp):
     rng = random.Random(7)
     size = lambda top: int(math.exp(rng.uniform(0, math.log(top))))
