@@ -416,14 +416,18 @@ esp_status esp_fit_prefill_model(
  *     restores the default).  The workspace sizes asked for on this thread follow.
  *     For tests that are about one of the kernels.
  * and, changing nothing,
- *   esp_debug_prefill_plan: what a call of these sizes with such a workspace would run
- *     on now, in the same form (0: the sizes are not valid).  Host code.
+ *   esp_debug_prefill_plan_for: what a call of these sizes, with or without a causal
+ *     mask, that keeps rows in the pool or not, with such a workspace would run on now,
+ *     in the same form (0: the sizes are not valid).  Host code.
+ *   esp_debug_prefill_plan: the same of a causal call that keeps no rows.
  */
 int32_t esp_debug_set_validate(int32_t on);
 int32_t esp_debug_set_prefill_sync_ticks(int32_t ticks);
 int32_t esp_debug_set_prefill_plan(int32_t plan);
 int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv,
                                int32_t Hq, int32_t Hkv, size_t workspace_bytes);
+int32_t esp_debug_prefill_plan_for(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv,
+                                   int32_t Hq, int32_t Hkv, size_t workspace_bytes, int32_t causal, int32_t kept);
 
 /* Message of the last error on the calling thread (static storage, never NULL). */
 const char* esp_last_error(void);

@@ -29,6 +29,7 @@ EXPORTS = (
     "esp_probe_mfma_bf16", "esp_probe_stream_read",
     "esp_partial_attn_prefill_f32", "esp_merge_partials_f32",
     "esp_debug_set_validate", "esp_debug_set_prefill_sync_ticks", "esp_debug_set_prefill_plan", "esp_debug_prefill_plan",
+    "esp_debug_prefill_plan_for",
     "esp_partial_attn_decode_static", "esp_partial_attn_prefill_retain", "esp_plan_prefill_batches_monotone",
     "esp_partial_attn_decode_merge", "esp_partial_attn_prefill_pool_direct",
 )
@@ -62,6 +63,8 @@ def _load() -> ctypes.CDLL:
     L.esp_debug_set_prefill_plan.restype = i32
     L.esp_debug_prefill_plan.argtypes = [i32] * 7 + [sz]
     L.esp_debug_prefill_plan.restype = i32
+    L.esp_debug_prefill_plan_for.argtypes = [i32] * 7 + [sz, i32, i32]
+    L.esp_debug_prefill_plan_for.restype = i32
     L.esp_partial_attn_prefill_retain.argtypes = [vp] * 7 + [i32] * 8 + [f32, i32, vp, vp, vp, i64, i32, vp, vp, vp, sz, vp]
     L.esp_partial_attn_prefill_retain.restype = i32
     L.esp_prefill_workspace_bytes.argtypes = [i32] * 6
@@ -203,9 +206,10 @@ def esp_debug_set_prefill_plan(plan: int) -> int:
     return int(lib.esp_debug_set_prefill_plan(int(plan)))
 
 
-def esp_debug_prefill_plan(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes=1 << 62) -> int:
-    """What a prefill call of these sizes runs on: n parts on the main kernel, -n on the one for few rows."""
-    return int(lib.esp_debug_prefill_plan(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes))
+def esp_debug_prefill_plan(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes=1 << 62, causal=True, kept=False) -> int:
+    """What a prefill call of these sizes (that keeps rows in the pool: `kept`) runs on: n parts on the main kernel, -n on the one for
+    few rows."""
+    return int(lib.esp_debug_prefill_plan_for(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes, int(bool(causal)), int(bool(kept))))
 
 
 def esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) -> int:

@@ -90,8 +90,12 @@ int32_t esp_debug_set_prefill_plan(int32_t plan) {
 }
 int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv,
                                size_t workspace_bytes) {
+    return esp_debug_prefill_plan_for(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes, 1, 0);
+}
+int32_t esp_debug_prefill_plan_for(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv,
+                                   size_t workspace_bytes, int32_t causal, int32_t kept) {
     if (Tq < 0 || Tkv < 0 || batch < 1 || max_q < 0 || max_q > Tq || max_kv < 0 || max_kv > Tkv || !heads_ok(Hq, Hkv)) return 0;
-    return query_prefill_plan(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv);
+    return query_prefill_plan(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, causal != 0, kept != 0);
 }
 const char* esp_version(void) { return "esp 0.1 gfx950"; }
 

@@ -143,7 +143,7 @@ int32_t set_prefill_sync_ticks(int32_t ticks);   // returns the previous value; 
 // estimate.  Returns the previous value.
 int32_t set_prefill_plan(int32_t plan);
 // what a call of these sizes would run on (the same form; never 0)
-int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv);
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool causal, bool kept);
 esp_status launch_decode_static(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx,
                                 const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                                 int32_t Hkv, float softmax_scale, void* O, float* LSE, hipStream_t stream);

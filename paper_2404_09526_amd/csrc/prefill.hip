@@ -100,30 +100,43 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // Main kernel: an item costs a set-up and an epilogue (8.5) beside its tiles (1.45 each; 0.8 where only one wavefront has rows,
 // as the others then only move tiles), the merge a launch (4) and its traffic.  Items of a chunk at the end of a long context are
 // alike, so rounds count whole; where the chunk is most of the shard the sweeps are a triangle, which the item pool evens out.
-// In a triangle a tile costs less, but for an owner of kept rows (1.05: a wavefront past its last one leaves the matrix pipe to the other), and where the items are one
-// round and uncut, halves of query tiles are paired (PAIRED at the kernel): 12 beside 0.5 .. 0.9 a tile of the longest sweep,
-// the more the more CUs are at it.
-// Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each, 1.3 in a triangle, while K and V come from the caches, 2.5 once they are more
-// than the 256 MB that the last of those holds; on average 0.75 of the last row block's in a triangle), but no faster than its row blocks can be fed from the L2 (12.5 TB/s).  Several row
-// blocks of a head share its K and V only on one XCD, i.e. where heads times parts is a multiple of 8 (51 tokens on 29013 rows,
-// 12 / 12 heads: 43 us in 8 parts, 40 in 10, 62 in 9).
+// In a triangle a tile costs less, but for an owner of kept rows (1.05: a wavefront past its last one leaves the matrix pipe to the
+// other), and where the items are one round and uncut, halves of query tiles are paired (PAIRED at the kernel): 12 beside
+// 0.5 .. 0.9 a tile of the longest sweep, the more the more CUs are at it.
+// Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each, 1.3 in a triangle, while K and V come from the caches, 2.5 once they are
+// more than the 256 MB that the last of those holds; on average 0.75 of the last row block's in a triangle), but no faster than its
+// row blocks can be fed from the L2 (12.5 TB/s).  Several row blocks of a head share its K and V only on one XCD, i.e. where heads times
+// parts is a multiple of 8 (51 tokens on 29013 rows, 12 / 12 heads: 43 us in 8 parts, 40 in 10, 62 in 9).
 // Measured (main kernel, best cut -> this): 27 tokens on 27, 32 / 8 heads, 10.5 -> 5.9 us, 256 on 512, 4 / 4, 17.9 -> 10.0,
 // 1024 on 1024, 8 / 8, 26.1 -> 14.8, 16 on 2016, 32 / 8, 19.6 -> 13.5, 100 on 3100, 8 / 8, 23.0 -> 15.8, 31 on 70195, 4 / 4, 62.3
 // -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
 // 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
-// With the terms of the triangle, over 32 shapes of 512 .. 14000 tokens, 4 / 4 .. 40 / 8 heads, the choice is 0.7 % from the best of up to seven on
-// average, 11 % at most (without them 6 %, 37 %): 512 on 512, 32 / 8, 14.1 (main kernel 17.7), 5000 on 5000, 4 / 4, 47.0 in four parts (uncut 64.5),
-// 6000 on 6000, 8 / 8, 83.5 uncut (two parts 88.6); kept: 700 on 700, 32 / 8, 25.0 (main kernel 28.6), two of 2000, 16 / 16, 113 in two parts (uncut 117).
+// Triangle or not: a chunk that is a good part of its shard (two fifths) may be the shard's own tokens, or a stripe of them, and see a
+// triangle of it; or lie behind it (every shard but the last of a contiguous sequence), or have no mask, and see all, where
+// nothing is paired away and items are as long as each other.  Without a mask the estimate is the latter's.  With one the sizes do not
+// say; the plan is the one that is least far from the best in the worse of the two, which costs the triangle up to a tenth (7370 on 7370,
+// 4 / 4 heads: 83 us in two parts, 75 in three; behind the shard 109 and 139).  Where rows are kept it is the triangle's: over 32 such
+// shapes that is 0.2 % from the best in a triangle and 2.6 % behind the shard, the other 2.3 % and 1.1 %.
+// Over 136 shapes of 126 .. 10000 tokens on 205 .. 10000 rows, 4 / 4 .. 64 / 8 heads, with up to thirteen plans each, the choice is 0.5 % from the
+// best on average in a triangle, 0.2 % behind the shard and 0.3 % without a mask (11 % at most; by the triangle's terms alone, whatever
+// the call, 0.6, 2.1 and 2.1 %, up to 39 %): 2427 on 3640, 4 / 4, behind it 37.0 in five parts (the short kernel 51.1), 510 on 1275, 32 / 8,
+// 25.6 (uncut on the main kernel 31.9), 2427 on 2427, 8 / 8, 40.6 in three parts (uncut 49.6); 512 on 512, 32 / 8, 14.1 (main kernel 17.7).
+// Kept: 700 on 700, 32 / 8, 25.0 (main kernel 28.6), two of 2000, 16 / 16, 113 in two parts (uncut 117).
 // Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
 // Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
 // last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
-// which rows the longest request has is not known (in a triangle it is, as good as: there the choice follows the longest).  Over 265 batches that it would cut differently, most of them random (time against
+// which rows the longest request has is not known.  Over 265 batches that it would cut differently, most of them random (time against
 // the even cut's): any gain promised 0.77 on average, 15 of them 3 .. 21 % slower; a fifth 0.78 and 8; three tenths 0.83 and 1.
 // Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 64.6 -> 32.1 us, 8 on 200000
 // beside 63 of 8 on 512 2222 -> 479, 300 on 20300 beside three of 300 on 600 330 -> 169; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
-// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).  In a triangle, by the average -> by the longest: 2000 tokens
-// beside fifteen of 32, 8 / 8, 34.3 -> 30.3; 4000 beside seven of 32, 4 / 4, 55.3 -> 47.7; 6000 beside fifteen of 32, 4 / 4, 75.4 -> 67.9.
+// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
+// Where the chunk is a good part of the shard the rows are as good as known, in proportion to the keys, and the plan follows the longest
+// request without that margin (46 batches of 2 .. 16 prompts: 0.7 % from the best on average, before 2.9 %): 2000 tokens beside
+// fifteen of 32, 8 / 8, 34.4 -> 29.8 us; 4000 beside seven of 32, 4 / 4, 55.0 -> 44.2; 6000 beside fifteen of 32, 4 / 4, 75.1 -> 70.6.
 struct PrefillPlan { int32_t splits, use_short; };
+// What the estimate is told of a call beside its sizes.  `kept`: rows are kept on the way; such items stay side by side (each owns the
+// tiles on its diagonal).
+struct PrefillKind { bool causal, kept; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
 constexpr double kCus = 256;
 // rounds of the main kernel's items, uncut (the lengths of a batch's requests are not known: half a ragged tile each)
@@ -131,79 +144,102 @@ static double prefill_rounds(int32_t Tq, int32_t batch, int32_t Hq, int32_t Hkv)
     const double rows = (double)Tq * (Hq / Hkv);
     return Hkv * (batch == 1 ? ceil(rows / kBM) : rows / kBM + 0.5 * batch) / kCus;
 }
-static bool prefill_paired(double rounds, int32_t S) { return S == 1 && rounds <= 1; }
-// `kept`: rows are kept on the way; such items stay side by side (each owns the tiles on its diagonal).
-static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool kept, int32_t most_splits) {
+// calls whose query tiles are halves in pairs
+static bool prefill_paired(PrefillKind kind, double rounds, int32_t S) { return kind.causal && !kind.kept && S == 1 && rounds <= 1; }
+// the chunk is so much of the shard that a causal mask may hide a triangle of it
+static bool prefill_near(int32_t Tq, int32_t Tkv) { return Tq >= 0.4 * Tkv; }
+static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, PrefillKind kind, int32_t most_splits) {
     constexpr double kTileLeast = 0.7, kTileRows = 0.75, kTileTriangle = 1.05, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
     constexpr double kPairTile = 0.5, kPairTileFull = 0.4, kPairItem = 12;
-    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortTriangle = 1.3, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
+    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortTriangle = 1.3, kShortLater = 0.9, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
     if (Tq <= 0 || Tkv <= 0) return {1, 0};
     if (t_forced_plan != 0) {
         const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
         return {S, t_forced_plan < 0 ? 1 : 0};
     }
+    const bool near = prefill_near(Tq, Tkv);
     const double rows = (double)Tq * (Hq / Hkv), tiles = ceil((double)Tkv / batch / kBN);
-    const double seen = Tq < Tkv ? 1.0 - 0.5 * Tq / Tkv : 0.5;        // of the tiles, on average, with the chunk at the shard's end
+    const double at_end = Tq < Tkv ? 1.0 - 0.5 * Tq / Tkv : 0.5;      // of the tiles, seen on average by a chunk at the shard's end
     const double rounds = prefill_rounds(Tq, batch, Hq, Hkv);
-    const bool triangle = seen <= 0.8;
-    const double kTile = fmin(kTileLeast + kTileRows * fmin(rows / batch / kBM, 1), triangle && !kept ? kTileTriangle : HUGE_VAL);
     const double blocks = Hkv * (batch == 1 ? ceil(rows / kShortRows) : rows / kShortRows + 0.5 * batch);
-    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim), step = kv_bytes > 2e8 ? kShortFar : triangle ? kShortTriangle + (kShortStep - kShortTriangle) * (seen - 0.5) / 0.3 : kShortStep;
-    // `longest`: tiles of the longest request, or of all alike (`tiles`).  In a triangle the requests of a batch are taken to have rows as they
-    // have keys, and a batch takes no less than its longest alone.
+    const double kv_bytes = (double)Tkv * Hkv * (4 * kHeadDim);
+    // `longest`: tiles of the longest request, or of all alike (`tiles`); `triangle`: the chunk is at the end of a shard that it is a good
+    // part of.  There the requests of a batch are taken to have rows as they have keys, and a batch takes no less than its longest alone.
     auto rows_of = [&](double longest) { return rows * fmin(longest * kBN / Tkv, 1); };
     auto merge_us = [&](int32_t S) { return S > 1 ? kMerge + S * rows * Hkv * (2 * 4 * kHeadDim) / kBytesPerUs : 0.0; };
-    auto main_us = [&](int32_t S, double longest) {
-        if (triangle && !kept && prefill_paired(rounds, S)) {
+    auto main_us = [&](int32_t S, double longest, bool triangle) {
+        if (triangle && prefill_paired(kind, rounds, S)) {
             const double alike = Tq < Tkv ? 1 - (double)Tq / Tkv : 0;   // of the tiles, seen by all rows
             return longest * (alike * kTileTriangle + (1 - alike) * (kPairTile + kPairTileFull * rounds)) + kPairItem;
         }
-        auto item_of = [&](double t) { return seen * t / S * kTile + kItem; };
-        auto rounds_us = [&](double n, double t) { return triangle ? fmax(t / S * kTile + kItem, (n + 0.3) * item_of(t)) : ceil(n) * item_of(t); };
+        const double seen = near && !triangle ? 1 : at_end;
+        const double tile = fmin(kTileLeast + kTileRows * fmin(rows / batch / kBM, 1), triangle && !kind.kept ? kTileTriangle : HUGE_VAL);
+        auto item_of = [&](double t) { return seen * t / S * tile + kItem; };
+        auto rounds_us = [&](double n, double t) { return triangle ? fmax(t / S * tile + kItem, (n + 0.3) * item_of(t)) : ceil(n) * item_of(t); };
         double us = rounds_us(rounds * S, tiles);
         if (longest > tiles) {
-            us = fmax(us, fmax(rounds * S - 1, 0) * item_of(tiles) + longest / S * kTile + kItem);
-            if (triangle) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kBM) / kCus * S, longest));
+            us = fmax(us, fmax(rounds * S - 1, 0) * item_of(tiles) + longest / S * tile + kItem);
+            if (near) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kBM) / kCus * S, longest));
         }
         return us + merge_us(S);
     };
-    auto short_us = [&](int32_t S, double longest) {
+    auto short_us = [&](int32_t S, double longest, bool triangle) {
+        const double seen = near && !triangle ? 1 : at_end;
+        const double step = kv_bytes > 2e8 ? kShortFar : triangle ? kShortTriangle + (kShortStep - kShortTriangle) * (seen - 0.5) / 0.3 : kShortStep;
         auto item_of = [&](double t) { return kShortItem + step * ceil(2 * t / S / kShortWaves); };
         auto rounds_us = [&](double n, double t) {
             const double item = item_of(t);
-            return !triangle ? ceil(n) * item : n <= 1 ? item : fmax(item, (n + 0.3) * (kShortItem + (0.5 + 0.5 * seen) * (item - kShortItem)));
+            if (!triangle) return (1 + (near ? kShortLater : 1) * (ceil(n) - 1)) * item;
+            return n <= 1 ? item : fmax(item, (n + 0.3) * (kShortItem + (0.5 + 0.5 * seen) * (item - kShortItem)));
         };
         double us = rounds_us(blocks * S / kCus, tiles), swept = blocks / Hkv / batch * seen * kv_bytes;
         if (longest > tiles) {
             us = fmax(us, fmax(blocks * S / kCus - 1, 0) * item_of(tiles) + item_of(longest));
-            const double their_rows = triangle ? rows_of(longest) / kShortRows * seen * Hkv : blocks / batch;
+            const double their_rows = near ? rows_of(longest) / kShortRows * seen * Hkv : blocks / batch;
             swept = fmax(swept, their_rows * longest * kBN * (4 * kHeadDim));
-            if (triangle) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kShortRows) / kCus * S, longest));
+            if (near) us = fmax(us, rounds_us(Hkv * ceil(rows_of(longest) / kShortRows) / kCus * S, longest));
         }
         return fmax(us, swept / kShortBytesPerUs) + merge_us(S);
     };
+    auto us_of = [&](const PrefillPlan& p, double longest, bool triangle) { return p.use_short ? short_us(p.splits, longest, triangle) : main_us(p.splits, longest, triangle); };
+    // Of a causal call with a near shard the sizes do not say whether its rows see a triangle of it or, lying behind it, all: its plan is the one
+    // whose time, as a multiple of the best plan's, is least in the worse of the two (where rows are kept: in the triangle).
+    const bool may_be[2] = {!(near && kind.causal && kind.kept), near && kind.causal};   // all rows see alike; a triangle
     auto least = [&](double longest) {
-        PrefillPlan plan = {1, 0};
-        double best_us = main_us(1, longest);
-        for (int32_t S = 2; S <= most_splits && longest >= 4 * S; ++S) {
-            const double us = main_us(S, longest);
-            if (us < 0.97 * best_us) { plan = {S, 0}; best_us = us; }
-        }
+        PrefillPlan plans[2 * ESP_MAX_PARTIALS];
+        double us[2][2 * ESP_MAX_PARTIALS], least_us[2] = {HUGE_VAL, HUGE_VAL};
+        int32_t n = 0;
+        auto add = [&](int32_t S, int32_t use_short) {
+            plans[n] = {S, use_short};
+            for (int triangle = 0; triangle < 2; ++triangle) {
+                if (!may_be[triangle]) continue;
+                us[triangle][n] = us_of(plans[n], longest, triangle != 0);
+                least_us[triangle] = fmin(least_us[triangle], us[triangle][n]);
+            }
+            ++n;
+        };
+        for (int32_t S = 1; S <= most_splits && (S == 1 || longest >= 4 * S); ++S) add(S, 0);
         for (int32_t S = 1; S <= most_splits && (S == 1 || 2 * longest >= kShortWaves * S); ++S) {
             if (S > 1 && blocks > Hkv * batch && Hkv * S % 8 != 0) continue;
             if ((rows / kShortRows + batch) * Hkv * S > 4e6) break;  // one workgroup each: what a launch holds
-            const double us = short_us(S, longest);
-            if (us < (plan.use_short ? 0.97 : 1.0) * best_us) { plan = {S, 1}; best_us = us; }
+            add(S, 1);
         }
-        return plan;
+        int32_t best = 0;
+        double best_cost = HUGE_VAL;
+        for (int32_t i = 0; i < n; ++i) {
+            double cost = 0;
+            for (int triangle = 0; triangle < 2; ++triangle)
+                if (may_be[triangle]) cost = fmax(cost, us[triangle][i] / least_us[triangle]);
+            if (cost < (plans[i].use_short == plans[best].use_short ? 0.97 : 1.0) * best_cost) { best = i; best_cost = cost; }
+        }
+        return plans[best];
     };
     const double longest = ceil((double)max_kv / kBN);
     if (longest <= tiles) return least(tiles);
     const PrefillPlan uneven = least(longest);
-    if (triangle) return uneven;
+    if (near) return uneven;
     const PrefillPlan even = least(tiles);
-    auto us_of = [&](const PrefillPlan& p) { return p.use_short ? short_us(p.splits, longest) : main_us(p.splits, longest); };
-    return us_of(uneven) < kUnevenGain * us_of(even) ? uneven : even;
+    return us_of(uneven, longest, false) < kUnevenGain * us_of(even, longest, false) ? uneven : even;
 }
 // bytes of the parts' results: O [S][Tq, Hq, 128] fp32, then LSE [S][Tq, Hq], each part on a 256-byte boundary
 static size_t split_o_bytes(int32_t Tq, int32_t Hq) { return (size_t)Tq * Hq * kHeadDim * 4; }
@@ -215,10 +251,14 @@ static size_t split_bytes(int32_t S, int32_t Tq, int32_t Hq) { return S > 1 ? S 
 // (which few rows fit, and cutting helps only those: the merge of 64 MB of parts takes 30 us).
 constexpr size_t kUnevenBytes = 64 << 20;
 static int32_t prefill_most_splits(int32_t Tq, int32_t Tkv, int32_t batch, int32_t Hq, int32_t Hkv) {
-    auto splits = [&](int32_t max_kv) {                              // (kept rows or not: not known either)
-        const int32_t plain = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, false, ESP_MAX_PARTIALS).splits;
-        const int32_t kept = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, true, ESP_MAX_PARTIALS).splits;
-        return plain > kept ? plain : kept;
+    auto splits = [&](int32_t max_kv) {                              // (what kind of call: not known either; without a mask, kept rows change nothing)
+        int32_t S = 1;
+        for (const PrefillKind kind : {PrefillKind{true, false}, PrefillKind{true, true}, PrefillKind{false, false}}) {
+            const int32_t its = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kind, ESP_MAX_PARTIALS).splits;
+            if (its > S) S = its;
+            if (!prefill_near(Tq, Tkv)) break;                      // all kinds alike
+        }
+        return S;
     };
     int32_t most = splits(0);
     if (batch > 1) {
@@ -238,18 +278,18 @@ int32_t set_prefill_plan(int32_t plan) {
     return before;
 }
 // what a call with a workspace of so many bytes runs on
-static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool kept) {
-    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, ESP_MAX_PARTIALS);
+static PrefillPlan prefill_plan_in(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, PrefillKind kind) {
+    PrefillPlan plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kind, ESP_MAX_PARTIALS);
     if (batch > 1 && plan.splits > 1) {                            // (a larger workspace than was asked for changes nothing)
         const int32_t most = prefill_most_splits(Tq, Tkv, batch, Hq, Hkv);
-        if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, most);
+        if (plan.splits > most) plan = prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kind, most);
     }
     int32_t fit = plan.splits;
     while (fit > 1 && workspace_bytes < kPrefillCounterBytes + split_bytes(fit, Tq, Hq)) --fit;
-    return fit == plan.splits ? plan : prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kept, fit);   // a block without room for all parts
+    return fit == plan.splits ? plan : prefill_plan(Tq, Tkv, batch, max_kv, Hq, Hkv, kind, fit);   // a block without room for all parts
 }
-int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv) {
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, false);
+int32_t query_prefill_plan(size_t workspace_bytes, int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, bool causal, bool kept) {
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, PrefillKind{causal, kept});
     return plan.use_short ? -plan.splits : plan.splits;
 }
 
@@ -1391,7 +1431,8 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
     a.q_pos = q_pos; a.kv_pos = kv_pos; a.cu_q = cu_q; a.cu_kv = cu_kv;
     const size_t counters = kPrefillCounterBytes;
-    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, retain_slot != nullptr);
+    const PrefillKind kind = {causal != 0, retain_slot != nullptr};
+    const PrefillPlan plan = prefill_plan_in(workspace_bytes, Tq, Tkv, batch, max_kv, Hq, Hkv, kind);
     const int32_t S = plan.splits;
     a.splits = S;
     if (S > 1) {
@@ -1438,7 +1479,7 @@ esp_status launch_prefill(const void* q, const void* k, const void* v, const int
     // start-of-round waits: one request with at least 512 KV tiles and a query chunk of at most an eighth of them
     // (a chunk against a long prefix: every query tile then sees nearly all of the shard, the items are alike)
     a.group_sync = a.by_head && S == 1 && Tkv >= 512 * kBN && (int64_t)Tkv >= 8 * (int64_t)Tq;
-    const bool paired = a.causal && !retain_slot && prefill_paired(prefill_rounds(Tq, batch, Hq, Hkv), S);
+    const bool paired = prefill_paired(kind, prefill_rounds(Tq, batch, Hq, Hkv), S);
     a.sync_ticks = g_sync_ticks.load(std::memory_order_relaxed);
 #define ESP_PREFILL_LAUNCH(...) hipLaunchKernelGGL((prefill_kernel<__VA_ARGS__>), dim3(grid), dim3(kPfWaves * 64), 0, stream, a)
     const bool one = a.G == 1 && batch == 1 && S == 1;

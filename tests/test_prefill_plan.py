@@ -85,6 +85,41 @@ def test_one_long_prompt_beside_short_ones(esp, prompts, Hq, Hkv, good):
     assert plan in good
 
 
+# tokens, rows, heads, the plans within 10 % of the best measured: with a causal mask, where rows may see a triangle of the shard or, lying
+# behind it, all (within 10 % in either; us, worse of the two, best of these and the triangle's own choice); without a mask
+NEAR = [(4088, 4088, 4, 4, {3, 4}, {3, 4}),                     # 51, 61 on the kernel for few rows
+        (2427, 3640, 4, 4, {5, 6}, {4, 5, 6}),                  # 37, 51 on the kernel for few rows
+        (1715, 2572, 12, 12, {2, 3}, {2, 3}),                   # 44, 54 uncut
+        (2427, 2427, 8, 8, {3}, {2, 3}),                        # 41, 50 uncut
+        (510, 1275, 32, 8, {-1}, {-1}),                         # 26, 32 uncut on the main kernel
+        (472, 472, 40, 8, {1}, {1, -1}),                        # 20, 22 on the kernel for few rows
+        (2048, 2048, 32, 8, {1}, {1}), (1000, 1000, 32, 32, {1}, {1}), (4000, 4000, 16, 16, {1}, {1}), (6000, 6000, 8, 8, {1}, {1})]   # pairs
+
+
+@pytest.mark.parametrize("Tq,Tkv,Hq,Hkv,causal,full", NEAR)
+def test_a_chunk_may_lie_behind_its_shard_or_have_no_mask(esp, Tq, Tkv, Hq, Hkv, causal, full):
+    assert esp.esp_debug_prefill_plan(Tq, Tkv, 1, Tq, Tkv, Hq, Hkv) in causal
+    assert esp.esp_debug_prefill_plan(Tq, Tkv, 1, Tq, Tkv, Hq, Hkv, causal=False) in full
+
+
+def test_the_plan_of_a_call_that_keeps_rows_is_told(esp):
+    """Such calls are not paired: 1500 on 1500, 12 / 12 heads, runs on one kernel or the other."""
+    plan = lambda kept: esp.esp_debug_prefill_plan(1500, 1500, 1, 1500, 1500, 12, 12, kept=kept)
+    assert plan(False) == 1 and plan(True) == -1
+
+
+def test_the_workspace_holds_the_parts_of_every_kind_of_call(esp):
+    rng = random.Random(9)
+    for _ in range(1000):
+        Hkv, batch, Tkv = rng.choice((1, 4, 8, 12, 32)), rng.choice((1, 1, 3, 20)), int(math.exp(rng.uniform(0, math.log(60000))))
+        Hq, Tq = Hkv * rng.choice((1, 2, 4, 8)), max(1, int(Tkv * rng.uniform(0.1, 1.2)))
+        room = esp.esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, 128)
+        for causal in (True, False):
+            for kept in (True, False):
+                plan = lambda **kw: esp.esp_debug_prefill_plan(Tq, Tkv, batch, Tq, Tkv, Hq, Hkv, causal=causal, kept=kept, **kw)
+                assert room_for(abs(plan()), Tq, Hq) <= room and plan(workspace_bytes=room) == plan()
+
+
 def test_a_batch_never_runs_in_more_parts_than_its_workspace_holds(esp):
     rng = random.Random(7)
     size = lambda top: int(math.exp(rng.uniform(0, math.log(top))))
