@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
     int32_t r0, t1, req_end;
     if (parts != 0) {
         const RequestRange at = parts > 0 ? request_part(w, parts, range, B, seq_offsets) : request_range(w, range, B, seq_offsets, lane);
-        b = at.b; r0 = at.t0; t1 = req_end = at.t1; w = at.w;
+        b = at.b; r0 = at.t0; t1 = req_end = min(at.t1, total_tokens); w = at.w;   // (never past the slot list)
         if (r0 >= t1) return;
     } else {
         r0 = w * range;

@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
     int32_t t0, t1, req_end, slots;
     if (BY_REQUEST) {
         const RequestRange at = parts > 0 ? request_part(w, parts, range, B, seq_offsets) : request_range(w, range, B, seq_offsets, lane);
-        b = at.b; t0 = at.t0; t1 = req_end = at.t1; w = at.w;
+        b = at.b; t0 = at.t0; t1 = req_end = min(at.t1, total_tokens); w = at.w;   // (never past the slot list)
         if (t0 >= t1) return;
         slots = slot_idx[min(t0 + 32 * wave + qi, t1 - 1)];
     } else {

@@ -575,6 +575,23 @@ def test_decode_slots_past_the_offsets_belong_to_no_request(esp, cuda, Hq, Hkv, 
     assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8)])
+@pytest.mark.parametrize("requests", [1, 3, 130])
+def test_decode_offsets_past_the_slots_read_none(esp, cuda, Hq, Hkv, unit, requests):
+    """Offsets that end three tokens behind the slot list, within its last range: along the list, with as many ranges for each request
+    and found by search, no slot behind the list is read (those that lie there in memory name rows of NaN)."""
+    lens = [5 * unit + 9] if requests == 1 else [unit + 1, 3, 2 * unit + 5] if requests == 3 else [unit // 4] * 129 + [40 * unit + 9]
+    dc = wl.decode_pool(f"decode-long-offsets-{requests} ({Hq}/{Hkv})", lens, 16384, Hq, Hkv, 46, cuda, n_new=3)
+    O, LSE, _, _ = run_decode_case(esp, dc)
+    for pool in (dc.k_pool, dc.v_pool):
+        pool[dc.new_slots.long()] = float("nan")
+    slots, past = torch.cat([dc.slot_idx, dc.new_slots])[:dc.total_tokens], dc.seq_offsets.clone()
+    past[-1] += 3
+    O1, L1 = esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, slots, past, max(lens), softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(O1.view(torch.int16), O.view(torch.int16)) and torch.equal(L1.view(torch.int32), LSE.view(torch.int32))
+
+
 @pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8)])
 @pytest.mark.parametrize("requests", [9, 64, 65, 130])
 def test_decode_ranges_found_by_search(esp, cuda, requests, Hq, Hkv, unit):
