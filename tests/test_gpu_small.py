@@ -334,6 +334,32 @@ def test_prefill_halves_of_tiles_in_pairs(esp, cuda, Hq, Hkv, chunks, first):
     run_pool_direct_case(esp, pc, 35)
 
 
+@pytest.mark.parametrize("Hq,Hkv,chunks", [(256, 256, [257]), (260, 260, [1]), (512, 256, [129, 0, 3]), (64, 64, [1100]), (520, 260, [64, 1, 63]),
+                                           (300, 300, [130, 259])])
+@pytest.mark.usefixtures("main_prefill_kernel")
+def test_prefill_whole_tiles_side_by_side(esp, cuda, Hq, Hkv, chunks):
+    """Causal calls of more than one round keep query tiles whole: ragged tails, tiles of one row, mask boundaries inside a tile, positions
+    in order and not; dense and pool rows; and one request with a query head per KV head, which has an instance of its own, bit for
+    bit as in the general one (with an empty request behind it)."""
+    assert sum(-(-n * (Hq // Hkv) // 256) for n in chunks) * Hkv > 256              # more than a round, as estimated too
+    gen = torch.Generator(device="cpu").manual_seed(38)
+    T = sum(chunks)
+    for shuffled in (False, True):
+        pc = wl.striped_prefill(f"whole-{Hq}/{Hkv}", chunks, 1, 0, Hq, Hkv, 37, cuda)
+        s = pc.shards[0]
+        s.v.mul_(0.25)                                          # few keys: |O| < 2 leaves room for half a unit of bf16 and the rounded probabilities
+        if shuffled:
+            s.kv_pos = s.kv_pos[torch.randperm(T, generator=gen).to(cuda)].contiguous()
+        ws = torch.empty(256, dtype=torch.uint8, device=cuda)
+        (O, LSE), = run_prefill_case(esp, pc, workspace=ws)
+        run_pool_direct_case(esp, pc, 39)
+        if len(chunks) == 1 and Hq == Hkv:
+            two = torch.tensor([0, T, T], dtype=torch.int32, device=cuda)
+            O2, L2 = esp.esp_partial_attn_prefill(pc.q, s.k, s.v, pc.q_pos, s.kv_pos, two, two, T, T, softmax_scale=pc.scale, workspace=ws)
+            torch.cuda.synchronize()
+            assert torch.equal(O2.view(torch.int16), O.view(torch.int16)) and torch.equal(L2.view(torch.int32), LSE.view(torch.int32))
+
+
 @pytest.mark.parametrize("causal", [True, False])
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (6, 2), (40, 8)])
 @pytest.mark.parametrize("Tq,Tkv", [(1, 1), (31, 31), (32, 32), (33, 65), (64, 255), (11, 257), (96, 289), (7, 2100)])
@@ -592,16 +618,19 @@ def test_decode_offsets_past_the_slots_read_none(esp, cuda, Hq, Hkv, unit, reque
     assert torch.equal(O1.view(torch.int16), O.view(torch.int16)) and torch.equal(L1.view(torch.int32), LSE.view(torch.int32))
 
 
-@pytest.mark.parametrize("Hq,Hkv,unit", [(8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8)])
-@pytest.mark.parametrize("requests", [9, 64, 65, 130])
+@pytest.mark.parametrize("requests,Hq,Hkv,unit", [(n, *layout) for n in (9, 64, 65, 130) for layout in ((8, 2, 128), (66, 2, 128), (4, 4, 64), (8, 8, 32), (32, 32, 8))]
+                         + [(9, 32, 8, 256), (33, 32, 8, 256)])
 def test_decode_ranges_found_by_search(esp, cuda, requests, Hq, Hkv, unit):
     """As many ranges as each request has, the whole ones of all requests first: one request far longer than the others, so that room for
-    as many in each would not fit; requests around one range, empty ones at the start, inside and at the end; counts of requests around one
-    and two steps of the search.  The bound on the lengths does not matter here."""
+    as many in each would not fit (by the rule of the launch, asserted here); requests around one range of `unit` tokens (one step of the
+    matrix-core kernel, and two), empty ones at the start, inside and at the end; counts of requests around one and two steps of
+    the search.  The bound on the lengths does not matter here."""
     rng = np.random.default_rng(requests)
     lens = rng.choice([0, 1, unit // 4, unit - 1, unit, unit + 1], requests, p=[0.2, 0.2, 0.45, 0.05, 0.05, 0.05])
-    lens[requests // 2] = 45 * unit + 3 if unit < 128 else 31 * unit + 3
+    lens[requests // 2] = 60 * unit + 3 if unit < 128 else 31 * unit + 3
     lens[0] = lens[-1] = 0
+    rows, ranges = (Hkv * -(-Hq // Hkv // 32) if unit >= 128 else 1), -(-int(lens.sum()) // unit)          # workgroups of a range
+    assert requests * -(-int(lens.max()) // unit) * rows > 512 and (ranges + requests // 2) * rows <= 512
     dc = wl.decode_pool(f"decode-search-{requests} ({Hq}/{Hkv})", lens.tolist(), 16384, Hq, Hkv, 43, cuda, n_new=0)
     O, LSE, _, _ = run_decode_case(esp, dc)
     assert torch.isneginf(LSE[0]).all() and (O[-1] == 0).all()
