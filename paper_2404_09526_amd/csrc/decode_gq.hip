@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
         for (int i = wave; 32 * i < seg; i += kGqWaves) {
             const int rows = min(32, seg - 32 * i);
             // ---- gather
-uint64_t row_at[8];
+            uint64_t row_at[8];
 #pragma unroll
             for (int n = 0; n < 8; ++n) {
                 row_at[n] = (uint64_t)(uint32_t)__shfl(slots, col_row(n, lane)) * row_bytes;

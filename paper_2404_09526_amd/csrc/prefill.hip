@@ -106,11 +106,11 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // Short kernel: 4.5 beside its steps of 8 x 32 keys (1.85 each, 1.3 in a triangle, while K and V come from the caches, 2.5 once they are
 // more than the 256 MB that the last of those holds; on average 0.75 of the last row block's in a triangle), but no faster than its
 // row blocks can be fed from the L2 (12.5 TB/s).  Several row blocks of a head share its K and V only on one XCD, i.e. where heads times
-// parts is a multiple of 8 (51 tokens on 29013 rows, 12 / 12 heads: 43 us in 8 parts, 40 in 10, 62 in 9).
-// Measured (main kernel, best cut -> this): 27 tokens on 27, 32 / 8 heads, 10.5 -> 5.9 us, 256 on 512, 4 / 4, 17.9 -> 10.0,
-// 1024 on 1024, 8 / 8, 26.1 -> 14.8, 16 on 2016, 32 / 8, 19.6 -> 13.5, 100 on 3100, 8 / 8, 23.0 -> 15.8, 31 on 70195, 4 / 4, 62.3
-// -> 50.2; where it ends: 512 on 512, 32 / 8, 20.1 -> 18.7, 200 on 5200, 16 / 16, 32.9 -> 30.3, and 600 on 1200, 32 / 8, stays at
-// 32.5 (the short kernel 38.9), eight prompts of 64, 32 / 8, at 12.8 (12.7).
+// parts is a multiple of 8 (51 tokens on 29013 rows, 12 / 12 heads: 54 us in 8 parts, 47 in 10, 63 in 9).
+// Measured (main kernel, best cut -> this, best cut): 27 tokens on 27, 32 / 8 heads, 9.3 -> 5.8 us, 256 on 512, 4 / 4, 17.2 -> 8.1,
+// 1024 on 1024, 8 / 8, 23.2 -> 11.9, 16 on 2016, 32 / 8, 19.5 -> 12.1, 100 on 3100, 8 / 8, 21.4 -> 13.5, 31 on 70195, 4 / 4, 67.3
+// -> 58.1; where it ends: 512 on 512, 32 / 8, 16.9 -> 14.4, 200 on 5200, 16 / 16, 29.8 -> 25.0, and 600 on 1200, 32 / 8, stays at
+// 29.4 (the short kernel 31.9), eight prompts of 64, 32 / 8, at 11.1 (12.5).
 // Triangle or not: a chunk that is a good part of its shard (two fifths) may be the shard's own tokens, or a stripe of them, and see a
 // triangle of it; or lie behind it (every shard but the last of a contiguous sequence), or have no mask, and see all, where
 // nothing is paired away and items are as long as each other.  Without a mask the estimate is the latter's.  With one the sizes do not
@@ -122,14 +122,14 @@ int32_t set_prefill_sync_ticks(int32_t ticks) {
 // the call, 0.6, 2.1 and 2.1 %, up to 39 %): 2427 on 3640, 4 / 4, behind it 37.0 in five parts (the short kernel 51.1), 510 on 1275, 32 / 8,
 // 25.6 (uncut on the main kernel 31.9), 2427 on 2427, 8 / 8, 40.6 in three parts (uncut 49.6); 512 on 512, 32 / 8, 14.1 (main kernel 17.7).
 // Kept: 700 on 700, 32 / 8, 25.0 (main kernel 28.6), two of 2000, 16 / 16, 113 in two parts (uncut 117).
-// Cut on the main kernel: 300 tokens on 20300 rows of the pool, 32 / 8 heads, 368 -> 104 us; 1488 on 101488, 32 / 32, 2.15 -> 2.00 ms.
+// Cut on the main kernel: 300 tokens on 20300 rows, 32 / 8 heads, 326 -> 99 us (of the pool 368 -> 104); 1488 on 101488, 32 / 32, 2.13 -> 1.97 ms.
 // Requests of unequal length: the average says nothing of the longest one's walk, which may start as late as the round before the
 // last ends.  With that in the estimate such a batch is cut differently where it promises a fifth less time; the estimate is rough, as
 // which rows the longest request has is not known.  Over 265 batches that it would cut differently, most of them random (time against
 // the even cut's): any gain promised 0.77 on average, 15 of them 3 .. 21 % slower; a fifth 0.78 and 8; three tenths 0.83 and 1.
-// Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 64.6 -> 32.1 us, 8 on 200000
-// beside 63 of 8 on 512 2222 -> 479, 300 on 20300 beside three of 300 on 600 330 -> 169; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
-// 409 -> 69; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
+// Measured (by the average -> by the longest, 32 / 8 heads): 16 tokens on 8192 rows beside seven of 16 on 512 53.0 -> 28.8 us, 8 on 200000
+// beside 63 of 8 on 512 2205 -> 479, 300 on 20300 beside three of 300 on 600 328 -> 156; 32 on 60000 beside 31 of 32 on 64, 4 / 4,
+// 405 -> 87; left alone: 20 tokens each on 700 .. 10000, 32 / 4, 46.1 (30.9).
 // Where the chunk is a good part of the shard the rows are as good as known, in proportion to the keys, and the plan follows the longest
 // request without that margin (46 batches of 2 .. 16 prompts: 0.7 % from the best on average, before 2.9 %): 2000 tokens beside
 // fifteen of 32, 8 / 8, 34.4 -> 29.8 us; 4000 beside seven of 32, 4 / 4, 55.0 -> 44.2; 6000 beside fifteen of 32, 4 / 4, 75.1 -> 70.6.
@@ -138,7 +138,7 @@ struct PrefillPlan { int32_t splits, use_short; };
 // tiles on its diagonal).
 struct PrefillKind { bool causal, kept; };
 static thread_local int32_t t_forced_plan = 0;                      // this thread's choice instead (set_prefill_plan); 0: none
-constexpr double kCus = 256;
+constexpr double kCus = 256;                                        // of the card that these times are of (a launch fills whatever there is)
 // rounds of the main kernel's items, uncut (the lengths of a batch's requests are not known: half a ragged tile each)
 static double prefill_rounds(int32_t Tq, int32_t batch, int32_t Hq, int32_t Hkv) {
     const double rows = (double)Tq * (Hq / Hkv);
@@ -148,10 +148,12 @@ static double prefill_rounds(int32_t Tq, int32_t batch, int32_t Hq, int32_t Hkv)
 static bool prefill_paired(PrefillKind kind, double rounds, int32_t S) { return kind.causal && !kind.kept && S == 1 && rounds <= 1; }
 // the chunk is so much of the shard that a causal mask may hide a triangle of it
 static bool prefill_near(int32_t Tq, int32_t Tkv) { return Tq >= 0.4 * Tkv; }
-static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, PrefillKind kind, int32_t most_splits) {
+static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_kv, int32_t Hq, int32_t Hkv, PrefillKind kind,
+                                int32_t most_splits) {
     constexpr double kTileLeast = 0.7, kTileRows = 0.75, kTileTriangle = 1.05, kItem = 8.5, kMerge = 4, kBytesPerUs = 4e6;
     constexpr double kPairTile = 0.5, kPairTileFull = 0.4, kPairItem = 12;
-    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortTriangle = 1.3, kShortLater = 0.9, kShortBytesPerUs = 12.5e6, kUnevenGain = 0.8;
+    constexpr double kShortItem = 4.5, kShortStep = 1.85, kShortFar = 2.5, kShortTriangle = 1.3, kShortLater = 0.9, kShortBytesPerUs = 12.5e6;
+    constexpr double kUnevenGain = 0.8;
     if (Tq <= 0 || Tkv <= 0) return {1, 0};
     if (t_forced_plan != 0) {
         const int32_t parts = t_forced_plan < 0 ? -t_forced_plan : t_forced_plan, S = parts <= most_splits ? parts : 1;
@@ -201,9 +203,11 @@ static PrefillPlan prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t 
         }
         return fmax(us, swept / kShortBytesPerUs) + merge_us(S);
     };
-    auto us_of = [&](const PrefillPlan& p, double longest, bool triangle) { return p.use_short ? short_us(p.splits, longest, triangle) : main_us(p.splits, longest, triangle); };
-    // Of a causal call with a near shard the sizes do not say whether its rows see a triangle of it or, lying behind it, all: its plan is the one
-    // whose time, as a multiple of the best plan's, is least in the worse of the two (where rows are kept: in the triangle).
+    auto us_of = [&](const PrefillPlan& p, double longest, bool triangle) {
+        return p.use_short ? short_us(p.splits, longest, triangle) : main_us(p.splits, longest, triangle);
+    };
+    // Of a causal call with a near shard the sizes do not say whether its rows see a triangle of it or, lying behind it, all: its plan
+    // is the one whose time, as a multiple of the best plan's, is least in the worse of the two (where rows are kept: in the triangle).
     const bool may_be[2] = {!(near && kind.causal && kind.kept), near && kind.causal};   // all rows see alike; a triangle
     auto least = [&](double longest) {
         PrefillPlan plans[2 * ESP_MAX_PARTIALS];

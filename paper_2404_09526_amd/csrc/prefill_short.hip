@@ -5,12 +5,13 @@
 // eight wavefronts take the tiles of 32 keys in turn, each alone, with an LDS block of its own and no barrier until the end,
 // and combine their results through LDS (column_tile.h).  A row block re-reads all of its K and V from the L2, eight times as often
 // as there, and a row costs several times as much: the launcher picks by an estimate of both times (prefill.hip).
-// A wavefront's own chain is two round trips before its first product (the request's bounds; everything else) and one for each tile
-// that follows, which starts as soon as the block that it lands in has been read.  Measured (positions, then queries and rows, each
-// tile's rows asked for when the one before is done -> this; kernel alone): 256 on 512, 4 / 4 heads, 9.9 -> 8.3 us, 16 on 2016 rows of the
-// pool, 32 / 8, 9.5 -> 8.3, 64 on 576 11.7 -> 9.9, 64 kept 8.4 -> 7.7, a single tile (27 on 27) 5.7 -> 5.8; calls: 130 on 3130, 32 / 8, 26.8
-// -> 23.5, 200 on 5200, 16 / 16, 28.4 -> 25.7, 17 on 517, 40 / 8, 9.7 -> 8.4, 31 on 70195, 4 / 4, 63.2 -> 59.8.  The next tile's rows in
-// registers while this one is in LDS (64 of them, 228 in all) was slower everywhere, 27 on 27 5.6 -> 6.8, 300 on 20300 280 -> 298 us.
+// A wavefront's own chain is two round trips before its first product (the request's bounds; everything else; with pool rows a third, as
+// their slots have to be there first) and one for each tile that follows, which starts as soon as the block that it lands in has
+// been read.  Measured (positions, then queries and rows, each tile's rows asked for when the one before is done -> this; kernel alone):
+// 256 on 512, 4 / 4 heads, 9.9 -> 8.3 us, 16 on 2016 rows of the pool, 32 / 8, 9.5 -> 8.3, 64 on 576 11.7 -> 9.9, 64 kept 8.4 -> 7.7, a
+// single tile (27 on 27) 5.7 -> 5.8; calls: 130 on 3130, 32 / 8, 26.8 -> 23.5, 200 on 5200, 16 / 16, 28.4 -> 25.7, 17 on 517, 40 / 8, 9.7
+// -> 8.4, 31 on 70195, 4 / 4, 63.2 -> 59.8.  The next tile's rows in registers while this one is in LDS (64 of them, 228 in all) was slower
+// everywhere, 27 on 27 5.6 -> 6.8, 300 on 20300 280 -> 298 us.
 #include <limits.h>
 #include <math.h>
 
