@@ -415,15 +415,23 @@ esp_status esp_fit_prefill_model(
  *     ESP_MAX_PARTIALS (in one where the workspace does not hold them; anything beyond
  *     restores the default).  The workspace sizes asked for on this thread follow.
  *     For tests that are about one of the kernels.
+ *   esp_debug_set_decode_plan: 1 makes every decode call of the CALLING THREAD work in
+ *     ranges of the token list and combine them in a second launch, 2 in one launch, a
+ *     workgroup to a request and key-value head; by default (0, and anything else) that
+ *     too follows from an estimate.  For tests as well.
  * and, changing nothing,
  *   esp_debug_prefill_plan_for: what a call of these sizes, with or without a causal
  *     mask, that keeps rows in the pool or not, with such a workspace would run on now,
  *     in the same form (0: the sizes are not valid).  Host code.
  *   esp_debug_prefill_plan: the same of a causal call that keeps no rows.
+ *   esp_debug_decode_plan: 1 or 2, what a decode call of these sizes would do now (0:
+ *     the sizes are not valid).  Host code.
  */
 int32_t esp_debug_set_validate(int32_t on);
 int32_t esp_debug_set_prefill_sync_ticks(int32_t ticks);
 int32_t esp_debug_set_prefill_plan(int32_t plan);
+int32_t esp_debug_set_decode_plan(int32_t plan);
+int32_t esp_debug_decode_plan(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv);
 int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv,
                                int32_t Hq, int32_t Hkv, size_t workspace_bytes);
 int32_t esp_debug_prefill_plan_for(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv,

@@ -29,7 +29,7 @@ EXPORTS = (
     "esp_probe_mfma_bf16", "esp_probe_stream_read",
     "esp_partial_attn_prefill_f32", "esp_merge_partials_f32",
     "esp_debug_set_validate", "esp_debug_set_prefill_sync_ticks", "esp_debug_set_prefill_plan", "esp_debug_prefill_plan",
-    "esp_debug_prefill_plan_for",
+    "esp_debug_prefill_plan_for", "esp_debug_set_decode_plan", "esp_debug_decode_plan",
     "esp_partial_attn_decode_static", "esp_partial_attn_prefill_retain", "esp_plan_prefill_batches_monotone",
     "esp_partial_attn_decode_merge", "esp_partial_attn_prefill_pool_direct",
 )
@@ -65,6 +65,10 @@ def _load() -> ctypes.CDLL:
     L.esp_debug_prefill_plan.restype = i32
     L.esp_debug_prefill_plan_for.argtypes = [i32] * 7 + [sz, i32, i32]
     L.esp_debug_prefill_plan_for.restype = i32
+    L.esp_debug_set_decode_plan.argtypes = [i32]
+    L.esp_debug_set_decode_plan.restype = i32
+    L.esp_debug_decode_plan.argtypes = [i32] * 5
+    L.esp_debug_decode_plan.restype = i32
     L.esp_partial_attn_prefill_retain.argtypes = [vp] * 7 + [i32] * 8 + [f32, i32, vp, vp, vp, i64, i32, vp, vp, vp, sz, vp]
     L.esp_partial_attn_prefill_retain.restype = i32
     L.esp_prefill_workspace_bytes.argtypes = [i32] * 6
@@ -210,6 +214,16 @@ def esp_debug_prefill_plan(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_byt
     """What a prefill call of these sizes (that keeps rows in the pool: `kept`) runs on: n parts on the main kernel, -n on the one for
     few rows."""
     return int(lib.esp_debug_prefill_plan_for(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes, int(bool(causal)), int(bool(kept))))
+
+
+def esp_debug_set_decode_plan(plan: int) -> int:
+    """Decode calls of this thread: 1 in ranges and a combination, 2 in one launch, 0 by estimate; returns the previous setting."""
+    return int(lib.esp_debug_set_decode_plan(int(plan)))
+
+
+def esp_debug_decode_plan(B, total_tokens, max_len, Hq, Hkv) -> int:
+    """What a decode call of these sizes does: 1 in ranges and a combination, 2 in one launch."""
+    return int(lib.esp_debug_decode_plan(B, total_tokens, max_len, Hq, Hkv))
 
 
 def esp_prefill_workspace_bytes(Tq, Tkv, batch, Hq, Hkv, D) -> int:

@@ -12,10 +12,13 @@
 //     unique because both indices only grow along the token list;
 //   * dot products on the vector ALU with a 16-lane butterfly per head, online softmax in
 //     the exp2 domain per batch of tokens, fp32 accumulation;
-//   * a second kernel combines the partials of each (request, head) and writes O, LSE.
+//   * a second kernel combines the partials of each (request, head) and writes O, LSE;
+//   * short requests go without ranges and combination (decode_whole below, decode_whole.hip).
+#include <math.h>
+
 #include <mutex>
 
-#include "esp_common.h"
+#include "decode_merge.h"
 
 namespace esp {
 
@@ -134,6 +137,38 @@ static int32_t decode_parts(const DecodeGeom& g, int32_t B, int32_t max_len, int
     return (g.nwg + (int64_t)B / 2) * rows <= 512 && steps <= 12 ? -1 : 0;
 }
 
+// Short requests, each by one workgroup and KV head (decode_whole.hip), where all of them are on the chip at once, one to a CU, and an
+// estimate of the step's time, its append included, in us, says so.  In one launch: a start and an end (7.6 on the matrix cores, 8.2 on the
+// vector ALU), the longest request's walk, which the others' traffic slows down, or the traffic where that takes longer.  In ranges: 11.2, or
+// 14 with two query heads per KV head, for the ranges' starts and the launch more, and the traffic.
+// Measured (in ranges -> in one launch, requests of equal length): one of 200, 4 / 4 heads, 11.9 -> 8.8 us, 12 of 400 12.7 -> 10.5, 50 of
+// 1000 24.6 -> 22.2, 12 of 1000 13.9 -> 16.7 (stays in ranges); four of 400, 32 / 32, 13.4 -> 11.5; 20 of 200, 8 / 4, 15.2 -> 9.4, eight of 1000,
+// 64 / 32, 39.0 -> 27.1; three of 200, 32 / 8, 11.3 -> 9.1, of 700 11.8 -> 12.9 (ranges), 30 of 400 18.0 -> 14.3, of 1000 29.2 -> 24.8; 250 of 520,
+// 32 / 1, 28.0 -> 16.2.  Unequal ones: four of 224 .. 485, 4 / 4, three peers 12.2 -> 9.5, 34 of 30, 8 / 4, 15.5 -> 10.8; 16 of 106 .. 3077, 32 / 8,
+// stay in ranges (the longest would walk for 23).  With more than 256 workgroups the second round's longest request decides: 10 of 186, 32 / 32,
+// 15.1 -> 16.2, 16 of 57, 64 / 32, 17.4 -> 24.1, though equal lengths gain (16 of 400, 32 / 32, 27.7 -> 23.0).
+static thread_local int32_t t_forced_decode = 0;                    // this thread's choice instead (set_decode_plan); 0: none
+static bool decode_whole(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv) {
+    const int G = Hq / Hkv;
+    const int64_t chunks = (G + 31) / 32;
+    if (B > 0 && t_forced_decode != 0) return t_forced_decode == 2;
+    if (total_tokens <= 0 || B * (int64_t)Hkv * chunks > 256) return false;
+    const bool burst = decode_burst_layout(Hq, Hkv);
+    const double bytes = (double)total_tokens * Hkv * chunks * (4 * kHeadDim), traffic = bytes / 7e6;
+    const double step = !burst ? 1 : G == 1 ? 256 : 128, walk = ceil(max_len / step) * step * (!burst ? 0.0075 : G == 1 ? 0.0045 : 0.0073);
+    const double whole = (burst ? 8.2 : 7.6) + fmax(walk + (burst ? 0.7 : 0.4) * traffic, 1.06 * traffic);
+    const double ranges = !burst ? fmax(11.2, 9.6 + bytes / 6.3e6) : G == 1 ? 11.2 + bytes / 6.8e6 : 14 + bytes / 5.5e6;
+    return whole < 0.97 * ranges;
+}
+int32_t set_decode_plan(int32_t plan) {
+    const int32_t before = t_forced_decode;
+    t_forced_decode = plan;
+    return before;
+}
+int32_t query_decode_plan(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv) {
+    return decode_whole(B, total_tokens, max_len, Hq, Hkv) ? 2 : 1;
+}
+
 static int64_t partial_bytes(int32_t Hq) { return (int64_t)Hq * (kHeadDim + 2) * (int64_t)sizeof(float); }
 
 static DecodeGeom decode_geom(int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv, size_t bytes) {
@@ -181,20 +216,6 @@ size_t decode_workspace_bytes(int32_t B, int32_t total_tokens, int32_t Hq, int32
     const DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, ESP_DECODE_STATIC_SCRATCH_BYTES);
     const size_t want = decode_slots(g, B) * (size_t)partial_bytes(Hq) + 256, least = decode_least_workspace_bytes(B, total_tokens, Hq, Hkv);
     return want > least ? want : least;
-}
-
-__device__ __forceinline__ float row16_sum(float x) {
-    // all-reduce over the 16 lanes of a DPP row by rotations (8, 4, 2, 1)
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x128, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x124, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x122, 0xf, 0xf, false));
-    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x121, 0xf, 0xf, false));
-    return x;
-}
-
-__device__ __forceinline__ void unpack8(const uint4& w, float (&f)[8]) {
-    f[0] = bf16_lo(w.x); f[1] = bf16_hi(w.x); f[2] = bf16_lo(w.y); f[3] = bf16_hi(w.y);
-    f[4] = bf16_lo(w.z); f[5] = bf16_hi(w.z); f[6] = bf16_lo(w.w); f[7] = bf16_hi(w.w);
 }
 
 // Bound by HBM.  A step is a chain: slots, rows (8 KiB a wavefront), products.  The chains of two steps overlap: rows are
@@ -406,18 +427,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
 // PEERS: the master of a multi-master decode (Sec. 4.2) also holds the partial results its peers returned for the
 // same queries (bf16 O, natural-log LSE).  They enter the same log-sum-exp combination here, shared out among the groups
 // like the partials, so the local result is never rounded to bf16 on its own and no separate merge launch follows.
-//
-// A partial whose every score is NaN has the maximum -inf (maxima pass NaN over) and the sum NaN.  It must not be taken for
-// an empty one: only a sum of exactly 0 is, and where no maximum is finite the exponentials are taken against 0.
-//
-// A peer may mark "no token" with a large negative number instead of -inf and leave its O unwritten, so an output whose weight
-// is 0 is left out rather than multiplied.  In a group that holds peers only (not `own`) that goes for the group's whole sum: it may be
-// such a peer's, taken at weight 1 before anything larger was seen.  (Not for this instance's own partials: those are written
-// whenever their sum is not 0, and a NaN in them has to show.)
 constexpr int kCombineShort = 32;
-struct U32x2 { uint32_t x, y; };      // O and the peers' O: the calls ask for 4-byte alignment, not for 8
-__device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY ? 0.f : m; }
-template <int V> struct IC { static constexpr int value = V; };
 template <int GROUPS, bool PEERS>
 __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __restrict__ seq_offsets,
                                                              int32_t range, int32_t parts, int32_t Hq, int32_t pairs,
@@ -431,56 +441,32 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     if (pair >= pairs) return;                                      // (only where a pair is a wavefront: no barrier follows)
     const int b = pair / Hq, h = pair - b * Hq;
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1];
-    float M = -INFINITY, L = 0.f;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    bool own = false;                                               // this group holds partials of this instance
-    // adds U partials (m: base-2 maximum, l: sum, 0 = nothing; v: l-weighted output)
-    auto add = [&](auto peer_c, const float (&m)[U], const float (&l)[U], const float4 (&v)[U]) {
-        constexpr bool PEER = decltype(peer_c)::value != 0;
-        float mx = M;
-#pragma unroll
-        for (int u = 0; u < U; ++u) mx = fmaxf(mx, l[u] != 0.f ? m[u] : -INFINITY);
-        const float ref = finite_offset(mx);
-        const float c_old = __builtin_amdgcn_exp2f(M - ref);
-        M = mx;
-        L *= c_old;
-        const bool drop = PEER && !own && c_old == 0.f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] = drop ? 0.f : acc[e] * c_old;
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (l[u] != 0.f) {                                      // keeps the garbage of an empty partial out of the sum
-                const float c = __builtin_amdgcn_exp2f(m[u] - ref);
-                L += l[u] * c;
-                if (PEER && c == 0.f) continue;
-                acc[0] += v[u].x * c; acc[1] += v[u].y * c; acc[2] += v[u].z * c; acc[3] += v[u].w * c;
-            }
-        }
-    };
+    Weighted<4> sum;
     if (s1 > s0) {
         const int w_lo = s0 / range;
         const int64_t first = w_lo + b;                             // the slots of consecutive ranges
         const int whole = (s1 - s0 + range - 1) / range, n = parts == 0 ? (s1 - 1) / range - w_lo + 1 : parts > 0 ? min(parts, whole) : whole;
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
-            float4 v[U];
+            float v[U][4];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int k = i + u * GROUPS;
                 const int64_t ph = (first + min(k, n - 1)) * Hq + h;
                 const float2 ml = *(const float2*)(part_ml + ph * 2);
-                v[u] = load_once((const float4*)(part_acc + ph * kHeadDim + lane * 4));
+                const float4 x = load_once((const float4*)(part_acc + ph * kHeadDim + lane * 4));
+                v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
                 m[u] = ml.x;
                 l[u] = k < n ? ml.y : 0.f;
             }
-            add(IC<0>{}, m, l, v);
+            sum.template add<false>(m, l, v);
         }
     }
     if (PEERS) {
-        own = L != 0.f;
+        sum.own = sum.L != 0.f;
         for (int p0 = g; p0 < n_peers; p0 += GROUPS * U) {
             float m[U], l[U];
-            float4 v[U];
+            float v[U][4];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int p = p0 + u * GROUPS, q = min(p, n_peers - 1);
@@ -488,11 +474,14 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
                 const U32x2 o = ((const U32x2*)peers.O_parts[q])[(int64_t)pair * (kHeadDim / 4) + lane];
                 m[u] = lse * kLog2e;
                 l[u] = p < n_peers && lse != -INFINITY ? 1.f : 0.f;  // a peer's rows are normalised
-                v[u] = make_float4(bf16_lo(o.x), bf16_hi(o.x), bf16_lo(o.y), bf16_hi(o.y));
+                v[u][0] = bf16_lo(o.x); v[u][1] = bf16_hi(o.x); v[u][2] = bf16_lo(o.y); v[u][3] = bf16_hi(o.y);
             }
-            add(IC<1>{}, m, l, v);
+            sum.template add<true>(m, l, v);
         }
     }
+    const float M = sum.M, L = sum.L;
+    const float (&acc)[4] = sum.acc;
+    const bool own = sum.own;
     // ---- the groups' results: exchanged by shuffles within a wavefront, through LDS otherwise
     float mx, Lt = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
     if (GROUPS == 2) {
@@ -551,6 +540,9 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
                          const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq,
                          int32_t Hkv, float softmax_scale, void* O, float* LSE, void* workspace, size_t workspace_bytes,
                          hipStream_t stream, const MergeArgs* peers, int32_t n_peers) {
+    if (decode_whole(B, total_tokens, max_len, Hq, Hkv))
+        return launch_decode_whole(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, decode_burst_layout(Hq, Hkv),
+                                   softmax_scale * kLog2e, O, LSE, peers, n_peers, stream);
     DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, workspace_bytes);
     const int32_t parts = decode_parts(g, B, max_len, Hq, Hkv);
     size_t n = decode_slots(g, B) * (size_t)Hq;

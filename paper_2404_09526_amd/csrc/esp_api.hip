@@ -88,6 +88,11 @@ int32_t esp_debug_set_prefill_sync_ticks(int32_t ticks) { return set_prefill_syn
 int32_t esp_debug_set_prefill_plan(int32_t plan) {
     return set_prefill_plan(plan < -ESP_MAX_PARTIALS || plan > ESP_MAX_PARTIALS ? 0 : plan);
 }
+int32_t esp_debug_set_decode_plan(int32_t plan) { return set_decode_plan(plan == 1 || plan == 2 ? plan : 0); }
+int32_t esp_debug_decode_plan(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv) {
+    if (B < 0 || total_tokens < 0 || max_len < 0 || !heads_ok(Hq, Hkv)) return 0;
+    return query_decode_plan(B, total_tokens, max_len, Hq, Hkv);
+}
 int32_t esp_debug_prefill_plan(int32_t Tq, int32_t Tkv, int32_t batch, int32_t max_q, int32_t max_kv, int32_t Hq, int32_t Hkv,
                                size_t workspace_bytes) {
     return esp_debug_prefill_plan_for(Tq, Tkv, batch, max_q, max_kv, Hq, Hkv, workspace_bytes, 1, 0);

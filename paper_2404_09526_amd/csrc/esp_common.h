@@ -138,6 +138,16 @@ esp_status launch_decode_gq(const void* q, const void* k_pool, const void* v_poo
                             const int32_t* seq_offsets, int32_t B, int32_t total_tokens, int32_t range, int32_t parts, int32_t nwg,
                             int32_t Hq, int32_t Hkv, float scale_log2, float* part_acc, float* part_ml, hipStream_t stream);
 
+// short requests in one launch (decode_whole.hip); `burst`: the layouts that decode.hip has on the vector ALU
+esp_status launch_decode_whole(const void* q, const void* k_pool, const void* v_pool, const int32_t* slot_idx, const int32_t* seq_offsets,
+                               int32_t B, int32_t total_tokens, int32_t Hq, int32_t Hkv, bool burst, float scale_log2, void* O, float* LSE,
+                               const MergeArgs* peers, int32_t n_peers, hipStream_t stream);
+
+// whether decode calls of this thread work in ranges (1), in one launch (2), or by estimate (0); returns the previous value; and what a
+// call of these sizes would do
+int32_t set_decode_plan(int32_t plan);
+int32_t query_decode_plan(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv);
+
 int32_t set_prefill_sync_ticks(int32_t ticks);   // returns the previous value; negative restores the built-in default
 // which kernel prefill calls of this thread run on, in how many parts: n: the main one in n, -n: the one for few rows in n, 0: by
 // estimate.  Returns the previous value.

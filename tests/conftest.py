@@ -43,3 +43,19 @@ def each_prefill_cut(request, cuda):
 @pytest.fixture
 def main_prefill_kernel(cuda):
     yield from on_plan(1)
+
+
+# The same of decode: in ranges and a combination (1), or in one launch (2).  What the decode tests claim, they claim of both.
+@pytest.fixture
+def decode_plan(request, cuda):
+    from paper_2404_09526_amd import binding
+    before = binding.esp_debug_set_decode_plan(request.param)
+    assert binding.esp_debug_decode_plan(4, 4000, 1000, 8, 2) == request.param
+    yield request.param
+    assert binding.esp_debug_set_decode_plan(before) == request.param
+
+
+def pytest_generate_tests(metafunc):
+    if metafunc.module.__name__ in ("test_gpu_small", "test_gpu_nonfinite") and metafunc.definition.name.startswith("test_decode_"):
+        metafunc.fixturenames.append("decode_plan")
+        metafunc.parametrize("decode_plan", [1, 2], ids=["ranges", "one-launch"], indirect=True)

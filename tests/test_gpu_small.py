@@ -528,6 +528,32 @@ def test_decode_any_head_counts(esp, cuda, Hq, Hkv):
     assert torch.isneginf(LSE[[0, 5, 10]]).all() and (O[[0, 5, 10]] == 0).all()
 
 
+@pytest.mark.parametrize("Hq,Hkv,step", [(4, 4, 256), (32, 32, 256), (8, 4, 128), (64, 32, 128), (32, 8, 256), (12, 12, 256), (40, 1, 256)])
+@pytest.mark.parametrize("n_peers", [0, 1, 4, 6])
+def test_decode_one_launch_edges(esp, cuda, Hq, Hkv, step, n_peers):
+    """Requests around what a load, a tile of a wavefront, and one to three steps of a workgroup hold (four or 32 tokens, `step`), empty ones
+    among them; as many peers as are asked for ahead, and more; a length bound that says too little."""
+    lens = [0, 1, 3, 4, 5, 31, 32, 33, 63, 64, 65, step - 1, step, step + 1, 2 * step - 1, 2 * step, 2 * step + 1, 3 * step + 7, 0]
+    dc = wl.decode_pool(f"decode-one-launch ({Hq}/{Hkv})", lens, 8192, Hq, Hkv, 57, cuda, n_new=0, n_peers=n_peers)
+    O, LSE, kp, vp = run_decode_case(esp, dc)
+    assert torch.isneginf(LSE[[0, 18]]).all() and (O[[0, 18]] == 0).all()
+    O1, L1 = esp.esp_partial_attn_decode(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, step, softmax_scale=dc.scale)
+    torch.cuda.synchronize()
+    # other sums in another order, rounded once: a unit of bf16 in O, 2^-8, and fp32 sums in the LSE
+    assert torch.allclose(O1.float(), O.float(), rtol=2.0 ** -7, atol=2e-3) and torch.allclose(L1, LSE, rtol=1e-5, atol=1e-5)
+    if n_peers:
+        dc.peer_LSE[-1][3:] = float("-inf"); dc.peer_O[-1][3:] = float("nan")
+        O, LSE = esp.esp_partial_attn_decode_merge(dc.q, dc.k_pool, dc.v_pool, dc.slot_idx, dc.seq_offsets, max(lens),
+                                                   list(dc.peer_O), list(dc.peer_LSE), softmax_scale=dc.scale)
+        torch.cuda.synchronize()
+        Or, Lr = oracle.partial_attn_decode_all(wl.bits(dc.q), kp, vp, wl.host_i32(dc.slot_idx), wl.host_i32(dc.seq_offsets), dc.scale)
+        Op = np.stack([Or] + [np.nan_to_num(oracle.bf16_bits_to_f64(wl.bits(t)), nan=0.0) for t in dc.peer_O])
+        Lp = np.stack([Lr] + [t.cpu().numpy().astype(np.float64) for t in dc.peer_LSE])
+        Oref, Lref = oracle.merge_partials(Op, Lp)
+        check_o_lse(O.float().cpu().numpy().reshape(-1, dc.D), LSE.cpu().numpy().reshape(-1), Oref.reshape(-1, dc.D), Lref.reshape(-1),
+                    f"{dc.name} + {n_peers} peers")
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2, 3, 4, 5, 6, 7])
 def test_decode_randomized_layouts(esp, cuda, seed):
     """Drawn from a seeded generator: head layout (both kernels), number of requests, and a length mix with many
