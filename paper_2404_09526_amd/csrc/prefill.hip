@@ -505,23 +505,18 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // row kv_lo, head kvh (POOL: slot 0, head kvh)
     const char* kreq = (const char*)a.k + ((int64_t)(POOL ? 0 : kv_lo) * a.Hkv + kvh) * (kHeadDim * 2);
     const char* vreq = (const char*)a.v + ((int64_t)(POOL ? 0 : kv_lo) * a.Hkv + kvh) * (kHeadDim * 2);
-    // POOL: per transfer of this lane, the tile row its 16 bytes belong to (times 4: byte offset into a ring stage,
-    // low byte) and where in the row's 256 bytes they sit (from bit 8 up)
-    auto pool_key = [&](int row, int within) { return (uint32_t)((within << 8) | (row << 2)); };
-    auto k_key = [&](int n) {
-        const int B = 1024 * n + 16 * lane, row = B / kKRow, within = B - row * kKRow;
-        return pool_key(min(row, kBN - 1), within < 256 ? within : 0);
-    };
-    const uint32_t pk0 = POOL ? k_key(wave) : 0, pk1 = POOL ? k_key(wave + 8) : 0, pk2 = POOL ? k_key(16) : 0;
-    const uint32_t pv0 = POOL ? pool_key(st_r0, (st_p ^ ((st_r0 & 3) << 2)) << 4) : 0;
-    const uint32_t pv1 = POOL ? pool_key(st_r1, (st_p ^ ((st_r1 & 3) << 2)) << 4) : 0;
-    // the row's address: its slot from ring stage st, one 32 x 32 -> 64-bit multiply-add
-    // (POOL: ring stage kStages holds the slots of tile 0)
-    auto pool_slot = [&](int st, uint32_t key) { return *(const int32_t*)(smem + kLdsSlot + st * (kBN * 4) + (key & 0xff)); };
-    auto pool_at = [&](const char* base, int32_t slot, uint32_t key) {
-        return base + ((uint64_t)(uint32_t)slot * kv_row_bytes + (key >> 8));
-    };
-    auto pool_src = [&](const char* base, int st, uint32_t key) { return pool_at(base, pool_slot(st, key), key); };
+    // POOL: K rows are not padded but swizzled, chunk c of row r at c ^ (r % 8), so that a wavefront moves rows 8w .. 8w+7 of K as it does
+    // of V, in transfers 2w and 2w + 1, and one read of the ring (stage kStages: tile 0) has both rows' slots.  From a slot to a row's
+    // address: one 32 x 32 -> 64-bit multiply-add on where this lane's 16 bytes lie in slot 0
+    // The loop is bound by the LDS port (289 KB a tile at 128 bytes a cycle, and the slot reads) and by power; with padded rows it took five
+    // slot reads a wavefront and tile, now two for two rows each.  Padded -> swizzled: a tile 2666 -> 2577 cycles; 300 tokens on 20300 rows of
+    // the pool, 32 / 8 heads, 108.8 -> 105.9 us, 2000 on 2000 51.7 -> 48.7, 8000 on 30000 2733 -> 2680, 2048 on 10240, 32 / 32, 285 -> 279.
+    const ESP_LDS int32_t* const slot_rd = (const ESP_LDS int32_t*)(uintptr_t)(lds_base0 + kLdsSlot + st_r0 * 4);
+    auto pool_slot = [&](int st, int part) { return slot_rd[st * kBN + 4 * part]; };
+    const char* const pk0 = kreq + ((st_p ^ (st_r0 & 7)) << 4);
+    const char* const pk1 = kreq + ((st_p ^ (st_r1 & 7)) << 4);
+    const char* const pv = vreq + ((st_p ^ ((st_r0 & 3) << 2)) << 4);
+    auto pool_at = [&](const char* at, int32_t slot) { return at + (uint64_t)(uint32_t)slot * kv_row_bytes; };
     // slots of tile t into ring stage st (wavefront 6); rows past the end of a ragged last tile repeat the last row's
     // slot, so their transfers re-read that row (their scores get masked)
     const int32_t* slot_req = POOL ? a.kv_slot + kv_lo : nullptr;
@@ -538,7 +533,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int32_t* preq = a.kv_pos + kv_lo;
     const uint32_t lds_base = lds_base0;
     const uint32_t lds_k0 = lds_base + kLdsK, lds_v0 = lds_base + kLdsV;
-    const uint32_t lds_kw = lds_base + wave * 1024, lds_vw = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
+    const uint32_t lds_kw = lds_base + wave * (POOL ? 2048 : 1024), lds_vw = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
 
     // K tile at kt into K stage st: 2 transfers per wavefront, 3 for wavefront 7; `part` picks one of them, so that
     // the sweep can spread them over an iteration (a burst of transfers from all wavefronts at once backs up the
@@ -546,10 +541,10 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // end re-read the last row (their scores get masked).
     auto fetch_k_part = [&](const char* kt, int st, bool tail, int part) {
         const uint32_t base = part == 2 ? lds_base : lds_kw;
-        const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + 8192 * part;
+        const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + (POOL ? 1024 : 8192) * part;
         const int n = part == 0 ? wave : part == 1 ? wave + 8 : 16;
-        if (part == 2 && wave != 7) return;
-        if constexpr (POOL) { load_to_lds_b128_at(base, off, pool_src(kreq, st, part == 0 ? pk0 : part == 1 ? pk1 : pk2)); return; }
+        if (part == 2 && (POOL || wave != 7)) return;
+        if constexpr (POOL) { load_to_lds_b128_at(base, off, pool_at(part == 0 ? pk0 : pk1, pool_slot(st, part))); return; }
         if (__builtin_expect(tail, 0)) load_to_lds_b128(base, off, kt, k_goff(n, tail_rows - 1));
         else load_to_lds_b128(base, off, kt, part == 0 ? gk0 : part == 1 ? gk1 : gk2);
     };
@@ -561,7 +556,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             if (wave != 0) return;
             load_to_lds_b32(lds_base, kLdsPos + st * (kBN * 4), pt, (tail ? min(lane, last) : lane) * 4);
         } else if constexpr (POOL) {
-            load_to_lds_b128_at(lds_vw, off, pool_src(vreq, slot_st < 0 ? st : slot_st, part == 0 ? pv0 : pv1));
+            load_to_lds_b128_at(lds_vw, off, pool_at(pv, pool_slot(slot_st < 0 ? st : slot_st, part)));
         } else if (__builtin_expect(tail, 0)) {
             const int r = part == 0 ? st_r0 : st_r1;
             load_to_lds_b128(lds_vw, off, vt, v_goff(r, min(r, last)));
@@ -800,8 +795,12 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     if (kTileRow * wave >= n_rows) n_need = 0;                           // a wavefront without rows: transfers and barriers only
 
     // ---- operand read offsets
-    // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> one base per lane, the rest are immediates
-    const uint32_t k_rd = lds_k0 + qi * kKRow + hi * 16;
+    // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> one base per lane, the rest are immediates (POOL: four, by the bits of t
+    // that the swizzle changes)
+    constexpr int kKBases = POOL ? 4 : 1, kKRead = POOL ? 256 : kKRow;
+    uint32_t k_rd[kKBases];
+#pragma unroll
+    for (int x = 0; x < kKBases; ++x) k_rd[x] = lds_k0 + qi * kKRead + (POOL ? ((2 * x + hi) ^ (qi & 7)) : hi) * 16;
     // V (A operand of O^T) by transposing reads: 16 lanes fetch a 4 (kv) x 16 (d) patch
     const int j16 = lane & 15, jq = j16 >> 2, dblk = (lane >> 4) & 1;
     uint32_t v_rd[4];
@@ -835,7 +834,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // K fragment i = (t, kvb) = (i / 2, i % 2) of the tile in K stage st; V^T fragment p = (kvb, t2, db) =
     // (p / 8, (p / 4) % 2, p % 4) of the tile at byte offset stage_off of the V stages
     auto read_k = [&](int slot, int st, int i) {
-        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd + st * kKTileBytes + (i & 1) * (32 * kKRow) + (i >> 1) * 32);
+        const int t = i >> 1;
+        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t % kKBases] + st * kKTileBytes + (i & 1) * (32 * kKRead) + t / kKBases * (32 * kKBases));
     };
     auto read_v = [&](int slot, uint32_t stage_off, int p) {
         const uint32_t vp = v_rd[p & 3] + stage_off + (32 * (p >> 3) + 16 * ((p >> 2) & 1)) * 256;
@@ -977,16 +977,15 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (!PLAIN && j >= mask_from) apply_mask(sc, ST);
         const bool do_k = PLAIN || j < n_vis - 4, do_v = PLAIN || j < n_vis - 2;
         const bool tail_k = !PLAIN && j + 4 == ragged_tile, tail_v = !PLAIN && j + 2 == ragged_tile;
+        int32_t pslot0 = 0, pslot1 = 0;
 #pragma unroll
         for (int m = 0; m < 16; ++m) {
             const int t = m >> 1, kvb = m & 1;
-            // POOL: the slot of this step's transfer is read first, ahead of the step's fragment reads: LDS answers in
-            // order, so a read placed next to the transfer would wait for those as well
-            int32_t pslot = 0;
+            // POOL: the slots of this step's transfer and of the operand's other one are read first, ahead of the step's fragment reads:
+            // LDS answers in order, so a read placed next to the transfer would wait for those as well
             if constexpr (POOL) {
-                if (m == 1 && do_k && wave == 7) pslot = pool_slot(ST, pk2);
-                if ((m == 3 || m == 6) && do_k) pslot = pool_slot(ST, m == 3 ? pk0 : pk1);
-                if ((m == 9 || m == 12) && do_v) pslot = pool_slot(ST2, m == 9 ? pv0 : pv1);
+                if (m == 3 && do_k) { pslot0 = pool_slot(ST, 0); pslot1 = pool_slot(ST, 1); }
+                if (m == 9 && do_v) { pslot0 = pool_slot(ST2, 0); pslot1 = pool_slot(ST2, 1); }
             }
             if (t == 0) {                                 // S^T of tile j+1 (after the last tile: stale data, unused)
                 floatx16 zero;
@@ -1016,18 +1015,14 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                     else if (j + 5 < n_vis) fetch_pool_slots(j + 5, ST1);
                 }
                 if (KEEP && !PLAIN && do_k && j >= own_lo) fetch_slots(j + 4);
-                if constexpr (POOL) {
-                    if (do_k && wave == 7) load_to_lds_b128_at(lds_base, kLdsK + ST * kKTileBytes + 1024 * 16, pool_at(kreq, pslot, pk2));
-                } else if (do_k) {
-                    fetch_k_part(k_next, ST, tail_k, 2);
-                }
+                if (do_k) fetch_k_part(k_next, ST, tail_k, 2);
                 if (do_v) fetch_v_part(v_next, p_next, ST2, tail_v, 2);
             }
             if constexpr (POOL) {
                 if (do_k && (m == 3 || m == 6))
-                    load_to_lds_b128_at(lds_kw, kLdsK + ST * kKTileBytes + 8192 * (m / 6), pool_at(kreq, pslot, m == 3 ? pk0 : pk1));
+                    load_to_lds_b128_at(lds_kw, kLdsK + ST * kKTileBytes + 1024 * (m / 6), pool_at(m == 3 ? pk0 : pk1, m == 3 ? pslot0 : pslot1));
                 if (do_v && (m == 9 || m == 12))
-                    load_to_lds_b128_at(lds_vw, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(vreq, pslot, m == 9 ? pv0 : pv1));
+                    load_to_lds_b128_at(lds_vw, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(pv, m == 9 ? pslot0 : pslot1));
             } else {
                 if (do_k && (m == 3 || m == 6)) fetch_k_part(k_next, ST, tail_k, m / 6);
                 if (do_v && (m == 9 || m == 12)) fetch_v_part(v_next, p_next, ST2, tail_v, m / 12);
@@ -1049,9 +1044,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     //      all wavefronts have read their Q rows, V(1) and K(3); first fragments
     auto first_scores = [&]() {
         if (n_need <= 0) return;
-        const uint32_t k_rd0 = k_rd + (uint32_t)(kLdsK0 - kLdsK);
         auto read_k0 = [&](int slot, int i) {
-            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd0 + (i & 1) * (32 * kKRow) + (i >> 1) * 32);
+            const int t = i >> 1;
+            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t % kKBases] + (uint32_t)(kLdsK0 - kLdsK) + (i & 1) * (32 * kKRead) + t / kKBases * (32 * kKBases));
         };
         read_k0(0, 0);
         read_k0(1, 1);
@@ -1075,7 +1070,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     if constexpr (!POOL) first_scores();
     // (POOL: the slots of tile 1 are read ahead of the barrier, since iteration 0 fetches those of tile 5 over them)
     int32_t v1_slot0 = 0, v1_slot1 = 0;
-    if constexpr (POOL) { v1_slot0 = pool_slot(1, pv0); v1_slot1 = pool_slot(1, pv1); }
+    if constexpr (POOL) { v1_slot0 = pool_slot(1, 0); v1_slot1 = pool_slot(1, 1); }
     wait_vm<0>();
     if (ragged_tile == 1) seal_tail(1);
     if (ragged_tile >= 0 && ragged_tile < 2) seal_slots();          // (in every other case before the iteration ahead of its own)
@@ -1083,8 +1078,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // what iterations 1 and 2 need (a sweep that is shorter does not wait for it)
     if (n_vis > 1) {
         if constexpr (POOL) {
-            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes, pool_at(vreq, v1_slot0, pv0));
-            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes + 1024, pool_at(vreq, v1_slot1, pv1));
+            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes, pool_at(pv, v1_slot0));
+            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes + 1024, pool_at(pv, v1_slot1));
         } else {
             fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 0);
             fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 1);
