@@ -16,8 +16,7 @@
 //   * the K tile is the A operand of S^T = K Q^T, so a lane ends up with scores of ONE query
 //     row (its column); P^T stays in registers and is the B operand of O^T = V^T P^T, whose A
 //     operand comes from transposing LDS reads of the row-major V tile;
-//   * LDS rows of K are padded to 272 bytes and the 16-byte chunks of V rows are XOR-swizzled, so
-//     that the operand reads spread over all banks;
+//   * the 16-byte chunks of K and V rows are XOR-swizzled in LDS, so that the operand reads spread over all banks;
 //   * one uniform instruction stream per wavefront, software pipelined at the level of single
 //     MFMAs: every step issues one MFMA of S^T for tile j+1, the exp2 of two scores of tile j,
 //     one MFMA of O^T += V^T P^T that trails the probabilities by one chunk of 16 keys, and the
@@ -51,8 +50,8 @@ constexpr int kBN = 64;    // KV rows per tile
 constexpr int kPfWaves = 8;
 constexpr long long kSyncTicks = 15000;   // longest wait at a round start, in ticks of the 100 MHz wall clock (150 us)
 constexpr int kTileBytes = kBN * kHeadDim * 2;   // 16 KiB: a V tile in LDS, rows of 256 bytes
-constexpr int kKRow = 272;                       // LDS row pitch of a K tile: 256 bytes + 16 of padding
-constexpr int kKTileBytes = kBN * kKRow;         // 17 KiB = 17 transfers of 1 KiB
+constexpr int kORow = 272;                       // LDS row pitch of the results on their way out: 256 bytes + 16 of padding
+constexpr int kKTileBytes = kBN * kORow;         // a stage of K: its tile, and room for the results (see the epilogue)
 
 
 // upper bound of the query tiles of one KV head: Tq * G packed rows, and one ragged tile per request
@@ -485,30 +484,28 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int ragged_tile = tail_rows < kBN ? nkt - 1 : -8;          // index of the ragged last tile, if any
 
     // ---- global -> LDS in transfers of 64 lanes x 16 bytes = 1 KiB of consecutive LDS bytes.
-    //      V tile (rows of 256 B, chunks XOR-swizzled): wavefront w moves rows 8w .. 8w+7 in two transfers; lane L
-    //      writes LDS chunk L % 16 of row r = base + L / 16, so it fetches the global chunk (L % 16) ^ f(r).
-    //      K tile (rows padded to 272 B): transfer n covers LDS bytes [1024 n, 1024 n + 1024) of the padded tile;
-    //      lane L's byte 1024 n + 16 L falls into row B / 272 at B % 272 (a padding slot fetches chunk 0, unused).
-    //      Wavefront w issues K transfers w and w + 8; wavefront 7 also the 17th; wavefront 0 the positions.
+    //      K and V tiles have rows of 256 B, their chunks XOR-swizzled: wavefront w moves rows 8w .. 8w+7 of either in two
+    //      transfers; lane L writes LDS chunk L % 16 of row r = base + L / 16, so it fetches the global chunk
+    //      (L % 16) ^ f(r).  Wavefront 0 also moves the positions.
+    //      (K rows padded to 272 bytes instead: operand reads with one address register for four, but 17 transfers, of which each lane's
+    //      bytes fell into rows of their own, and wavefront 7 had one more.  Padded -> swizzled, 32 / 8 heads: 1000 .. 8192 against two
+    //      shards, kept, 1374 -> 1343 us; 32 / 32: 8192 against four of 8192 1866 -> 1841, merge included, 32768 on 262144 103.8 -> 103.3 ms, 1000 on 1000
+    //      24.8 -> 24.5; pool rows below.)
     const uint32_t kv_row_bytes = (uint32_t)a.Hkv * kHeadDim * 2;
     const int64_t tile_bytes = (int64_t)kBN * kv_row_bytes;
     const int st_sub = lane >> 4, st_p = lane & 15;
     const int st_r0 = wave * 8 + st_sub, st_r1 = st_r0 + 4;
     auto v_goff = [&](int r_lds, int r_glb) { return r_glb * kv_row_bytes + ((st_p ^ ((r_lds & 3) << 2)) << 4); };
-    auto k_goff = [&](int n, int last_row) {
-        const int B = 1024 * n + 16 * lane, row = B / kKRow, within = B - row * kKRow;
-        return (uint32_t)(min(row, last_row) * kv_row_bytes + (within < 256 ? within : 0));
-    };
+    auto k_goff = [&](int r_lds, int r_glb) { return r_glb * kv_row_bytes + ((st_p ^ (r_lds & 7)) << 4); };
     const uint32_t gv0 = v_goff(st_r0, st_r0), gv1 = v_goff(st_r1, st_r1);
-    const uint32_t gk0 = k_goff(wave, kBN - 1), gk1 = k_goff(wave + 8, kBN - 1), gk2 = k_goff(16, kBN - 1);
+    const uint32_t gk0 = k_goff(st_r0, st_r0), gk1 = k_goff(st_r1, st_r1);
     const uint32_t lds_base0 = (uint32_t)(uintptr_t)(ESP_LDS unsigned char*)smem;
     // row kv_lo, head kvh (POOL: slot 0, head kvh)
     const char* kreq = (const char*)a.k + ((int64_t)(POOL ? 0 : kv_lo) * a.Hkv + kvh) * (kHeadDim * 2);
     const char* vreq = (const char*)a.v + ((int64_t)(POOL ? 0 : kv_lo) * a.Hkv + kvh) * (kHeadDim * 2);
-    // POOL: K rows are not padded but swizzled, chunk c of row r at c ^ (r % 8), so that a wavefront moves rows 8w .. 8w+7 of K as it does
-    // of V, in transfers 2w and 2w + 1, and one read of the ring (stage kStages: tile 0) has both rows' slots.  From a slot to a row's
-    // address: one 32 x 32 -> 64-bit multiply-add on where this lane's 16 bytes lie in slot 0
-    // The loop is bound by the LDS port (289 KB a tile at 128 bytes a cycle, and the slot reads) and by power; with padded rows it took five
+    // POOL: one read of the ring (stage kStages: tile 0) has the slots of both rows that a lane moves of K or V.  From a slot to a row's
+    // address: one 32 x 32 -> 64-bit multiply-add on where this lane's 16 bytes lie in slot 0.
+    // The loop is bound by the LDS port (288 KB a tile at 128 bytes a cycle, and the slot reads) and by power; with padded rows of K it took five
     // slot reads a wavefront and tile, now two for two rows each.  Padded -> swizzled: a tile 2666 -> 2577 cycles; 300 tokens on 20300 rows of
     // the pool, 32 / 8 heads, 108.8 -> 105.9 us, 2000 on 2000 51.7 -> 48.7, 8000 on 30000 2733 -> 2680, 2048 on 10240, 32 / 32, 285 -> 279.
     const ESP_LDS int32_t* const slot_rd = (const ESP_LDS int32_t*)(uintptr_t)(lds_base0 + kLdsSlot + st_r0 * 4);
@@ -533,20 +530,21 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int32_t* preq = a.kv_pos + kv_lo;
     const uint32_t lds_base = lds_base0;
     const uint32_t lds_k0 = lds_base + kLdsK, lds_v0 = lds_base + kLdsV;
-    const uint32_t lds_kw = lds_base + wave * (POOL ? 2048 : 1024), lds_vw = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
+    const uint32_t lds_w = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
 
-    // K tile at kt into K stage st: 2 transfers per wavefront, 3 for wavefront 7; `part` picks one of them, so that
+    // K tile at kt into K stage st: 2 transfers per wavefront; `part` picks one of them, so that
     // the sweep can spread them over an iteration (a burst of transfers from all wavefronts at once backs up the
     // memory pipeline and stalls the issuing wavefronts).  `tail`: it is the ragged last tile, whose rows past the
     // end re-read the last row (their scores get masked).
     auto fetch_k_part = [&](const char* kt, int st, bool tail, int part) {
-        const uint32_t base = part == 2 ? lds_base : lds_kw;
-        const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + (POOL ? 1024 : 8192) * part;
-        const int n = part == 0 ? wave : part == 1 ? wave + 8 : 16;
-        if (part == 2 && (POOL || wave != 7)) return;
-        if constexpr (POOL) { load_to_lds_b128_at(base, off, pool_at(part == 0 ? pk0 : pk1, pool_slot(st, part))); return; }
-        if (__builtin_expect(tail, 0)) load_to_lds_b128(base, off, kt, k_goff(n, tail_rows - 1));
-        else load_to_lds_b128(base, off, kt, part == 0 ? gk0 : part == 1 ? gk1 : gk2);
+        const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + 1024 * part;
+        if constexpr (POOL) { load_to_lds_b128_at(lds_w, off, pool_at(part == 0 ? pk0 : pk1, pool_slot(st, part))); return; }
+        if (__builtin_expect(tail, 0)) {
+            const int r = part == 0 ? st_r0 : st_r1;
+            load_to_lds_b128(lds_w, off, kt, k_goff(r, min(r, tail_rows - 1)));
+        } else {
+            load_to_lds_b128(lds_w, off, kt, part == 0 ? gk0 : gk1);
+        }
     };
     // V tile at vt and its positions at pt into V stage st: 2 transfers per wavefront, 3 for wavefront 0
     auto fetch_v_part = [&](const char* vt, const int32_t* pt, int st, bool tail, int part, int slot_st = -1) {
@@ -556,16 +554,16 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             if (wave != 0) return;
             load_to_lds_b32(lds_base, kLdsPos + st * (kBN * 4), pt, (tail ? min(lane, last) : lane) * 4);
         } else if constexpr (POOL) {
-            load_to_lds_b128_at(lds_vw, off, pool_at(pv, pool_slot(slot_st < 0 ? st : slot_st, part)));
+            load_to_lds_b128_at(lds_w, off, pool_at(pv, pool_slot(slot_st < 0 ? st : slot_st, part)));
         } else if (__builtin_expect(tail, 0)) {
             const int r = part == 0 ? st_r0 : st_r1;
-            load_to_lds_b128(lds_vw, off, vt, v_goff(r, min(r, last)));
+            load_to_lds_b128(lds_w, off, vt, v_goff(r, min(r, last)));
         } else {
-            load_to_lds_b128(lds_vw, off, vt, part == 0 ? gv0 : gv1);
+            load_to_lds_b128(lds_w, off, vt, part == 0 ? gv0 : gv1);
         }
     };
     auto fetch_k = [&](const char* kt, int st, bool tail) {
-        fetch_k_part(kt, st, tail, 0); fetch_k_part(kt, st, tail, 1); fetch_k_part(kt, st, tail, 2);
+        fetch_k_part(kt, st, tail, 0); fetch_k_part(kt, st, tail, 1);
     };
     auto fetch_v = [&](const char* vt, const int32_t* pt, int st, bool tail) {
         fetch_v_part(vt, pt, st, tail, 0); fetch_v_part(vt, pt, st, tail, 1); fetch_v_part(vt, pt, st, tail, 2);
@@ -592,9 +590,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     // K and V rows of tile t (both in stage st, K(0) in its own place) to the pool, at the top of iteration t.  Every wavefront stores
-    // exactly the LDS bytes its own transfers fill: of V the rows 8w .. 8w+7, of K the 1 KiB pieces w and w + 8 of
-    // the padded tile (wavefront 7 also the 17th), lane L the 16 bytes at 1024 n + 16 L, i.e. row B / 272 at
-    // B % 272 (nothing if that is padding).  The K stage is refilled during this very iteration, but each
+    // exactly the LDS bytes its own transfers fill, rows 8w .. 8w+7 of either.  The K stage is refilled during this very iteration, but each
     // wavefront's own refills follow its own reads in program order, and it reads nobody else's bytes.
     // All LDS reads first (slots and rows, one round trip), then the stores.
     auto keep_tile = [&](int t, int st) {
@@ -604,23 +600,19 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         const unsigned char* kt = smem + (t == 0 ? kLdsK0 : kLdsK + st * kKTileBytes);
         const unsigned char* vt = smem + kLdsV + st * kTileBytes;
         const int r0 = wave * 8 + st_sub, r1 = r0 + 4;
-        const int b0 = 1024 * wave + 16 * lane, b1 = b0 + 8192, b2 = 16384 + 16 * lane;
-        const int kr0 = b0 / kKRow, kr1 = b1 / kKRow, kr2 = b2 / kKRow;
-        const int kw0 = b0 - kr0 * kKRow, kw1 = b1 - kr1 * kKRow, kw2 = b2 - kr2 * kKRow;
-        const int32_t sv0 = ring[r0], sv1 = ring[r1];
-        const int32_t sk0 = ring[kr0], sk1 = ring[kr1], sk2 = ring[kr2];
+        const int32_t s0 = ring[r0], s1 = ring[r1];
+        const uint4 wk0 = *(const uint4*)(kt + r0 * 256 + ((st_p ^ (r0 & 7)) << 4));
+        const uint4 wk1 = *(const uint4*)(kt + r1 * 256 + ((st_p ^ (r1 & 7)) << 4));
         const uint4 wv0 = *(const uint4*)(vt + r0 * 256 + ((st_p ^ ((r0 & 3) << 2)) << 4));
         const uint4 wv1 = *(const uint4*)(vt + r1 * 256 + ((st_p ^ ((r1 & 3) << 2)) << 4));
-        const uint4 wk0 = *(const uint4*)(kt + b0), wk1 = *(const uint4*)(kt + b1), wk2 = *(const uint4*)(kt + b2);
         // address of a pool row's piece: one 32 x 32 -> 64-bit multiply-add each
         const uint32_t row_pitch = (uint32_t)a.Hkv * (kHeadDim * 2);
-        ESP_GLOBAL char* kb = (ESP_GLOBAL char*)a.k_pool + (uint32_t)kvh * (kHeadDim * 2);
+        ESP_GLOBAL char* kb = (ESP_GLOBAL char*)a.k_pool + (uint32_t)kvh * (kHeadDim * 2) + 16 * st_p;
         ESP_GLOBAL char* vb = (ESP_GLOBAL char*)a.v_pool + (uint32_t)kvh * (kHeadDim * 2) + 16 * st_p;
-        if (sk0 >= 0 && kw0 < 256) *(ESP_GLOBAL u32x4*)(kb + (uint64_t)(uint32_t)sk0 * row_pitch + kw0) = u32x4{wk0.x, wk0.y, wk0.z, wk0.w};
-        if (sk1 >= 0 && kw1 < 256) *(ESP_GLOBAL u32x4*)(kb + (uint64_t)(uint32_t)sk1 * row_pitch + kw1) = u32x4{wk1.x, wk1.y, wk1.z, wk1.w};
-        if (wave == 7 && sk2 >= 0 && kw2 < 256) *(ESP_GLOBAL u32x4*)(kb + (uint64_t)(uint32_t)sk2 * row_pitch + kw2) = u32x4{wk2.x, wk2.y, wk2.z, wk2.w};
-        if (sv0 >= 0) *(ESP_GLOBAL u32x4*)(vb + (uint64_t)(uint32_t)sv0 * row_pitch) = u32x4{wv0.x, wv0.y, wv0.z, wv0.w};
-        if (sv1 >= 0) *(ESP_GLOBAL u32x4*)(vb + (uint64_t)(uint32_t)sv1 * row_pitch) = u32x4{wv1.x, wv1.y, wv1.z, wv1.w};
+        if (s0 >= 0) *(ESP_GLOBAL u32x4*)(kb + (uint64_t)(uint32_t)s0 * row_pitch) = u32x4{wk0.x, wk0.y, wk0.z, wk0.w};
+        if (s1 >= 0) *(ESP_GLOBAL u32x4*)(kb + (uint64_t)(uint32_t)s1 * row_pitch) = u32x4{wk1.x, wk1.y, wk1.z, wk1.w};
+        if (s0 >= 0) *(ESP_GLOBAL u32x4*)(vb + (uint64_t)(uint32_t)s0 * row_pitch) = u32x4{wv0.x, wv0.y, wv0.z, wv0.w};
+        if (s1 >= 0) *(ESP_GLOBAL u32x4*)(vb + (uint64_t)(uint32_t)s1 * row_pitch) = u32x4{wv1.x, wv1.y, wv1.z, wv1.w};
     };
 
     // ---- this lane's query row (column of S^T); its position is needed first (schedule scan), so it is loaded first
@@ -797,10 +789,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // ---- operand read offsets
     // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> one base per lane, the rest are immediates (POOL: four, by the bits of t
     // that the swizzle changes)
-    constexpr int kKBases = POOL ? 4 : 1, kKRead = POOL ? 256 : kKRow;
-    uint32_t k_rd[kKBases];
+    uint32_t k_rd[4];
 #pragma unroll
-    for (int x = 0; x < kKBases; ++x) k_rd[x] = lds_k0 + qi * kKRead + (POOL ? ((2 * x + hi) ^ (qi & 7)) : hi) * 16;
+    for (int x = 0; x < 4; ++x) k_rd[x] = lds_k0 + qi * 256 + (((2 * x + hi) ^ (qi & 7)) << 4);
     // V (A operand of O^T) by transposing reads: 16 lanes fetch a 4 (kv) x 16 (d) patch
     const int j16 = lane & 15, jq = j16 >> 2, dblk = (lane >> 4) & 1;
     uint32_t v_rd[4];
@@ -835,7 +826,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // (p / 8, (p / 4) % 2, p % 4) of the tile at byte offset stage_off of the V stages
     auto read_k = [&](int slot, int st, int i) {
         const int t = i >> 1;
-        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t % kKBases] + st * kKTileBytes + (i & 1) * (32 * kKRead) + t / kKBases * (32 * kKBases));
+        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + st * kKTileBytes + (i & 1) * (32 * 256) + (t >> 2) * 128);
     };
     auto read_v = [&](int slot, uint32_t stage_off, int p) {
         const uint32_t vp = v_rd[p & 3] + stage_off + (32 * (p >> 3) + 16 * ((p >> 2) & 1)) * 256;
@@ -1005,7 +996,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             read_k(m & 1, m + 2 < 16 ? ST1 : ST2, (m + 2) & 15);
             pair_sum_pack(m, !PLAIN);
             // the transfers of this iteration, spread out (a burst from all wavefronts at once backs up the memory
-            // pipeline); the odd ones of wavefronts 7 and 0 go first, so that "all but the last four have landed"
+            // pipeline); the odd ones, wavefront 0's positions and slots, go first, so that "all but the last four have landed"
             // is the same wait for every wavefront.  (Issued last instead, with a wait count per wavefront, they
             // would have a whole iteration more to land; measured, that is slower: 1.6 % on the 8K x 8K causal
             // shard, 6 % on a chunk against a 256K prefix.)
@@ -1015,14 +1006,13 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                     else if (j + 5 < n_vis) fetch_pool_slots(j + 5, ST1);
                 }
                 if (KEEP && !PLAIN && do_k && j >= own_lo) fetch_slots(j + 4);
-                if (do_k) fetch_k_part(k_next, ST, tail_k, 2);
                 if (do_v) fetch_v_part(v_next, p_next, ST2, tail_v, 2);
             }
             if constexpr (POOL) {
                 if (do_k && (m == 3 || m == 6))
-                    load_to_lds_b128_at(lds_kw, kLdsK + ST * kKTileBytes + 1024 * (m / 6), pool_at(m == 3 ? pk0 : pk1, m == 3 ? pslot0 : pslot1));
+                    load_to_lds_b128_at(lds_w, kLdsK + ST * kKTileBytes + 1024 * (m / 6), pool_at(m == 3 ? pk0 : pk1, m == 3 ? pslot0 : pslot1));
                 if (do_v && (m == 9 || m == 12))
-                    load_to_lds_b128_at(lds_vw, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(pv, m == 9 ? pslot0 : pslot1));
+                    load_to_lds_b128_at(lds_w, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(pv, m == 9 ? pslot0 : pslot1));
             } else {
                 if (do_k && (m == 3 || m == 6)) fetch_k_part(k_next, ST, tail_k, m / 6);
                 if (do_v && (m == 9 || m == 12)) fetch_v_part(v_next, p_next, ST2, tail_v, m / 12);
@@ -1046,7 +1036,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (n_need <= 0) return;
         auto read_k0 = [&](int slot, int i) {
             const int t = i >> 1;
-            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t % kKBases] + (uint32_t)(kLdsK0 - kLdsK) + (i & 1) * (32 * kKRead) + t / kKBases * (32 * kKBases));
+            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + (uint32_t)(kLdsK0 - kLdsK) + (i & 1) * (32 * 256) + (t >> 2) * 128);
         };
         read_k0(0, 0);
         read_k0(1, 1);
@@ -1078,8 +1068,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // what iterations 1 and 2 need (a sweep that is shorter does not wait for it)
     if (n_vis > 1) {
         if constexpr (POOL) {
-            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes, pool_at(pv, v1_slot0));
-            load_to_lds_b128_at(lds_vw, kLdsV + kTileBytes + 1024, pool_at(pv, v1_slot1));
+            load_to_lds_b128_at(lds_w, kLdsV + kTileBytes, pool_at(pv, v1_slot0));
+            load_to_lds_b128_at(lds_w, kLdsV + kTileBytes + 1024, pool_at(pv, v1_slot1));
         } else {
             fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 0);
             fetch_v_part(vreq + tile_bytes, preq, 1, 1 == ragged_tile, 1);
@@ -1141,7 +1131,6 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (KEEP && jj < n_vis - 4) keep_tile(jj, jj & 3);
         if (do_k && jj >= own_lo) fetch_slots(jj + 4);
         if (POOL && jj + 5 < n_vis) fetch_pool_slots(jj + 5, (jj + 1) & 3);
-        if (do_k) fetch_k_part(k_next, jj & 3, tail_k, 2);
         if (do_v) fetch_v_part(v_next, p_next, (jj + 2) & 3, tail_v, 2);
         if (do_k) { fetch_k_part(k_next, jj & 3, tail_k, 0); fetch_k_part(k_next, jj & 3, tail_k, 1); }
         if (do_v) { fetch_v_part(v_next, p_next, (jj + 2) & 3, tail_v, 0); fetch_v_part(v_next, p_next, (jj + 2) & 3, tail_v, 1); }
@@ -1249,7 +1238,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int rows_here = cut && n_need == 0 ? 0 : min(32, n_rows - kTileRow * ew);
     char* const O_part = (char*)a.O + part * a.o_part;
     if (!a.o_f32) {
-        unsigned char* blk = smem + kLdsK + ew * (32 * kKRow);
+        unsigned char* blk = smem + kLdsK + ew * (32 * kORow);
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -1257,7 +1246,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
                 uint2 w;
                 w.x = pack_bf16(oacc[db][4 * bb + 0] * inv, oacc[db][4 * bb + 1] * inv);
                 w.y = pack_bf16(oacc[db][4 * bb + 2] * inv, oacc[db][4 * bb + 3] * inv);
-                *(uint2*)(blk + e_qi * kKRow + (32 * db + 8 * bb + 4 * e_hi) * 2) = w;
+                *(uint2*)(blk + e_qi * kORow + (32 * db + 8 * bb + 4 * e_hi) * 2) = w;
             }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // same wavefront wrote what it reads next
         const int rsub = el >> 4, c16 = el & 15;
@@ -1266,14 +1255,14 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (rows_here >= 32) {                                      // all rows exist: eight stores in a row, no branches
             uint4 w[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) w[i] = *(const uint4*)(blk + (4 * i + rsub) * kKRow + 16 * c16);
+            for (int i = 0; i < 8; ++i) w[i] = *(const uint4*)(blk + (4 * i + rsub) * kORow + 16 * c16);
 #pragma unroll
             for (int i = 0; i < 8; ++i) *out(i) = w[i];
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int r = 4 * i + rsub;
-                const uint4 w = *(const uint4*)(blk + r * kKRow + 16 * c16);
+                const uint4 w = *(const uint4*)(blk + r * kORow + 16 * c16);
                 if (r < rows_here) *out(i) = w;
             }
         }
