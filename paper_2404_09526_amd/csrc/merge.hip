@@ -21,8 +21,7 @@ namespace esp {
 // wavefronts (one at a time, each behind a test for P -> this, with 16 lanes on a pair: sixteen of 31 x 4 9.7 -> 7.2, eight of 32 x 32 5.6 -> 4.7,
 // twelve of 64 x 32 8.8 -> 7.0; six fp32 ones of 300 x 32 7.6, with four at a time 8.2).
 template <bool F32, bool OUT32, int N, int GROUPS>
-__global__ __launch_bounds__(256) void merge_kernel(MergeArgs parts, int32_t P, int64_t pairs,
-                                                    void* O, float* LSE_out) {
+__global__ __launch_bounds__(256) void merge_kernel(int32_t P, int64_t pairs, void* O, float* LSE_out, MergeArgs parts) {
     constexpr int LANES = F32 ? 32 : 16, E = kHeadDim / LANES;       // of a pair; output elements of a lane
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, pair = i / LANES;
     if (pair >= pairs) return;
@@ -91,7 +90,7 @@ esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_
     int64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "merge: too many rows for one launch");
 #define ESP_MERGE_KERNEL(F32, OUT32, N, GROUPS) \
-    hipLaunchKernelGGL((merge_kernel<F32, OUT32, N, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, stream, parts, P, pairs, O, LSE_out)
+    hipLaunchKernelGGL((merge_kernel<F32, OUT32, N, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, stream, P, pairs, O, LSE_out, parts)
 #define ESP_MERGE_LAUNCH(F32, OUT32)                                  \
     if (P == 1) ESP_MERGE_KERNEL(F32, OUT32, 1, 1);                   \
     else if (P == 2) ESP_MERGE_KERNEL(F32, OUT32, 2, 1);              \

@@ -996,7 +996,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             read_k(m & 1, m + 2 < 16 ? ST1 : ST2, (m + 2) & 15);
             pair_sum_pack(m, !PLAIN);
             // the transfers of this iteration, spread out (a burst from all wavefronts at once backs up the memory
-            // pipeline); the odd ones, wavefront 0's positions and slots, go first, so that "all but the last four have landed"
+            // pipeline); the odd ones, wavefront 0's positions and wavefront 6's slots, go first, so that "all but the last four have landed"
             // is the same wait for every wavefront.  (Issued last instead, with a wait count per wavefront, they
             // would have a whole iteration more to land; measured, that is slower: 1.6 % on the 8K x 8K causal
             // shard, 6 % on a chunk against a 256K prefix.)
