@@ -1323,9 +1323,13 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         const int L = split ? P >> 3 : P, l = split ? p >> 3 : p, x = split ? p & 7 : 0;
         const int width = split ? a.heads_per_xcd : a.Hkv * a.splits;
         const int M = a.q_tiles * width;
-        // rounds dealt statically (M <= L: one item each).  With start-of-round waits everything is dealt: the items
-        // are long and alike, a pool could not even them out further, and its items would walk K/V alone
-        const int S = M <= L ? 1 : a.group_sync ? (M + L - 1) / L : max(1, (M - L) / L);
+        // Rounds dealt statically (M <= L: one item each).  With start-of-round waits the items are long and alike: a pool of them does not
+        // even out the workgroups of an XCD, and its items walk K/V alone (of two to four rounds the last drawn from the pool: 0.3 .. 1 %
+        // slower).  But XCDs differ by 7 % and more, and from eight rounds on that is an item's time or near it: then the last round
+        // goes to the pool all the same.  All dealt -> the last drawn, two cards: 32768 tokens on 262144, 32 / 32 heads, 106.5 -> 104.7 and 112.1 -> 105.5 ms,
+        // 16384 on 180000 37.0 -> 35.5, 10000 on 90000, 64 / 8, 21.3 -> 21.1; the last two rounds drawn 105.8 and 21.1.
+        const int S = M <= L ? 1 : a.group_sync && M < 8 * L ? (M + L - 1) / L : max(1, (M - L) / L);
+        const int synced = min(S, M / L);                             // dealt rounds that are full: all but the first start together
         const int pool_items = M > S * L ? (M - S * L) * (split ? 8 : 1) : 0;
         // One workgroup starts this launch's count of the pool while the others are at their first items (a single round trip: the
         // last draw of the launch before left a 0).  Without that the first draws start it themselves, and where many items end
@@ -1352,9 +1356,9 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             // not, so the total a count reaches is known beforehand, and the arrival that completes it clears the count (a
             // launch replayed from a captured graph carries the tag it was recorded with and must not find its own
             // earlier counts).
-            if (a.group_sync && s >= 1 && (s + 1) * L <= M && tid == 0) {
+            if (a.group_sync && s >= 1 && s < synced && tid == 0) {
                 unsigned long long* ctr = a.pool + 2 + x;
-                const uint32_t target = (uint32_t)(L * s), total = (uint32_t)(L * (M / L - 1));   // rounds up to this one; all that wait
+                const uint32_t target = (uint32_t)(L * s), total = (uint32_t)(L * (synced - 1));   // rounds up to this one; all that wait
                 const int before_me = draw_finish(ctr, __hip_atomic_fetch_add(ctr, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
                 if ((uint32_t)before_me + 1 == total) {
                     __hip_atomic_store(ctr, 0ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

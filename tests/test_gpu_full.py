@@ -161,6 +161,42 @@ def test_round_start_waits_replayed_from_a_graph(esp, cuda):
     assert int((words[2:2 + 2 * 32] != 0).sum()) == 0
 
 
+@pytest.mark.parametrize("ticks", [None, 0])
+def test_round_start_waits_and_an_item_pool(esp, cuda, main_prefill_kernel, ticks):
+    """Eight rounds of alike items (4096 tokens, 16 query heads to each of eight KV heads): all but the last are dealt and start together, the
+    last is drawn from the pool.  Against the oracle; bit for bit the two halves of the chunk, which have no pool; and replayed from
+    a graph between eager calls, which the pool's counter and the arrival counts must survive."""
+    was = esp.esp_debug_set_prefill_sync_ticks(ticks) if ticks is not None else None
+    try:
+        pc = wl.contiguous_prefill("chunk-and-pool", 4096, 32768 - 4096, [(0, 32768)], 128, 8, 35, cuda)
+        check_prefill_sampled(esp, pc, 256, 5)
+        s = pc.shards[0]
+        ws = torch.zeros(esp.esp_prefill_workspace_bytes(pc.Tq, 32768, 1, 128, 8, 128), dtype=torch.uint8, device=cuda)
+        run = lambda q, pos, O, L: esp.esp_partial_attn_prefill(q, s.k, s.v, pos, s.kv_pos, softmax_scale=pc.scale, O=O, LSE=L, workspace=ws)
+        O_ref = torch.empty_like(pc.q); L_ref = torch.empty((pc.Tq, pc.Hq), dtype=torch.float32, device=cuda)
+        for half in (slice(0, 2048), slice(2048, 4096)):
+            run(pc.q[half], pc.q_pos[half], O_ref[half], L_ref[half])
+        O, L = torch.empty_like(O_ref), torch.empty_like(L_ref)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            run(pc.q, pc.q_pos, O, L)
+        torch.cuda.current_stream().wait_stream(side)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            run(pc.q, pc.q_pos, O, L)
+        for rep in range(4):
+            O.fill_(float("nan")); L.fill_(float("nan"))
+            g.replay() if rep % 2 == 0 else run(pc.q, pc.q_pos, O, L)
+            torch.cuda.synchronize()
+            assert torch.equal(O.view(torch.int16), O_ref.view(torch.int16)) and torch.equal(L.view(torch.int32), L_ref.view(torch.int32)), rep
+            assert int((ws[:256].view(torch.int64) != 0).sum()) == 0
+    finally:
+        if was is not None:
+            esp.esp_debug_set_prefill_sync_ticks(was)
+
+
 def test_config5_prefill_varlen_gqa(esp, cuda):
     pc = wl.config5_prefill(cuda)
     assert pc.visible_pairs_per_head == 2994661376
