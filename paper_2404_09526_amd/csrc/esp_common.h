@@ -51,6 +51,14 @@ __device__ __forceinline__ void store_once(uint4* p, const uint4& v) {
     __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, (u32x4*)p);
 }
 
+// Grids of one thread block after another along rows.  A launch counts its work-items in 32 bits a dimension, and one that asks for more
+// starts, without an error, with what the count keeps of them; so block i is (i % kGridX, i / kGridX), and blocks past the last
+// find no row.
+constexpr int kGridX = 1 << 23;
+constexpr int64_t kGridMost = (int64_t)65535 * kGridX;
+inline dim3 row_grid(int64_t blocks) { return dim3((unsigned)(blocks < kGridX ? blocks : kGridX), (unsigned)((blocks + kGridX - 1) / kGridX)); }
+__device__ __forceinline__ int64_t row_block() { return (int64_t)blockIdx.y * kGridX + blockIdx.x; }
+
 // ---- launchers (one per kernel file) -------------------------------------------------
 struct MergeArgs {
     const void* O_parts[ESP_MAX_PARTIALS];

@@ -23,7 +23,7 @@ namespace esp {
 template <bool F32, bool OUT32, int N, int GROUPS>
 __global__ __launch_bounds__(256) void merge_kernel(int32_t P, int64_t pairs, void* O, float* LSE_out, MergeArgs parts) {
     constexpr int LANES = F32 ? 32 : 16, E = kHeadDim / LANES;       // of a pair; output elements of a lane
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, pair = i / LANES;
+    const int64_t i = row_block() * 256 + threadIdx.x, pair = i / LANES;
     if (pair >= pairs) return;
     const int seg = (int)(i % LANES);
 
@@ -86,11 +86,11 @@ __global__ __launch_bounds__(256) void merge_kernel(int32_t P, int64_t pairs, vo
 
 esp_status launch_merge(const MergeArgs& parts, int32_t P, int64_t pairs, int32_t parts_f32, void* O, float* LSE_out,
                         hipStream_t stream, int32_t o_f32) {
-    int64_t threads = pairs * (parts_f32 ? 32 : 16);
-    int64_t blocks = (threads + 255) / 256;
-    if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "merge: too many rows for one launch");
+    const int64_t per_block = parts_f32 ? 8 : 16;
+    const int64_t blocks = (pairs + per_block - 1) / per_block;
+    if (blocks > kGridMost) return fail(ESP_ERR_INVALID_ARG, "merge: too many rows for one launch");
 #define ESP_MERGE_KERNEL(F32, OUT32, N, GROUPS) \
-    hipLaunchKernelGGL((merge_kernel<F32, OUT32, N, GROUPS>), dim3((unsigned)blocks), dim3(256), 0, stream, P, pairs, O, LSE_out, parts)
+    hipLaunchKernelGGL((merge_kernel<F32, OUT32, N, GROUPS>), row_grid(blocks), dim3(256), 0, stream, P, pairs, O, LSE_out, parts)
 #define ESP_MERGE_LAUNCH(F32, OUT32)                                  \
     if (P == 1) ESP_MERGE_KERNEL(F32, OUT32, 1, 1);                   \
     else if (P == 2) ESP_MERGE_KERNEL(F32, OUT32, 2, 1);              \

@@ -128,6 +128,15 @@ def test_host_side_argument_errors(lib):
     assert prefill_direct(Tq=0, max_q=0) == lib.ESP_OK
 
 
+def test_calls_that_no_grid_holds_are_refused(lib):
+    L = lib.lib
+    nul, one, most = ctypes.c_void_p(0), ctypes.c_void_p(256), 2 ** 31 - 1
+    arr, far = (ctypes.c_void_p * 1)(256), ctypes.c_void_p(1 << 20)
+    assert L.esp_merge_partials(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
+    assert L.esp_merge_partials_f32(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
+    assert "one launch" in lib.last_error()
+
+
 def test_no_oracle_or_fallback_in_product():
     """The product path must not import the oracle (it is test infrastructure)."""
     pkg = os.path.join(ROOT, "paper_2404_09526_amd")
