@@ -10,7 +10,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const uint4* __restrict_
                                                         const int32_t* __restrict__ slot_idx, int64_t total_chunks,
                                                         int32_t chunks_per_row, uint4* __restrict__ k_pool,
                                                         uint4* __restrict__ v_pool) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int64_t i = row_block() * 256 + threadIdx.x;
     if (i >= total_chunks) return;
     int32_t t = (int32_t)(i / chunks_per_row);
     int32_t c = (int32_t)(i - (int64_t)t * chunks_per_row);
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void kv_gather_kernel(const uint4* __restrict_
                                                         const int32_t* __restrict__ slot_idx, int64_t total_chunks,
                                                         int32_t chunks_per_row, int64_t num_slots,
                                                         uint4* __restrict__ k, uint4* __restrict__ v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int64_t i = row_block() * 256 + threadIdx.x;
     if (i >= total_chunks) return;
     int32_t t = (int32_t)(i / chunks_per_row);
     int32_t c = (int32_t)(i - (int64_t)t * chunks_per_row);
@@ -47,8 +47,8 @@ esp_status launch_kv_gather(const void* k_pool, const void* v_pool, const int32_
     int32_t cpr = row_bytes / 16;
     int64_t total = (int64_t)T * cpr;
     int64_t blocks = (total + 255) / 256;
-    if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "gather: too many rows for one launch");
-    hipLaunchKernelGGL(kv_gather_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)k_pool,
+    if (blocks > kGridMost) return fail(ESP_ERR_INVALID_ARG, "gather: too many rows for one launch");
+    hipLaunchKernelGGL(kv_gather_kernel, row_grid(blocks), dim3(256), 0, stream, (const uint4*)k_pool,
                        (const uint4*)v_pool, slot_idx, total, cpr, num_slots, (uint4*)k, (uint4*)v);
     return check_launch("kv_gather_kernel");
 }
@@ -58,8 +58,8 @@ esp_status launch_kv_append(const void* k, const void* v, const int32_t* slot_id
     int32_t cpr = row_bytes / 16;
     int64_t total = (int64_t)T * cpr;
     int64_t blocks = (total + 255) / 256;
-    if (blocks > 0x7fffffff) return fail(ESP_ERR_INVALID_ARG, "append: too many rows for one launch");
-    hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)k,
+    if (blocks > kGridMost) return fail(ESP_ERR_INVALID_ARG, "append: too many rows for one launch");
+    hipLaunchKernelGGL(kv_append_kernel, row_grid(blocks), dim3(256), 0, stream, (const uint4*)k,
                        (const uint4*)v, slot_idx, total, cpr, (uint4*)k_pool, (uint4*)v_pool);
     return check_launch("kv_append_kernel");
 }

@@ -135,6 +135,10 @@ def test_calls_that_no_grid_holds_are_refused(lib):
     assert L.esp_merge_partials(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
     assert L.esp_merge_partials_f32(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
     assert "one launch" in lib.last_error()
+    heads = 8_000_000                                               # a row of 2 GB, less than an int32 of bytes
+    assert L.esp_kv_append(one, one, one, most, one, one, 8, heads, 128, nul) == lib.ESP_ERR_INVALID_ARG
+    assert L.esp_kv_gather(one, one, one, most, 8, heads, 128, one, one, nul) == lib.ESP_ERR_INVALID_ARG
+    assert "one launch" in lib.last_error()
 
 
 def test_no_oracle_or_fallback_in_product():

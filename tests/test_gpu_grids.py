@@ -1,5 +1,5 @@
 """Calls with more work-items than a launch counts in one dimension (2^32): every row of them is written.  Values are small whole numbers,
-so the results are exact.  The largest takes 130 GiB."""
+so the results are exact.  The largest takes 140 GiB."""
 import pytest
 import torch
 
@@ -43,3 +43,29 @@ def test_merge_of_more_pairs_than_a_grid_dimension_holds(esp, cuda, dtype, T):
     for i in range(0, T, CHUNK):
         n = min(i + CHUNK, T)
         assert (O[i:n] == value(i, n, cuda).to(torch.bfloat16)).all(), i
+
+
+def test_append_and_gather_of_more_pieces_than_a_grid_dimension_holds(esp, cuda):
+    H, T, S = 32, (1 << 23) + 3, 1024                               # 512 pieces of 16 bytes a row: just above 2^32
+    print(f"[case] append, gather {T} x {H}", flush=True)
+    k_pool = torch.zeros((S, H, 128), dtype=torch.bfloat16, device=cuda)
+    v_pool = torch.zeros_like(k_pool)
+    x = by_row(T, H, torch.bfloat16, cuda)
+    kept = torch.cat([torch.arange(100), torch.arange(T // 2, T // 2 + 100), torch.arange(T - 100, T)]).to(cuda)
+    slots = torch.full((T,), -1, dtype=torch.int32, device=cuda)
+    slots[kept] = torch.arange(300, dtype=torch.int32, device=cuda) * 3
+    esp.esp_kv_append(x, x, slots, k_pool, v_pool)
+    torch.cuda.synchronize()
+    want = torch.zeros_like(k_pool)
+    want[slots[kept].long()] = x[kept]
+    assert torch.equal(k_pool, want) and torch.equal(v_pool, want)
+    del x
+
+    k_pool.copy_(value(0, S, cuda).to(torch.bfloat16))
+    v_pool.copy_(value(7, S + 7, cuda).to(torch.bfloat16))
+    slots = (torch.arange(T, device=cuda) % S).to(torch.int32)
+    k, v = esp.esp_kv_gather(k_pool, v_pool, slots)
+    torch.cuda.synchronize()
+    for i in range(0, T, CHUNK):
+        s = slots[i:i + CHUNK].long()
+        assert torch.equal(k[i:i + CHUNK], k_pool[s]) and torch.equal(v[i:i + CHUNK], v_pool[s]), i
