@@ -437,8 +437,9 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
                                                              U32x2* __restrict__ O, float* __restrict__ LSE) {
     constexpr int U = 4;
     const int lane = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int pair = blockIdx.x * (8 / GROUPS) + grp / GROUPS, g = grp % GROUPS;
-    if (pair >= pairs) return;                                      // (only where a pair is a wavefront: no barrier follows)
+    const int64_t at = row_block() * (8 / GROUPS) + grp / GROUPS;
+    if (at >= pairs) return;                                        // (a whole workgroup, or a pair is a wavefront and no barrier follows)
+    const int pair = (int)at, g = grp % GROUPS;
     const int b = pair / Hq, h = pair - b * Hq;
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1];
     Weighted<4> sum;
@@ -543,6 +544,8 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
     if (decode_whole(B, total_tokens, max_len, Hq, Hkv))
         return launch_decode_whole(q, k_pool, v_pool, slot_idx, seq_offsets, B, total_tokens, Hq, Hkv, decode_burst_layout(Hq, Hkv),
                                    softmax_scale * kLog2e, O, LSE, peers, n_peers, stream);
+    if ((int64_t)B * Hq > INT32_MAX) return fail(ESP_ERR_INVALID_ARG, "decode: too many rows for one launch");
+    const int32_t pairs = B * Hq;
     DecodeGeom g = decode_geom(B, total_tokens, Hq, Hkv, workspace_bytes);
     const int32_t parts = decode_parts(g, B, max_len, Hq, Hkv);
     size_t n = decode_slots(g, B) * (size_t)Hq;
@@ -569,11 +572,10 @@ esp_status launch_decode(const void* q, const void* k_pool, const void* v_pool, 
         esp_status st = check_launch("decode_partial_kernel");
         if (st != ESP_OK) return st;
     }
-    const int32_t pairs = B * Hq;
     const bool with_peers = peers != nullptr && n_peers > 0;
     const bool wave = (int64_t)max_len / g.range + 2 <= kCombineShort;
 #define ESP_COMBINE_LAUNCH(GROUPS, PEERS)                                                                                 \
-    hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), dim3((unsigned)((pairs + 8 / GROUPS - 1) / (8 / GROUPS))), dim3(256), 0, \
+    hipLaunchKernelGGL((decode_combine_kernel<GROUPS, PEERS>), row_grid(((int64_t)pairs + 8 / GROUPS - 1) / (8 / GROUPS)), dim3(256), 0, \
                        stream, seq_offsets, g.range, parts, Hq, pairs, (const float*)part_acc, (const float*)part_ml,        \
                        with_peers ? *peers : MergeArgs{}, n_peers, (U32x2*)O, LSE)
     if (wave && with_peers) ESP_COMBINE_LAUNCH(2, true);

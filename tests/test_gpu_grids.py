@@ -69,3 +69,27 @@ def test_append_and_gather_of_more_pieces_than_a_grid_dimension_holds(esp, cuda)
     for i in range(0, T, CHUNK):
         s = slots[i:i + CHUNK].long()
         assert torch.equal(k[i:i + CHUNK], k_pool[s]) and torch.equal(v[i:i + CHUNK], v_pool[s]), i
+
+
+def test_decode_of_more_pairs_than_a_grid_dimension_holds(esp, cuda):
+    """A workgroup of the combination to each of 2^24 and more (request, head) pairs: one long request, the others of one token."""
+    Hq, B, long, S = 32, (1 << 19) + 5, 600_000, 1024
+    print(f"[case] decode {B} x {Hq}/1", flush=True)
+    lens = torch.ones(B, dtype=torch.int64)
+    lens[1] = long
+    offsets = torch.cat([torch.zeros(1, dtype=torch.int64), lens.cumsum(0)]).to(torch.int32).to(cuda)
+    rows = torch.arange(B, device=cuda) % S                         # a request's tokens are all in one row
+    slots = rows.repeat_interleave(lens.to(cuda)).to(torch.int32)
+    k_pool = torch.zeros((S, 1, 128), dtype=torch.bfloat16, device=cuda)
+    v_pool = torch.empty_like(k_pool)
+    v_pool.copy_(value(0, S, cuda).to(torch.bfloat16))
+    q = torch.ones((B, Hq, 128), dtype=torch.bfloat16, device=cuda)
+    before = esp.esp_debug_set_decode_plan(1)
+    try:
+        O, LSE = esp.esp_partial_attn_decode(q, k_pool, v_pool, slots, offsets, long, softmax_scale=1.0)
+        torch.cuda.synchronize()
+    finally:
+        esp.esp_debug_set_decode_plan(before)
+    assert (LSE.view(B, Hq) - lens.to(cuda).log().view(-1, 1)).abs().max() < 1e-4
+    for i in range(0, B, CHUNK):
+        assert (O[i:i + CHUNK] == v_pool[rows[i:i + CHUNK]]).all(), i
