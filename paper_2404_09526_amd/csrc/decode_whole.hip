@@ -313,6 +313,8 @@ esp_status launch_decode_whole(const void* q, const void* k_pool, const void* v_
     const int G = Hq / Hkv;
     const bool with_peers = peers != nullptr && n_peers > 0;
     const MergeArgs none = {};
+    if (B > (int32_t)(UINT32_MAX / (kWholeWaves * 64)) || Hkv > 65535 || (G + 31) / 32 > 65535)   // (only where a test asks for this form)
+        return fail(ESP_ERR_UNSUPPORTED, "decode: too many requests or heads for one launch of a workgroup each");
 #define ESP_WHOLE_LAUNCH(KERNEL, WAVES, Z, ...)                                                                                          \
     hipLaunchKernelGGL(KERNEL, dim3(B, Hkv, Z), dim3(WAVES * 64), 0, stream, (const uint16_t*)q, (const char*)k_pool, (const char*)v_pool, \
                        slot_idx, seq_offsets, total_tokens, __VA_ARGS__, scale_log2, n_peers, (U32x2*)O, LSE, with_peers ? *peers : none)

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 2) void prefill_short_kernel(Pref
 esp_status launch_prefill_short(const PrefillArgs& a, hipStream_t stream) {
     const int64_t rows = (int64_t)a.Tq * a.G;
     const int64_t blocks = a.batch == 1 ? (rows + kShortRows - 1) / kShortRows : rows / kShortRows + a.batch;
-    if (blocks * a.Hkv * a.splits > 0x7fffffff) return fail(ESP_ERR_UNSUPPORTED, "prefill: too many rows for one launch of the kernel for few");
+    if (blocks * a.Hkv * a.splits > UINT32_MAX / (kShortWaves * 64)) return fail(ESP_ERR_UNSUPPORTED, "prefill: too many rows for one launch of the kernel for few");
     const dim3 grid((unsigned)(blocks * a.Hkv * a.splits));
     if (a.kv_slot) hipLaunchKernelGGL((prefill_short_kernel<2>), grid, dim3(kShortWaves * 64), 0, stream, a);
     else if (a.retain_slot) hipLaunchKernelGGL((prefill_short_kernel<1>), grid, dim3(kShortWaves * 64), 0, stream, a);

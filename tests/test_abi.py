@@ -135,6 +135,21 @@ def test_calls_that_no_grid_holds_are_refused(lib):
     assert L.esp_merge_partials(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
     assert L.esp_merge_partials_f32(arr, arr, 1, most, most, 128, far, nul, nul) == lib.ESP_ERR_INVALID_ARG
     assert "one launch" in lib.last_error()
+    # kernels that a test asks for, on calls too large for their launch (refused before the device is asked for)
+    f = ctypes.c_float(0.1)
+    before = lib.esp_debug_set_prefill_plan(-1)
+    try:
+        assert L.esp_partial_attn_prefill(one, one, one, one, one, nul, nul, 1, 1 << 26, 64, 1 << 26, 64, 8, 8, 128, f, 1, one, one, one,
+                                          1 << 20, nul) == lib.ESP_ERR_UNSUPPORTED
+    finally:
+        lib.esp_debug_set_prefill_plan(before)
+    before = lib.esp_debug_set_decode_plan(2)
+    try:
+        for B, Hkv in ((1 << 22, 4), (1, 65536)):
+            assert L.esp_partial_attn_decode(one, one, one, 8, one, one, B, B, 1, Hkv, Hkv, 128, f, one, one, one, 1 << 50, nul) \
+                == lib.ESP_ERR_UNSUPPORTED, (B, Hkv)
+    finally:
+        lib.esp_debug_set_decode_plan(before)
     heads = 8_000_000                                               # a row of 2 GB, less than an int32 of bytes
     assert L.esp_kv_append(one, one, one, most, one, one, 8, heads, 128, nul) == lib.ESP_ERR_INVALID_ARG
     assert L.esp_kv_gather(one, one, one, most, 8, heads, 128, one, one, nul) == lib.ESP_ERR_INVALID_ARG
