@@ -92,6 +92,9 @@ __global__ __launch_bounds__(kWholeWaves * 64, 4) void decode_whole_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = blockIdx.x, kvh = blockIdx.y;
     const int32_t s0 = seq_offsets[b], s1 = min(seq_offsets[b + 1], total_tokens);   // (never past the slot list)
+    // tokens are counted from the request's first on, without a sign: steps that are looked ahead to may start past 2^31
+    const uint32_t n = max(s1 - s0, 0);
+    const int32_t* const list = slot_idx + s0;
     const int dseg = (lane & 15) * 8;
     const uint32_t row_bytes = (uint32_t)Hkv * (kHeadDim * 2), within = (uint32_t)kvh * (kHeadDim * 2) + dseg * 2;
     const int64_t pair0 = ((int64_t)b * Hkv + kvh) * G;
@@ -112,11 +115,11 @@ __global__ __launch_bounds__(kWholeWaves * 64, 4) void decode_whole_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.f;
     }
-    const int first = wave * 4 + (lane >> 4);                       // of a step's tokens: this one, and every 64th after it
+    const uint32_t first = wave * 4 + (lane >> 4);                      // of a step's tokens: this one, and every 64th after it
     struct Rows { uint4 k[U], v[U]; };
-    auto slots_of = [&](int t, uint32_t (&s)[U]) {
+    auto slots_of = [&](uint32_t t, uint32_t (&s)[U]) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) s[u] = (uint32_t)slot_idx[min(t + first + 64 * u, s1 - 1)];
+        for (int u = 0; u < U; ++u) s[u] = (uint32_t)list[min(t + first + 64 * u, n - 1)];
     };
     auto load = [&](Rows& r, const uint32_t (&s)[U]) {
 #pragma unroll
@@ -126,12 +129,12 @@ __global__ __launch_bounds__(kWholeWaves * 64, 4) void decode_whole_kernel(
             r.v[u] = load_once((const uint4*)(v_pool + at));
         }
     };
-    auto attend = [&](const Rows& r, int t) {
+    auto attend = [&](const Rows& r, uint32_t t) {
         float s[U][G];
         bool here[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            here[u] = t + first + 64 * u < s1;
+            here[u] = t + first + 64 * u < n;
             float kf[8];
             unpack8(r.k[u], kf);
 #pragma unroll
@@ -170,23 +173,23 @@ __global__ __launch_bounds__(kWholeWaves * 64, 4) void decode_whole_kernel(
             }
         }
     };
-    constexpr int kStep = kWholeWaves * 4 * U;
-    if (s0 < s1) {
+    constexpr uint32_t kStep = kWholeWaves * 4 * U;
+    if (n > 0) {
         Rows a, c;
         uint32_t sa[U], sc[U];
-        slots_of(s0, sa);
-        slots_of(s0 + kStep, sc);
+        slots_of(0, sa);
+        slots_of(kStep, sc);
         load(a, sa);
-        int t = s0;
-        for (; t + kStep < s1; t += 2 * kStep) {
+        uint32_t t = 0;
+        for (; t + kStep < n; t += 2 * kStep) {
             load(c, sc);
-            const bool more = t + 2 * kStep < s1;
+            const bool more = t + 2 * kStep < n;
             if (more) { slots_of(t + 2 * kStep, sa); slots_of(t + 3 * kStep, sc); }
             attend(a, t);
             if (more) load(a, sa);
             attend(c, t + kStep);
         }
-        if (t < s1) attend(a, t);
+        if (t < n) attend(a, t);
     }
 
     // the lanes that are left at the end (32 a head, four elements each) ask for the peers' rows
@@ -238,9 +241,10 @@ __global__ __launch_bounds__(kWholeGqWaves * 64, 2) void decode_whole_gq_kernel(
     const int qi = lane & 31, hi = lane >> 5;
     const int b = blockIdx.x, kvh = blockIdx.y;
     const int32_t s0 = seq_offsets[b], s1 = min(seq_offsets[b + 1], total_tokens);   // (never past the slot list)
-    const int n = s1 - s0;
+    const uint32_t n = max(s1 - s0, 0);                             // (without a sign, as above)
+    const int32_t* const list = slot_idx + s0;
     // slots of a tile: lane holds that of tile row lane % 32 (rows past the end: the last)
-    auto tile_slots = [&](int i) { return slot_idx[s0 + min(32 * i + qi, n - 1)]; };
+    auto tile_slots = [&](uint32_t i) { return list[min(32 * i + qi, n - 1)]; };
     int32_t slots = 0, slots_next = 0;
     if (32 * wave < n) { slots = tile_slots(wave); slots_next = tile_slots(wave + kWholeGqWaves); }
     const int G = Hq / Hkv, g0 = blockIdx.z * 32;
@@ -271,8 +275,8 @@ __global__ __launch_bounds__(kWholeGqWaves * 64, 2) void decode_whole_gq_kernel(
             load_to_lds_b128_at_nt(to + 1024 * x, base + ((uint64_t)(uint32_t)__shfl(of, col_row(x, lane)) * row_bytes + (is_k ? col_k_within(x, lane) : col_v_within(lane))));
     };
     if (32 * wave < n) { fetch(lds_k, kbase, slots, true); fetch(lds_v, vbase, slots, false); }
-    for (int i = wave; 32 * i < n; i += kWholeGqWaves) {
-        const int here = min(32, n - 32 * i);
+    for (uint32_t i = wave; 32 * i < n; i += kWholeGqWaves) {
+        const int here = min(32u, n - 32 * i);
         const bool next = 32 * (i + kWholeGqWaves) < n;
         wait_vm<8>();                                               // K has landed; V may be on its way
         floatx16 sc = cols.scores(qf);
