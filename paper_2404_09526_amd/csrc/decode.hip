@@ -253,7 +253,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 4) void decode_partial_kernel(
         if (r0 >= t1) return;
     } else {
         r0 = w * range;
-        t1 = min(r0 + range, total_tokens);
+        t1 = r0 + min(range, total_tokens - r0);                    // (r0 + range may be past 2^31)
         if (r0 >= t1) return;
         const RequestAt at = request_of(r0, seq_offsets, B, lane);
         b = at.b; req_end = at.end;

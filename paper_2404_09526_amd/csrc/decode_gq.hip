@@ -53,10 +53,10 @@ __global__ __launch_bounds__(kGqWaves * 64, 2) void decode_partial_gq_kernel(
         const RequestRange at = parts > 0 ? request_part(w, parts, range, B, seq_offsets) : request_range(w, range, B, seq_offsets, lane);
         b = at.b; t0 = at.t0; t1 = req_end = min(at.t1, total_tokens); w = at.w;   // (never past the slot list)
         if (t0 >= t1) return;
-        slots = slot_idx[min(t0 + 32 * wave + qi, t1 - 1)];
+        slots = slot_idx[t0 + min(32 * wave + qi, t1 - 1 - t0)];
     } else {
         t0 = w * range;
-        t1 = min(t0 + range, total_tokens);
+        t1 = t0 + min(range, total_tokens - t0);                    // (t0 + range may be past 2^31)
         if (t0 >= t1) return;
         // slots of this wavefront's first tile, as far as they do not depend on where its request ends: asked for before the search
         slots = slot_idx[min(t0 + 32 * wave + qi, total_tokens - 1)];

@@ -107,7 +107,7 @@ struct RequestRange { int32_t b, t0, t1, w; };
 __device__ __forceinline__ RequestRange request_part(int32_t i, int32_t parts, int32_t range, int32_t B, const int32_t* seq_offsets) {
     const int32_t part = i / B, at = i - part * B, b = (B & 1) != 0 ? at : (at + B - part % B) % B;
     const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1], t0 = s0 + part * range;
-    return {b, t0, part == parts - 1 ? s1 : min(t0 + range, s1), s0 / range + part};
+    return {b, t0, part == parts - 1 ? s1 : t0 + min(range, s1 - t0), s0 / range + part};
 }
 // As many as each request has: the whole ranges of all requests first, then what is left of each, so that workgroups which find no
 // room at first have little to do.  Requests are looked at 64 at a time, one per lane; a scan finds the one that holds range i.
@@ -131,7 +131,7 @@ __device__ __forceinline__ RequestRange request_range(int32_t i, int32_t range, 
                 const int32_t start = __builtin_amdgcn_readlane(s0, l), end = __builtin_amdgcn_readlane(s1, l);
                 const int32_t part = rest ? __builtin_amdgcn_readlane(whole, l) : i - (__builtin_amdgcn_readlane(upto, l) - __builtin_amdgcn_readlane(n, l));
                 const int32_t t0 = start + part * range;
-                return {base + l, t0, min(t0 + range, end), start / range + part};
+                return {base + l, t0, t0 + min(range, end - t0), start / range + part};
             }
             i -= __builtin_amdgcn_readlane(upto, 63);
         }

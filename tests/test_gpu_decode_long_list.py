@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("Hq,Hkv,B", [(4, 4, 50), (8, 4, 50), (32, 1, 200)])
-@pytest.mark.parametrize("plan", [2], ids=["one-launch"])
+@pytest.mark.parametrize("plan", [1, 2], ids=["ranges", "one-launch"])
 def test_decode_of_a_token_list_of_int32_length(cuda, plan, Hq, Hkv, B):
     from paper_2404_09526_amd import binding as esp
     torch.cuda.empty_cache()
