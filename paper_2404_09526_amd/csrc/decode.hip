@@ -137,28 +137,37 @@ static int32_t decode_parts(const DecodeGeom& g, int32_t B, int32_t max_len, int
     return (g.nwg + (int64_t)B / 2) * rows <= 512 && steps <= 12 ? -1 : 0;
 }
 
-// Short requests, each by one workgroup and KV head (decode_whole.hip), where all of them are on the chip at once, one to a CU, and an
-// estimate of the step's time, its append included, in us, says so.  In one launch: a start and an end (7.6 on the matrix cores, 8.2 on the
-// vector ALU), the longest request's walk, which the others' traffic slows down, or the traffic where that takes longer.  In ranges: 11.2, or
-// 14 with two query heads per KV head, for the ranges' starts and the launch more, and the traffic.
-// Measured (in ranges -> in one launch, requests of equal length): one of 200, 4 / 4 heads, 11.9 -> 8.8 us, 12 of 400 12.7 -> 10.5, 50 of
-// 1000 24.6 -> 22.2, 12 of 1000 13.9 -> 16.7 (stays in ranges); four of 400, 32 / 32, 13.4 -> 11.5; 20 of 200, 8 / 4, 15.2 -> 9.4, eight of 1000,
-// 64 / 32, 39.0 -> 27.1; three of 200, 32 / 8, 11.3 -> 9.1, of 700 11.8 -> 12.9 (ranges), 30 of 400 18.0 -> 14.3, of 1000 29.2 -> 24.8; 250 of 520,
-// 32 / 1, 28.0 -> 16.2.  Unequal ones: four of 224 .. 485, 4 / 4, three peers 12.2 -> 9.5, 34 of 30, 8 / 4, 15.5 -> 10.8; 16 of 106 .. 3077, 32 / 8,
-// stay in ranges (the longest would walk for 23).  With more than 256 workgroups the second round's longest request decides: 10 of 186, 32 / 32,
-// 15.1 -> 16.2, 16 of 57, 64 / 32, 17.4 -> 24.1, though equal lengths gain (16 of 400, 32 / 32, 27.7 -> 23.0).
+// Short requests, each by one workgroup and KV head (decode_whole.hip), where all of them are on the chip at once, one to a CU, and the
+// estimates of both forms' times, in us, say so.  In one launch: a start and an end, then the longest request's walk, which the others'
+// traffic slows down, or the traffic where that takes longer (16 wavefronts a CU, or eight with a tile each in flight, do not
+// reach the memory's rate: 5.9 TB/s, 6.3 on the matrix cores, 6.8 with one KV head; ranges 6.5 .. 6.8).  In ranges: the lesser of two lines
+// in the traffic.  With few KV heads rows are read in shorter pieces by fewer workgroups at a time, and ranges of many short requests cross;
+// but more than 32 query heads read a row again, from the caches in ranges.  The lines were fitted to 3770 calls of 1 .. 256 requests of up to
+// 64000 tokens, all alike, down to 0.6 and down to 0.1 of the longest, 18 head layouts, rows not cached and repeated.  Of those calls 0.04 of the time
+// promised keeps all but nine from losing more than 1.5 % to ranges (at most 8.6 %); to the better form the choice loses
+// 0.1 .. 0.4 % on average.  Beyond the stated lengths the estimates are no closer than what there is to gain.
+// Measured, all requests alike, rows not cached (in ranges -> in one launch; * stays in ranges): 64 of 1000 and 4000, 4 / 4 heads, 31.1 -> 26.4,
+// 89.4 -> 93.3*; 8 of 1000 and 4000, 32 / 32, 31.1 -> 26.2, 90.8 -> 88.6*; 64 of 1000, 8000 and 64000, 8 / 4, 39.0 -> 27.9, 186 -> 182, 1259 -> 1404*; 8 of
+// 1000, 16 / 8, 15.1 -> 19.4*; 32 of 1000, 4000 and 64000, 32 / 8, 30.5 -> 26.9, 94.2 -> 89.0, 1258 -> 1340*; 256 of 1000 and 16000, 32 / 1,
+// 32.7 -> 25.3, 329 -> 313.  Unequal ones: 64 of 700 .. 7000, 32 / 4, 94.8 -> 113.8*, 16 of 106 .. 3077, 32 / 8 (the longest would walk for 23).
+// With more than 256 workgroups the second round's longest request decides: 10 of 186, 32 / 32, 15.1 -> 16.2*, 16 of 57, 64 / 32, 17.4 -> 24.1*,
+// though equal lengths gain (16 of 400, 32 / 32, 27.7 -> 23.0*).
+constexpr int32_t kWholeMost = 256;                                 // CUs of the card that these times are of
 static thread_local int32_t t_forced_decode = 0;                    // this thread's choice instead (set_decode_plan); 0: none
 static bool decode_whole(int32_t B, int32_t total_tokens, int32_t max_len, int32_t Hq, int32_t Hkv) {
     const int G = Hq / Hkv;
     const int64_t chunks = (G + 31) / 32;
     if (B > 0 && t_forced_decode != 0) return t_forced_decode == 2;
-    if (total_tokens <= 0 || B * (int64_t)Hkv * chunks > 256) return false;
-    const bool burst = decode_burst_layout(Hq, Hkv);
-    const double bytes = (double)total_tokens * Hkv * chunks * (4 * kHeadDim), traffic = bytes / 7e6;
-    const double step = !burst ? 1 : G == 1 ? 256 : 128, walk = ceil(max_len / step) * step * (!burst ? 0.0075 : G == 1 ? 0.0045 : 0.0073);
-    const double whole = (burst ? 8.2 : 7.6) + fmax(walk + (burst ? 0.7 : 0.4) * traffic, 1.06 * traffic);
-    const double ranges = !burst ? fmax(11.2, 9.6 + bytes / 6.3e6) : G == 1 ? 11.2 + bytes / 6.8e6 : 14 + bytes / 5.5e6;
-    return whole < 0.97 * ranges;
+    const bool burst = decode_burst_layout(Hq, Hkv), few = !burst && Hkv <= 3 && chunks == 1;
+    if (total_tokens <= 0 || B * (int64_t)Hkv * chunks > kWholeMost || max_len > (few ? 16384 : 8192)) return false;
+    struct Lines { double step, start, token, beside, alone, short_start, short_traffic, long_start, long_traffic; };
+    constexpr Lines kBurst1 = {256, 3.2, 0.0104, 0.49, 1.15, 9.2, 1.05, 11, 1.04}, kBurst2 = {128, 4.9, 0.0108, 0.55, 1.15, 11.1, 1.3, 17.4, 1.15};
+    constexpr Lines kFew = {1, 5.5, 0.0084, 0.41, 1.035, 9.2, 1.17, 12.8, 1.06}, kMany = {1, 5.0, 0.0095, 0.48, 1.11, 8.6, 1.13, 15, 1.05};
+    const Lines& at = burst ? (G == 1 ? kBurst1 : kBurst2) : few ? kFew : kMany;
+    const double traffic = (double)total_tokens * Hkv * chunks * (4 * kHeadDim) / 7e6;   // us at 7 TB/s
+    const double whole = at.start + fmax(ceil(max_len / at.step) * at.step * at.token + at.beside * traffic, at.alone * traffic);
+    const double ranges = fmin(at.short_start + at.short_traffic * traffic, at.long_start + at.long_traffic * traffic);
+    return whole < 0.96 * ranges;
 }
 int32_t set_decode_plan(int32_t plan) {
     const int32_t before = t_forced_decode;
