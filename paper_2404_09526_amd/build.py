@@ -39,9 +39,10 @@ def _older(built: str, sources) -> bool:
 
 
 def is_stale() -> bool:
-    if _older(LIB, SOURCES + HEADERS):
+    """Built before its sources, or before this file, which has the flags."""
+    if _older(LIB, SOURCES + HEADERS + [__file__]):
         return True
-    return shutil.which("g++") is not None and _older(marshal_path(), [MARSHAL_SOURCE, os.path.join(ROOT, "include", "esp.h")])
+    return shutil.which("g++") is not None and _older(marshal_path(), [MARSHAL_SOURCE, os.path.join(ROOT, "include", "esp.h"), __file__])
 
 
 def build_lib(force: bool = True, verbose: bool = False) -> str:

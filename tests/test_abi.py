@@ -156,6 +156,16 @@ def test_calls_that_no_grid_holds_are_refused(lib):
     assert "one launch" in lib.last_error()
 
 
+def test_a_library_older_than_what_it_is_built_from_is_stale(lib, monkeypatch):
+    """Its sources, its headers, and the file that has its flags."""
+    from paper_2404_09526_amd import build
+    assert not build.is_stale()
+    mtime = os.path.getmtime
+    for newer in (build.SOURCES[0], build.HEADERS[0], os.path.join(ROOT, "include", "esp.h"), os.path.join(build.PKG, "build.py")):
+        monkeypatch.setattr(os.path, "getmtime", lambda f: mtime(build.LIB) + 1 if f == newer else min(mtime(f), mtime(build.LIB)))
+        assert build.is_stale(), newer
+
+
 def test_no_oracle_or_fallback_in_product():
     """The product path must not import the oracle (it is test infrastructure)."""
     pkg = os.path.join(ROOT, "paper_2404_09526_amd")
