@@ -7,7 +7,6 @@ namespace esp {
 
 struct U32x2 { uint32_t x, y; };      // O and the peers' O: the calls ask for 4-byte alignment, not for 8
 __device__ __forceinline__ float finite_offset(float m) { return m == -INFINITY ? 0.f : m; }
-template <int V> struct IC { static constexpr int value = V; };
 
 __device__ __forceinline__ float row16_sum(float x) {
     // all-reduce over the 16 lanes of a DPP row by rotations (8, 4, 2, 1)

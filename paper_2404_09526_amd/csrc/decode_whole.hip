@@ -1,7 +1,7 @@
 // Decode of short requests in one launch: a workgroup has a whole request and one KV head (a chunk of its query heads), and leaves the
 // result, with the peers' partials folded in; no partials, no kernel to combine them.  Such a call is a chain of round trips: offsets, slots,
-// rows, and a second launch with three of its own (3.6 us), longer than one CU takes for the rows of a few hundred tokens (62 GB/s a
-// workgroup on the matrix cores, up to 110 on the vector ALU, when few are at it).  Which calls: decode_whole (decode.hip), with both sides'
+// rows, and a second launch with three of its own (3.6 us), longer than one CU takes for the rows of a few hundred tokens (46 .. 56 GB/s a
+// workgroup on the matrix cores, 43 on the vector ALU, when few are at it).  Which calls: decode_whole (decode.hip), with both sides'
 // figures.  A step of four requests of 224 .. 485 tokens, 4 / 4 heads, three peers, its append included: 12.0 -> 9.0 us.
 #include "column_tile.h"
 #include "decode_merge.h"

@@ -787,8 +787,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     if (kTileRow * wave >= n_rows) n_need = 0;                           // a wavefront without rows: transfers and barriers only
 
     // ---- operand read offsets
-    // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> one base per lane, the rest are immediates (POOL: four, by the bits of t
-    // that the swizzle changes)
+    // K (A operand of S^T): row 32*kvb + qi, chunk 2t + hi -> four bases per lane, by the bits of t that the swizzle changes; the
+    // rest are immediates
     uint32_t k_rd[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) k_rd[x] = lds_k0 + qi * 256 + (((2 * x + hi) ^ (qi & 7)) << 4);
@@ -1325,9 +1325,10 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         const int M = a.q_tiles * width;
         // Rounds dealt statically (M <= L: one item each).  With start-of-round waits the items are long and alike: a pool of them does not
         // even out the workgroups of an XCD, and its items walk K/V alone (of two to four rounds the last drawn from the pool: 0.3 .. 1 %
-        // slower).  But XCDs differ by 7 % and more, and from eight rounds on that is an item's time or near it: then the last round
-        // goes to the pool all the same.  All dealt -> the last drawn, two cards: 32768 tokens on 262144, 32 / 32 heads, 106.5 -> 104.7 and 112.1 -> 105.5 ms,
-        // 16384 on 180000 37.0 -> 35.5, 10000 on 90000, 64 / 8, 21.3 -> 21.1; the last two rounds drawn 105.8 and 21.1.
+        // slower).  But XCDs differ by 7 % and more, and from eight rounds on that is an item's time or near it: then the pool has the last
+        // full round all the same, and what there is of a next one (L .. 2 L - 1 items).  All dealt -> these drawn, two cards: 32768 tokens on
+        // 262144, 32 / 32 heads, 106.5 -> 104.7 and 112.1 -> 105.5 ms, 16384 on 180000 37.0 -> 35.5, 10000 on 90000, 64 / 8 (57 items of 32
+        // workgroups), 21.3 -> 21.1; one more round drawn 105.8 and 21.1.
         const int S = M <= L ? 1 : a.group_sync && M < 8 * L ? (M + L - 1) / L : max(1, (M - L) / L);
         const int synced = min(S, M / L);                             // dealt rounds that are full: all but the first start together
         const int pool_items = M > S * L ? (M - S * L) * (split ? 8 : 1) : 0;
