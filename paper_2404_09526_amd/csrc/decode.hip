@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const int32_t* __re
     if (s1 > s0) {
         const int w_lo = s0 / range;
         const int64_t first = w_lo + b;                             // the slots of consecutive ranges
-        const int whole = (s1 - s0 + range - 1) / range, n = parts == 0 ? (s1 - 1) / range - w_lo + 1 : parts > 0 ? min(parts, whole) : whole;
+        const int whole = (s1 - s0 - 1) / range + 1, n = parts == 0 ? (s1 - 1) / range - w_lo + 1 : parts > 0 ? min(parts, whole) : whole;
         for (int i = g; i < n; i += GROUPS * U) {
             float m[U], l[U];
             float v[U][4];

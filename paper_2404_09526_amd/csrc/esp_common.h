@@ -106,7 +106,7 @@ struct RequestRange { int32_t b, t0, t1, w; };
 // number of them from one part to the next (all parts of a request on one XCD: 31 us for 16 requests of 900, 32 / 8 heads, against 21).
 __device__ __forceinline__ RequestRange request_part(int32_t i, int32_t parts, int32_t range, int32_t B, const int32_t* seq_offsets) {
     const int32_t part = i / B, at = i - part * B, b = (B & 1) != 0 ? at : (at + B - part % B) % B;
-    const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1], t0 = s0 + part * range;
+    const int32_t s0 = seq_offsets[b], s1 = seq_offsets[b + 1], t0 = s0 + min(part * range, s1 - s0);   // (s0 + part * range may be past 2^31)
     return {b, t0, part == parts - 1 ? s1 : t0 + min(range, s1 - t0), s0 / range + part};
 }
 // As many as each request has: the whole ranges of all requests first, then what is left of each, so that workgroups which find no
