@@ -161,20 +161,20 @@ def test_round_start_waits_replayed_from_a_graph(esp, cuda):
     assert int((words[2:2 + 2 * 32] != 0).sum()) == 0
 
 
-@pytest.mark.parametrize("ticks", [None, 0])
-def test_round_start_waits_and_an_item_pool(esp, cuda, main_prefill_kernel, ticks):
-    """Eight rounds of alike items (4096 tokens, 16 query heads to each of eight KV heads): all but the last are dealt and start together, the
-    last is drawn from the pool.  Against the oracle; bit for bit the two halves of the chunk, which have no pool; and replayed from
+@pytest.mark.parametrize("ticks,Tq,Tkv", [(None, 4096, 32768), (0, 4096, 32768), (None, 4500, 36864), (0, 4500, 36864)])
+def test_round_start_waits_and_an_item_pool(esp, cuda, main_prefill_kernel, ticks, Tq, Tkv):
+    """Eight rounds of alike items, or eight and 26 of 32 (4096 or 4500 tokens, 16 query heads to each of eight KV heads): seven are dealt and start
+    together, the others are drawn from the pool.  Against the oracle; bit for bit the two halves of the chunk, which have no pool; and replayed from
     a graph between eager calls, which the pool's counter and the arrival counts must survive."""
     was = esp.esp_debug_set_prefill_sync_ticks(ticks) if ticks is not None else None
     try:
-        pc = wl.contiguous_prefill("chunk-and-pool", 4096, 32768 - 4096, [(0, 32768)], 128, 8, 35, cuda)
+        pc = wl.contiguous_prefill("chunk-and-pool", Tq, Tkv - Tq, [(0, Tkv)], 128, 8, 35, cuda)
         check_prefill_sampled(esp, pc, 256, 5)
         s = pc.shards[0]
-        ws = torch.zeros(esp.esp_prefill_workspace_bytes(pc.Tq, 32768, 1, 128, 8, 128), dtype=torch.uint8, device=cuda)
+        ws = torch.zeros(esp.esp_prefill_workspace_bytes(pc.Tq, Tkv, 1, 128, 8, 128), dtype=torch.uint8, device=cuda)
         run = lambda q, pos, O, L: esp.esp_partial_attn_prefill(q, s.k, s.v, pos, s.kv_pos, softmax_scale=pc.scale, O=O, LSE=L, workspace=ws)
         O_ref = torch.empty_like(pc.q); L_ref = torch.empty((pc.Tq, pc.Hq), dtype=torch.float32, device=cuda)
-        for half in (slice(0, 2048), slice(2048, 4096)):
+        for half in (slice(0, 2048), slice(2048, Tq)):             # (whole query tiles of 16 tokens)
             run(pc.q[half], pc.q_pos[half], O_ref[half], L_ref[half])
         O, L = torch.empty_like(O_ref), torch.empty_like(L_ref)
         side = torch.cuda.Stream()
