@@ -53,6 +53,25 @@ constexpr int kTileBytes = kBN * kHeadDim * 2;   // 16 KiB: a V tile in LDS, row
 constexpr int kORow = 272;                       // LDS row pitch of the results on their way out: 256 bytes + 16 of padding
 constexpr int kKTileBytes = kBN * kORow;         // a stage of K: its tile, and room for the results (see the epilogue)
 
+// Where K lies in a stage.  LDS has 64 banks, 256 bytes in a row, and reads 16 lanes of 16 bytes at a time, here one chunk of 16 rows: the chunks
+// of a row are swizzled by the row modulo 8, which spreads eight rows over half of the banks, and every second eight rows lie half a row
+// on.  (A swizzle by the row modulo 16 would do the same, with eight address registers for four.)  With all rows 256 bytes apart 34.5 of
+// the 105 million cycles that the LDS of all CUs was busy in a call of 8192 on 8192 rows, 32 / 32 heads, were conflicts, now 0.1 of 71.  The loop does
+// not wait for them: six prompts of 37 .. 2047 tokens, 32 / 8 heads, 59.6 -> 59.3 us, other calls within 0.2 %.
+constexpr int kKGroup = 8 * 256 + 128;
+__host__ __device__ constexpr int k_row(int r) { return r * 256 + (r >> 3) * 128; }
+__host__ __device__ constexpr int k_chunk(int r, int c) { return k_row(r) + ((c ^ (r & 7)) << 4); }
+constexpr bool k_reads_spread() {
+    for (int c = 0; c < 16; ++c)
+        for (int first = 0; first < kBN; first += 16) {
+            unsigned seen = 0;
+            for (int r = first; r < first + 16; ++r) seen |= 1u << (k_chunk(r, c) / 16 % 16);
+            if (seen != 0xffff) return false;
+        }
+    return k_row(8) == kKGroup && k_row(kBN) <= kKTileBytes;
+}
+static_assert(k_reads_spread(), "an operand read of K must touch every bank once");
+
 
 // upper bound of the query tiles of one KV head: Tq * G packed rows, and one ragged tile per request
 static int32_t prefill_q_tiles_bound(int32_t Tq, int32_t G, int32_t batch) {
@@ -484,7 +503,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int ragged_tile = tail_rows < kBN ? nkt - 1 : -8;          // index of the ragged last tile, if any
 
     // ---- global -> LDS in transfers of 64 lanes x 16 bytes = 1 KiB of consecutive LDS bytes.
-    //      K and V tiles have rows of 256 B, their chunks XOR-swizzled: wavefront w moves rows 8w .. 8w+7 of either in two
+    //      K and V tiles have rows of 256 B, their chunks XOR-swizzled: wavefront w moves rows 8w .. 8w+7 of either, 2 KiB in a row, in two
     //      transfers; lane L writes LDS chunk L % 16 of row r = base + L / 16, so it fetches the global chunk
     //      (L % 16) ^ f(r).  Wavefront 0 also moves the positions.
     //      (K rows padded to 272 bytes instead: operand reads with one address register for four, but 17 transfers, of which each lane's
@@ -530,7 +549,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const int32_t* preq = a.kv_pos + kv_lo;
     const uint32_t lds_base = lds_base0;
     const uint32_t lds_k0 = lds_base + kLdsK, lds_v0 = lds_base + kLdsV;
-    const uint32_t lds_w = lds_base + wave * 2048;   // this wavefront's first pieces of K and V tiles
+    const uint32_t lds_w = lds_base + wave * 2048, lds_wk = lds_base + wave * kKGroup;   // this wavefront's first pieces of V and K tiles
 
     // K tile at kt into K stage st: 2 transfers per wavefront; `part` picks one of them, so that
     // the sweep can spread them over an iteration (a burst of transfers from all wavefronts at once backs up the
@@ -538,12 +557,12 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // end re-read the last row (their scores get masked).
     auto fetch_k_part = [&](const char* kt, int st, bool tail, int part) {
         const int off = (st == kStages ? kLdsK0 : kLdsK + st * kKTileBytes) + 1024 * part;
-        if constexpr (POOL) { load_to_lds_b128_at(lds_w, off, pool_at(part == 0 ? pk0 : pk1, pool_slot(st, part))); return; }
+        if constexpr (POOL) { load_to_lds_b128_at(lds_wk, off, pool_at(part == 0 ? pk0 : pk1, pool_slot(st, part))); return; }
         if (__builtin_expect(tail, 0)) {
             const int r = part == 0 ? st_r0 : st_r1;
-            load_to_lds_b128(lds_w, off, kt, k_goff(r, min(r, tail_rows - 1)));
+            load_to_lds_b128(lds_wk, off, kt, k_goff(r, min(r, tail_rows - 1)));
         } else {
-            load_to_lds_b128(lds_w, off, kt, part == 0 ? gk0 : gk1);
+            load_to_lds_b128(lds_wk, off, kt, part == 0 ? gk0 : gk1);
         }
     };
     // V tile at vt and its positions at pt into V stage st: 2 transfers per wavefront, 3 for wavefront 0
@@ -601,8 +620,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         const unsigned char* vt = smem + kLdsV + st * kTileBytes;
         const int r0 = wave * 8 + st_sub, r1 = r0 + 4;
         const int32_t s0 = ring[r0], s1 = ring[r1];
-        const uint4 wk0 = *(const uint4*)(kt + r0 * 256 + ((st_p ^ (r0 & 7)) << 4));
-        const uint4 wk1 = *(const uint4*)(kt + r1 * 256 + ((st_p ^ (r1 & 7)) << 4));
+        const uint4 wk0 = *(const uint4*)(kt + k_chunk(r0, st_p));
+        const uint4 wk1 = *(const uint4*)(kt + k_chunk(r1, st_p));
         const uint4 wv0 = *(const uint4*)(vt + r0 * 256 + ((st_p ^ ((r0 & 3) << 2)) << 4));
         const uint4 wv1 = *(const uint4*)(vt + r1 * 256 + ((st_p ^ ((r1 & 3) << 2)) << 4));
         // address of a pool row's piece: one 32 x 32 -> 64-bit multiply-add each
@@ -791,7 +810,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // rest are immediates
     uint32_t k_rd[4];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) k_rd[x] = lds_k0 + qi * 256 + (((2 * x + hi) ^ (qi & 7)) << 4);
+    for (int x = 0; x < 4; ++x) k_rd[x] = lds_k0 + k_chunk(qi, 2 * x + hi);
     // V (A operand of O^T) by transposing reads: 16 lanes fetch a 4 (kv) x 16 (d) patch
     const int j16 = lane & 15, jq = j16 >> 2, dblk = (lane >> 4) & 1;
     uint32_t v_rd[4];
@@ -826,7 +845,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     // (p / 8, (p / 4) % 2, p % 4) of the tile at byte offset stage_off of the V stages
     auto read_k = [&](int slot, int st, int i) {
         const int t = i >> 1;
-        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + st * kKTileBytes + (i & 1) * (32 * 256) + (t >> 2) * 128);
+        frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + st * kKTileBytes + (i & 1) * k_row(32) + (t >> 2) * 128);
     };
     auto read_v = [&](int slot, uint32_t stage_off, int p) {
         const uint32_t vp = v_rd[p & 3] + stage_off + (32 * (p >> 3) + 16 * ((p >> 2) & 1)) * 256;
@@ -1010,7 +1029,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
             }
             if constexpr (POOL) {
                 if (do_k && (m == 3 || m == 6))
-                    load_to_lds_b128_at(lds_w, kLdsK + ST * kKTileBytes + 1024 * (m / 6), pool_at(m == 3 ? pk0 : pk1, m == 3 ? pslot0 : pslot1));
+                    load_to_lds_b128_at(lds_wk, kLdsK + ST * kKTileBytes + 1024 * (m / 6), pool_at(m == 3 ? pk0 : pk1, m == 3 ? pslot0 : pslot1));
                 if (do_v && (m == 9 || m == 12))
                     load_to_lds_b128_at(lds_w, kLdsV + ST2 * kTileBytes + 1024 * (m / 12), pool_at(pv, m == 9 ? pslot0 : pslot1));
             } else {
@@ -1036,7 +1055,7 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
         if (n_need <= 0) return;
         auto read_k0 = [&](int slot, int i) {
             const int t = i >> 1;
-            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + (uint32_t)(kLdsK0 - kLdsK) + (i & 1) * (32 * 256) + (t >> 2) * 128);
+            frk[slot].v = *(const ESP_LDS bf16x8*)(uintptr_t)(k_rd[t & 3] + (uint32_t)(kLdsK0 - kLdsK) + (i & 1) * k_row(32) + (t >> 2) * 128);
         };
         read_k0(0, 0);
         read_k0(1, 1);
