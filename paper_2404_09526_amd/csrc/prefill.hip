@@ -524,8 +524,8 @@ __global__ __launch_bounds__(kPfWaves * 64) void prefill_kernel(PrefillArgs a) {
     const char* vreq = (const char*)a.v + ((int64_t)(POOL ? 0 : kv_lo) * a.Hkv + kvh) * (kHeadDim * 2);
     // POOL: one read of the ring (stage kStages: tile 0) has the slots of both rows that a lane moves of K or V.  From a slot to a row's
     // address: one 32 x 32 -> 64-bit multiply-add on where this lane's 16 bytes lie in slot 0.
-    // The loop is bound by the LDS port (288 KB a tile at 128 bytes a cycle, and the slot reads) and by power; with padded rows of K it took five
-    // slot reads a wavefront and tile, now two for two rows each.  Padded -> swizzled: a tile 2666 -> 2577 cycles; 300 tokens on 20300 rows of
+    // The loop is bound by issue and by power (the LDS is busy in 35 % of its cycles); with padded rows of K it took five slot reads a wavefront and
+    // tile, each an instruction and a round trip in front of a transfer, now two for two rows each.  Padded -> swizzled: a tile 2666 -> 2577 cycles; 300 tokens on 20300 rows of
     // the pool, 32 / 8 heads, 108.8 -> 105.9 us, 2000 on 2000 51.7 -> 48.7, 8000 on 30000 2733 -> 2680, 2048 on 10240, 32 / 32, 285 -> 279.
     const ESP_LDS int32_t* const slot_rd = (const ESP_LDS int32_t*)(uintptr_t)(lds_base0 + kLdsSlot + st_r0 * 4);
     auto pool_slot = [&](int st, int part) { return slot_rd[st * kBN + 4 * part]; };
